@@ -347,7 +347,8 @@ int hstu_attn_schedule_stats(const hstu_attn_params* p, const void* workspace, i
  * launch made by the entry points above is bracketed by HIP events on its stream (up to 64 launches
  * between two reads).  hstu_profile_read waits for those events and returns the number of entries
  * written: names[i] (static strings: "attn_fwd", "attn_bwd_dq", "attn_bwd_dkdv", "gated_norm_fwd",
- * "gated_norm_bwd" [the latter includes its column-sum kernel], "schedule_fwd", "schedule_bwd" [both backward lists, one launch], "bias_expand", "dbias_zero", "dbias_reduce",
+ * "gated_norm_bwd" [the latter includes its column-sum kernel], "schedule_fwd", "schedule_bwd" [both backward lists; each also expands the bias table, in the
+ * same launch; with reuse_schedule only the expansion is left: "bias_expand_fwd", "bias_expand_bwd"], "dbias_reduce",
  * "truncate_offsets", "truncate_fwd", "truncate_bwd", and from the layer entry points "layer_norm_fwd",
  * "gemm_uvqk", "silu_fwd", "gemm_out", "gemm_dy", "gemm_dw2", "gemm_dxn", "gemm_dw1", "layer_norm_bwd",
  * and "norm_quant_fp8", "fp8_gemm_bias2d";

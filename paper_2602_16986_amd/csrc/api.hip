@@ -129,26 +129,31 @@ AttnArgs make_args(const hstu_attn_params* p, const void* q, const void* k, cons
   return a;
 }
 
-// Enqueues the bias expansion (if any) and fills the bias fields.
-hipError_t prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws, const Layout& l, hipStream_t stream,
-                        bool for_forward) {
+// Fills the bias fields of the kernel arguments and describes the tables behind them.
+ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws, const Layout& l, bool for_forward) {
+  ExpandJob ex = {};
   a.bias = nullptr;
   a.bias_stride = p->max_seqlen + 1;
   a.seed = nullptr;
+  ex.table = p->rab_table; ex.bounds = p->rab_bounds; ex.num_buckets = p->num_buckets;
   if (p->dtype == HSTU_BF16 && p->head_dim == 128 && p->query_tail == 0 && for_forward) {   // the pipelined forward takes bias and mask from the seed tables
-    a.seed = (const float*)(ws + l.seed);
-    a.seed_len = seed_len_for(p->max_seqlen);
-    a.seed_dmax = seed_dmax_for(p->max_seqlen);
-    return launch_seed_expand(p->rab_table, p->rab_bounds, p->num_buckets, p->num_heads, p->max_seqlen, a.K1,
-                              (float*)(ws + l.seed), stream);           // (that kernel needs no other table)
+    ex.seed = (float*)(ws + l.seed);                                       // (that kernel needs no other table)
+    ex.seed_len = seed_len_for(p->max_seqlen);
+    ex.seed_dmax = seed_dmax_for(p->max_seqlen);
+    a.seed = ex.seed; a.seed_len = ex.seed_len; a.seed_dmax = ex.seed_dmax;
+    return ex;
   }
-  if (!p->rab_table) return hipSuccess;
-  float* bias = (float*)(ws + l.bias);
-  a.bias = bias;
-  int32_t* bucket_end = nullptr;                      // only the bias-table gradient needs the bucket ends
-  if (!for_forward && p->d_rab_table) bucket_end = (int32_t*)(ws + l.dbias) + (size_t)p->num_heads * a.bias_stride;
-  a.bucket_end = bucket_end;
-  return launch_bias_expand(p->rab_table, p->rab_bounds, p->num_buckets, p->num_heads, a.bias_stride, bias, bucket_end, stream);
+  if (!p->rab_table) return ex;
+  ex.bias = (float*)(ws + l.bias);
+  ex.bias_len = a.bias_stride;
+  a.bias = ex.bias;
+  if (!for_forward && p->d_rab_table) {               // only the bias-table gradient needs the bucket ends and the sums per distance
+    const int64_t n = (int64_t)p->num_heads * a.bias_stride;
+    a.dbias_dist = ex.zero = (float*)(ws + l.dbias);
+    ex.zero_count = n;
+    a.bucket_end = ex.bucket_end = (int32_t*)(ws + l.dbias) + n;
+  }
+  return ex;
 }
 
 }  // namespace
@@ -238,16 +243,13 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
   a.items = (const WorkItem*)(ws + l.items[0]);
   a.splits = (const SplitItem*)(ws + l.splits);
   a.partial = (float*)(ws + l.partial);
-  if (!p->reuse_schedule) {
-    ProfScope ps("schedule_fwd", stream);
-    if (launch_schedule(a, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), false,
-                        (SchedHeader*)(ws + l.header[0]), (WorkItem*)(ws + l.items[0]), (int32_t*)(ws + l.seq_base[0]),
-                        (SplitItem*)(ws + l.splits), l.slot_cap, stream) != hipSuccess)
-      return HSTU_ERR_LAUNCH;
-  }
   {
-    ProfScope ps("bias_expand_fwd", stream);
-    if (prepare_bias(p, a, ws, l, stream, true) != hipSuccess) return HSTU_ERR_LAUNCH;
+    const ExpandJob ex = prepare_bias(p, a, ws, l, true);
+    ProfScope ps(p->reuse_schedule ? "bias_expand_fwd" : "schedule_fwd", stream);
+    if (launch_schedule(a, !p->reuse_schedule, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim),
+                        (SchedHeader*)(ws + l.header[0]), (WorkItem*)(ws + l.items[0]), (int32_t*)(ws + l.seq_base[0]),
+                        (SplitItem*)(ws + l.splits), l.slot_cap, ex, stream) != hipSuccess)
+      return HSTU_ERR_LAUNCH;
   }
   {
     ProfScope ps("attn_fwd", stream);                      // includes the kernel that combines the pieces of cut blocks
@@ -297,11 +299,8 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   a.pre_q = pre_q; a.pre_k = pre_k; a.pre_v = pre_v; a.s_pre = s_pre;
   const int tile = stream_tile_rows(p->dtype, p->head_dim);
   {
-    ProfScope ps("bias_expand_bwd", stream);
-    if (prepare_bias(p, a, ws, l, stream, false) != hipSuccess) return HSTU_ERR_LAUNCH;
-  }
-  if (!p->reuse_schedule) {
-    ProfScope ps("schedule_bwd", stream);
+    const ExpandJob ex = prepare_bias(p, a, ws, l, false);
+    ProfScope ps(p->reuse_schedule ? "bias_expand_bwd" : "schedule_bwd", stream);
     const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
     const int cols[2] = {tile, dkv_tile_rows(p->dtype, p->head_dim)};
     SchedHeader* const hd[2] = {(SchedHeader*)(ws + l.header[0]), (SchedHeader*)(ws + l.header[1])};
@@ -309,13 +308,8 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     int32_t* const sb[2] = {(int32_t*)(ws + l.seq_base[0]), (int32_t*)(ws + l.seq_base[1])};
     SplitItem* const sp[2] = {(SplitItem*)(ws + l.splits_dq), (SplitItem*)(ws + l.splits)};
     const int caps[2] = {l.slot_cap_dq, l.slot_cap};
-    if (launch_schedule_pair(a, rows, cols, hd, it, sb, sp, caps, stream) != hipSuccess)
+    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ex, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
-  }
-  if (p->d_rab_table) {
-    ProfScope ps("dbias_zero", stream);
-    a.dbias_dist = (float*)(ws + l.dbias);
-    if (launch_fill_zero(a.dbias_dist, (size_t)p->num_heads * a.bias_stride, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   for (int s = 0; s < 2; ++s) {                          // s = 0: dQ pass (query blocks), s = 1: dK/dV pass (key blocks)
     a.max_items = l.max_items[s];

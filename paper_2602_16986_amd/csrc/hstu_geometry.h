@@ -46,7 +46,21 @@ struct TileRanges {
   }
 };
 
-HSTU_HD TileRanges tile_ranges(const SeqGeom& g, int r0, int r1, int BN) {
+// The column tile that holds a column, for a tile width known to the compiler or one that is a power of two (device code that
+// takes the width as an argument: a shift instead of the twenty-odd instructions of an integer division).
+struct TileWidth {
+  int bn;
+  HSTU_HD int index(int col) const { return col / bn; }
+  HSTU_HD int width() const { return bn; }
+};
+struct TileShift {
+  int shift;
+  HSTU_HD int index(int col) const { return col >> shift; }
+  HSTU_HD int width() const { return 1 << shift; }
+};
+
+template <class W>
+HSTU_HD TileRanges tile_ranges_of(const SeqGeom& g, int r0, int r1, const W tile) {
   TileRanges t = {0, 0, 0, 0, 0, 0};
   const bool has_hist = r0 < g.n;
   const bool has_cand = r1 >= g.n;
@@ -56,16 +70,16 @@ HSTU_HD TileRanges tile_ranges(const SeqGeom& g, int r0, int r1, int BN) {
   int end = 0;
   if (maxkey >= 0) {
     if (g.K1 < 0) {
-      t.a1 = maxkey / BN + 1;
+      t.a1 = tile.index(maxkey) + 1;
       end = t.a1;
     } else {
       const int pre = imin(g.K2, maxkey + 1);                 // prefix keys [0, pre)
-      t.a1 = (pre + BN - 1) / BN;
+      t.a1 = tile.index(pre + tile.width() - 1);
       end = t.a1;
       const int lo = imax(0, p_lo - g.K1 + 1);                // band keys [lo, maxkey]
       if (g.K1 > 0 && lo <= maxkey) {
-        t.b0 = imax(lo / BN, end);
-        t.b1 = imax(maxkey / BN + 1, t.b0);
+        t.b0 = imax(tile.index(lo), end);
+        t.b1 = imax(tile.index(maxkey) + 1, t.b0);
         end = t.b1;
       }
     }
@@ -73,17 +87,19 @@ HSTU_HD TileRanges tile_ranges(const SeqGeom& g, int r0, int r1, int BN) {
   if (t.b1 == 0) { t.b0 = t.b1 = end; }
   if (has_cand) {                                            // self pairs of candidate rows
     const int c_lo = imax(r0, g.n);
-    t.c0 = imax(c_lo / BN, end);
-    t.c1 = imax(r1 / BN + 1, t.c0);
+    t.c0 = imax(tile.index(c_lo), end);
+    t.c1 = imax(tile.index(r1) + 1, t.c0);
   } else {
     t.c0 = t.c1 = end;
   }
   return t;
 }
+HSTU_HD TileRanges tile_ranges(const SeqGeom& g, int r0, int r1, int BN) { return tile_ranges_of(g, r0, r1, TileWidth{BN}); }
 
 // Query-row tiles (height BN) that see at least one key of [k0, k1] (k1 < L): the mirror image of
 // tile_ranges(), used by the key-stationary backward pass.
-HSTU_HD TileRanges row_tile_ranges(const SeqGeom& g, int k0, int k1, int BN) {
+template <class W>
+HSTU_HD TileRanges row_tile_ranges_of(const SeqGeom& g, int k0, int k1, const W tile) {
   TileRanges t = {0, 0, 0, 0, 0, 0};
   int end = 0;
   bool cands_see_block = false;
@@ -93,8 +109,8 @@ HSTU_HD TileRanges row_tile_ranges(const SeqGeom& g, int k0, int k1, int BN) {
     if (g.K1 < 0 || k0 < g.K2) hi = g.n - 1;
     else if (g.K1 > 0) hi = imin(kh1 + g.K1 - 1, g.n - 1);
     if (hi >= k0) {
-      t.a0 = k0 / BN;
-      t.a1 = hi / BN + 1;
+      t.a0 = tile.index(k0);
+      t.a1 = tile.index(hi) + 1;
       end = t.a1;
     }
     cands_see_block = (g.K1 < 0) || (k0 < g.K2) || (g.n - kh1 < g.K1);
@@ -104,13 +120,14 @@ HSTU_HD TileRanges row_tile_ranges(const SeqGeom& g, int k0, int k1, int BN) {
   if (g.n < g.L && cands_see_block) { c_lo = g.n; c_hi = g.L - 1; }
   else if (k1 >= g.n) { c_lo = imax(k0, g.n); c_hi = k1; }
   if (c_hi >= c_lo) {
-    t.c0 = imax(c_lo / BN, end);
-    t.c1 = imax(c_hi / BN + 1, t.c0);
+    t.c0 = imax(tile.index(c_lo), end);
+    t.c1 = imax(tile.index(c_hi) + 1, t.c0);
   } else {
     t.c0 = t.c1 = end;
   }
   return t;
 }
+HSTU_HD TileRanges row_tile_ranges(const SeqGeom& g, int k0, int k1, int BN) { return row_tile_ranges_of(g, k0, k1, TileWidth{BN}); }
 
 // How a block of query rows [w0, w1] relates to a key tile [j0, j1] (j1 may exceed L-1).
 enum TileKind { kTileEmpty = 0, kTileFull = 1, kTilePartial = 2 };

@@ -67,22 +67,23 @@ inline int seed_dmax_for(int max_seqlen) { return max_seqlen + 128; }
 inline int seed_len_for(int max_seqlen) { return (seed_dmax_for(max_seqlen) + 1 + 192 + 63) / 64 * 64; }
 
 // schedule.hip
-// Builds the work list for blocks of `block_rows` rows (query rows in the forward and the dQ pass,
-// key rows when `key_major` is set) against column tiles of `tile_cols`.
-// `splits` / `slot_cap` (optional): blocks much longer than the rest may be cut into pieces that leave partial sums in slots.
-hipError_t launch_schedule(const AttnArgs& a, int block_rows, int tile_cols, bool key_major, SchedHeader* header,
-                           WorkItem* items, int32_t* seq_base, SplitItem* splits, int slot_cap, hipStream_t stream);
-// The two lists of the backward pass in one launch: [0] query blocks (dQ pass), [1] key blocks (dK/dV pass).
-// `splits` / `slot_cap`: list of cut key blocks and number of partial-sum slots available to the dK/dV list.
-hipError_t launch_schedule_pair(const AttnArgs& a, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
+// Tables that an attention pass reads, filled in the scheduler's launch.
+struct ExpandJob {
+  const float* table; const int32_t* bounds; int num_buckets;   // bias table [H, num_buckets] or nullptr
+  float* bias; int bias_len;                                    // optional: AttnArgs::bias [H, bias_len]
+  int32_t* bucket_end;                                          // optional, with bias: [bias_len], the first distance of the next bucket
+  float* seed; int seed_len, seed_dmax;                         // optional: AttnArgs::seed (table may be nullptr: no bias)
+  float* zero; int64_t zero_count;                              // optional: floats to clear
+};
+// Builds the work list of the forward for blocks of `block_rows` query rows against column tiles of `tile_cols`, and fills the
+// tables of `ex`.  lists = false: the tables only.  Blocks much longer than the rest may be cut into pieces that leave
+// partial sums in `slot_cap` slots, listed in `splits`.
+hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
+                           int32_t* seq_base, SplitItem* splits, int slot_cap, const ExpandJob& ex, hipStream_t stream);
+// The two lists of the backward pass: [0] query blocks (dQ pass), [1] key blocks (dK/dV pass).
+hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], hipStream_t stream);
-// bucket_end (optional, [len]): for every distance the first distance of the next bucket
-hipError_t launch_bias_expand(const float* table, const int32_t* bounds, int num_buckets, int H, int len, float* out, int32_t* bucket_end,
-                              hipStream_t stream);
-// fills AttnArgs::seed (table may be nullptr: no bias)
-hipError_t launch_seed_expand(const float* table, const int32_t* bounds, int num_buckets, int H, int max_seqlen, int K1,
-                              float* out, hipStream_t stream);
+                                const int slot_cap[2], const ExpandJob& ex, hipStream_t stream);
 
 // attn_core.hip
 int fwd_block_rows(int dtype, int D);     // query rows per workgroup, forward
