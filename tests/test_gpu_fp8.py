@@ -111,6 +111,13 @@ def test_fp8_gemm_bias2d(hb, M, N, K):
     run_gemm(hb, M, N, K)
 
 
+@pytest.mark.parametrize("M,N,K,in_place", [(12_800, 448, 128, True), (12_801, 448, 512, False), (6_400, 960, 1024, True)])
+def test_fp8_gemm_output_features_divided_unevenly(hb, M, N, K, in_place):
+    """Row counts for which the output features are divided among workgroups into parts of several chunks, the last one
+    shorter (7 chunks by twos; 15 chunks by threes or eights)."""
+    run_gemm(hb, M, N, K, in_place=in_place, rows=np.unique(np.concatenate([np.arange(0, M, 37), [M - 1]])))
+
+
 def test_fp8_gemm_without_c_and_in_place(hb):
     run_gemm(hb, 700, 256, 512, with_c=False)
     run_gemm(hb, 700, 256, 512, in_place=True)
