@@ -116,10 +116,11 @@ size_t hstu_attn_workspace_bytes(const hstu_attn_params* p, int for_backward);
 
 /* Paper Eq. 3, forward (attention_forward of the appendix pseudocode).
  * q, k, v: inputs [T, H, d]; out: A [T, H, d]; all DEVICE, dtype p->dtype.
- * Enqueues: tile scheduler (skips fully masked blocks), bias expansion, attention kernel, combine kernel.
+ * Enqueues: tile scheduler (skips fully masked blocks), bias expansion (one launch), attention kernel, and, unless no block
+ * can be cut, a kernel that finishes the cut blocks.
  * A query block whose list of key tiles is longer than a workgroup slot's share of the whole batch (small batches: one
  * long sequence, a few short ones) is cut into equal pieces along the key axis; the pieces write fp32 partial sums into
- * the workspace and the combine kernel adds them in piece order (deterministic) and writes the rows. */
+ * the workspace and the finishing kernel adds them in piece order (deterministic) and writes the rows. */
 int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const void* v, void* out,
                   void* workspace, size_t workspace_bytes, void* stream);
 
@@ -348,11 +349,12 @@ int hstu_attn_schedule_stats(const hstu_attn_params* p, const void* workspace, i
  * between two reads).  hstu_profile_read waits for those events and returns the number of entries
  * written: names[i] (static strings: "attn_fwd", "attn_bwd_dq", "attn_bwd_dkdv", "gated_norm_fwd",
  * "gated_norm_bwd" [the latter includes its column-sum kernel], "schedule_fwd", "schedule_bwd" [both backward lists; each also expands the bias table, in the
- * same launch; with reuse_schedule only the expansion is left: "bias_expand_fwd", "bias_expand_bwd"], "dbias_reduce",
+ * same launch; with reuse_schedule only the expansion is left: "bias_expand_fwd", "bias_expand_bwd"], "attn_bwd_finish" [the kernel that
+ * adds the partial sums of cut blocks and folds the bias-table gradient],
  * "truncate_offsets", "truncate_fwd", "truncate_bwd", and from the layer entry points "layer_norm_fwd",
  * "gemm_uvqk", "silu_fwd", "gemm_out", "gemm_dy", "gemm_dw2", "gemm_dxn", "gemm_dw1", "layer_norm_bwd",
  * and "norm_quant_fp8", "fp8_gemm_bias2d";
- * "attn_bwd_dkdv" includes the kernel that combines the partial sums of cut key blocks) and
+ * "attn_fwd" includes the kernel that adds the partial sums of cut blocks) and
  * ms[i] = elapsed milliseconds.  HOST arrays.  Not thread-safe; enable(1) creates the events once. */
 int hstu_profile_enable(int on);
 int hstu_profile_read(int max_entries, const char** names, float* ms);

@@ -252,9 +252,11 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
       return HSTU_ERR_LAUNCH;
   }
   {
-    ProfScope ps("attn_fwd", stream);                      // includes the kernel that combines the pieces of cut blocks
+    ProfScope ps("attn_fwd", stream);                      // includes the kernel that adds up the pieces of cut blocks
     if (launch_attn_fwd(a, p->dtype, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
-    if (launch_fwd_combine(a, p->dtype, l.slot_cap / 2, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+    if (schedule_may_cut(a, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), p->seq_offsets_host) &&
+        launch_fwd_finish(a, p->dtype, a.header, a.splits, a.partial, stream) != hipSuccess)
+      return HSTU_ERR_LAUNCH;
   }
   return HSTU_OK;
 }
@@ -297,12 +299,11 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   AttnArgs a = make_args(p, q, k, v);
   a.dout = dout; a.dq = dq; a.dk = dk; a.dv = dv;
   a.pre_q = pre_q; a.pre_k = pre_k; a.pre_v = pre_v; a.s_pre = s_pre;
-  const int tile = stream_tile_rows(p->dtype, p->head_dim);
+  const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
+  const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, false);
     ProfScope ps(p->reuse_schedule ? "bias_expand_bwd" : "schedule_bwd", stream);
-    const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
-    const int cols[2] = {tile, dkv_tile_rows(p->dtype, p->head_dim)};
     SchedHeader* const hd[2] = {(SchedHeader*)(ws + l.header[0]), (SchedHeader*)(ws + l.header[1])};
     WorkItem* const it[2] = {(WorkItem*)(ws + l.items[0]), (WorkItem*)(ws + l.items[1])};
     int32_t* const sb[2] = {(int32_t*)(ws + l.seq_base[0]), (int32_t*)(ws + l.seq_base[1])};
@@ -311,25 +312,25 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ex, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }
+  const SchedHeader* headers[2];
+  const SplitItem* const splits[2] = {(const SplitItem*)(ws + l.splits_dq), (const SplitItem*)(ws + l.splits)};
+  const float* const partial[2] = {(const float*)(ws + l.partial_dq), (const float*)(ws + l.partial)};
   for (int s = 0; s < 2; ++s) {                          // s = 0: dQ pass (query blocks), s = 1: dK/dV pass (key blocks)
     a.max_items = l.max_items[s];
-    a.header = (const SchedHeader*)(ws + l.header[s]);
+    a.header = headers[s] = (const SchedHeader*)(ws + l.header[s]);
     a.items = (const WorkItem*)(ws + l.items[s]);
-    a.partial = (float*)(ws + (s == 0 ? l.partial_dq : l.partial));
-    a.splits = (const SplitItem*)(ws + (s == 0 ? l.splits_dq : l.splits));
-    {
-      ProfScope ps(s == 0 ? "attn_bwd_dq" : "attn_bwd_dkdv", stream);     // each figure includes its combine kernel
-      const hipError_t e = s == 0 ? launch_attn_bwd_dq(a, p->dtype, stream) : launch_attn_bwd_dkdv(a, p->dtype, stream);
-      if (e != hipSuccess) return HSTU_ERR_LAUNCH;
-      if (s == 0 && launch_dq_combine(a, p->dtype, l.slot_cap_dq / 2, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
-      if (s == 1 && launch_dkdv_combine(a, p->dtype, l.slot_cap / 2, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
-    }
-    if (s == 0 && p->d_rab_table) {
-      ProfScope ps2("dbias_reduce", stream);
-      if (launch_dbias_reduce(a.dbias_dist, p->rab_bounds, p->num_buckets, p->num_heads, a.bias_stride, p->inv_n,
-                              p->d_rab_table, stream) != hipSuccess)
-        return HSTU_ERR_LAUNCH;
-    }
+    a.partial = const_cast<float*>(partial[s]);
+    a.splits = splits[s];
+    ProfScope ps(s == 0 ? "attn_bwd_dq" : "attn_bwd_dkdv", stream);
+    if ((s == 0 ? launch_attn_bwd_dq(a, p->dtype, stream) : launch_attn_bwd_dkdv(a, p->dtype, stream)) != hipSuccess) return HSTU_ERR_LAUNCH;
+  }
+  for (int s = 0; s < 2; ++s)
+    if (!schedule_may_cut(a, 1 + s, rows[s], cols[s], p->seq_offsets_host)) headers[s] = nullptr;
+  DbiasJob db = {};
+  if (p->d_rab_table) db = {p->rab_bounds, p->num_buckets, p->d_rab_table};
+  {
+    ProfScope ps("attn_bwd_finish", stream);             // the pieces of cut blocks, the bias-table gradient
+    if (launch_bwd_finish(a, p->dtype, headers, splits, partial, db, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   return HSTU_OK;
 }

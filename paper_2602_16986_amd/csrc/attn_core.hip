@@ -156,7 +156,7 @@ __device__ __forceinline__ void diag_all(std::integer_sequence<int, R...>, const
 }
 
 // DBIAS (dQ pass only): also sum dS along the diagonals of every tile (pairs of equal distance i - j) into
-// a.dbias_dist[h, distance]; dbias_reduce_kernel folds distances into buckets afterwards.
+// a.dbias_dist[h, distance]; finish_kernel folds distances into buckets afterwards.
 // CAND (batches with candidate rows): the fast paths also cover candidate rows against history keys.  A candidate row
 // stands at position n for the mask and for the bias, so full and mask-edge tiles of such rows work like those of history
 // rows once the bias strip is addressed with the row's effective position (query-stationary passes) or anchored at n
@@ -1091,7 +1091,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   // ---- epilogue: scale once, convert, store.  Lane x holds features ob*32 + 8*(r/4) + 4*hf + r%4.
   {
     if (item.slot >= 0) {
-      // a piece of a cut block: raw fp32 sums go to its slot [outputs][block row][D]; the combine kernel finishes
+      // a piece of a cut block: raw fp32 sums go to its slot [outputs][block row][D]; finish_kernel adds them up
       float* dst = a.partial + (((int64_t)item.slot * C::NOUT) * C::BX + (wave * 32 + l32)) * D;
 #pragma unroll
       for (int o = 0; o < C::NOUT; ++o)
@@ -1149,46 +1149,94 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
 #endif
 }
 
-// Adds the partial sums of one cut block in piece order (fixed order: deterministic), applies the output scale and
-// writes the rows: dK and dV of a key block cut along the query axis, or the attention output (forward) or dQ (dQ pass) of
-// a query block cut along the key axis (small batches; the forward over a query tail: few rows against long histories).
-// Grid: (possible cut blocks, 8); block (b, rb, h) rows split 8 ways.
-enum { kCombineDKDV = 0, kCombineFwd = 1, kCombineDQ = 2 };
-template <typename E, int D, int WHAT>
-__global__ __launch_bounds__(256) void combine_kernel(const AttnArgs a, int block_rows) {
-  constexpr bool FWD = WHAT == kCombineFwd;
-  const int si = blockIdx.x;
-  if (si >= a.header->splits) return;
-  const SplitItem it = a.splits[si];
-  const int seq0 = a.offsets[it.b], L = a.offsets[it.b + 1] - seq0;
+// What is left to do after the attention kernels of a call, in one launch:
+//   - cut blocks: the partial sums of their pieces are added in piece order (fixed order: deterministic), scaled, converted and
+//     written: the attention output, or dQ, of a query block cut along the key axis, or dK and dV of a key block cut along the
+//     query axis;
+//   - bias-table gradient: dtable[h, c] = inv_n * sum of the per-distance sums over the distances of bucket c
+//     (bounds[c] <= x < bounds[c+1], x < bias_stride), a fixed-order tree per (bucket, head).
+// A unit of work is a quarter of one output of a cut block (32 rows), or one (bucket, head); workgroups take units
+// round-robin.  Nothing but latency bounds it: a thread has the loads of 4 rows x 2 pieces in flight (64 prefix blocks of the
+// semi-local 8k-16k workload, 8 pieces of 128 KB each: 25 us with one load in flight and 16
+// rows per workgroup, 15.6 now).  One launch for both passes and the table's gradient: the backward of an ordinary batch had 23 us in three.
+enum { kFinishDKDV = 0, kFinishFwd = 1, kFinishDQ = 2 };
+constexpr int kFinishThreads = 256, kBlockRows = 128, kUnitRows = 32, kUnits = kBlockRows / kUnitRows;
+
+template <typename E, int D>
+__device__ __forceinline__ void finish_unit(const AttnArgs& a, const FinishJob& job, int split, int unit) {
+  constexpr int VPR = D / 4, RPI = kFinishThreads / VPR, NR = kUnitRows / RPI;   // 16-byte groups per row, rows per step, rows per thread
+  const SplitItem it = job.splits[split];
   const int xb = it.rb_h >> 8, h = it.rb_h & 255;
-  constexpr int VPR = D / 4;                                           // float4 per row
-  constexpr int NOUT = WHAT == kCombineDKDV ? 2 : 1;
-  int q0 = 0;
-  if (FWD && a.query_tail > 0) q0 = max(L - (a.num_targets ? a.num_targets[it.b] : 0) - a.query_tail, 0);
-  const int rows_here = block_rows / 8;
-  for (int i = threadIdx.x; i < NOUT * rows_here * VPR; i += 256) {
-    const int o = i / (rows_here * VPR), r = blockIdx.y * rows_here + (i / VPR) % rows_here, c4 = i % VPR;
-    const int x = xb * block_rows + r;
-    if (x >= L || x < q0) continue;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int pc = 0; pc < it.pieces; ++pc)
-      acc += *(const f32x4*)(a.partial + ((((int64_t)(it.first_slot + pc) * NOUT + o) * block_rows + r) * D) + 4 * c4);
-    const float scale = (!FWD && o == 0) ? a.inv_n * a.alpha : a.inv_n * kLn2;      // dQ and dK owe alpha, the forward and dV ln 2
-    acc *= scale;
-    E* base = FWD ? (E*)a.out : (WHAT == kCombineDQ ? (E*)a.dq : (E*)(o == 0 ? a.dk : a.dv));
-    const int64_t stride = FWD ? a.so : (WHAT == kCombineDQ ? a.sq : (o == 0 ? a.sk : a.sv));
-    E* dst = base + (int64_t)(seq0 + x) * stride + (int64_t)h * D + 4 * c4;
-    if constexpr (sizeof(E) == 2 && !FWD) {
-      const __bf16* pre = (const __bf16*)(WHAT == kCombineDQ ? a.pre_q : (o == 0 ? a.pre_k : a.pre_v));
+  const int o = unit / kUnits, r0 = (unit % kUnits) * kUnitRows + (int)threadIdx.x / VPR, c4 = (int)threadIdx.x % VPR;
+  const int64_t piece = (job.what == kFinishDKDV ? 2 : 1) * kBlockRows * VPR;
+  const f32x4* src = (const f32x4*)job.partial + it.first_slot * piece + (int64_t)(o * kBlockRows + r0) * VPR + c4;
+  f32x4 acc[NR];
+#pragma unroll
+  for (int e = 0; e < NR; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  int pc = 0;
+  for (; pc + 2 <= it.pieces; pc += 2, src += 2 * piece) {
+    f32x4 p0[NR], p1[NR];
+#pragma unroll
+    for (int e = 0; e < NR; ++e) { p0[e] = src[e * RPI * VPR]; p1[e] = src[piece + e * RPI * VPR]; }
+#pragma unroll
+    for (int e = 0; e < NR; ++e) { acc[e] += p0[e]; acc[e] += p1[e]; }
+  }
+  if (pc < it.pieces) {
+#pragma unroll
+    for (int e = 0; e < NR; ++e) acc[e] += src[e * RPI * VPR];
+  }
+  const float scale = (job.what != kFinishFwd && o == 0) ? a.inv_n * a.alpha : a.inv_n * kLn2;      // dQ and dK owe alpha, the forward and dV ln 2
+  E* base = job.what == kFinishFwd ? (E*)a.out : (job.what == kFinishDQ ? (E*)a.dq : (E*)(o == 0 ? a.dk : a.dv));
+  const int64_t stride = job.what == kFinishFwd ? a.so : (job.what == kFinishDQ ? a.sq : (o == 0 ? a.sk : a.sv));
+  const int q0 = (job.what == kFinishFwd && a.query_tail > 0) ? max(it.hist - a.query_tail, 0) : 0;
+#pragma unroll
+  for (int e = 0; e < NR; ++e) {
+    const int x = xb * kBlockRows + r0 + e * RPI;
+    if (x >= it.len || x < q0) continue;
+    f32x4 v = acc[e] * scale;
+    E* dst = base + (int64_t)(it.seq0 + x) * stride + (int64_t)h * D + 4 * c4;
+    if constexpr (sizeof(E) == 2) {
+      const __bf16* pre = job.what == kFinishFwd ? nullptr : (const __bf16*)(job.what == kFinishDQ ? a.pre_q : (o == 0 ? a.pre_k : a.pre_v));
       if (pre) {
-        const u32x2 t = *(const u32x2*)(pre + (int64_t)(seq0 + x) * a.s_pre + (int64_t)h * D + 4 * c4);
-        acc[0] *= dsilu(__uint_as_float(t[0] << 16)); acc[1] *= dsilu(__uint_as_float(t[0] & 0xFFFF0000u));
-        acc[2] *= dsilu(__uint_as_float(t[1] << 16)); acc[3] *= dsilu(__uint_as_float(t[1] & 0xFFFF0000u));
+        const u32x2 t = *(const u32x2*)(pre + (int64_t)(it.seq0 + x) * a.s_pre + (int64_t)h * D + 4 * c4);
+        v[0] *= dsilu(__uint_as_float(t[0] << 16)); v[1] *= dsilu(__uint_as_float(t[0] & 0xFFFF0000u));
+        v[2] *= dsilu(__uint_as_float(t[1] << 16)); v[3] *= dsilu(__uint_as_float(t[1] & 0xFFFF0000u));
       }
+      *(u32x2*)dst = (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    } else {
+      *(f32x4*)dst = v;
     }
-    if constexpr (sizeof(E) == 2) *(u32x2*)dst = (u32x2){pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])};
-    else *(f32x4*)dst = acc;
+  }
+}
+
+__device__ void dbias_unit(const AttnArgs& a, const DbiasJob& job, int c, int h) {
+  __shared__ float red[kFinishThreads / 64];
+  const int len = a.bias_stride, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lo = min(job.bounds[c], len), hi = c + 1 < job.num_buckets ? min(job.bounds[c + 1], len) : len;
+  const float* dist = a.dbias_dist + (size_t)h * len;
+  float acc = 0.f;
+  for (int x = lo + (int)threadIdx.x; x < hi; x += kFinishThreads) acc += dist[x];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
+  __syncthreads();                                                     // (a workgroup may take several units)
+  if (lane == 0) red[wave] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) job.dtable[(size_t)h * job.num_buckets + c] = (red[0] + red[1] + red[2] + red[3]) * a.inv_n;
+}
+
+template <typename E, int D>
+__global__ __launch_bounds__(kFinishThreads) void finish_kernel(const AttnArgs a, FinishJob j0, FinishJob j1, DbiasJob db) {
+  const int per0 = (j0.what == kFinishDKDV ? 2 : 1) * kUnits, per1 = (j1.what == kFinishDKDV ? 2 : 1) * kUnits;
+  const int n0 = j0.header ? j0.header->splits * per0 : 0, n1 = j1.header ? j1.header->splits * per1 : 0;
+  const int nd = db.num_buckets * a.H;
+  for (int u = blockIdx.x; u < n0 + n1 + nd; u += gridDim.x) {
+    if (u < nd) {
+      dbias_unit(a, db, u % db.num_buckets, u / db.num_buckets);
+    } else {                                             // (one copy of the code: it is fetched through a cold cache)
+      const bool second = u >= nd + n0;
+      const int v = second ? u - nd - n0 : u - nd, per = second ? per1 : per0;
+      finish_unit<E, D>(a, second ? j1 : j0, v / per, v % per);
+    }
   }
 }
 
@@ -1234,6 +1282,8 @@ static hipError_t dispatch(const AttnArgs& a, int dtype, hipStream_t stream) {
 constexpr int kFwdWavesBf16 = 4, kFwdWavesFp32 = 4;
 constexpr int kDqWavesBf16 = 4, kDqWavesFp32 = 4;
 constexpr int kDkvWavesBf16 = 4, kDkvWavesFp32 = 4;
+static_assert(kFwdWavesBf16 * 32 == kBlockRows && kFwdWavesFp32 * 32 == kBlockRows && kDqWavesBf16 * 32 == kBlockRows && kDqWavesFp32 * 32 == kBlockRows &&
+              kDkvWavesBf16 * 32 == kBlockRows && kDkvWavesFp32 * 32 == kBlockRows, "finish_kernel takes blocks of 128 rows");
 
 int fwd_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kFwdWavesBf16 : kFwdWavesFp32); }
 int dq_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDqWavesBf16 : kDqWavesFp32); }
@@ -1256,24 +1306,6 @@ hipError_t launch_attn_bwd_dq(const AttnArgs& a, int dtype, hipStream_t stream) 
   return dispatch<kBwdDQ, kDqWavesBf16, kDqWavesFp32>(a, dtype, stream);
 }
 
-// dtable[h, c] = scale * sum of dist[h, x] over the distances x of bucket c (bounds[c] <= x < bounds[c+1], x < len).
-// One workgroup per (bucket, head); fixed-order tree reduction.
-__global__ __launch_bounds__(256) void dbias_reduce_kernel(const float* __restrict__ dist, const int32_t* __restrict__ bounds,
-                                                           int nb, int len, float scale, float* __restrict__ dtable) {
-  __shared__ float red[256];
-  const int c = blockIdx.x, h = blockIdx.y;
-  const int lo = min(bounds[c], len), hi = c + 1 < nb ? min(bounds[c + 1], len) : len;
-  float acc = 0.f;
-  for (int x = lo + threadIdx.x; x < hi; x += 256) acc += dist[(size_t)h * len + x];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) dtable[(size_t)h * nb + c] = red[0] * scale;
-}
-
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0.f;
 }
@@ -1284,49 +1316,46 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_dbias_reduce(const float* dist, const int32_t* bounds, int num_buckets, int H, int len, float scale,
-                               float* dtable, hipStream_t stream) {
-  hipLaunchKernelGGL(dbias_reduce_kernel, dim3(num_buckets, H), dim3(256), 0, stream, dist, bounds, num_buckets, len, scale,
-                     dtable);
-  return hipGetLastError();
-}
 hipError_t launch_attn_bwd_dkdv(const AttnArgs& a, int dtype, hipStream_t stream) {
   if (a.num_targets) return dispatch<kBwdDKDV, kDkvWavesBf16, kDkvWavesFp32, false, true>(a, dtype, stream);
   return dispatch<kBwdDKDV, kDkvWavesBf16, kDkvWavesFp32>(a, dtype, stream);
 }
 
-template <int FWD>
-static hipError_t launch_combine(const AttnArgs& a, int dtype, int rows, int max_splits, hipStream_t stream) {
-  if (max_splits <= 0) return hipSuccess;
-  const dim3 grid(max_splits, 8), block(256);
+static hipError_t launch_finish(const AttnArgs& a, int dtype, const FinishJob& j0, const FinishJob& j1, const DbiasJob& db, hipStream_t stream) {
+  // the number of cut blocks is known on the device only: at most 2,048 workgroups share the units
+  const int64_t most = (int64_t)db.num_buckets * a.H + (j0.header || j1.header ? 2048 : 0);
+  if (most == 0) return hipSuccess;
+  const dim3 grid((unsigned)(most < 2048 ? most : 2048)), block(kFinishThreads);
   if (dtype == 0) {
     switch (a.D) {
-      case 32: hipLaunchKernelGGL((combine_kernel<__bf16, 32, FWD>), grid, block, 0, stream, a, rows); break;
-      case 64: hipLaunchKernelGGL((combine_kernel<__bf16, 64, FWD>), grid, block, 0, stream, a, rows); break;
-      case 128: hipLaunchKernelGGL((combine_kernel<__bf16, 128, FWD>), grid, block, 0, stream, a, rows); break;
+      case 32: hipLaunchKernelGGL((finish_kernel<__bf16, 32>), grid, block, 0, stream, a, j0, j1, db); break;
+      case 64: hipLaunchKernelGGL((finish_kernel<__bf16, 64>), grid, block, 0, stream, a, j0, j1, db); break;
+      case 128: hipLaunchKernelGGL((finish_kernel<__bf16, 128>), grid, block, 0, stream, a, j0, j1, db); break;
       default: return hipErrorInvalidValue;
     }
   } else {
     switch (a.D) {
-      case 32: hipLaunchKernelGGL((combine_kernel<float, 32, FWD>), grid, block, 0, stream, a, rows); break;
-      case 64: hipLaunchKernelGGL((combine_kernel<float, 64, FWD>), grid, block, 0, stream, a, rows); break;
-      case 128: hipLaunchKernelGGL((combine_kernel<float, 128, FWD>), grid, block, 0, stream, a, rows); break;
+      case 32: hipLaunchKernelGGL((finish_kernel<float, 32>), grid, block, 0, stream, a, j0, j1, db); break;
+      case 64: hipLaunchKernelGGL((finish_kernel<float, 64>), grid, block, 0, stream, a, j0, j1, db); break;
+      case 128: hipLaunchKernelGGL((finish_kernel<float, 128>), grid, block, 0, stream, a, j0, j1, db); break;
       default: return hipErrorInvalidValue;
     }
   }
   return hipGetLastError();
 }
 
-hipError_t launch_dkdv_combine(const AttnArgs& a, int dtype, int max_splits, hipStream_t stream) {
-  return launch_combine<kCombineDKDV>(a, dtype, dkv_block_rows(dtype, a.D), max_splits, stream);
+hipError_t launch_fwd_finish(const AttnArgs& a, int dtype, const SchedHeader* header, const SplitItem* splits, const float* partial,
+                             hipStream_t stream) {
+  const FinishJob job = {header, splits, partial, kFinishFwd};
+  const FinishJob none = {nullptr, nullptr, nullptr, kFinishFwd};
+  return launch_finish(a, dtype, job, none, DbiasJob{}, stream);
 }
 
-hipError_t launch_fwd_combine(const AttnArgs& a, int dtype, int max_splits, hipStream_t stream) {
-  return launch_combine<kCombineFwd>(a, dtype, fwd_block_rows(dtype, a.D), max_splits, stream);
-}
-
-hipError_t launch_dq_combine(const AttnArgs& a, int dtype, int max_splits, hipStream_t stream) {
-  return launch_combine<kCombineDQ>(a, dtype, dq_block_rows(dtype, a.D), max_splits, stream);
+hipError_t launch_bwd_finish(const AttnArgs& a, int dtype, const SchedHeader* const header[2], const SplitItem* const splits[2],
+                             const float* const partial[2], const DbiasJob& db, hipStream_t stream) {
+  const FinishJob dq = {header[0], splits[0], partial[0], kFinishDQ};
+  const FinishJob dkdv = {header[1], splits[1], partial[1], kFinishDKDV};
+  return launch_finish(a, dtype, dq, dkdv, db, stream);
 }
 
 }  // namespace hstu

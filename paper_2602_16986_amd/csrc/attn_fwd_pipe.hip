@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   HSTU_TL(2);
 
   // ---- epilogue.  Lane x holds features 32 ob + 8 (r / 4) + 4 hf + r % 4.
-  if (item.slot >= 0) {                                                 // a piece of a cut block: raw sums, the combine kernel finishes
+  if (item.slot >= 0) {                                                 // a piece of a cut block: raw sums, finish_kernel adds them up
     float* dst = a.partial + ((int64_t)item.slot * kBX + (wave * 32 + l32)) * kD;
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob)

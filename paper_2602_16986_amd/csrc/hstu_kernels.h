@@ -29,6 +29,7 @@ struct WorkItem {
 
 struct SplitItem {        // a row block whose pieces left partial sums in slots [first_slot, first_slot + pieces)
   int32_t b, rb_h, first_slot, pieces;
+  int32_t seq0, len, hist, unused;       // of its sequence, as in WorkItem
 };
 
 // Everything a kernel needs to know about the attention problem.
@@ -84,6 +85,9 @@ hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int ti
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
                                 const int slot_cap[2], const ExpandJob& ex, hipStream_t stream);
+// false: no list that the scheduler can build for this problem has a cut block (host arithmetic on bounds; host_offsets may be
+// nullptr).  which: 0 forward, 1 dQ list, 2 dK/dV list.
+bool schedule_may_cut(const AttnArgs& a, int which, int block_rows, int tile_cols, const int32_t* host_offsets);
 
 // attn_core.hip
 int fwd_block_rows(int dtype, int D);     // query rows per workgroup, forward
@@ -102,15 +106,19 @@ int attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* 
                           void* workspace, size_t workspace_bytes, void* stream);
 hipError_t launch_attn_bwd_dq(const AttnArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_attn_bwd_dkdv(const AttnArgs& a, int dtype, hipStream_t stream);
-// bias-table gradient: clear the per-distance sums, fold them into buckets (times `scale`) after the dQ pass
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream);
-hipError_t launch_dbias_reduce(const float* dist, const int32_t* bounds, int num_buckets, int H, int len, float scale,
-                               float* dtable, hipStream_t stream);
-// adds the partial sums of every cut key block in piece order, scales, converts and writes dK, dV
-hipError_t launch_dkdv_combine(const AttnArgs& a, int dtype, int max_splits, hipStream_t stream);
-// the same for query blocks of the forward whose key axis was cut (forward over a query tail): writes the output rows
-hipError_t launch_fwd_combine(const AttnArgs& a, int dtype, int max_splits, hipStream_t stream);
-hipError_t launch_dq_combine(const AttnArgs& a, int dtype, int max_splits, hipStream_t stream);
+// After the attention kernels: the outputs of cut blocks from their pieces' partial sums, and the bias-table gradient from the
+// sums per distance (AttnArgs::dbias_dist).  A null header: no block of that list is cut.
+struct FinishJob {
+  const SchedHeader* header; const SplitItem* splits; const float* partial;
+  int what;
+};
+struct DbiasJob { const int32_t* bounds; int num_buckets; float* dtable; };    // num_buckets = 0: not wanted
+hipError_t launch_fwd_finish(const AttnArgs& a, int dtype, const SchedHeader* header, const SplitItem* splits, const float* partial,
+                             hipStream_t stream);
+// [0]: dQ list, [1]: dK/dV list
+hipError_t launch_bwd_finish(const AttnArgs& a, int dtype, const SchedHeader* const header[2], const SplitItem* const splits[2],
+                             const float* const partial[2], const DbiasJob& db, hipStream_t stream);
 
 // gated_norm.hip
 // Row-wise layer norm with weight (and optional bias), optionally gated by U; row strides in elements.

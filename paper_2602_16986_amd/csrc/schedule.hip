@@ -21,6 +21,8 @@
 // the expansion in it: 10 blocks 4.9 us (11.3 with a comparison sort and 49 KB of unrolled code), 346 blocks of 512-2048-token
 // sequences 8.7 us (18.4 + 5.2 for the expansion's own launch), 690 blocks of 8k-16k tokens 9.4 us (27 + 5); of the last, 1.0 us
 // go to the offsets and their scan, 1.1 to pricing, 1.1 to each pass of the sort, 1.2 to writing the list.
+#include <cmath>
+
 #include "hstu_common.h"
 #include "hstu_kernels.h"
 
@@ -294,7 +296,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
         int unused;
         const WorkItem it = locate(idx, 1, false, unused);
 #pragma unroll 1
-        for (int h = 0; h < H; ++h) job.splits[rank * H + h] = SplitItem{it.b, it.rb_h | h, slot * H + h * pieces, pieces};
+        for (int h = 0; h < H; ++h) job.splits[rank * H + h] = SplitItem{it.b, it.rb_h | h, slot * H + h * pieces, pieces, it.seq0, it.len, it.hist, 0};
         slot += pieces;
         ++rank;
       }
@@ -442,6 +444,35 @@ hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_r
   const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, 1.0 / kDqTargetChunks, header[0], items[0], seq_base[0], splits[0]};
   const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, 1.0 / kTargetChunks, header[1], items[1], seq_base[1], splits[1]};
   return launch(a, lists ? 2 : 0, j0, j1, ex, stream);
+}
+
+// Most batches are cut nowhere, and a launch that would add up pieces costs 4.5 us for finding that out.  A block is cut
+// when it is longer than 2 x chunk, chunk >= kMinChunk and >= share x (all tiles).  The longest block is bounded by the longest
+// sequence and the mask, the tiles from below by the visible pairs, which takes the lengths: without a host copy of the offsets
+// only kMinChunk counts, and so it does with candidates (their counts are known on the device only) or a query tail.
+bool schedule_may_cut(const AttnArgs& a, int which, int block_rows, int tile_cols, const int32_t* host_offsets) {
+  const bool key_major = which == 2, by_position = a.num_targets == nullptr && a.query_tail == 0;
+  const double share = 1.0 / (which == 0 ? kFwdTargetChunks : which == 1 ? kDqTargetChunks : kTargetChunks);
+  double longest = a.max_seqlen, pairs = 0.0;
+  if (host_offsets) {
+    longest = 0.0;
+    for (int b = 0; b < a.B; ++b) {
+      const double L = host_offsets[b + 1] - host_offsets[b];
+      longest = L > longest ? L : longest;
+      pairs += a.K1 < 0 || L <= a.K1 ? 0.5 * L * L : a.K1 * (L - 0.5 * a.K1);       // (those of a global prefix left out)
+    }
+  }
+  double most = ceil(longest / tile_cols);               // tiles of the longest block
+  if (a.K1 >= 0 && by_position && !(key_major && a.K2 > 0)) {
+    const double band = floor((double)(block_rows + a.K1) / tile_cols) + 2, prefix = key_major ? 0 : ceil((double)a.K2 / tile_cols);
+    if (band + prefix < most) most = band + prefix;
+  }
+  double chunk = kMinChunk;
+  if (by_position) {
+    const double tiles = ceil(share * pairs * a.H / ((double)block_rows * tile_cols) * (1 - 1e-9));
+    if (tiles > chunk) chunk = tiles;
+  }
+  return most > 2 * chunk;
 }
 
 }  // namespace hstu
