@@ -105,9 +105,14 @@ typedef struct hstu_attn_params {
 } hstu_attn_params;
 
 /* Bytes of device scratch (256-byte aligned) that hstu_attn_fwd (for_backward = 0)
- * or hstu_attn_bwd (for_backward != 0) needs for this problem.  Depends only on
- * batch, num_heads, head_dim, total_tokens, max_seqlen and dtype.  Returns 0 for an
- * invalid description (the compute call then reports the error).  The backward figure
+ * or hstu_attn_bwd (for_backward != 0) can use for this problem.  Depends on
+ * batch, num_heads, head_dim, total_tokens, max_seqlen, dtype and, for the backward, on the mask and the host copy of the
+ * offsets.  Returns 0 for an invalid description (the compute call then reports the error).
+ * bf16 backward with head_dim 128: the figure ends with room for dS (2 bytes per pair of every 32 x 128 tile that holds a visible
+ * pair: 4.2 GB for eight sequences of 8k-16k tokens and 4 heads, dense causal; 1.2 GB under a 1024 + 256 semi-local mask), which
+ * the dK/dV pass leaves for the dQ product, up to 16 GiB; a problem that would take more gets none.  hstu_attn_bwd also accepts a
+ * workspace without that room (any size from the figure's other parts on) and then recomputes the scores for dQ.  Without a
+ * host copy of the offsets the room is a bound from total_tokens and max_seqlen.  The backward figure
  * includes fp32 partial-sum slots for key blocks that the scheduler cuts along the query
  * axis (at most 768 x 2 x 128 x head_dim floats, about 100 MB at head_dim 128) and for query blocks that the dQ pass cuts
  * along the key axis (768 x 128 x head_dim floats); the forward figure includes the same kind of slots for its query blocks
@@ -127,8 +132,8 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
 /* Backward of Eq. 3 (attention_backward(dattn, q, k, v) -> dq, dk, dv): the scores are
  * recomputed from q, k; nothing saved by the forward is needed.  dout uses row_stride_o,
  * dq/dk/dv use the strides of q/k/v.  dq, dk, dv are deterministic: no atomics; partial sums
- * of cut blocks (key blocks of a global prefix; query blocks of a small batch) are added in a fixed order.  With p->d_rab_table set the dQ pass also sums
- * dS per distance with fp32 atomics (run-to-run differences at rounding level) and a small
+ * of cut blocks (key blocks of a global prefix; query blocks of a small batch) are added in a fixed order.  With p->d_rab_table set the pass that
+ * forms dS also sums it per distance with fp32 atomics (run-to-run differences at rounding level) and a small
  * kernel folds the distances into buckets. */
 int hstu_attn_bwd(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* dout,
                   void* dq, void* dk, void* dv, void* workspace, size_t workspace_bytes, void* stream);

@@ -5,6 +5,7 @@
 #include "hstu_kernels.h"
 #include "profile.h"
 
+#include <algorithm>
 #include <mutex>
 
 using namespace hstu;
@@ -20,7 +21,7 @@ inline int64_t max_items_for(const hstu_attn_params* p, int block_rows) {
 }
 
 struct Layout {           // byte offsets inside a workspace
-  size_t header[2], items[2], seq_base[2], bias, seed, splits, partial, splits_dq, partial_dq, dbias, total;
+  size_t header[2], items[2], seq_base[2], bias, seed, splits, partial, splits_dq, partial_dq, dbias, ds_table, total, ds, total_ds;
   int max_items[2];
   int slot_cap;           // partial-sum slots of the dK/dV pass (key blocks cut along the query axis) or of the forward
   int slot_cap_dq;        // ... of the dQ pass (query blocks of a small batch cut along the key axis)
@@ -31,6 +32,34 @@ struct Layout {           // byte offsets inside a workspace
 // masks never have one block much longer than the rest of its sequence... they may still be cut when sequences differ
 // a lot in length, which the same bound covers).
 inline int slot_cap_for(int max_items) { return max_items < 384 ? 2 * max_items : 768; }
+
+// dS tiles (32 queries x 128 keys) that the dK/dV pass can leave for the dQ product: an upper bound over all heads.  From the host
+// copy of the lengths where there is one, else from the longest sequence; candidates (their counts are known on the device only) can
+// add whole columns for the key blocks that the window in front of position n reaches.
+int64_t ds_tiles_bound(const hstu_attn_params* p) {
+  const int64_t K1 = p->local_window < (1 << 28) ? p->local_window : (1 << 28), K2 = p->global_prefix < (1 << 28) ? p->global_prefix : (1 << 28);
+  const int64_t wide = K1 >= 0 ? (K1 + 158) / 32 : 0, cand_blocks = p->num_targets && K1 >= 0 ? K1 / 128 + 2 : 0;
+  auto of = [&](int64_t L) -> int64_t {
+    const int64_t nq = (L + 31) / 32, nk = (L + 127) / 128;
+    const int64_t dense = nk * nq - 2 * nk * (nk - 1);
+    if (K1 < 0) return dense;
+    const int64_t pre = std::min(nk, (K2 + 127) / 128);
+    return std::min(dense, pre * nq - 2 * pre * (pre - 1) + (nk - pre) * wide + std::min(nk, cand_blocks) * nq);
+  };
+  int64_t tiles = 0;
+  if (p->seq_offsets_host) {
+    for (int b = 0; b < p->batch; ++b) tiles += of((int64_t)p->seq_offsets_host[b + 1] - p->seq_offsets_host[b]);
+  } else {
+    const int64_t most = std::min(p->max_seqlen, p->total_tokens), blocks = (int64_t)p->total_tokens / 128 + p->batch;
+    const int64_t nq = (most + 31) / 32, nk = (most + 127) / 128;
+    tiles = blocks * (2 * nk + 2);
+    if (K1 >= 0) tiles = std::min(tiles, p->batch * (std::min(nk, (K2 + 127) / 128) + std::min(nk, cand_blocks)) * nq + blocks * wide);
+  }
+  return tiles * p->num_heads;
+}
+// 1/18 of the card's memory: eight sequences of 16k tokens with eight heads under the dense mask; beyond it the two passes stay
+// independent of each other (dQ recomputes S and dP).
+constexpr int64_t kDsMaxBytes = (int64_t)16 << 30;
 
 // One schedule for the forward; two (dQ pass, dK/dV pass) for the backward.
 Layout make_layout(const hstu_attn_params* p, int for_backward) {
@@ -72,8 +101,15 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     off += align_up((size_t)l.slot_cap_dq * dq_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
     l.dbias = off;                                     // per-distance sums of dS for the bias-table gradient, then the bucket ends per distance
     off += align_up((size_t)(p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
+    // dS, behind everything else: a workspace without room for it is accepted (32 and 64 features: a dQ product would move as many
+    // bytes as for 128 and save a half or a quarter of the matrix work)
+    const bool ds = p->dtype == HSTU_BF16 && p->head_dim == 128 && (int64_t)p->total_tokens / 128 + p->batch <= schedule_sorted_pairs();
+    if (ds) { l.ds_table = off; off += align_up(((size_t)p->total_tokens / 128 + p->batch) * 16); }
+    const int64_t bytes = ds ? ds_tiles_bound(p) * kDsTileBytes : 0;
+    if (bytes > 0 && bytes <= kDsMaxBytes) { l.ds = off; l.total_ds = off + (size_t)bytes; }
   }
   l.total = off;
+  if (l.total_ds == 0) l.total_ds = l.total;
   return l;
 }
 
@@ -221,7 +257,7 @@ const char* hstu_status_string(int status) {
 
 size_t hstu_attn_workspace_bytes(const hstu_attn_params* p, int for_backward) {
   if (validate(p) != HSTU_OK) return 0;
-  return make_layout(p, for_backward).total;
+  return make_layout(p, for_backward).total_ds;
 }
 
 int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const void* v, void* out, void* workspace,
@@ -268,6 +304,10 @@ int hstu_attn_bwd(const hstu_attn_params* p, const void* q, const void* k, const
 
 }  // extern "C"
 
+size_t hstu::attn_workspace_least(const hstu_attn_params* p, int for_backward) {
+  return validate(p) != HSTU_OK ? 0 : make_layout(p, for_backward).total;
+}
+
 int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* pre_q,
                                 const void* pre_k, const void* pre_v, int64_t s_pre, const void* dout, void* dq, void* dk,
                                 void* dv, void* workspace, size_t workspace_bytes, void* stream_) {
@@ -299,6 +339,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   AttnArgs a = make_args(p, q, k, v);
   a.dout = dout; a.dq = dq; a.dk = dk; a.dv = dv;
   a.pre_q = pre_q; a.pre_k = pre_k; a.pre_v = pre_v; a.s_pre = s_pre;
+  const bool ds_room = l.ds != 0 && workspace_bytes >= l.total_ds;
   const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
   const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
   {
@@ -309,20 +350,31 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     int32_t* const sb[2] = {(int32_t*)(ws + l.seq_base[0]), (int32_t*)(ws + l.seq_base[1])};
     SplitItem* const sp[2] = {(SplitItem*)(ws + l.splits_dq), (SplitItem*)(ws + l.splits)};
     const int caps[2] = {l.slot_cap_dq, l.slot_cap};
-    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ex, stream) != hipSuccess)
+    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ds_room ? (int32_t*)(ws + l.ds_table) : nullptr,
+                             (int64_t)(l.total_ds - l.ds) / kDsTileBytes, ex, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }
   const SchedHeader* headers[2];
   const SplitItem* const splits[2] = {(const SplitItem*)(ws + l.splits_dq), (const SplitItem*)(ws + l.splits)};
   const float* const partial[2] = {(const float*)(ws + l.partial_dq), (const float*)(ws + l.partial)};
-  for (int s = 0; s < 2; ++s) {                          // s = 0: dQ pass (query blocks), s = 1: dK/dV pass (key blocks)
+  const bool through_ds = ds_room;
+  if (through_ds) {
+    a.ds = ws + l.ds;
+    a.ds_table = (const int32_t*)(ws + l.ds_table);
+    a.ds_pair0 = (const int32_t*)(ws + l.seq_base[1]);
+    a.ds_header = (const SchedHeader*)(ws + l.header[1]);
+  }
+  for (int i = 0; i < 2; ++i) {
+    const int s = through_ds ? 1 - i : i;                // s = 0: dQ pass (query blocks), s = 1: dK/dV pass (key blocks)
     a.max_items = l.max_items[s];
     a.header = headers[s] = (const SchedHeader*)(ws + l.header[s]);
     a.items = (const WorkItem*)(ws + l.items[s]);
     a.partial = const_cast<float*>(partial[s]);
     a.splits = splits[s];
     ProfScope ps(s == 0 ? "attn_bwd_dq" : "attn_bwd_dkdv", stream);
-    if ((s == 0 ? launch_attn_bwd_dq(a, p->dtype, stream) : launch_attn_bwd_dkdv(a, p->dtype, stream)) != hipSuccess) return HSTU_ERR_LAUNCH;
+    const hipError_t e = s == 1 ? launch_attn_bwd_dkdv(a, p->dtype, stream)
+                                : (through_ds ? launch_attn_dq_from_ds(a, stream) : launch_attn_bwd_dq(a, p->dtype, stream));
+    if (e != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   for (int s = 0; s < 2; ++s)
     if (!schedule_may_cut(a, 1 + s, rows[s], cols[s], p->seq_offsets_host)) headers[s] = nullptr;

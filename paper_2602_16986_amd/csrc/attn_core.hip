@@ -155,6 +155,39 @@ __device__ __forceinline__ void diag_all(std::integer_sequence<int, R...>, const
   (diag_step<R>(vals, bq, x0, x1, x2), ...);
 }
 
+// The same sums for the dK/dV pass, shared out over a whole wave: of a 32 x 32 block of dS (lane = key l32, register R of half-wave hf =
+// query 8 (R / 4) + 4 hf + R % 4) the sum over the pairs with query - key = o lands at lane -o mod 64, part 0 of it plus part 1 of the
+// lane 4 further (the upper half-wave's queries are 4 further).  The rotations shift zeros in, so that a value and what comes around
+// the row end go to their sums without a select: two adds per register.
+template <int CTRL>
+__device__ __forceinline__ float dpp0(float v) {                         // the value DPP control CTRL brings, 0 where it brings none
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int R>
+__device__ __forceinline__ void key_diag_step(float v, float& x0, float& x1, float& x2) {
+  constexpr int q = R >> 2, rho = 8 * (q & 1) + (R & 3);
+  float& lo = (q >> 1) == 0 ? x0 : x1;
+  float& hi = (q >> 1) == 0 ? x1 : x2;
+  if constexpr (rho == 0) {
+    lo += v;
+  } else {
+    lo += dpp0<0x100 + rho>(v);                                          // row_shl: lane b of a row reads lane b + rho
+    hi += dpp0<0x110 + 16 - rho>(v);                                     // row_shr: ... lane b + rho - 16
+  }
+}
+template <int... R, typename V>
+__device__ __forceinline__ void key_diag_all(std::integer_sequence<int, R...>, const V& vals, float& part0, float& part1) {
+  float x0 = 0.f, x1 = 0.f, x2 = 0.f;
+  (key_diag_step<R>(vals[R], x0, x1, x2), ...);
+  // row g of a half-wave is 16 keys further: its class j meets class j - g of row 0
+  const uint32_t m = __builtin_bit_cast(uint32_t, x1);
+  x0 += __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_permlane16_swap(m, 0u, false, false)[1]);
+  x2 += __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_permlane16_swap(0u, m, false, false)[0]);
+  const auto parts = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x0), __builtin_bit_cast(uint32_t, x2), false, false);
+  part0 = __builtin_bit_cast(float, (uint32_t)parts[0]);                 // queries of the lower half-wave ...
+  part1 = __builtin_bit_cast(float, (uint32_t)parts[1]);                 // ... and of the upper one
+}
+
 // DBIAS (dQ pass only): also sum dS along the diagonals of every tile (pairs of equal distance i - j) into
 // a.dbias_dist[h, distance]; finish_kernel folds distances into buckets afterwards.
 // CAND (batches with candidate rows): the fast paths also cover candidate rows against history keys.  A candidate row
@@ -168,9 +201,11 @@ __device__ __forceinline__ float dsilu(float t) {
   return sg * (1.0f + t * (1.0f - sg));
 }
 
-template <typename E, int D, int MODE, int NWAVES, bool DBIAS = false, bool CAND = false>
+template <typename E, int D, int MODE, int NWAVES, bool DBIAS = false, bool CAND = false, bool DS = false>
 __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) void attn_kernel(const AttnArgs a) {
-  static_assert(!DBIAS || MODE == kBwdDQ, "the bias gradient rides with the dQ pass");
+  static_assert(!DBIAS || MODE == kBwdDQ || DS, "the bias gradient rides with the dQ pass, or with the dK/dV pass that hands dS on");
+  constexpr bool DBQ = DBIAS && MODE == kBwdDQ, DBK = DBIAS && MODE == kBwdDKDV;
+  static_assert(!DS || (MODE == kBwdDKDV && sizeof(E) == 2 && D == 128), "dS is handed on by the dK/dV pass");
   constexpr bool CANDQ = CAND && MODE != kBwdDKDV, CANDK = CAND && MODE == kBwdDKDV;
   using C = Cfg<E, D, MODE, NWAVES>;
   using RFrag = typename ResidentFrag<E>::type;
@@ -387,10 +422,26 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
 #pragma unroll
     for (int c = 0; c < C::CPT; ++c) gload_piece(c, stage);
   };
-  auto lstore = [&](int stage) {
+  // DS: this wave's 32 keys x 32 queries of dS of a tile leave as the two 1 KB halves that attn_dq.hip reads back (queries 0..15 and
+  // 16..31 of the tile, lane slots swizzled for its transpose reads): exactly two stores per tile, behind the tile's loads.
+  unsigned char* ds_tile = nullptr;                        // this wave's part of the tile (a block's tiles are consecutive)
+  if constexpr (DS) {
+    const int pair = a.ds_pair0[item.b] + (L - 1) / C::BX - xb;
+    const int base = a.ds_table[4 * pair], cost = a.ds_table[4 * pair + 2];
+    ds_tile = (unsigned char*)a.ds + (int64_t)(base + h * cost + t_begin) * kDsTileBytes + wave * (kDsTileBytes / 4);
+  }
+  const uint32_t ds_voff = (uint32_t)((32 * hf + (l32 ^ (8 * hf))) * 16);
+  auto ds_store = [&](int half, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+    uint32_t voff = ds_voff;
+    asm volatile("" : "+v"(voff));                         // (else the whole address becomes a vector that the loop advances)
+    __builtin_nontemporal_store((u32x4){w0, w1, w2, w3}, (u32x4*)(ds_tile + (voff ^ (uint32_t)(64 * half)) + 1024u * half));
+  };
+  auto lstore = [&](int stage, bool behind_stores) {
     // this wave's direct-to-LDS pieces (strip runs, 256-byte-row tiles) have landed once its load counter
     // drains; the barrier that follows publishes them to the other waves
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (DS: the tile's two stores came after them and may still be on their way)
+    if (DS && behind_stores) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if constexpr (!C::kDma) {
 #pragma unroll
       for (int c = 0; c < C::CPT; ++c) {
@@ -416,12 +467,12 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       dma16(tile_rsrc(R2, rowb, x0 + 4 * rg), voff, dst);
     }
   }
-  // ---- bias gradient (DBIAS): dacc[p][s] collects dS of tile parity p along strip index
+  // ---- bias gradient (DBQ): dacc[p][s] collects dS of tile parity p along strip index
   // s = (y - tile start) + (BX - 1 - (x - x0)), i.e. distance x - y = x0 + BX - 1 - tile start - s
   float* dacc = (float*)(smem + C::DACC_BASE);
   const int dacc_lane = wave * C::DACC_LEN + C::BX - 1 - wave * 32 + 4 * hf - (lane & 15) - 16 * ((lane >> 4) & 1);   // + 32 * sub-block + 16 * class
   auto dacc_flush = [&](int parity, int yt_of) {                         // every wave has passed the barrier after that tile
-    if constexpr (DBIAS) {
+    if constexpr (DBQ) {
       if (a.dbias_dist && tid < C::BX + C::BN - 1) {
         float vsum = 0.f;
 #pragma unroll
@@ -476,7 +527,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     }
   };
   auto run_flush = [&]() {
-    if constexpr (DBIAS) { run_flush_slot(run_sum0, run_end0, run_dist0); run_flush_slot(run_sum1, run_end1, run_dist1); }
+    if constexpr (DBQ) { run_flush_slot(run_sum0, run_end0, run_dist0); run_flush_slot(run_sum1, run_end1, run_dist1); }
   };
   auto run_to = [&](int end, int dist, float v) {                        // adds v to the bucket that ends at `end` (dist: one of its distances)
     if (run_end0 == end) run_sum0 += v;
@@ -504,13 +555,53 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     run_to(end, dist, total - hi);
     run_to(end2, end, hi);
   };
-  if constexpr (DBIAS) {
+  if constexpr (DBQ) {
     for (int i = tid; i < 2 * C::DACC_COPIES * C::DACC_LEN; i += C::NT) dacc[i] = 0.f;
   }
+  // ---- bias gradient in the dK/dV pass (DBK).  A tile of this wave whose 63 distances lie in one bucket of the table adds the plain
+  // sum of its dS, kept per lane until the bucket is left.  Any other tile adds along its diagonals: lane l of `win` collects
+  // distance win_y0 - xw0 + o, o = -l mod 64 in [-31, 32]; the next tile is 32 queries further, so the lower half of the window is
+  // complete then and leaves for the table of sums per distance, and the upper half becomes the lower one.
+  constexpr int kNoWindow = -(1 << 30);
+  float win = 0.f, run_k = 0.f;
+  int win_y0 = kNoWindow, run_k_end = 0, run_k_dist = 0;
+  float* const dist_h = DBK ? a.dbias_dist + (int64_t)h * a.bias_stride : nullptr;
+  auto dist_add = [&](int dist, float v) {
+    if (v != 0.f && (uint32_t)dist < (uint32_t)a.bias_stride) atomicAdd(dist_h + dist, v);
+  };
+  auto win_flush = [&]() {
+    if (win_y0 != kNoWindow) dist_add(win_y0 - xw0 + (lane < 32 ? -lane : 64 - lane), win);
+    win = 0.f;
+    win_y0 = kNoWindow;
+  };
+  auto run_k_flush = [&]() {
+    if (run_k_end != 0) {
+      float v = run_k;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+      if (lane == 0) dist_add(run_k_dist, v);
+    }
+    run_k = 0.f;
+    run_k_end = 0;
+  };
+  auto win_add = [&](const auto& vals, int y0_) {          // the tile's 16 dS of this lane, history queries
+    if (win_y0 == y0_ - C::BN) {
+      const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, win), 0u, false, false);
+      if (lane < 32) dist_add(win_y0 - xw0 - lane, __builtin_bit_cast(float, (uint32_t)halves[0]));
+      win = __builtin_bit_cast(float, (uint32_t)halves[1]);
+    } else {
+      win_flush();
+    }
+    win_y0 = y0_;
+    float part0, part1;
+    key_diag_all(std::make_integer_sequence<int, 16>{}, vals, part0, part1);
+    win += part0;
+    win += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * ((lane + 4) & 63), __builtin_bit_cast(int, part1)));
+  };
   set_next(t_begin < ntiles ? tr.at(t_begin) : 0, t_begin < ntiles);
   gload(0);
   finish_resident();
-  lstore(0);
+  lstore(0, false);
   __syncthreads();
   HSTU_TLB(1);
 
@@ -523,15 +614,15 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     const int stage = (t - t_begin) & 1;
     const bool has_next = t + 1 < ntiles;
     set_next(has_next ? tr.at(t + 1) : 0, has_next);
-    if constexpr (DBIAS) {
+    if constexpr (DBQ) {
       if (t > t_begin && !prev_fast) dacc_flush(stage ^ 1, tr.at(t - 1));
     }
     const unsigned char* y1s = smem + stage * C::STAGE_BYTES;
     const unsigned char* y2s = y1s + C::TILE0;
     const int y0 = yt * C::BN;
-    bool wg_fast = false;                                                 // DBIAS: the whole block's pairs of this tile lie in one or two buckets
+    bool wg_fast = false;                                                 // DBQ: the whole block's pairs of this tile lie in one or two buckets
     int fast_end = 0, fast_dist = 0, fast_end2 = 0;
-    if constexpr (DBIAS) {
+    if constexpr (DBQ) {
       const int xhi = x0 + C::BX - 1, dmin_b = x0 - (y0 + C::BN - 1);
       if (a.bucket_end && a.dbias_dist && dmin_b >= 0 && xhi < g.n && classify_tile(g, x0, xhi, y0, y0 + C::BN - 1, false) == kTileFull) {
         fast_end = a.bucket_end[dmin_b];
@@ -551,14 +642,17 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     // for batches with candidates, but not with the bias gradient, which adds the dS of candidate rows to the table by the
     // distance n - j one by one: those take the masked path.
     int kind = (MODE == kBwdDKDV) ? classify_tile(g, y0, y0 + C::BN - 1, xw0, xw0 + 31, CANDK)
-                                  : classify_tile(g, xw0, xw0 + 31, y0, y0 + C::BN - 1, CANDQ && !DBIAS);
+                                  : classify_tile(g, xw0, xw0 + 31, y0, y0 + C::BN - 1, CANDQ && !DBQ);
     if (xw0 >= L || xw0 + 31 < q0) kind = kTileEmpty;
 
     // The next tile's global loads are issued piecewise between the score products: the compute unit's
     // memory pipeline takes a 16-byte-per-lane load every few tens of cycles, and a wave that issues
     // its whole share at once sits in that queue instead of feeding the matrix pipe.  A wave with
     // nothing to compute issues them all now.
-    if (kind == kTileEmpty) gload(stage ^ 1);
+    if (kind == kTileEmpty) {
+      gload(stage ^ 1);
+      if constexpr (DS) { ds_store(0, 0u, 0u, 0u, 0u); ds_store(1, 0u, 0u, 0u, 0u); }
+    }
 
     // Swizzled (direct-to-LDS) tiles: LDS addresses are formed next to each read with one XOR instead of
     // being kept as loop invariants (one register per k-step / feature block otherwise).  For tile row
@@ -623,7 +717,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
         };
         f32x16 sv[2], dp[2];
         uint32_t pds[2][8], pp[2][8];
-        float dsf[DBIAS ? 2 : 1][16];                                      // dS in fp32 for the bias gradient
+        float dsf[DBQ ? 2 : 1][16];                                      // dS in fp32 for the bias gradient
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
           if (bias_h) {
@@ -647,7 +741,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           const float ds0 = dp[sb][2 * m] * dsilu_l2(p0v, g0), ds1 = dp[sb][2 * m + 1] * dsilu_l2(p1v, g1);
           pds[sb][m] = pack_bf16x2(ds0, ds1);
           if constexpr (MODE == kBwdDKDV) pp[sb][m] = pack_bf16x2(p0v, p1v);
-          if constexpr (DBIAS) { dsf[sb][2 * m] = ds0; dsf[sb][2 * m + 1] = ds1; }
+          if constexpr (DBQ) { dsf[sb][2 * m] = ds0; dsf[sb][2 * m + 1] = ds1; }
         };
         constexpr int PF = (MODE == kBwdDQ) ? 2 : 4;                      // the dQ pass runs two waves per SIMD: 256 registers
         bf16x8 fr[PF];
@@ -665,7 +759,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           if (n >= 16 && (n & 1)) pointwise(0, (n - 16) >> 1);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (DBIAS) {                                            // fully visible tile: history rows, distance x - y
+        if constexpr (DBQ) {                                            // fully visible tile: history rows, distance x - y
           if (wg_fast) run_add(dsf[0], 0, y0, fast_end, fast_dist, fast_end2); else dacc_add(stage, 0, dsf[0]);
         }
         constexpr int NO = 16 * C::NOUT;                                  // output products of the tile
@@ -684,7 +778,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           if (sb == 0 && o == C::NOUT - 1) pointwise(1, step);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (DBIAS) {
+        if constexpr (DBQ) {
           if (wg_fast) run_add(dsf[1], 1, y0, fast_end, fast_dist, fast_end2); else dacc_add(stage, 1, dsf[1]);
         }
         done = true;
@@ -703,6 +797,11 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       // first 16-row k-step of the output products.)
       const bool tile_hist_f = min(y0 + C::BN, L) - 1 < g.n;               // candidate queries take the general path
       if (kind == kTileFull && (!CANDK || tile_hist_f)) {
+        int one_end = 0;                                                 // DBK: the end of the bucket that holds all the tile's distances
+        if constexpr (DBK) {
+          const int end = ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.bucket_end)[y0 - xw0 - 31];
+          if (end > y0 + C::BN - 1 - xw0) one_end = end;
+        }
         f32x16 sv, dp;
         if (bias_h) {
           const float* strip = (const float*)(smem + C::STRIP_BASE + stage * C::STRIP_BYTES) + strip_lane;
@@ -732,7 +831,9 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           if (r & 1) { pp[r >> 1] = pack_bf16x2(sv[r - 1], sv[r]); asm volatile("" : "+v"(pp[r >> 1])); }
         };
         auto DS_ = [&](int m) {                                           // registers 2m, 2m + 1
-          pds[m] = pack_bf16x2(dp[2 * m] * fac[2 * m], dp[2 * m + 1] * fac[2 * m + 1]);
+          const float ds0 = dp[2 * m] * fac[2 * m], ds1 = dp[2 * m + 1] * fac[2 * m + 1];
+          pds[m] = pack_bf16x2(ds0, ds1);
+          if constexpr (DBK) { dp[2 * m] = ds0; dp[2 * m + 1] = ds1; }
           asm volatile("" : "+v"(pds[m]));
         };
         // what slot `sl` carries of the chain (register r: E in slot 6 + r, but not before slot 8; R one slot later; F two)
@@ -786,7 +887,26 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           }
           __builtin_amdgcn_sched_barrier(0);
           chain(n);
+          if constexpr (DS) {
+            if (n == 20) ds_store(0, pds[0], pds[1], pds[2], pds[3]);
+            if (n == 28) ds_store(1, pds[4], pds[5], pds[6], pds[7]);
+          }
           __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (DBK) {
+          if (one_end != 0) {                                            // (distances ascend: a bucket that is left does not come back)
+            if (one_end != run_k_end) {
+              run_k_flush();
+              run_k_end = one_end;
+              run_k_dist = y0 - xw0 - 31;
+            }
+            float t0 = dp[0], t1 = dp[1];
+#pragma unroll
+            for (int r = 2; r < 16; r += 2) { t0 += dp[r]; t1 += dp[r + 1]; }
+            run_k += t0 + t1;
+          } else {
+            win_add(dp, y0);
+          }
         }
         done = true;
       }
@@ -1001,7 +1121,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           }
         }
 
-        if constexpr (DBIAS) {
+        if constexpr (DBQ) {
           // dS per distance: history rows add along the tile's diagonals in LDS; candidate rows (their distance
           // is n - j, not i - j) are few and add to the global table directly
 #pragma unroll
@@ -1018,6 +1138,21 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             }
             if (wg_fast) run_add(hv, sg + u, y0, fast_end, fast_dist, fast_end2); else dacc_add(stage, sg + u, hv);
           }
+        }
+
+        if constexpr (DBK) {
+          // candidate queries stand at position n: one distance per key (their own key: distance 0)
+          float hv[16];
+          const int nh = g.n - y0 - 4 * hf;                                  // c < nh  <=>  history query
+#pragma unroll
+          for (int r = 0; r < 16; ++r) hv[r] = 8 * (r >> 2) + (r & 3) < nh ? c1[0][r] : 0.f;
+          if (CANDK && y0 + C::BN > g.n) {
+            float cand = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) cand += 8 * (r >> 2) + (r & 3) < nh ? 0.f : c1[0][r];
+            dist_add(x < g.n ? g.n - x : 0, cand);
+          }
+          if (y0 < g.n) win_add(hv, y0);
         }
 
         // ---- second products: out^T[feature][x] += Y^T[feature][y] * coeff[y][x]
@@ -1038,6 +1173,11 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
               pk1[u][m] = pack_bf16x2(c1[u][2 * m], c1[u][2 * m + 1]);
               if (MODE == kBwdDKDV) pk2[u][m] = pack_bf16x2(c2[u][2 * m], c2[u][2 * m + 1]);
             }
+          if constexpr (DS) {
+            static_assert(SBG == 1 && NSB == 1, "one sub-block per tile");
+            ds_store(0, pk1[0][0], pk1[0][1], pk1[0][2], pk1[0][3]);
+            ds_store(1, pk1[0][4], pk1[0][5], pk1[0][6], pk1[0][7]);
+          }
           bf16x8 a1[2], a2[2];
           a1[0] = fetch(0, TSRC);
           if (MODE == kBwdDKDV) a2[0] = fetch(0, 1);
@@ -1079,14 +1219,16 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       }
     }
 
-    lstore(stage ^ 1);                                      // also after the last tile: its (empty) loads must have landed before the LDS is given up
+    if constexpr (DS) ds_tile += kDsTileBytes;
+    lstore(stage ^ 1, true);                                // also after the last tile: its (empty) loads must have landed before the LDS is given up
     __syncthreads();
   }
 
-  if constexpr (DBIAS) {
+  if constexpr (DBQ) {
     if (ntiles > t_begin && !prev_fast) dacc_flush((ntiles - 1 - t_begin) & 1, tr.at(ntiles - 1));
     run_flush();
   }
+  if constexpr (DBK) { win_flush(); run_k_flush(); }
   HSTU_TLB(2);
   // ---- epilogue: scale once, convert, store.  Lane x holds features ob*32 + 8*(r/4) + 4*hf + r%4.
   {
@@ -1241,11 +1383,11 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(const AttnArgs a
 }
 
 // ------------------------------------------------------------------------------------------------
-template <typename E, int D, int MODE, int NWAVES, bool DBIAS = false, bool CAND = false>
+template <typename E, int D, int MODE, int NWAVES, bool DBIAS = false, bool CAND = false, bool DS = false>
 static hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
   using C = Cfg<E, D, MODE, NWAVES>;
-  auto kern = attn_kernel<E, D, MODE, NWAVES, DBIAS, CAND>;
-  constexpr int smem_bytes = C::SMEM_BYTES + (DBIAS ? C::DACC_BYTES : 0);
+  auto kern = attn_kernel<E, D, MODE, NWAVES, DBIAS, CAND, DS>;
+  constexpr int smem_bytes = C::SMEM_BYTES + (DBIAS && MODE == kBwdDQ ? C::DACC_BYTES : 0);
   static bool attr_set[64] = {};                                         // per instantiation and device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
@@ -1317,6 +1459,12 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream) {
 }
 
 hipError_t launch_attn_bwd_dkdv(const AttnArgs& a, int dtype, hipStream_t stream) {
+  if (a.ds) {
+    if (a.dbias_dist && a.num_targets) return launch_one<__bf16, 128, kBwdDKDV, kDkvWavesBf16, true, true, true>(a, stream);
+    if (a.dbias_dist) return launch_one<__bf16, 128, kBwdDKDV, kDkvWavesBf16, true, false, true>(a, stream);
+    if (a.num_targets) return launch_one<__bf16, 128, kBwdDKDV, kDkvWavesBf16, false, true, true>(a, stream);
+    return launch_one<__bf16, 128, kBwdDKDV, kDkvWavesBf16, false, false, true>(a, stream);
+  }
   if (a.num_targets) return dispatch<kBwdDKDV, kDkvWavesBf16, kDkvWavesFp32, false, true>(a, dtype, stream);
   return dispatch<kBwdDKDV, kDkvWavesBf16, kDkvWavesFp32>(a, dtype, stream);
 }

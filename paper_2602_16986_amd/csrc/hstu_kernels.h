@@ -62,7 +62,15 @@ struct AttnArgs {
   // semi-local mask) also has -1e30 for d >= K1.  seed_dmax >= max_seqlen + 128, seed_len >= seed_dmax + 1 + 192.
   const float* seed;
   int32_t seed_len, seed_dmax;
+  // Backward, bf16 with 128 features, optional: dS in bf16, handed from the dK/dV pass to the dQ product (attn_dq.hip says in
+  // which layout).  ds_table[4 p ..]: of (sequence, key block) pair p of the dK/dV list: its first tile of 32 queries x 128 keys in
+  // `ds` over all heads, the first query tile it visits, the number of them; pairs of sequence b start at ds_pair0[b], last block first.
+  void* ds;
+  const int32_t* ds_table;
+  const int32_t* ds_pair0;
+  const SchedHeader* ds_header;     // of the dK/dV list: bad_batch = no dS was left
 };
+constexpr int kDsTileBytes = 32 * 128 * 2;
 constexpr int kSeedVariants = 2;
 inline int seed_dmax_for(int max_seqlen) { return max_seqlen + 128; }
 inline int seed_len_for(int max_seqlen) { return (seed_dmax_for(max_seqlen) + 1 + 192 + 63) / 64 * 64; }
@@ -81,13 +89,17 @@ struct ExpandJob {
 // partial sums in `slot_cap` slots, listed in `splits`.
 hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
                            int32_t* seq_base, SplitItem* splits, int slot_cap, const ExpandJob& ex, hipStream_t stream);
-// The two lists of the backward pass: [0] query blocks (dQ pass), [1] key blocks (dK/dV pass).
+// The two lists of the backward pass: [0] query blocks (dQ pass), [1] key blocks (dK/dV pass).  ds_table: AttnArgs::ds_table to fill
+// (with seq_base[1] as AttnArgs::ds_pair0), or nullptr; ds_cap: the dS tiles
+// there is room for; at most schedule_sorted_pairs() pairs.
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], const ExpandJob& ex, hipStream_t stream);
+                                const int slot_cap[2], int32_t* ds_table, int64_t ds_cap, const ExpandJob& ex, hipStream_t stream);
 // false: no list that the scheduler can build for this problem has a cut block (host arithmetic on bounds; host_offsets may be
 // nullptr).  which: 0 forward, 1 dQ list, 2 dK/dV list.
 bool schedule_may_cut(const AttnArgs& a, int which, int block_rows, int tile_cols, const int32_t* host_offsets);
+
+int schedule_sorted_pairs();              // lists of up to this many (sequence, block) pairs are sorted
 
 // attn_core.hip
 int fwd_block_rows(int dtype, int D);     // query rows per workgroup, forward
@@ -104,7 +116,11 @@ hipError_t launch_attn_fwd_pipe(const AttnArgs& a, hipStream_t stream);
 int attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* pre_q,
                           const void* pre_k, const void* pre_v, int64_t s_pre, const void* dout, void* dq, void* dk, void* dv,
                           void* workspace, size_t workspace_bytes, void* stream);
+// the least that hstu_attn_fwd / hstu_attn_bwd accept (hstu_attn_workspace_bytes: with room for dS); 0: invalid description
+size_t attn_workspace_least(const hstu_attn_params* p, int for_backward);
 hipError_t launch_attn_bwd_dq(const AttnArgs& a, int dtype, hipStream_t stream);
+// attn_dq.hip: dQ from the dS that the dK/dV pass left in a.ds (bf16, 128 features; the work list of launch_attn_bwd_dq)
+hipError_t launch_attn_dq_from_ds(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_attn_bwd_dkdv(const AttnArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream);
 // After the attention kernels: the outputs of cut blocks from their pieces' partial sums, and the bias-table gradient from the

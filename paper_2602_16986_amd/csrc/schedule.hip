@@ -53,6 +53,8 @@ struct SchedJob {
   WorkItem* items;
   int32_t* seq_base;
   SplitItem* splits;
+  int32_t* ds_table;       // key-major list, optional: AttnArgs::ds_table ...
+  int64_t ds_cap;          // ... and the dS tiles there is room for; lengths that need more than the host's copy of them does get an empty list
 };
 
 struct SchedShared {
@@ -62,7 +64,7 @@ struct SchedShared {
   uint16_t slot_c[kSortMax];             // pair -> its first slot (x H: slot of head 0), 0xFFFF = not cut
   int32_t base_c[kSeqCache + 1], len_c[kSeqCache], hist_c[kSeqCache], row_c[kSeqCache];
   uint32_t count[kDigits * kCountPitch]; // [digit][wave]
-  int32_t wave_total[7][kSchedWaves];    // scratch of scans and reductions
+  int32_t wave_total[8][kSchedWaves];    // scratch of scans and reductions
   unsigned long long tiles, dense;       // of a list that is not sorted
   int32_t bad;
 };
@@ -144,7 +146,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     const int excl = blocks_per_head + block_scan(nb, sh.wave_total[(c0 / kSchedThreads) & 1], total);
     if (b < B) {
       if (cached) { sh.base_c[b] = excl; sh.len_c[b] = L; sh.hist_c[b] = L - m; sh.row_c[b] = o0; }
-      else seq_base[b] = excl;
+      if (!cached || job.ds_table) seq_base[b] = excl;
     }
     blocks_per_head += total;
   }
@@ -164,6 +166,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
 
   // Item idx of `heads` heads in natural order (sequence-major, then head, then block index descending; the leading blocks are
   // absent with a query tail) -> its work item (whole) and, if wanted, its cost in tiles.  heads = 1 enumerates the pairs.
+  int first_tile = 0;                                    // out of locate(): the first tile of a priced item
   auto locate = [&](int idx, int heads, bool priced, int& cost) {
     int lo = 0, hi = B;                                  // invariant: base[lo]*heads <= idx < base[hi]*heads
 #pragma unroll 1
@@ -191,7 +194,9 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     if (priced) {
       const SeqGeom g = {it.len, it.hist, K1, K2};
       const int r0 = rb << block_shift, r1 = min(r0 + block_rows, it.len) - 1;
-      cost = (job.key_major ? row_tile_ranges_of(g, r0, r1, tile) : tile_ranges_of(g, r0, r1, tile)).count();
+      const TileRanges tr = job.key_major ? row_tile_ranges_of(g, r0, r1, tile) : tile_ranges_of(g, r0, r1, tile);
+      cost = tr.count();
+      first_tile = tr.at(0);
     }
     return it;
   };
@@ -209,6 +214,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     my_tiles += cost;
     my_dense += tile.index(it.len + tile.width() - 1);
     my_max = max(my_max, cost);
+    if (sorted && job.ds_table) { job.ds_table[4 * idx + 1] = first_tile; job.ds_table[4 * idx + 2] = cost; }
     if (sorted) costs[idx] = cost;
     else items[idx] = it;
   }
@@ -248,6 +254,18 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   };
   const int ipt = (pairs + kSchedThreads - 1) / kSchedThreads;
   const int own0 = min(tid * ipt, pairs), own1 = min(own0 + ipt, pairs);   // the scans below give every thread consecutive pairs
+  if (job.ds_table) {                                      // where the dS tiles of a pair's heads start
+    int sum = 0, all;
+#pragma unroll 1
+    for (int idx = own0; idx < own1; ++idx) sum += (int)costs[idx];
+    sum = block_scan(sum, sh.wave_total[7], all);
+    if ((int64_t)all * H > job.ds_cap) {
+      if (tid == 0) *header = SchedHeader{0, 0, 0, 0, 0, 1};
+      return;
+    }
+#pragma unroll 1
+    for (int idx = own0; idx < own1; ++idx) { job.ds_table[4 * idx] = sum * H; sum += (int)costs[idx]; }
+  }
   int slot0 = 0, rank0 = 0, slots = 0, nsplit = 0, entries = pairs;        // first slot and rank of this thread's pairs among the cut ones; totals
   bool cuts = false;                                       // uniform: some block is cut
 #pragma unroll 1
@@ -433,18 +451,20 @@ hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int ti
   // query tail keeps the finer pieces of the key-major lists (few blocks, each against a whole history)
   const bool even = a.query_tail == 0;
   const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), 0, a.query_tail, slot_cap, even ? 1 : 0, 1.0 / (even ? kFwdTargetChunks : kTargetChunks),
-                        header, items, seq_base, splits};
+                        header, items, seq_base, splits, nullptr, 0};
   return launch(a, lists ? 1 : 0, job, job, ex, stream);
 }
 
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], const ExpandJob& ex, hipStream_t stream) {
+                                const int slot_cap[2], int32_t* ds_table, int64_t ds_cap, const ExpandJob& ex, hipStream_t stream) {
   // dQ list (query-major): equal pieces of about one slot's share, 512 slots at two workgroups per compute unit
-  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, 1.0 / kDqTargetChunks, header[0], items[0], seq_base[0], splits[0]};
-  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, 1.0 / kTargetChunks, header[1], items[1], seq_base[1], splits[1]};
+  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, 1.0 / kDqTargetChunks, header[0], items[0], seq_base[0], splits[0], nullptr, 0};
+  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, 1.0 / kTargetChunks, header[1], items[1], seq_base[1], splits[1], ds_table, ds_cap};
   return launch(a, lists ? 2 : 0, j0, j1, ex, stream);
 }
+
+int schedule_sorted_pairs() { return kSortMax; }
 
 // Most batches are cut nowhere, and a launch that would add up pieces costs 4.5 us for finding that out.  A block is cut
 // when it is longer than 2 x chunk, chunk >= kMinChunk and >= share x (all tiles).  The longest block is bounded by the longest
