@@ -20,6 +20,11 @@ inline int64_t max_items_for(const hstu_attn_params* p, int block_rows) {
   return ((int64_t)p->total_tokens / block_rows + p->batch) * p->num_heads;
 }
 
+// Copies of the sums per distance: one per die while they stay small (16 MB: clearing and adding them up takes a few microseconds).
+inline int dbias_copies_for(const hstu_attn_params* p) {
+  return (int64_t)kDbiasCopies * p->num_heads * ((int64_t)p->max_seqlen + 1) <= (int64_t)4 << 20 ? kDbiasCopies : 1;
+}
+
 struct Layout {           // byte offsets inside a workspace
   size_t header[2], items[2], seq_base[2], bias, seed, splits, partial, splits_dq, partial_dq, dbias, ds_table, total, ds, total_ds;
   int max_items[2];
@@ -100,7 +105,7 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     l.partial_dq = off;
     off += align_up((size_t)l.slot_cap_dq * dq_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
     l.dbias = off;                                     // per-distance sums of dS for the bias-table gradient, then the bucket ends per distance
-    off += align_up((size_t)(p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
+    off += align_up((size_t)(dbias_copies_for(p) * p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
     // dS, behind everything else: a workspace without room for it is accepted (32 and 64 features: a dQ product would move as many
     // bytes as for 128 and save a half or a quarter of the matrix work)
     const bool ds = p->dtype == HSTU_BF16 && p->head_dim == 128 && (int64_t)p->total_tokens / 128 + p->batch <= schedule_sorted_pairs();
@@ -184,7 +189,8 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   ex.bias_len = a.bias_stride;
   a.bias = ex.bias;
   if (!for_forward && p->d_rab_table) {               // only the bias-table gradient needs the bucket ends and the sums per distance
-    const int64_t n = (int64_t)p->num_heads * a.bias_stride;
+    a.dbias_copies = dbias_copies_for(p);
+    const int64_t n = (int64_t)a.dbias_copies * p->num_heads * a.bias_stride;
     a.dbias_dist = ex.zero = (float*)(ws + l.dbias);
     ex.zero_count = n;
     a.bucket_end = ex.bucket_end = (int32_t*)(ws + l.dbias) + n;

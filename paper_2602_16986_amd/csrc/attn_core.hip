@@ -106,11 +106,6 @@ struct Cfg {
   static constexpr int STAT_BASE = 2 * STAGE_BYTES + 2 * STRIP_BYTES;
   static constexpr int STAT_BYTES = kStatLds ? BX * ROW_BYTES : 0;      // stationary operand 1, same swizzle as the tiles
   static constexpr int SMEM_BYTES = STAT_BASE + STAT_BYTES;             // 2 stages x (2 tensors + strip) [+ stationary rows]
-  // bias-gradient variant of the dQ pass: two (double-buffered) strips of per-distance sums behind everything else
-  static constexpr int DACC_LEN = (BX + BN - 1 + 63) / 64 * 64;
-  static constexpr int DACC_BASE = SMEM_BYTES;
-  static constexpr int DACC_COPIES = NWAVES;                     // one strip per wave: plain read-add-write, no LDS atomics
-  static constexpr int DACC_BYTES = 2 * DACC_COPIES * DACC_LEN * 4;
 };
 
 template <typename E> struct ResidentFrag;
@@ -136,29 +131,10 @@ __device__ __forceinline__ float sigmoid_l2(float t) {           // sigmoid(t * 
 // dS / dP = sigmoid (1 + s (1 - sigmoid)) = sigmoid + (t sigmoid) * ln2 (1 - sigmoid)
 __device__ __forceinline__ float dsilu_l2(float tp, float sig) { return fmaf(tp, fmaf(-kLn2, sig, kLn2), sig); }
 
-// One register of the diagonal sum of a 32 x 32 score-gradient block (lane = query 16*a + b of the block, register R
-// = key yo = 8*(R/4) + R%4 (+4 for the upper half-wave)).  Rotating register R by rho = yo % 16 lanes inside its
-// 16-lane row puts every value next to the others of its diagonal: at lane b' it belongs to strip offset
-// 16*j - b' with j = yo/16 + (1 if it came around the row end), so three running sums per lane collect all 16.
-template <int R>
-__device__ __forceinline__ void diag_step(const float* vals, int bq, float& x0, float& x1, float& x2) {
-  constexpr int q = R >> 2, rho = 8 * (q & 1) + (R & 3);
-  float rv = vals[R];
-  if constexpr (rho != 0)                                                // row_ror:(16 - rho): lane b' reads lane (b' + rho) % 16
-    rv = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, rv), 0x120 + (16 - rho), 0xF, 0xF, false));
-  const bool wrapped = bq >= 16 - rho;
-  const float lo = wrapped ? 0.f : rv, hi = wrapped ? rv : 0.f;
-  if constexpr ((q >> 1) == 0) { x0 += lo; x1 += hi; } else { x1 += lo; x2 += hi; }
-}
-template <int... R>
-__device__ __forceinline__ void diag_all(std::integer_sequence<int, R...>, const float* vals, int bq, float& x0, float& x1, float& x2) {
-  (diag_step<R>(vals, bq, x0, x1, x2), ...);
-}
-
-// The same sums for the dK/dV pass, shared out over a whole wave: of a 32 x 32 block of dS (lane = key l32, register R of half-wave hf =
-// query 8 (R / 4) + 4 hf + R % 4) the sum over the pairs with query - key = o lands at lane -o mod 64, part 0 of it plus part 1 of the
-// lane 4 further (the upper half-wave's queries are 4 further).  The rotations shift zeros in, so that a value and what comes around
-// the row end go to their sums without a select: two adds per register.
+// Diagonal sums of a 32 x 32 block of dS, shared out over the wave.  Lane l32 of half-wave hf holds, in register R, the streamed row
+// 8 (R / 4) + 4 hf + R % 4 of the block; the sum over the pairs with (streamed row - lane row) = o lands at lane -o mod 64: part 0 of it,
+// plus part 1 of the lane 4 further (the upper half-wave's rows are 4 further).  The rotations shift zeros in, so that a value and what
+// comes around the end of a 16-lane row go to their sums without a select: two adds per register.
 template <int CTRL>
 __device__ __forceinline__ float dpp0(float v) {                         // the value DPP control CTRL brings, 0 where it brings none
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
@@ -175,6 +151,22 @@ __device__ __forceinline__ void key_diag_step(float v, float& x0, float& x1, flo
     hi += dpp0<0x110 + 16 - rho>(v);                                     // row_shr: ... lane b + rho - 16
   }
 }
+// Sums of 16 registers over the 16 lanes of a row, handed out: lane i of a row leaves with the sum of register i.
+template <int CTRL, int HALF>
+__device__ __forceinline__ void row_fold(float (&v)[16], bool upper) {
+#pragma unroll
+  for (int r = 0; r < HALF; ++r) {
+    const float keep = upper ? v[r + HALF] : v[r], give = upper ? v[r] : v[r + HALF];
+    v[r] = keep + dpp0<CTRL>(give);
+  }
+}
+__device__ __forceinline__ float row_sums(float (&v)[16], int i16) {
+  row_fold<0x140, 8>(v, i16 & 8);                                        // row_mirror: lane ^ 15
+  row_fold<0x141, 4>(v, i16 & 4);                                        // row_half_mirror: lane ^ 7
+  row_fold<0x1B, 2>(v, i16 & 2);                                         // quad_perm: lane ^ 3
+  row_fold<0xB1, 1>(v, i16 & 1);                                         // quad_perm: lane ^ 1
+  return v[0];
+}
 template <int... R, typename V>
 __device__ __forceinline__ void key_diag_all(std::integer_sequence<int, R...>, const V& vals, float& part0, float& part1) {
   float x0 = 0.f, x1 = 0.f, x2 = 0.f;
@@ -188,8 +180,8 @@ __device__ __forceinline__ void key_diag_all(std::integer_sequence<int, R...>, c
   part1 = __builtin_bit_cast(float, (uint32_t)parts[1]);                 // ... and of the upper one
 }
 
-// DBIAS (dQ pass only): also sum dS along the diagonals of every tile (pairs of equal distance i - j) into
-// a.dbias_dist[h, distance]; finish_kernel folds distances into buckets afterwards.
+// DBIAS (dQ pass, or the dK/dV pass that hands dS on): also sum dS per distance into a.dbias_dist[h, distance]; finish_kernel folds
+// distances into buckets afterwards.
 // CAND (batches with candidate rows): the fast paths also cover candidate rows against history keys.  A candidate row
 // stands at position n for the mask and for the bias, so full and mask-edge tiles of such rows work like those of history
 // rows once the bias strip is addressed with the row's effective position (query-stationary passes) or anchored at n
@@ -209,6 +201,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   constexpr bool CANDQ = CAND && MODE != kBwdDKDV, CANDK = CAND && MODE == kBwdDKDV;
   using C = Cfg<E, D, MODE, NWAVES>;
   using RFrag = typename ResidentFrag<E>::type;
+  constexpr int NSB = C::BN / 32;                     // 32-row sub-blocks of a streamed tile
   // 256-byte alignment: the fragment reads below form LDS addresses as integers, base included, and XOR the swizzle in
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
 
@@ -467,136 +460,85 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       dma16(tile_rsrc(R2, rowb, x0 + 4 * rg), voff, dst);
     }
   }
-  // ---- bias gradient (DBQ): dacc[p][s] collects dS of tile parity p along strip index
-  // s = (y - tile start) + (BX - 1 - (x - x0)), i.e. distance x - y = x0 + BX - 1 - tile start - s
-  float* dacc = (float*)(smem + C::DACC_BASE);
-  const int dacc_lane = wave * C::DACC_LEN + C::BX - 1 - wave * 32 + 4 * hf - (lane & 15) - 16 * ((lane >> 4) & 1);   // + 32 * sub-block + 16 * class
-  auto dacc_flush = [&](int parity, int yt_of) {                         // every wave has passed the barrier after that tile
-    if constexpr (DBQ) {
-      if (a.dbias_dist && tid < C::BX + C::BN - 1) {
-        float vsum = 0.f;
-#pragma unroll
-        for (int c = 0; c < C::DACC_COPIES; ++c) {
-          vsum += dacc[(parity * C::DACC_COPIES + c) * C::DACC_LEN + tid];
-          dacc[(parity * C::DACC_COPIES + c) * C::DACC_LEN + tid] = 0.f;
-        }
-        const int dist = x0 + C::BX - 1 - yt_of * C::BN - tid;
-        if (vsum != 0.f && dist >= 0 && dist < a.bias_stride) atomicAdd(a.dbias_dist + (int64_t)h * a.bias_stride + dist, vsum);
-      }
-    }
-  };
-  // adds the 16 scores-gradients this lane holds for one 32-row sub-block of the tile in `stage` (LDS float
-  // atomics run one lane per cycle on this part; the private strips make them unnecessary)
-  auto dacc_add = [&](int stage, int sub, const float* vals) {
-    float x0 = 0.f, x1 = 0.f, x2 = 0.f;
-    diag_all(std::make_integer_sequence<int, 16>{}, vals, lane & 15, x0, x1, x2);
-    // Strip index of class j at this lane: dacc_lane + 32 * sub + 16 * j.  Two lanes of a wave meet at one address
-    // (different half-waves, different classes), so the half-waves and the classes take turns.
-    float* base = dacc + stage * C::DACC_COPIES * C::DACC_LEN + dacc_lane + sub * 32;
-    const int room = C::DACC_LEN - (dacc_lane - wave * C::DACC_LEN + sub * 32);   // entries from base to the end of the strip
-    // (lanes of the two 16-lane rows of a half-wave meet in neighbouring classes, so the classes take turns as well)
-#pragma unroll
-    for (int hs = 0; hs < 2; ++hs)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const float xv = j == 0 ? x0 : (j == 1 ? x1 : x2);
-        if (hf == hs && 16 * j < room) {                                 // beyond the strip only zeros would land
-          volatile float* p = base + 16 * j;
-          *p = *p + xv;
-        }
-      }
-  };
-  // A tile that lies far from the diagonal has all its distances inside ONE bucket of the table, or in two neighbouring
-  // ones (the buckets of a log-spaced table are hundreds of distances wide there); which distance of a bucket receives a
-  // sum does not matter, so such a tile adds plain sums of its dS: one per bucket, kept per lane across consecutive tiles
-  // (two open buckets, since the tiles walk from one bucket into the next) and reduced over the wave only when a bucket
-  // is left behind.  The test is made for the whole block (its 128 rows against the tile's keys: AttnArgs::bucket_end
-  // gives the first distance of the next bucket), so that all waves agree and the per-tile flush of the diagonal strips
-  // can be skipped too.
-  float run_sum0 = 0.f, run_sum1 = 0.f;
-  int run_end0 = 0, run_end1 = 0, run_dist0 = 0, run_dist1 = 0;          // run_end = 0: slot free; a bucket is named by its end
-  int run_old = 0;                                                        // the slot opened first
-  auto run_flush_slot = [&](float& sum, int& end, int dist) {
-    if (end != 0) {
-      float v = sum;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0 && v != 0.f) atomicAdd(a.dbias_dist + (int64_t)h * a.bias_stride + dist, v);
-      sum = 0.f;
-      end = 0;
-    }
-  };
-  auto run_flush = [&]() {
-    if constexpr (DBQ) { run_flush_slot(run_sum0, run_end0, run_dist0); run_flush_slot(run_sum1, run_end1, run_dist1); }
-  };
-  auto run_to = [&](int end, int dist, float v) {                        // adds v to the bucket that ends at `end` (dist: one of its distances)
-    if (run_end0 == end) run_sum0 += v;
-    else if (run_end1 == end) run_sum1 += v;
-    else if (run_old == 0) {
-      run_flush_slot(run_sum0, run_end0, run_dist0);
-      run_end0 = end; run_dist0 = dist; run_sum0 = v; run_old = 1;
-    } else {
-      run_flush_slot(run_sum1, run_end1, run_dist1);
-      run_end1 = end; run_dist1 = dist; run_sum1 = v; run_old = 0;
-    }
-  };
-  // vals: the 16 dS of this lane in sub-block `sub` of the tile (keys y0 + 32 sub + 8 (r / 4) + 4 hf + r % 4).  The block's
-  // pairs of this tile lie in the bucket that ends at `end` (distances < end) and, if split >= 0, above it in the bucket
-  // that ends at `end2`.
-  auto run_add = [&](const float* vals, int sub, int y0_, int end, int dist, int end2) {
-    float total = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) total += vals[r];
-    if (end2 == 0) { run_to(end, dist, total); return; }
-    const int thr = x - y0_ - 32 * sub - 4 * hf - end;                   // key offset c <= thr  <=>  distance >= end
-    float hi = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) hi += (8 * (r >> 2) + (r & 3) <= thr) ? vals[r] : 0.f;
-    run_to(end, dist, total - hi);
-    run_to(end2, end, hi);
-  };
-  if constexpr (DBQ) {
-    for (int i = tid; i < 2 * C::DACC_COPIES * C::DACC_LEN; i += C::NT) dacc[i] = 0.f;
-  }
-  // ---- bias gradient in the dK/dV pass (DBK).  A tile of this wave whose 63 distances lie in one bucket of the table adds the plain
-  // sum of its dS, kept per lane until the bucket is left.  Any other tile adds along its diagonals: lane l of `win` collects
-  // distance win_y0 - xw0 + o, o = -l mod 64 in [-31, 32]; the next tile is 32 queries further, so the lower half of the window is
-  // complete then and leaves for the table of sums per distance, and the upper half becomes the lower one.
+  // ---- bias gradient (DBIAS).  A 32 x 32 block of this wave, w0 = the distance of its first pair, holds the 63 distances around w0.
+  // Far from the diagonal they lie in one bucket of the table (the buckets of a log-spaced one are hundreds of distances wide there) and
+  // which distance of a bucket receives a sum does not matter: the block adds the plain sum of its dS, kept per lane until the
+  // bucket is left.  Any other block adds along its diagonals: lane l of `win` collects distance win_w0 + SGN * (l, or l - 64 for the upper
+  // half); the next block is 32 further, so the lower half of the window is complete then and leaves for the table of sums per
+  // distance, and the upper half becomes the lower one.  All of it stays in registers: strips in LDS with one read-add-write per class and
+  // half-wave, and a flush per tile by the workgroup, cost the dQ pass as much again as its products (64 features, 1024 + 256 semi-local,
+  // 8k-16k tokens: 0.31 ms without the gradient, 0.66 with it, 0.43 this way; 0.53 with one copy of the table for all dies).
+  constexpr int SGN = MODE == kBwdDKDV ? -1 : 1;           // distance = streamed row - lane row in the dK/dV pass, and the negative in the dQ pass
   constexpr int kNoWindow = -(1 << 30);
-  float win = 0.f, run_k = 0.f;
-  int win_y0 = kNoWindow, run_k_end = 0, run_k_dist = 0;
-  float* const dist_h = DBK ? a.dbias_dist + (int64_t)h * a.bias_stride : nullptr;
-  auto dist_add = [&](int dist, float v) {
-    if (v != 0.f && (uint32_t)dist < (uint32_t)a.bias_stride) atomicAdd(dist_h + dist, v);
+  constexpr int kLate = DBIAS && !DS ? NSB : 0;            // sums that leave at the start of the next tile: the wait for a tile's loads would wait for them
+  float win = 0.f, run_sum = 0.f, late[NSB];
+  int win_w0 = kNoWindow, run_end = 0, run_w0 = 0, late_w0[NSB];
+#pragma unroll
+  for (int u = 0; u < NSB; ++u) { late[u] = 0.f; late_w0[u] = kNoWindow; }
+  float* const dist_h = DBIAS ? a.dbias_dist + (int64_t)(xcd % a.dbias_copies * a.H + h) * a.bias_stride : nullptr;
+  auto win_out = [&](int w0, float v) {
+    // (the lane's number is made here: as a value that lives through the tile loop it would be spilled, and its reload wait for the tile's loads)
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    const uint32_t off = (uint32_t)(32 + SGN * ((int)((uint32_t)l << 26) >> 26));
+    if (v != 0.f && (uint32_t)(w0 - 32) + off < (uint32_t)a.bias_stride) atomicAdd(dist_h + (w0 - 32) + off, v);
   };
   auto win_flush = [&]() {
-    if (win_y0 != kNoWindow) dist_add(win_y0 - xw0 + (lane < 32 ? -lane : 64 - lane), win);
+    if (win_w0 != kNoWindow) win_out(win_w0, win);
     win = 0.f;
-    win_y0 = kNoWindow;
+    win_w0 = kNoWindow;
   };
-  auto run_k_flush = [&]() {
-    if (run_k_end != 0) {
-      float v = run_k;
+  auto run_flush = [&]() {
+    if (run_end != 0) {
+      float v = run_sum;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0) dist_add(run_k_dist, v);
+      if (lane == 0 && v != 0.f) atomicAdd(dist_h + run_w0, v);
     }
-    run_k = 0.f;
-    run_k_end = 0;
+    run_sum = 0.f;
+    run_end = 0;
   };
-  auto win_add = [&](const auto& vals, int y0_) {          // the tile's 16 dS of this lane, history queries
-    if (win_y0 == y0_ - C::BN) {
+  auto late_out = [&]() {
+#pragma unroll
+    for (int u = 0; u < kLate; ++u) {
+      if (late_w0[u] != kNoWindow) win_out(late_w0[u], late[u]);
+      late_w0[u] = kNoWindow;
+    }
+  };
+  // the end of the bucket that holds all distances of a fully visible block of history rows, 0: they lie in several
+  auto one_bucket = [&](int w0) -> int {
+    const int end = ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.bucket_end)[w0 - 31];
+    return end > w0 + 31 ? end : 0;
+  };
+  // adds the 16 dS of this lane in sub-block `sub` of the tile; end: of one_bucket()
+  auto dist_sum = [&](const auto& vals, int sub, int w0, int end) {
+    if (end != 0) {
+      if (end != run_end) {                                // (distances are walked in order: a bucket that is left does not come back)
+        run_flush();
+        run_end = end;
+        run_w0 = w0 - 31;
+      }
+      float t0 = vals[0], t1 = vals[1];
+#pragma unroll
+      for (int r = 2; r < 16; r += 2) { t0 += vals[r]; t1 += vals[r + 1]; }
+      run_sum += t0 + t1;
+      return;
+    }
+    if (w0 == win_w0 - 32 * SGN) {
       const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, win), 0u, false, false);
-      if (lane < 32) dist_add(win_y0 - xw0 - lane, __builtin_bit_cast(float, (uint32_t)halves[0]));
+      const float done = __builtin_bit_cast(float, (uint32_t)halves[0]);
+      if constexpr (kLate > 0) { late[sub] = done; late_w0[sub] = win_w0; } else win_out(win_w0, done);
       win = __builtin_bit_cast(float, (uint32_t)halves[1]);
     } else {
       win_flush();
     }
-    win_y0 = y0_;
+    win_w0 = w0;
     float part0, part1;
     key_diag_all(std::make_integer_sequence<int, 16>{}, vals, part0, part1);
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
     win += part0;
-    win += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * ((lane + 4) & 63), __builtin_bit_cast(int, part1)));
+    win += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * l + 16, __builtin_bit_cast(int, part1)));      // (of lane l + 4 mod 64)
   };
   set_next(t_begin < ntiles ? tr.at(t_begin) : 0, t_begin < ntiles);
   gload(0);
@@ -606,36 +548,16 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   HSTU_TLB(1);
 
   const bool stat_hist = min(xw0 + 32, L) - 1 < g.n;  // this wave's stationary rows are all history rows
-  constexpr int NSB = C::BN / 32;                     // 32-row sub-blocks of a streamed tile
   constexpr int SBG = (MODE == kFwd && NSB >= 2) ? 2 : 1;   // sub-blocks whose products are interleaved
-  bool prev_fast = false;
   for (int t = t_begin; t < ntiles; ++t) {
     const int yt = nx_yt;                                    // set_next() of the previous round (or of the prologue) named this tile
     const int stage = (t - t_begin) & 1;
     const bool has_next = t + 1 < ntiles;
     set_next(has_next ? tr.at(t + 1) : 0, has_next);
-    if constexpr (DBQ) {
-      if (t > t_begin && !prev_fast) dacc_flush(stage ^ 1, tr.at(t - 1));
-    }
+    if constexpr (kLate > 0) late_out();
     const unsigned char* y1s = smem + stage * C::STAGE_BYTES;
     const unsigned char* y2s = y1s + C::TILE0;
     const int y0 = yt * C::BN;
-    bool wg_fast = false;                                                 // DBQ: the whole block's pairs of this tile lie in one or two buckets
-    int fast_end = 0, fast_dist = 0, fast_end2 = 0;
-    if constexpr (DBQ) {
-      const int xhi = x0 + C::BX - 1, dmin_b = x0 - (y0 + C::BN - 1);
-      if (a.bucket_end && a.dbias_dist && dmin_b >= 0 && xhi < g.n && classify_tile(g, x0, xhi, y0, y0 + C::BN - 1, false) == kTileFull) {
-        fast_end = a.bucket_end[dmin_b];
-        fast_dist = dmin_b;
-        wg_fast = true;
-        if (fast_end <= xhi - y0) {                                       // a bucket boundary inside the tile's distances
-          fast_end2 = a.bucket_end[fast_end];
-          wg_fast = fast_end2 > xhi - y0;                                 // ... and only one
-        }
-      }
-      prev_fast = wg_fast;
-    }
-
     // How this wave's 32 stationary rows relate to the tile: nothing visible (skip), everything
     // visible (no mask arithmetic, bias from the strip), or mixed (generic per-element path).
     // Fully visible tiles of candidate rows (all at position n) against history keys are recognised in the instantiations
@@ -760,7 +682,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (DBQ) {                                            // fully visible tile: history rows, distance x - y
-          if (wg_fast) run_add(dsf[0], 0, y0, fast_end, fast_dist, fast_end2); else dacc_add(stage, 0, dsf[0]);
+          dist_sum(dsf[0], 0, xw0 - y0, one_bucket(xw0 - y0));
         }
         constexpr int NO = 16 * C::NOUT;                                  // output products of the tile
 #pragma unroll
@@ -779,7 +701,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (DBQ) {
-          if (wg_fast) run_add(dsf[1], 1, y0, fast_end, fast_dist, fast_end2); else dacc_add(stage, 1, dsf[1]);
+          dist_sum(dsf[1], 1, xw0 - y0 - 32, one_bucket(xw0 - y0 - 32));
         }
         done = true;
       }
@@ -797,11 +719,8 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       // first 16-row k-step of the output products.)
       const bool tile_hist_f = min(y0 + C::BN, L) - 1 < g.n;               // candidate queries take the general path
       if (kind == kTileFull && (!CANDK || tile_hist_f)) {
-        int one_end = 0;                                                 // DBK: the end of the bucket that holds all the tile's distances
-        if constexpr (DBK) {
-          const int end = ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.bucket_end)[y0 - xw0 - 31];
-          if (end > y0 + C::BN - 1 - xw0) one_end = end;
-        }
+        int one_end = 0;
+        if constexpr (DBK) one_end = one_bucket(y0 - xw0);
         f32x16 sv, dp;
         if (bias_h) {
           const float* strip = (const float*)(smem + C::STRIP_BASE + stage * C::STRIP_BYTES) + strip_lane;
@@ -893,21 +812,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           }
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (DBK) {
-          if (one_end != 0) {                                            // (distances ascend: a bucket that is left does not come back)
-            if (one_end != run_k_end) {
-              run_k_flush();
-              run_k_end = one_end;
-              run_k_dist = y0 - xw0 - 31;
-            }
-            float t0 = dp[0], t1 = dp[1];
-#pragma unroll
-            for (int r = 2; r < 16; r += 2) { t0 += dp[r]; t1 += dp[r + 1]; }
-            run_k += t0 + t1;
-          } else {
-            win_add(dp, y0);
-          }
-        }
+        if constexpr (DBK) dist_sum(dp, 0, y0 - xw0, one_end);
         done = true;
       }
     }
@@ -1122,24 +1027,24 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
         }
 
         if constexpr (DBQ) {
-          // dS per distance: history rows add along the tile's diagonals in LDS; candidate rows (their distance
-          // is n - j, not i - j) are few and add to the global table directly
 #pragma unroll
           for (int u = 0; u < SBG; ++u) {
             float hv[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              hv[r] = x < g.n ? c1[u][r] : 0.f;
-              if (x >= g.n && c1[u][r] != 0.f) {
-                int delta;
-                if (visible(g, x, y0 + (sg + u) * 32 + 8 * (r >> 2) + 4 * hf + (r & 3), delta))
-                  atomicAdd(a.dbias_dist + (int64_t)h * a.bias_stride + delta, c1[u][r]);
-              }
+            for (int r = 0; r < 16; ++r) hv[r] = x < g.n ? c1[u][r] : 0.f;
+            if (xw0 + 31 >= g.n) {
+              // candidate rows stand at position n: one distance per key (their own key: distance 0), summed over the rows
+              float cv[16];
+#pragma unroll
+              for (int r = 0; r < 16; ++r) cv[r] = x < g.n ? 0.f : c1[u][r];
+              const float v = row_sums(cv, i16);
+              const int y = y0 + (sg + u) * 32 + 8 * (i16 >> 2) + 4 * hf + (i16 & 3);
+              if (v != 0.f) atomicAdd(dist_h + max(g.n - y, 0), v);
             }
-            if (wg_fast) run_add(hv, sg + u, y0, fast_end, fast_dist, fast_end2); else dacc_add(stage, sg + u, hv);
+            const int w0 = xw0 - y0 - 32 * (sg + u);
+            if (xw0 < g.n) dist_sum(hv, sg + u, w0, kind == kTileFull ? one_bucket(w0) : 0);
           }
         }
-
         if constexpr (DBK) {
           // candidate queries stand at position n: one distance per key (their own key: distance 0)
           float hv[16];
@@ -1150,9 +1055,9 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             float cand = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) cand += 8 * (r >> 2) + (r & 3) < nh ? 0.f : c1[0][r];
-            dist_add(x < g.n ? g.n - x : 0, cand);
+            if (cand != 0.f) atomicAdd(dist_h + (x < g.n ? g.n - x : 0), cand);
           }
-          if (y0 < g.n) win_add(hv, y0);
+          if (y0 < g.n) dist_sum(hv, 0, y0 - xw0, 0);
         }
 
         // ---- second products: out^T[feature][x] += Y^T[feature][y] * coeff[y][x]
@@ -1224,11 +1129,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     __syncthreads();
   }
 
-  if constexpr (DBQ) {
-    if (ntiles > t_begin && !prev_fast) dacc_flush((ntiles - 1 - t_begin) & 1, tr.at(ntiles - 1));
-    run_flush();
-  }
-  if constexpr (DBK) { win_flush(); run_k_flush(); }
+  if constexpr (DBIAS) { late_out(); win_flush(); run_flush(); }
   HSTU_TLB(2);
   // ---- epilogue: scale once, convert, store.  Lane x holds features ob*32 + 8*(r/4) + 4*hf + r%4.
   {
@@ -1357,7 +1258,13 @@ __device__ void dbias_unit(const AttnArgs& a, const DbiasJob& job, int c, int h)
   const int lo = min(job.bounds[c], len), hi = c + 1 < job.num_buckets ? min(job.bounds[c + 1], len) : len;
   const float* dist = a.dbias_dist + (size_t)h * len;
   float acc = 0.f;
-  for (int x = lo + (int)threadIdx.x; x < hi; x += kFinishThreads) acc += dist[x];
+  for (int x = lo + (int)threadIdx.x; x < hi; x += kFinishThreads) {
+    float v[kDbiasCopies];
+#pragma unroll
+    for (int c8 = 0; c8 < kDbiasCopies; ++c8) v[c8] = c8 < a.dbias_copies ? dist[(size_t)c8 * a.H * len + x] : 0.f;
+#pragma unroll
+    for (int c8 = 0; c8 < kDbiasCopies; ++c8) acc += v[c8];
+  }
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
   __syncthreads();                                                     // (a workgroup may take several units)
@@ -1387,7 +1294,7 @@ template <typename E, int D, int MODE, int NWAVES, bool DBIAS = false, bool CAND
 static hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
   using C = Cfg<E, D, MODE, NWAVES>;
   auto kern = attn_kernel<E, D, MODE, NWAVES, DBIAS, CAND, DS>;
-  constexpr int smem_bytes = C::SMEM_BYTES + (DBIAS && MODE == kBwdDQ ? C::DACC_BYTES : 0);
+  constexpr int smem_bytes = C::SMEM_BYTES;
   static bool attr_set[64] = {};                                         // per instantiation and device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;

@@ -50,7 +50,10 @@ struct AttnArgs {
   float* partial;                   // dK/dV pass: fp32 partial sums [slot][dK, dV][block row][D] of cut key blocks
   const SplitItem* splits;
   int32_t query_tail;               // forward only, > 0: compute only the last query_tail history rows and the candidates of every sequence
-  float* dbias_dist;                // dQ pass, optional: sum of dS per head and distance [H, bias_stride] (zeroed by the caller)
+  // backward, optional: sums of dS per distance [dbias_copies][H, bias_stride] (zeroed by the caller), the workgroups of a die adding to
+  // one copy: with one copy for the chip the dies take turns at a few hundred lines
+  float* dbias_dist;
+  int32_t dbias_copies;
   // optional (bf16 backward): q, k, v = SiLU(pre_q / pre_k / pre_v) [T, H, D] with row stride s_pre; dq, dk, dv then leave
   // as the gradients of those pre-activations (multiplied by SiLU' on the way out)
   const void* pre_q; const void* pre_k; const void* pre_v; int64_t s_pre;
@@ -71,6 +74,7 @@ struct AttnArgs {
   const SchedHeader* ds_header;     // of the dK/dV list: bad_batch = no dS was left
 };
 constexpr int kDsTileBytes = 32 * 128 * 2;
+constexpr int kDbiasCopies = 8;          // one per die
 constexpr int kSeedVariants = 2;
 inline int seed_dmax_for(int max_seqlen) { return max_seqlen + 128; }
 inline int seed_len_for(int max_seqlen) { return (seed_dmax_for(max_seqlen) + 1 + 192 + 63) / 64 * 64; }
