@@ -60,8 +60,13 @@ struct Cfg {
   // Forward with 128 features: 32-row tiles need 161 registers and 39 KB of LDS, so three workgroups share a compute
   // unit (three independent instruction streams per SIMD); measured 5 % faster than two with 64-row tiles and an
   // in-wave software pipeline.
-  static constexpr bool kThreePerCu = kBf16 && D == 128 && MODE == kFwd && NWAVES == 4;
-  static constexpr int BN = kBf16 ? ((kStatLds || kThreePerCu) ? 32 : 64) : 32;  // streamed rows per LDS tile
+  // dQ pass with 64 features: the same arrangement (168 registers); 8 x 8k-16k semi-local 304 -> 290 us, short ragged histories 117 -> 108.
+  // (32 features take 64-row tiles at two workgroups: 211 us against 233 with 32-row ones at three; the narrow forwards are
+  // equal or slower with 32-row tiles.)
+  static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && ((D == 128 && MODE == kFwd) || (D == 64 && MODE == kBwdDQ));
+  // dK/dV pass: 32-row tiles for every width.  With 64 features a 64-row tile took more than 256 registers, one workgroup per compute
+  // unit: 8 x 8k-16k dense 2.49 ms, 1.85 when made to fit (29 registers spilled), 1.54 with 32-row tiles; 32 features 0.29 -> 0.23 semi-local.
+  static constexpr int BN = kBf16 ? ((MODE == kBwdDKDV || kThreePerCu) ? 32 : 64) : 32;  // streamed rows per LDS tile
   static constexpr int NT = 64 * NWAVES;
   static constexpr int ROW_BYTES = D * (int)sizeof(E);
   // LDS tiles are read two ways: 16-byte reads with one streamed row per lane (score products)
@@ -81,7 +86,7 @@ struct Cfg {
   static constexpr bool kSwz0 = kDma, kSwz1 = kDma;
   // 4-wave bf16 workgroups run two per compute unit (two independent instruction streams per SIMD):
   // 256 registers per lane and half of the 160 KB of LDS each.
-  static constexpr bool kTwoPerCu = kBf16 && NWAVES == 4 && (MODE != kBwdDKDV || kStatLds);
+  static constexpr bool kTwoPerCu = kBf16 && NWAVES == 4;
   static constexpr int kWgPerCu = kThreePerCu ? 3 : (kTwoPerCu ? 2 : 1);
   static constexpr int PAD0 = !kBf16 ? 16 : (kSwz0 ? 0 : (kBoth0 ? 80 : 16));
   static constexpr int PAD1 = !kBf16 ? 16 : (kSwz1 ? 0 : (kBoth1 ? 80 : (MODE == kFwd ? 64 : 16)));
@@ -1337,9 +1342,9 @@ static_assert(kFwdWavesBf16 * 32 == kBlockRows && kFwdWavesFp32 * 32 == kBlockRo
 int fwd_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kFwdWavesBf16 : kFwdWavesFp32); }
 int dq_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDqWavesBf16 : kDqWavesFp32); }
 int dkv_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDkvWavesBf16 : kDkvWavesFp32); }
-int stream_tile_rows(int dtype, int) { return dtype == 0 ? 64 : 32; }
+int stream_tile_rows(int dtype, int D) { return dtype == 0 && D != 64 ? 64 : 32; }
 int fwd_tile_rows(int dtype, int D) { return dtype == 0 ? (D == 128 ? 32 : 64) : 32; }
-int dkv_tile_rows(int dtype, int D) { return dtype == 0 ? (D == 128 ? 32 : 64) : 32; }
+int dkv_tile_rows(int, int) { return 32; }
 
 hipError_t launch_attn_fwd(const AttnArgs& a, int dtype, hipStream_t stream) {
   // bf16 with 128 features: the pipelined kernel (a forward restricted to a query tail keeps the kernel below, which
