@@ -57,13 +57,10 @@ struct Cfg {
   // workgroup's keys stay in LDS (not in registers) and the streamed tiles are 32 rows; that fits 256
   // registers and half the LDS, i.e. two workgroups per compute unit like the other passes.
   static constexpr bool kStatLds = kBf16 && D == 128 && MODE == kBwdDKDV;
-  // Forward with 128 features: 32-row tiles need 161 registers and 39 KB of LDS, so three workgroups share a compute
-  // unit (three independent instruction streams per SIMD); measured 5 % faster than two with 64-row tiles and an
-  // in-wave software pipeline.
-  // dQ pass with 64 features: the same arrangement (168 registers); 8 x 8k-16k semi-local 304 -> 290 us, short ragged histories 117 -> 108.
+  // dQ pass with 64 features: 32-row tiles fit 168 registers and three workgroups per compute unit; 8 x 8k-16k semi-local 304 -> 290 us, short ragged histories 117 -> 108.
   // (32 features take 64-row tiles at two workgroups: 211 us against 233 with 32-row ones at three; the narrow forwards are
   // equal or slower with 32-row tiles.)
-  static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && ((D == 128 && MODE == kFwd) || (D == 64 && MODE == kBwdDQ));
+  static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && D == 64 && MODE == kBwdDQ;
   // dK/dV pass: 32-row tiles for every width.  With 64 features a 64-row tile took more than 256 registers, one workgroup per compute
   // unit: 8 x 8k-16k dense 2.49 ms, 1.85 when made to fit (29 registers spilled), 1.54 with 32-row tiles; 32 features 0.29 -> 0.23 semi-local.
   static constexpr int BN = kBf16 ? ((MODE == kBwdDKDV || kThreePerCu) ? 32 : 64) : 32;  // streamed rows per LDS tile
@@ -230,7 +227,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // scalar: per-wave decisions stay on the SALU
   const int hf = lane >> 5, l32 = lane & 31, grp16 = lane >> 4, i16 = lane & 15;
-  const int x0 = xb * C::BX;
+  const int x0 = xb * C::BX + (MODE == kFwd ? tail_origin(g.n, a.query_tail) : 0);
   const int xw0 = x0 + wave * 32;
   const int x = xw0 + l32;
   const bool x_ok = x < L;
@@ -1140,6 +1137,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   {
     if (item.slot >= 0) {
       // a piece of a cut block: raw fp32 sums go to its slot [outputs][block row][D]; finish_kernel adds them up
+      if (xw0 >= L) { HSTU_TLB(3); return; }
       float* dst = a.partial + (((int64_t)item.slot * C::NOUT) * C::BX + (wave * 32 + l32)) * D;
 #pragma unroll
       for (int o = 0; o < C::NOUT; ++o)
@@ -1208,40 +1206,45 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
 // semi-local 8k-16k workload, 8 pieces of 128 KB each: 25 us with one load in flight and 16
 // rows per workgroup, 15.6 now).  One launch for both passes and the table's gradient: the backward of an ordinary batch had 23 us in three.
 enum { kFinishDKDV = 0, kFinishFwd = 1, kFinishDQ = 2 };
-constexpr int kFinishThreads = 256, kBlockRows = 128, kUnitRows = 32, kUnits = kBlockRows / kUnitRows;
+constexpr int kFinishThreads = 256, kBlockRows = 128, kPiecesAhead = 8;
+constexpr int finish_units(int D) { return kBlockRows * D / (4 * kFinishThreads); }     // units per output of a block
 
 template <typename E, int D>
 __device__ __forceinline__ void finish_unit(const AttnArgs& a, const FinishJob& job, int split, int unit) {
-  constexpr int VPR = D / 4, RPI = kFinishThreads / VPR, NR = kUnitRows / RPI;   // 16-byte groups per row, rows per step, rows per thread
+  constexpr int VPR = D / 4, kUnitRows = kFinishThreads / VPR, kUnits = finish_units(D);   // 16-byte groups per row, rows of a unit
   const SplitItem it = job.splits[split];
   const int xb = it.rb_h >> 8, h = it.rb_h & 255;
   const int o = unit / kUnits, r0 = (unit % kUnits) * kUnitRows + (int)threadIdx.x / VPR, c4 = (int)threadIdx.x % VPR;
+  const int x0 = xb * kBlockRows + (job.what == kFinishFwd ? tail_origin(it.hist, a.query_tail) : 0);
+  if (x0 + unit % kUnits * kUnitRows >= it.len) return;                  // 32 rows past the end (their waves left nothing)
   const int64_t piece = (job.what == kFinishDKDV ? 2 : 1) * kBlockRows * VPR;
   const f32x4* src = (const f32x4*)job.partial + it.first_slot * piece + (int64_t)(o * kBlockRows + r0) * VPR + c4;
-  f32x4 acc[NR];
-#pragma unroll
-  for (int e = 0; e < NR; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   int pc = 0;
-  for (; pc + 2 <= it.pieces; pc += 2, src += 2 * piece) {
-    f32x4 p0[NR], p1[NR];
+  for (; pc + kPiecesAhead <= it.pieces; pc += kPiecesAhead, src += kPiecesAhead * piece) {
+    f32x4 p[kPiecesAhead];
 #pragma unroll
-    for (int e = 0; e < NR; ++e) { p0[e] = src[e * RPI * VPR]; p1[e] = src[piece + e * RPI * VPR]; }
+    for (int e = 0; e < kPiecesAhead; ++e) p[e] = src[e * piece];
 #pragma unroll
-    for (int e = 0; e < NR; ++e) { acc[e] += p0[e]; acc[e] += p1[e]; }
+    for (int e = 0; e < kPiecesAhead; ++e) acc += p[e];
   }
-  if (pc < it.pieces) {
+  if (pc < it.pieces) {                                    // the rest, the last piece standing in for those past the end
+    const int left = it.pieces - pc;
+    f32x4 p[kPiecesAhead - 1];
 #pragma unroll
-    for (int e = 0; e < NR; ++e) acc[e] += src[e * RPI * VPR];
+    for (int e = 0; e < kPiecesAhead - 1; ++e) p[e] = src[min(e, left - 1) * piece];
+#pragma unroll
+    for (int e = 0; e < kPiecesAhead - 1; ++e)
+      if (e < left) acc += p[e];
   }
   const float scale = (job.what != kFinishFwd && o == 0) ? a.inv_n * a.alpha : a.inv_n * kLn2;      // dQ and dK owe alpha, the forward and dV ln 2
   E* base = job.what == kFinishFwd ? (E*)a.out : (job.what == kFinishDQ ? (E*)a.dq : (E*)(o == 0 ? a.dk : a.dv));
   const int64_t stride = job.what == kFinishFwd ? a.so : (job.what == kFinishDQ ? a.sq : (o == 0 ? a.sk : a.sv));
   const int q0 = (job.what == kFinishFwd && a.query_tail > 0) ? max(it.hist - a.query_tail, 0) : 0;
-#pragma unroll
-  for (int e = 0; e < NR; ++e) {
-    const int x = xb * kBlockRows + r0 + e * RPI;
-    if (x >= it.len || x < q0) continue;
-    f32x4 v = acc[e] * scale;
+  {
+    const int x = x0 + r0;
+    if (x >= it.len || x < q0) return;
+    f32x4 v = acc * scale;
     E* dst = base + (int64_t)(it.seq0 + x) * stride + (int64_t)h * D + 4 * c4;
     if constexpr (sizeof(E) == 2) {
       const __bf16* pre = job.what == kFinishFwd ? nullptr : (const __bf16*)(job.what == kFinishDQ ? a.pre_q : (o == 0 ? a.pre_k : a.pre_v));
@@ -1280,7 +1283,7 @@ __device__ void dbias_unit(const AttnArgs& a, const DbiasJob& job, int c, int h)
 
 template <typename E, int D>
 __global__ __launch_bounds__(kFinishThreads) void finish_kernel(const AttnArgs a, FinishJob j0, FinishJob j1, DbiasJob db) {
-  const int per0 = (j0.what == kFinishDKDV ? 2 : 1) * kUnits, per1 = (j1.what == kFinishDKDV ? 2 : 1) * kUnits;
+  const int per0 = (j0.what == kFinishDKDV ? 2 : 1) * finish_units(D), per1 = (j1.what == kFinishDKDV ? 2 : 1) * finish_units(D);
   const int n0 = j0.header ? j0.header->splits * per0 : 0, n1 = j1.header ? j1.header->splits * per1 : 0;
   const int nd = db.num_buckets * a.H;
   for (int u = blockIdx.x; u < n0 + n1 + nd; u += gridDim.x) {
@@ -1321,7 +1324,9 @@ static hipError_t dispatch(const AttnArgs& a, int dtype, hipStream_t stream) {
     switch (a.D) {
       case 32: return launch_one<__bf16, 32, MODE, NW_BF16, DBIAS, CAND>(a, stream);
       case 64: return launch_one<__bf16, 64, MODE, NW_BF16, DBIAS, CAND>(a, stream);
-      case 128: return launch_one<__bf16, 128, MODE, NW_BF16, DBIAS, CAND>(a, stream);
+      case 128:
+        if constexpr (MODE != kFwd) return launch_one<__bf16, 128, MODE, NW_BF16, DBIAS, CAND>(a, stream);    // (the forward: attn_fwd_pipe.hip)
+        break;
     }
   } else {
     switch (a.D) {
@@ -1347,9 +1352,7 @@ int fwd_tile_rows(int dtype, int D) { return dtype == 0 ? (D == 128 ? 32 : 64) :
 int dkv_tile_rows(int, int) { return 32; }
 
 hipError_t launch_attn_fwd(const AttnArgs& a, int dtype, hipStream_t stream) {
-  // bf16 with 128 features: the pipelined kernel (a forward restricted to a query tail keeps the kernel below, which
-  // skips the waves in front of the tail)
-  if (dtype == 0 && a.D == 128 && a.seed && a.query_tail == 0) return launch_attn_fwd_pipe(a, stream);
+  if (dtype == 0 && a.D == 128) return launch_attn_fwd_pipe(a, stream);
   if (a.num_targets) return dispatch<kFwd, kFwdWavesBf16, kFwdWavesFp32, false, true>(a, dtype, stream);
   return dispatch<kFwd, kFwdWavesBf16, kFwdWavesFp32>(a, dtype, stream);
 }

@@ -1,6 +1,6 @@
 // Forward attention for bf16 with 128 features per head: the tile loop as a software pipeline inside every wave.
 //
-// Computes what attn_kernel<..., forward, ...> computes (paper Eq. 3 under the masks of Section 4.2.1, same work items, same
+// Computes for this width what attn_kernel<..., forward, ...> computes for the others (paper Eq. 3 under the masks of Section 4.2.1, same work items, same
 // LDS tile format), with the instruction stream arranged for the way a gfx950 SIMD issues.  Measured on the part: a
 // matrix instruction hides vector instructions only when they follow it in the SAME wave (a second wave's vector work
 // does not overlap with this wave's matrix work), and every instruction a wave issues, scalar ones included, delays its
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hf = lane >> 5, l32 = lane & 31, grp16 = lane >> 4, i16 = lane & 15;
-  const int x0 = xb * kBX, xw0 = x0 + wave * 32, x = xw0 + l32;
+  const int x0 = xb * kBX + tail_origin(g.n, a.query_tail), xw0 = x0 + wave * 32, x = xw0 + l32;
   const bool x_ok = x < L;
   const int q0 = a.query_tail > 0 ? max(g.n - a.query_tail, 0) : 0;    // rows before q0 are not written
 
@@ -428,6 +428,24 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
     vdesc0 = vdesc1; vdesc1 = cur.v;
   };
 
+  // A wave past the end of the sequence only does its share of the loads, step for step with the others (wave-uniform): the last
+  // block of a query tail often has one or two live waves, and its products would take the matrix pipe from other workgroups'.
+  if (xw0 >= L) {
+#pragma unroll 1
+    for (int s = 0; s <= n; ++s) {
+      const int p = s & 1;
+      if (!kNoDma) { load_vd(vdesc0, p, 0); load_vd(vdesc0, p, 1); }
+      asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+      __syncthreads();
+      cur = next_src(cur, s + 2);
+      if (!kNoDma) { load_k(cur, p, 0); load_k(cur, p, 1); load_strip(cur, p); }
+      asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+      __syncthreads();
+      vdesc0 = vdesc1; vdesc1 = cur.v;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    return;
+  }
   // steps whose seeded sub-block needs no patch, in pairs; then the rest (patched sub-blocks and the two draining steps)
   int s = 0;
   for (; s + 2 < nfast; s += 2) {

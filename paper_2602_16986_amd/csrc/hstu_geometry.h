@@ -32,6 +32,10 @@ HSTU_HD bool visible(const SeqGeom& g, int i, int j, int& delta) {
   return (i < g.L) && (self || hist);
 }
 
+// First row of the query blocks of a sequence of which only the last `tail` history rows and the candidates are wanted (tail > 0): the
+// blocks start at the 32 rows (a wave's) that hold the first of them.  0: every row is wanted, blocks start at the first one.
+HSTU_HD int tail_origin(int hist, int tail) { return tail > 0 ? imax(hist - tail, 0) & ~31 : 0; }
+
 // Column tiles (width BN) that hold at least one visible key for the query rows
 // [r0, r1] (inclusive, r1 < L) of one sequence: up to three disjoint ascending
 // half-open ranges: the global prefix, the local band, the candidates' own diagonal.

@@ -137,9 +137,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
       bad |= (o0 < 0) | (o1 < o0) | (o1 > T) | (m < 0) | (b == 0 && o0 != 0);
       L = bad ? 0 : o1 - o0;
       bad |= (L > max_seqlen) | (m > L);
-      nb = blocks_in(L);
-      // a query tail needs the blocks from the one that holds its first row on
-      if (tail > 0 && nb > 0) nb -= max(L - m - tail, 0) >> block_shift;
+      nb = blocks_in(L - tail_origin(L - m, tail));
     }
     if (__ballot(bad) != 0 && lane == 0) sh.bad = 1;
     int total;
@@ -164,8 +162,8 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   const int pairs = blocks_per_head;                     // (sequence, block) pairs: what is priced, cut and sorted
   auto base_of = [&](int b) { return cached ? sh.base_c[b] : seq_base[b]; };
 
-  // Item idx of `heads` heads in natural order (sequence-major, then head, then block index descending; the leading blocks are
-  // absent with a query tail) -> its work item (whole) and, if wanted, its cost in tiles.  heads = 1 enumerates the pairs.
+  // Item idx of `heads` heads in natural order (sequence-major, then head, then block index descending; with a query
+  // tail the blocks start at tail_origin()) -> its work item (whole) and, if wanted, its cost in tiles.  heads = 1 enumerates the pairs.
   int first_tile = 0;                                    // out of locate(): the first tile of a priced item
   auto locate = [&](int idx, int heads, bool priced, int& cost) {
     int lo = 0, hi = B;                                  // invariant: base[lo]*heads <= idx < base[hi]*heads
@@ -188,12 +186,13 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
       h = rank / nb;
       rank -= h * nb;
     }
-    const int rb = blocks_in(it.len) - 1 - rank;
+    const int row0 = tail_origin(it.hist, tail);
+    const int rb = blocks_in(it.len - row0) - 1 - rank;
     it.rb_h = (rb << 8) | h;
     it.t0 = 0; it.t1 = 0x7FFFFFFF; it.slot = -1;
     if (priced) {
       const SeqGeom g = {it.len, it.hist, K1, K2};
-      const int r0 = rb << block_shift, r1 = min(r0 + block_rows, it.len) - 1;
+      const int r0 = row0 + (rb << block_shift), r1 = min(r0 + block_rows, it.len) - 1;
       const TileRanges tr = job.key_major ? row_tile_ranges_of(g, r0, r1, tile) : tile_ranges_of(g, r0, r1, tile);
       cost = tr.count();
       first_tile = tr.at(0);
@@ -241,6 +240,9 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   // becomes an entry of the list and accumulates into a partial-sum slot of its own (one per head).  The piece size
   // doubles until the slots and the list fit.
   int chunk = (int)fmin((double)0x3FFFFFFF, fmax((double)kMinChunk, ceil((double)all_tiles * job.share)));
+  // a query tail: few blocks, nearly all of them cut; the finest pieces that the slots hold (n tiles in pieces of c make less than
+  // n / c + blocks), found without doubling
+  if (tail > 0) chunk = max(chunk, (int)fmin((double)0x3FFFFFFF, ceil((double)all_tiles / max(job.slot_cap - min(total, job.slot_cap / 2), 1))));
   // pieces of a block of `cost` tiles and their length: key-major lists take pieces of `chunk` tiles (a block of a global
   // prefix is hundreds of times longer than the rest); query-major lists, where the longest block is a few slot shares at
   // most, take the fewest equal pieces of at most 2 x chunk tiles (every piece costs a partial-sum slot and its traffic)
@@ -448,7 +450,7 @@ hipError_t launch(const AttnArgs& a, int njobs, const SchedJob& j0, const SchedJ
 hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
                            int32_t* seq_base, SplitItem* splits, int slot_cap, const ExpandJob& ex, hipStream_t stream) {
   // equal pieces of about one workgroup slot's share (768 slots at three workgroups per compute unit); the forward over a
-  // query tail keeps the finer pieces of the key-major lists (few blocks, each against a whole history)
+  // query tail takes finer pieces (few blocks, each against a whole history)
   const bool even = a.query_tail == 0;
   const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), 0, a.query_tail, slot_cap, even ? 1 : 0, 1.0 / (even ? kFwdTargetChunks : kTargetChunks),
                         header, items, seq_base, splits, nullptr, 0};

@@ -1,0 +1,41 @@
+"""Forward over a query tail: its blocks start at the 32 rows that hold the first wanted row, waves past the end of a sequence only load,
+and pieces of the long key lists are added row by row.  Wanted rows against the oracle, all others untouched."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hstu_oracle as orc
+from paper_2602_16986_amd import binding as hb
+from paper_2602_16986_amd import workloads as wl
+from test_gpu_parity import check, oracle_args, to_np, TOL
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [1, 31, 32, 33, 64, 127, 128, 129, 160, 161, 1500, 2049]
+TARGETS = [0, 31, 1, 2, 0, 100, 128, 1, 33, 0, 70, 129]
+
+
+@pytest.mark.parametrize("dim,dtype", [(128, "bf16"), (64, "bf16"), (32, "fp32")])
+@pytest.mark.parametrize("tail", [1, 31, 32, 33, 97, 4000])
+@pytest.mark.parametrize("candidates", [False, True])
+def test_tail_block_edges(dim, dtype, tail, candidates):
+    targets = np.array(TARGETS, dtype=np.int32) if candidates else None
+    K1, K2 = (200, 40) if candidates else (-1, 0)
+    w = wl.build("tail-edges", LENGTHS, 2, dim, dtype, seed=11, K1=K1, K2=K2, num_targets=targets)
+    from paper_2602_16986_amd.runner import DeviceWorkload
+    dw = DeviceWorkload(w)
+    prob = hb.AttnProblem(dw.q, dw.k, dw.v, dw.out, dw.offsets, max_seqlen=w.max_seqlen, num_targets=dw.num_targets, local_window=K1,
+                          global_prefix=K2, alpha=w.alpha, inv_n=1.0 / w.N, rab_table=dw.table, rab_bounds=dw.bounds, query_tail=tail)
+    ws = hb.new_workspace(hb.hstu_attn_workspace_bytes(prob, False), "cuda")
+    ws.fill_(0xFF)                                          # NaNs: no partial sum may be read that was not written
+    dw.out.fill_(7.0)
+    hb.hstu_attn_fwd(prob, dw.q, dw.k, dw.v, dw.out, ws)
+    torch.cuda.synchronize()
+    got = to_np(dw.out)
+    ref = orc.attn_fwd(w.q, w.k, w.v, w.offsets, **oracle_args(w))
+    wanted = np.zeros(w.T, dtype=bool)
+    for b, L in enumerate(LENGTHS):
+        hist = L - (TARGETS[b] if candidates else 0)
+        wanted[w.offsets[b] + max(hist - tail, 0):w.offsets[b] + L] = True
+    check("A", got[wanted], ref[wanted], TOL[dtype])
+    assert np.all(got[~wanted] == 7.0)
