@@ -6,6 +6,8 @@
 // Both operands have the reduction index as their slow axis, which is the wrong way round for the matrix cores (a lane
 // wants 8 consecutive k of one output row): the 32-row tiles go to LDS as they are and both fragments come out through the
 // LDS transpose loads (ds_read_b64_tr_b16).  Both operands use the same k assignment, which is all the product needs.
+#include <algorithm>
+
 #include "hstu_common.h"
 #include "hstu_kernels.h"
 
@@ -124,13 +126,22 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_kernel(const __bf16* __restric
       for (int q = 0; q < 16; ++q) out[(int64_t)(32 * i + 8 * (q >> 2) + 4 * hf + (q & 3)) * N2 + 32 * j] = acc[i][j][q];
 }
 
+constexpr int kSlabsAhead = 8;             // loads that a thread has in flight
 // C = sum over slabs of partial, in slab order
 __global__ __launch_bounds__(256) void gemm_tn_reduce_kernel(int64_t elems4, int nslab, const f32x4* __restrict__ partial,
                                                              f32x4* __restrict__ C) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= elems4) return;
-  f32x4 s = partial[i];
-  for (int k = 1; k < nslab; ++k) s += partial[(int64_t)k * elems4 + i];
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  int k = 0;
+  for (; k + kSlabsAhead <= nslab; k += kSlabsAhead) {
+    f32x4 p[kSlabsAhead];
+#pragma unroll
+    for (int e = 0; e < kSlabsAhead; ++e) p[e] = partial[(int64_t)(k + e) * elems4 + i];
+#pragma unroll
+    for (int e = 0; e < kSlabsAhead; ++e) s += p[e];
+  }
+  for (; k < nslab; ++k) s += partial[(int64_t)k * elems4 + i];
   C[i] = s;
 }
 
@@ -138,11 +149,14 @@ __global__ __launch_bounds__(256) void gemm_tn_reduce_kernel(int64_t elems4, int
 
 bool gemm_tn_supported(int N1, int N2) { return N1 >= kTile && N2 >= kTile && N1 % kTile == 0 && N2 % kTile == 0; }
 
-// slabs so that the grid is about 1024 workgroups (two rounds of two per compute unit), each slab a multiple of the row tile
+// Slabs so that the grid is one round of two workgroups per compute unit; a slab is at least eight row tiles, or four where that leaves a
+// workgroup per compute unit.  Every slab is an fp32 copy of the output to write and read: with 1024 workgroups the two weight gradients of
+// 6,418 rows (2048 x 512, 512 x 512) took 42 + 23 us, now 33 + 19; of 87,728 rows 278 + 103, now 266 + 80 (with 256: 418 + 115).
 int gemm_tn_slabs(int64_t T, int N1, int N2) {
   const int tiles = (N1 / kTile) * (N2 / kTile);
-  int64_t nslab = (1024 + tiles - 1) / tiles;
-  const int64_t max_slabs = (T + 4 * kBK - 1) / (4 * kBK);           // at least four tiles per slab
+  int64_t nslab = (512 + tiles - 1) / tiles;
+  const int64_t row_tiles = (T + kBK - 1) / kBK;
+  const int64_t max_slabs = std::max((row_tiles + 7) / 8, std::min((row_tiles + 3) / 4, (int64_t)(256 / tiles)));
   if (nslab > max_slabs) nslab = max_slabs;
   if (nslab < 1) nslab = 1;
   return (int)nslab;
