@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0
 ROOT = os.path.dirname(os.path.abspath(__file__))
 
 
-TRAFFIC_SOURCES = ("attn_core.hip", "attn_fwd_pipe.hip", "gated_norm.hip", "schedule.hip", "api.hip", "hstu_common.h", "hstu_geometry.h",
+TRAFFIC_SOURCES = ("attn_core.hip", "attn_fwd_pipe.hip", "attn_dq.hip", "gated_norm.hip", "schedule.hip", "api.hip", "hstu_common.h", "hstu_geometry.h",
                    "hstu_kernels.h")
 
 
@@ -412,10 +412,15 @@ def main():
     peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_FP32_TFLOPS
 
     # Roofline of the dominant kernel, in USEFUL FLOPs: of the 10 d the backward owes per unmasked pair (S, dP, dV, dK,
-    # dQ) the dK/dV pass is credited with dV, dK and half of the S and dP that both passes compute (6 d), the dQ pass with dQ
-    # and the other half (4 d); the forward with its 4 d.  What the passes execute (4 d, 6 d, 8 d) is reported beside it.
-    useful_d = {"attn_fwd": 4.0, "attn_bwd_dq": 4.0, "attn_bwd_dkdv": 6.0}
-    executed_d = {"attn_fwd": 4.0, "attn_bwd_dq": 6.0, "attn_bwd_dkdv": 8.0}
+    # dQ) the dK/dV pass computes 8 d and hands dS on to the dQ product, 2 d (bf16 with 128 features).  Where the two passes are
+    # independent both compute S and dP: the dK/dV pass is then credited with dV, dK and half of them (6 of the 8 d it executes), the
+    # dQ pass with dQ and the other half (4 of 6 d).  The forward has its 4 d.  What the passes execute is reported beside it.
+    if w.dtype == "bf16" and w.d == 128:
+        useful_d = {"attn_fwd": 4.0, "attn_bwd_dq": 2.0, "attn_bwd_dkdv": 8.0}
+        executed_d = useful_d
+    else:
+        useful_d = {"attn_fwd": 4.0, "attn_bwd_dq": 4.0, "attn_bwd_dkdv": 6.0}
+        executed_d = {"attn_fwd": 4.0, "attn_bwd_dq": 6.0, "attn_bwd_dkdv": 8.0}
     dom = max((k for k in kern if k in useful_d), key=lambda k: kern[k])
     achieved = useful_d[dom] * w.d * fl["pairs"] / (kern[dom] * 1e-3) / 1e12
     roofline = {"kernel": dom, "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
