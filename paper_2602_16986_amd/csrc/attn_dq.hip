@@ -62,12 +62,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_dq_kernel(const AttnArgs 
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" :: "s"(dst), "v"(voff), "s"(rs) : "memory", "m0");
   };
   auto entry_of = [&](int yt) -> i32x4 { return table[last_pair - (yt >> 1)]; };
-  auto has_ds = [&](const i32x4& e) { return qt >= e[1] && qt < e[1] + e[2]; };
-  // loads of key tile yt (its table entry: e) into LDS stage s; a wave whose queries see none of the tile's key block has no dS there
-  auto issue = [&](int yt, const i32x4& e, int s) {
+  // (a 32 x 64 block without a visible pair holds zeros, where it was written: neither read nor multiplied)
+  auto has_ds = [&](int yt, const i32x4& e) {
+    return qt >= e[1] && qt < e[1] + e[2] && classify_tile(g, 32 * qt, 32 * qt + 31, yt * kBN, yt * kBN + kBN - 1) != kTileEmpty;
+  };
+  // loads of key tile yt (its table entry: e) into LDS stage s; some: has_ds()
+  auto issue = [&](int yt, const i32x4& e, bool some, int s) {
     const uint32_t dst0 = (uint32_t)(uintptr_t)(lds_void)(smem + s * kStage);
     const uint64_t ds = (uint64_t)(uintptr_t)a.ds + (uint64_t)(uint32_t)(e[0] + h * e[2] + qt - e[1]) * kDsTileBytes + (yt & 1) * (kDsTileBytes / 2);
-    const uint32_t ds_bytes = has_ds(e) ? kDsTileBytes / 2 : 0;
+    const uint32_t ds_bytes = some ? kDsTileBytes / 2 : 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) dma16_nt(ds, ds_bytes, ds_voff + 1024 * j, dst0 + kTileK + wave * (kTileDs / 4) + 1024 * j);
 #pragma unroll
@@ -90,10 +93,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_dq_kernel(const AttnArgs 
 
   i32x4 e = {0, 0, 0, 0}, e_next = {0, 0, 0, 0};
   int yt_next = 0;
+  bool some = false;
   if (t_begin < ntiles) {
     const int yt = tr.at(t_begin);
     e = entry_of(yt);
-    issue(yt, e, 0);
+    some = has_ds(yt, e);
+    issue(yt, e, some, 0);
     yt_next = tr.at(min(t_begin + 1, ntiles - 1));
     e_next = entry_of(yt_next);
   }
@@ -101,10 +106,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_dq_kernel(const AttnArgs 
     const int s = (t - t_begin) & 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's loads of tile t have landed; the barrier publishes them
     __syncthreads();
-    const bool mine = has_ds(e);
+    const bool mine = some;
     e = e_next;
     if (t + 1 < ntiles) {
-      issue(yt_next, e, s ^ 1);
+      some = has_ds(yt_next, e);
+      issue(yt_next, e, some, s ^ 1);
       yt_next = tr.at(min(t + 2, ntiles - 1));
       e_next = entry_of(yt_next);
     }
