@@ -248,7 +248,8 @@ typedef struct hstu_layer_params {
 
 /* Bytes of device scratch (256-byte aligned) for hstu_layer_fwd (for_backward = 0) or hstu_layer_bwd; 0 for an
  * invalid description.  Forward: X, the projection and Y (T*(E + 5*H*d) bf16), backward: 17 such [T, 512]-sized
- * buffers at E = H*d = 512; both include the attention workspace and 64 MiB offered to the GEMM library. */
+ * buffers at E = H*d = 512; both include the attention workspace and 64 MiB offered to the GEMM library.  The backward's figure
+ * includes the room for dS of hstu_attn_workspace_bytes, and hstu_layer_bwd too accepts a workspace without it. */
 size_t hstu_layer_workspace_bytes(const hstu_layer_params* p, int for_backward);
 
 int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u_saved, void* attn_saved, float* mean,
