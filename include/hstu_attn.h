@@ -346,7 +346,8 @@ const char* hstu_status_string(int status);
  * grid would have.  Reads device memory with a blocking copy; for reporting only.
  * Returns HSTU_ERR_SHAPE (out[0] = 0) when the scheduler of that call found the DEVICE copies of seq_offsets / num_targets
  * inconsistent with the description (offsets not starting at 0, decreasing, a sequence longer than max_seqlen, an end past
- * total_tokens, a candidate count outside [0, L]): such a call computes nothing and leaves every output untouched, instead of
+ * total_tokens, a candidate count outside [0, L]; in a backward that was given room for dS: lengths that need more of it than the
+ * host copy's): such a call computes nothing and leaves every output untouched (d_rab_table is cleared), instead of
  * addressing rows outside the tensors (the host cannot see device-side offsets when seq_offsets_host is NULL). */
 int hstu_attn_schedule_stats(const hstu_attn_params* p, const void* workspace, int for_backward, int64_t out[3]);
 

@@ -356,8 +356,8 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     int32_t* const sb[2] = {(int32_t*)(ws + l.seq_base[0]), (int32_t*)(ws + l.seq_base[1])};
     SplitItem* const sp[2] = {(SplitItem*)(ws + l.splits_dq), (SplitItem*)(ws + l.splits)};
     const int caps[2] = {l.slot_cap_dq, l.slot_cap};
-    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ds_room ? (int32_t*)(ws + l.ds_table) : nullptr,
-                             (int64_t)(l.total_ds - l.ds) / kDsTileBytes, ex, stream) != hipSuccess)
+    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ds_room ? (int32_t*)(ws + l.ds_table) : nullptr, ex,
+                             stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }
   const SchedHeader* headers[2];
@@ -368,7 +368,8 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     a.ds = ws + l.ds;
     a.ds_table = (const int32_t*)(ws + l.ds_table);
     a.ds_pair0 = (const int32_t*)(ws + l.seq_base[1]);
-    a.ds_header = (const SchedHeader*)(ws + l.header[1]);
+    a.ds_cap = std::min((int64_t)((workspace_bytes - l.ds) / kDsTileBytes), (int64_t)0x7FFFFFFF);
+    for (int s = 0; s < 2; ++s) a.ds_lists[s] = (SchedHeader*)(ws + l.header[s]);
   }
   for (int i = 0; i < 2; ++i) {
     const int s = through_ds ? 1 - i : i;                // s = 0: dQ pass (query blocks), s = 1: dK/dV pass (key blocks)

@@ -214,7 +214,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   const int pos = ((slot / kXcdGroup) * kNumXcd + xcd) * kXcdGroup + slot % kXcdGroup;
   // (the list's length and the entry are fetched together; an entry beyond the length is read, inside the list's
   // capacity, and dropped)
-  const int count = a.header->count;
+  const int count = DS && !ds_fits(a.header, a.ds_cap) ? 0 : a.header->count;
   const WorkItem item = a.items[min(pos, a.max_items - 1)];
   if (pos >= count) return;
   HSTU_TLB(0);

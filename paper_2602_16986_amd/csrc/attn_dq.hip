@@ -36,8 +36,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_dq_kernel(const AttnArgs 
   const int wg = blockIdx.x;
   const int xcd = wg % kNumXcd, slot = wg / kNumXcd;
   const int pos = ((slot / kXcdGroup) * kNumXcd + xcd) * kXcdGroup + slot % kXcdGroup;
-  const int count = a.ds_header->bad_batch ? 0 : a.header->count;
+  const int count = a.header->count;
   const WorkItem item = a.items[min(pos, a.max_items - 1)];
+  if (!ds_fits(a.ds_lists[1], a.ds_cap)) {                 // the dK/dV pass has left nothing: neither list has anything to finish
+    if (wg == 0 && threadIdx.x == 0) {
+      for (SchedHeader* const list : {a.ds_lists[0], a.ds_lists[1]}) {
+        list->count = 0;
+        list->splits = 0;
+        list->bad_batch = 1;
+      }
+    }
+    return;
+  }
   if (pos >= count) return;
   const int xb = item.rb_h >> 8, h = item.rb_h & 255, seq0 = item.seq0, L = item.len;
   const SeqGeom g = {L, item.hist, a.K1, a.K2};

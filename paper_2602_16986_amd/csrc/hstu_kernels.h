@@ -16,7 +16,11 @@ struct SchedHeader {
   int32_t chunk_tiles;    // piece size used for the cut blocks
   int32_t bad_batch;      // 1: seq_offsets / num_targets on the device contradict the description (then count = 0: no kernel
                           // touches a token row)
+  int64_t ds_tiles;       // dS tiles of a dK/dV list whose AttnArgs::ds_table is filled, all heads; -1: it is not
 };
+
+// a call that has room for `cap` tiles may leave dS for the items of this dK/dV list
+__host__ __device__ inline bool ds_fits(const SchedHeader* list, int64_t cap) { return (uint64_t)list->ds_tiles <= (uint64_t)cap; }
 
 struct WorkItem {
   int32_t b;              // sequence
@@ -71,7 +75,10 @@ struct AttnArgs {
   void* ds;
   const int32_t* ds_table;
   const int32_t* ds_pair0;
-  const SchedHeader* ds_header;     // of the dK/dV list: bad_batch = no dS was left
+  // Tiles that `ds` holds.  The host plans the room from its copy of the offsets; where the device's need more, the dK/dV pass and the dQ
+  // product leave at once, and the latter empties both lists (of the two passes), so that nothing that was never written is added up.
+  int64_t ds_cap;
+  SchedHeader* ds_lists[2];
 };
 constexpr int kDsTileBytes = 32 * 128 * 2;
 constexpr int kDbiasCopies = 8;          // one per die
@@ -94,11 +101,10 @@ struct ExpandJob {
 hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
                            int32_t* seq_base, SplitItem* splits, int slot_cap, const ExpandJob& ex, hipStream_t stream);
 // The two lists of the backward pass: [0] query blocks (dQ pass), [1] key blocks (dK/dV pass).  ds_table: AttnArgs::ds_table to fill
-// (with seq_base[1] as AttnArgs::ds_pair0), or nullptr; ds_cap: the dS tiles
-// there is room for; at most schedule_sorted_pairs() pairs.
+// (with seq_base[1] as AttnArgs::ds_pair0), or nullptr; at most schedule_sorted_pairs() pairs then.
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], int32_t* ds_table, int64_t ds_cap, const ExpandJob& ex, hipStream_t stream);
+                                const int slot_cap[2], int32_t* ds_table, const ExpandJob& ex, hipStream_t stream);
 // false: no list that the scheduler can build for this problem has a cut block (host arithmetic on bounds; host_offsets may be
 // nullptr).  which: 0 forward, 1 dQ list, 2 dK/dV list.
 bool schedule_may_cut(const AttnArgs& a, int which, int block_rows, int tile_cols, const int32_t* host_offsets);

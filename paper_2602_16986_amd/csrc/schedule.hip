@@ -53,8 +53,7 @@ struct SchedJob {
   WorkItem* items;
   int32_t* seq_base;
   SplitItem* splits;
-  int32_t* ds_table;       // key-major list, optional: AttnArgs::ds_table ...
-  int64_t ds_cap;          // ... and the dS tiles there is room for; lengths that need more than the host's copy of them does get an empty list
+  int32_t* ds_table;       // key-major list, optional: AttnArgs::ds_table
 };
 
 struct SchedShared {
@@ -155,7 +154,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   __threadfence_block();
   __syncthreads();
   if (sh.bad) {
-    if (tid == 0) *header = SchedHeader{0, 0, 0, 0, 0, 1};
+    if (tid == 0) *header = SchedHeader{0, 0, 0, 0, 0, 1, 0};
     return;
   }
   const int total = blocks_per_head * H;                 // <= max_items by construction of the bound
@@ -221,7 +220,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     atomicAdd(&sh.tiles, my_tiles);
     atomicAdd(&sh.dense, my_dense);
     __syncthreads();
-    if (tid == 0) *header = SchedHeader{total, 0, (int64_t)sh.tiles, (int64_t)sh.dense, 0, 0};
+    if (tid == 0) *header = SchedHeader{total, 0, (int64_t)sh.tiles, (int64_t)sh.dense, 0, 0, -1};
     return;
   }
   {
@@ -256,17 +255,15 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   };
   const int ipt = (pairs + kSchedThreads - 1) / kSchedThreads;
   const int own0 = min(tid * ipt, pairs), own1 = min(own0 + ipt, pairs);   // the scans below give every thread consecutive pairs
+  int64_t ds_tiles = -1;
   if (job.ds_table) {                                      // where the dS tiles of a pair's heads start
     int sum = 0, all;
 #pragma unroll 1
     for (int idx = own0; idx < own1; ++idx) sum += (int)costs[idx];
     sum = block_scan(sum, sh.wave_total[7], all);
-    if ((int64_t)all * H > job.ds_cap) {
-      if (tid == 0) *header = SchedHeader{0, 0, 0, 0, 0, 1};
-      return;
-    }
+    ds_tiles = (int64_t)all * H;
 #pragma unroll 1
-    for (int idx = own0; idx < own1; ++idx) { job.ds_table[4 * idx] = sum * H; sum += (int)costs[idx]; }
+    for (int idx = own0; idx < own1; ++idx) { job.ds_table[4 * idx] = (int)((uint32_t)sum * (uint32_t)H); sum += (int)costs[idx]; }
   }
   int slot0 = 0, rank0 = 0, slots = 0, nsplit = 0, entries = pairs;        // first slot and rank of this thread's pairs among the cut ones; totals
   bool cuts = false;                                       // uniform: some block is cut
@@ -290,7 +287,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     chunk *= 2;                                                // ends: with no pair cut, entries = pairs <= kSortMax
   }
   if (!cuts) { entries = pairs; nsplit = 0; }
-  if (tid == 0) *header = SchedHeader{entries * H, nsplit * H, all_tiles, all_dense, chunk, 0};
+  if (tid == 0) *header = SchedHeader{entries * H, nsplit * H, all_tiles, all_dense, chunk, 0, ds_tiles};
   const int key_max = cuts ? min(max_cost, 2 * chunk) : max_cost;            // no entry is longer than this
   const int key_bits = max(32 - __clz(key_max), 1);
   const int shift = max(key_bits - kKeyBits, 0);
@@ -453,16 +450,16 @@ hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int ti
   // query tail takes finer pieces (few blocks, each against a whole history)
   const bool even = a.query_tail == 0;
   const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), 0, a.query_tail, slot_cap, even ? 1 : 0, 1.0 / (even ? kFwdTargetChunks : kTargetChunks),
-                        header, items, seq_base, splits, nullptr, 0};
+                        header, items, seq_base, splits, nullptr};
   return launch(a, lists ? 1 : 0, job, job, ex, stream);
 }
 
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], int32_t* ds_table, int64_t ds_cap, const ExpandJob& ex, hipStream_t stream) {
+                                const int slot_cap[2], int32_t* ds_table, const ExpandJob& ex, hipStream_t stream) {
   // dQ list (query-major): equal pieces of about one slot's share, 512 slots at two workgroups per compute unit
-  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, 1.0 / kDqTargetChunks, header[0], items[0], seq_base[0], splits[0], nullptr, 0};
-  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, 1.0 / kTargetChunks, header[1], items[1], seq_base[1], splits[1], ds_table, ds_cap};
+  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, 1.0 / kDqTargetChunks, header[0], items[0], seq_base[0], splits[0], nullptr};
+  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, 1.0 / kTargetChunks, header[1], items[1], seq_base[1], splits[1], ds_table};
   return launch(a, lists ? 2 : 0, j0, j1, ex, stream);
 }
 
