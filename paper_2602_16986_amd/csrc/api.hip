@@ -88,28 +88,30 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     l.items[s] = off; off += align_up((size_t)l.max_items[s] * sizeof(WorkItem));
     l.seq_base[s] = off; off += align_up(((size_t)p->batch + 1) * sizeof(int32_t));
   }
+  // All that a later call with reuse_schedule takes from this one comes first, at places that follow from the sizes such calls share (not
+  // from max_seqlen, the host copy of the offsets or the room for dS).
+  l.splits = off; off += align_up((size_t)(l.slot_cap / 2 + 1) * sizeof(SplitItem));
+  // (dS for 32 and 64 features: its product would move as many bytes as for 128 and save a half or a quarter of the matrix work)
+  const bool ds = for_backward && p->dtype == HSTU_BF16 && p->head_dim == 128 &&
+                  (int64_t)p->total_tokens / 128 + p->batch <= schedule_sorted_pairs();
+  if (for_backward) { l.splits_dq = off; off += align_up((size_t)(l.slot_cap_dq / 2 + 1) * sizeof(SplitItem)); }
+  if (ds) { l.ds_table = off; off += align_up(((size_t)p->total_tokens / 128 + p->batch) * 16); }
   l.bias = off;
   off += align_up((size_t)p->num_heads * ((size_t)p->max_seqlen + 1) * sizeof(float));
   l.seed = off;                                        // score seeds by distance (bias + mask) of the pipelined kernels
   off += align_up((size_t)kSeedVariants * p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float));
   if (!for_backward) {
-    l.splits = off; off += align_up((size_t)(l.slot_cap / 2 + 1) * sizeof(SplitItem));
     l.partial = off;
     off += align_up((size_t)l.slot_cap * fwd_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
   }
   if (for_backward) {
-    l.splits = off; off += align_up((size_t)(l.slot_cap / 2 + 1) * sizeof(SplitItem));
     l.partial = off;
     off += align_up((size_t)l.slot_cap * 2 * dkv_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
-    l.splits_dq = off; off += align_up((size_t)(l.slot_cap_dq / 2 + 1) * sizeof(SplitItem));
     l.partial_dq = off;
     off += align_up((size_t)l.slot_cap_dq * dq_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
     l.dbias = off;                                     // per-distance sums of dS for the bias-table gradient, then the bucket ends per distance
     off += align_up((size_t)(dbias_copies_for(p) * p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
-    // dS, behind everything else: a workspace without room for it is accepted (32 and 64 features: a dQ product would move as many
-    // bytes as for 128 and save a half or a quarter of the matrix work)
-    const bool ds = p->dtype == HSTU_BF16 && p->head_dim == 128 && (int64_t)p->total_tokens / 128 + p->batch <= schedule_sorted_pairs();
-    if (ds) { l.ds_table = off; off += align_up(((size_t)p->total_tokens / 128 + p->batch) * 16); }
+    // dS, behind everything else: a workspace without room for it is accepted
     const int64_t bytes = ds ? ds_tiles_bound(p) * kDsTileBytes : 0;
     if (bytes > 0 && bytes <= kDsMaxBytes) { l.ds = off; l.total_ds = off + (size_t)bytes; }
   }
@@ -345,7 +347,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   AttnArgs a = make_args(p, q, k, v);
   a.dout = dout; a.dq = dq; a.dk = dk; a.dv = dv;
   a.pre_q = pre_q; a.pre_k = pre_k; a.pre_v = pre_v; a.s_pre = s_pre;
-  const bool ds_room = l.ds != 0 && workspace_bytes >= l.total_ds;
+  const bool through_ds = l.ds != 0 && workspace_bytes >= l.total_ds;
   const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
   const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
   {
@@ -356,14 +358,14 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     int32_t* const sb[2] = {(int32_t*)(ws + l.seq_base[0]), (int32_t*)(ws + l.seq_base[1])};
     SplitItem* const sp[2] = {(SplitItem*)(ws + l.splits_dq), (SplitItem*)(ws + l.splits)};
     const int caps[2] = {l.slot_cap_dq, l.slot_cap};
-    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, ds_room ? (int32_t*)(ws + l.ds_table) : nullptr, ex,
+    // (the table of dS tiles goes with the lists, whether this call has room for dS or not: a later one that reuses them decides for itself)
+    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, l.ds_table ? (int32_t*)(ws + l.ds_table) : nullptr, ex,
                              stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }
   const SchedHeader* headers[2];
   const SplitItem* const splits[2] = {(const SplitItem*)(ws + l.splits_dq), (const SplitItem*)(ws + l.splits)};
   const float* const partial[2] = {(const float*)(ws + l.partial_dq), (const float*)(ws + l.partial)};
-  const bool through_ds = ds_room;
   if (through_ds) {
     a.ds = ws + l.ds;
     a.ds_table = (const int32_t*)(ws + l.ds_table);

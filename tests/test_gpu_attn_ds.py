@@ -65,6 +65,37 @@ def test_backward_through_ds(name):
     check("dtable (no room)", to_np(dw.dtable), ref_table, TOL["bf16"])
 
 
+@pytest.mark.parametrize("name", ["tile-edges", "window-and-prefix", "candidates", "one-bucket-tiles"])
+@pytest.mark.parametrize("build_room,use_room,longer", [(False, True, 0), (True, False, 0), (False, True, 3000), (True, True, 3000)])
+def test_lists_of_a_call_with_other_room(name, build_room, use_room, longer):
+    """reuse_schedule between calls that decide differently about dS (a host copy of the offsets in one of them only, in a workspace that is
+    too small without it) or that give another max_seqlen: the lists and the table of dS tiles lie where the second call looks for them."""
+    from paper_2602_16986_amd.runner import DeviceWorkload
+    w = workload(name)
+    dw = DeviceWorkload(w, bias_grad=True)
+    p = dw.problem.params
+    host = p.seq_offsets_host
+    sizes = []
+    for extra in (0, longer):
+        p.max_seqlen = w.max_seqlen + extra
+        sizes.append(hb.hstu_attn_workspace_bytes(dw.problem, True))
+    ws = hb.new_workspace(max(sizes), "cuda")
+    refs = orc.attn_bwd(w.q, w.k, w.v, w.dout, w.offsets, **oracle_args(w))
+    ref_table = orc.attn_bwd_bias(w.q, w.k, w.v, w.dout, w.offsets, **oracle_args(w))
+    ws.fill_(0xFF)
+    for call, (room, extra) in enumerate(((build_room, 0), (use_room, longer))):
+        p.max_seqlen = w.max_seqlen + extra
+        p.seq_offsets_host = host if room else None
+        p.reuse_schedule = call
+        size = sizes[call] if room else sizes[call] - 256
+        outs = [torch.full_like(t, float("nan")) for t in (dw.q, dw.k, dw.v)]
+        dw.dtable.fill_(float("nan"))
+        hb.hstu_attn_bwd(dw.problem, dw.q, dw.k, dw.v, dw.dout, *outs, ws[:size])
+        torch.cuda.synchronize()
+        for what, g, r in zip(("dQ", "dK", "dV", "dtable"), [*outs, dw.dtable], [*refs, ref_table]):
+            check(f"{what} (call {call})", to_np(g), r, TOL["bf16"])
+
+
 def test_room_for_other_lengths_computes_nothing():
     """The host's copy of the offsets says sixteen short sequences, the device's say one long one that needs more room for dS: an empty
     list and untouched outputs, not a write behind the workspace."""
