@@ -99,8 +99,8 @@ typedef struct hstu_attn_params {
   int32_t reuse_schedule;   /* 0: the call builds its work lists (tile scheduler) in the workspace.  1: the workspace still holds the
                                lists that the same entry point (hstu_attn_fwd, or hstu_attn_bwd) wrote for the same batch,
                                num_heads, head_dim, dtype, mask and query_tail, and no other call has used the workspace since
-                               (max_seqlen, the biases, the host copy of the offsets and workspace_bytes may differ): the
-                               scheduler is skipped (the layers of one model share seq_offsets and mask, so only the first layer
+                               (max_seqlen, the biases, the host copy of the offsets, workspace_bytes and a layer's embed_dim
+                               may differ): the scheduler is skipped (the layers of one model share seq_offsets and mask, so only the first layer
                                of a forward or of a backward sweep needs it).  The bias table is expanded on every call.  The
                                layer entry points pass it on to their attention calls */
 } hstu_attn_params;

@@ -26,7 +26,8 @@ inline int dbias_copies_for(const hstu_attn_params* p) {
 }
 
 struct Layout {           // byte offsets inside a workspace
-  size_t header[2], items[2], seq_base[2], bias, seed, splits, partial, splits_dq, partial_dq, dbias, ds_table, total, ds, total_ds;
+  size_t header[2], items[2], seq_base[2], bias, seed, splits, partial, splits_dq, partial_dq, dbias, ds_table, total;
+  size_t ds_bytes;        // room for dS that the backward can use behind `total`, or elsewhere; 0: none
   int max_items[2];
   int slot_cap;           // partial-sum slots of the dK/dV pass (key blocks cut along the query axis) or of the forward
   int slot_cap_dq;        // ... of the dQ pass (query blocks of a small batch cut along the key axis)
@@ -111,12 +112,10 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     off += align_up((size_t)l.slot_cap_dq * dq_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
     l.dbias = off;                                     // per-distance sums of dS for the bias-table gradient, then the bucket ends per distance
     off += align_up((size_t)(dbias_copies_for(p) * p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
-    // dS, behind everything else: a workspace without room for it is accepted
     const int64_t bytes = ds ? ds_tiles_bound(p) * kDsTileBytes : 0;
-    if (bytes > 0 && bytes <= kDsMaxBytes) { l.ds = off; l.total_ds = off + (size_t)bytes; }
+    if (bytes <= kDsMaxBytes) l.ds_bytes = (size_t)bytes;
   }
   l.total = off;
-  if (l.total_ds == 0) l.total_ds = l.total;
   return l;
 }
 
@@ -265,7 +264,8 @@ const char* hstu_status_string(int status) {
 
 size_t hstu_attn_workspace_bytes(const hstu_attn_params* p, int for_backward) {
   if (validate(p) != HSTU_OK) return 0;
-  return make_layout(p, for_backward).total_ds;
+  const Layout l = make_layout(p, for_backward);
+  return l.total + l.ds_bytes;
 }
 
 int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const void* v, void* out, void* workspace,
@@ -307,7 +307,7 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
 
 int hstu_attn_bwd(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* dout, void* dq,
                   void* dk, void* dv, void* workspace, size_t workspace_bytes, void* stream_) {
-  return hstu::attn_bwd_through_silu(p, q, k, v, nullptr, nullptr, nullptr, 0, dout, dq, dk, dv, workspace, workspace_bytes, stream_);
+  return hstu::attn_bwd_through_silu(p, q, k, v, nullptr, nullptr, nullptr, 0, dout, dq, dk, dv, workspace, workspace_bytes, nullptr, 0, stream_);
 }
 
 }  // extern "C"
@@ -318,7 +318,7 @@ size_t hstu::attn_workspace_least(const hstu_attn_params* p, int for_backward) {
 
 int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* pre_q,
                                 const void* pre_k, const void* pre_v, int64_t s_pre, const void* dout, void* dq, void* dk,
-                                void* dv, void* workspace, size_t workspace_bytes, void* stream_) {
+                                void* dv, void* workspace, size_t workspace_bytes, void* ds, size_t ds_bytes, void* stream_) {
   const int st = validate(p);
   if (st != HSTU_OK) return st;
   if (pre_q || pre_k || pre_v) {
@@ -347,7 +347,11 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   AttnArgs a = make_args(p, q, k, v);
   a.dout = dout; a.dq = dq; a.dk = dk; a.dv = dv;
   a.pre_q = pre_q; a.pre_k = pre_k; a.pre_v = pre_v; a.s_pre = s_pre;
-  const bool through_ds = l.ds != 0 && workspace_bytes >= l.total_ds;
+  if (!ds) {                                             // behind everything else: a workspace without that room is accepted
+    ds = ws + l.total;
+    ds_bytes = workspace_bytes - l.total;
+  }
+  const bool through_ds = l.ds_bytes != 0 && ds_bytes >= l.ds_bytes;
   const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
   const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
   {
@@ -367,10 +371,10 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   const SplitItem* const splits[2] = {(const SplitItem*)(ws + l.splits_dq), (const SplitItem*)(ws + l.splits)};
   const float* const partial[2] = {(const float*)(ws + l.partial_dq), (const float*)(ws + l.partial)};
   if (through_ds) {
-    a.ds = ws + l.ds;
+    a.ds = ds;
     a.ds_table = (const int32_t*)(ws + l.ds_table);
     a.ds_pair0 = (const int32_t*)(ws + l.seq_base[1]);
-    a.ds_cap = std::min((int64_t)((workspace_bytes - l.ds) / kDsTileBytes), (int64_t)0x7FFFFFFF);
+    a.ds_cap = std::min((int64_t)(ds_bytes / kDsTileBytes), (int64_t)0x7FFFFFFF);
     for (int s = 0; s < 2; ++s) a.ds_lists[s] = (SchedHeader*)(ws + l.header[s]);
   }
   for (int i = 0; i < 2; ++i) {

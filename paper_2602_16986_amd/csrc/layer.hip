@@ -17,7 +17,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct LayerLayout {
   size_t attn, gemm, norm_partial, xn, pre, act, y, dy, dattn, dact, dxn, qscale, tn_partial, total;
-  size_t most;             // with room for all that the attention can use: its part is the last one
+  size_t ds, most;         // dS of the attention backward, if there is room for it: up to here
 };
 
 hstu_attn_params attn_problem(const hstu_layer_params* p) {
@@ -49,6 +49,10 @@ LayerLayout make_layer_layout(const hstu_layer_params* p, int for_backward) {
   const hstu_attn_params a = attn_problem(p);
   const size_t T = (size_t)a.total_tokens, E = (size_t)p->embed_dim, HD = (size_t)a.num_heads * a.head_dim;
   size_t off = 0;
+  // The attention's part, without dS, is the first one: its work lists lie at the same place for every layer of a batch, whatever
+  // their embed_dim (reuse_schedule).
+  const size_t least = attn_workspace_least(&a, for_backward);
+  l.attn = off; off += least;
   l.gemm = off; off += kGemmWorkspace;
   l.xn = off; off += align_up(T * E * 2);
   l.act = off; off += align_up(T * 4 * HD * 2);
@@ -71,9 +75,8 @@ LayerLayout make_layer_layout(const hstu_layer_params* p, int for_backward) {
     }
     l.tn_partial = off; off += align_up(tn);
   }
-  l.attn = off;
-  l.total = off + attn_workspace_least(&a, for_backward);
-  l.most = off + hstu_attn_workspace_bytes(&a, for_backward);
+  l.ds = l.total = off;
+  l.most = off + (hstu_attn_workspace_bytes(&a, for_backward) - least);
   return l;
 }
 
@@ -105,7 +108,7 @@ int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u
       bad16(p->gated_norm_w) || bad16(p->w1_q) || bad16(p->w1_scale) || bad16(p->w2_q) || bad16(p->w2_scale))
     return HSTU_ERR_SHAPE;
   const LayerLayout l = make_layer_layout(p, 0);
-  if (l.most == l.attn) return HSTU_ERR_SHAPE;
+  if (l.gemm == l.attn) return HSTU_ERR_SHAPE;
   if (!workspace || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < l.total) return HSTU_ERR_WORKSPACE;
   unsigned char* ws = (unsigned char*)workspace;
   __bf16* xn = (__bf16*)(ws + l.xn);
@@ -152,7 +155,7 @@ int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u
     }
   }
   // Eq. 3: A = attention(Q, K, V) on column blocks of the projection buffer
-  st = hstu_attn_fwd(&ap, act + 2 * HD, act + 3 * HD, act + HD, attn_saved, ws + l.attn, workspace_bytes - l.attn, stream_);
+  st = hstu_attn_fwd(&ap, act + 2 * HD, act + 3 * HD, act + HD, attn_saved, ws + l.attn, l.gemm - l.attn, stream_);
   if (st != HSTU_OK) return st;
   if (fp8) {
     {  // Eq. 4 before f2 with the quantisation fused in
@@ -206,7 +209,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
       bad16(p->norm_w) || bad16(p->gated_norm_w) || bad16(p->w1_q) || bad16(p->w1_scale))
     return HSTU_ERR_SHAPE;
   const LayerLayout l = make_layer_layout(p, 1);
-  if (l.most == l.attn) return HSTU_ERR_SHAPE;
+  if (l.gemm == l.attn) return HSTU_ERR_SHAPE;
   if (!workspace || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < l.total) return HSTU_ERR_WORKSPACE;
   unsigned char* ws = (unsigned char*)workspace;
   __bf16* xn = (__bf16*)(ws + l.xn);
@@ -271,7 +274,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
   }
   // attention backward: the gradients of the V, Q, K pre-activations land in their column blocks (SiLU' applied on the way out)
   st = attn_bwd_through_silu(&ap, act + 2 * HD, act + 3 * HD, act + HD, pre + 2 * HD, pre + 3 * HD, pre + HD, 4 * HD, dattn,
-                             dact + 2 * HD, dact + 3 * HD, dact + HD, ws + l.attn, workspace_bytes - l.attn, stream_);
+                             dact + 2 * HD, dact + 3 * HD, dact + HD, ws + l.attn, l.gemm - l.attn, ws + l.ds, workspace_bytes - l.ds, stream_);
   if (st != HSTU_OK) return st;
   {  // pre = X W1^T:  dX = dpre W1,  dW1 = dpre^T X
     ProfScope ps("gemm_dxn", stream);

@@ -108,6 +108,34 @@ def test_layer_backward_twice_is_identical(hb):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("d,lengths", [(128, [2600, 300]), (64, [700, 0, 130])])
+@pytest.mark.parametrize("first_E,E", [(64, 256), (512, 128)])
+def test_layer_reuses_the_work_lists_of_a_layer_of_another_width(hb, d, lengths, first_E, E):
+    """reuse_schedule between layers that share the batch and the heads but not embed_dim: same results as with lists of its own."""
+    from paper_2602_16986_amd.runner import DeviceLayer
+    first, second = (DeviceLayer(wl.build_layer("reuse", lengths, 2, d, e, seed=7)) for e in (first_E, E))
+    ws = [hb.new_workspace(max(a.numel(), b.numel()), "cuda") for a, b in ((first.ws_fwd, second.ws_fwd), (first.ws_bwd, second.ws_bwd))]
+    results = []
+    for reuse in (0, 1):
+        for w in ws:
+            w.fill_(0xFF)
+        for layer, flag in ((first, 0), (second, reuse)):
+            layer.ws_fwd, layer.ws_bwd = ws
+            layer.problem.params.attn.reuse_schedule = flag
+        for t in (second.out, second.u_saved, second.attn_saved, second.dz, second.d_norm_w, second.d_w1, second.d_gated_norm_w, second.d_w2):
+            t.fill_(float("nan"))
+        first.fwd()
+        second.fwd()
+        first.bwd()
+        second.bwd()
+        torch.cuda.synchronize()
+        results.append([t.clone() for t in (second.out, second.attn_saved, second.dz, second.d_norm_w, second.d_w1, second.d_gated_norm_w,
+                                            second.d_w2)])
+    for a, b in zip(*results):
+        assert not torch.isnan(a).any()
+        assert torch.equal(a, b)
+
+
 def test_layer_new_token_count_of_a_known_class_tunes_nothing(hb):
     """The GEMM kernels are chosen once per shape class (layer dimensions, token count rounded up to a power of two).
     A batch with another token count of the same class must not time candidates again (that would block the host on
