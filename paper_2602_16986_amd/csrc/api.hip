@@ -287,20 +287,20 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
   a.items = (const WorkItem*)(ws + l.items[0]);
   a.splits = (const SplitItem*)(ws + l.splits);
   a.partial = (float*)(ws + l.partial);
+  // (a list is cut only where the launch that finishes cut blocks follows: lengths on the device may be longer than the host's copy says)
+  const bool may_cut = schedule_may_cut(a, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), p->seq_offsets_host);
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, true);
     ProfScope ps(p->reuse_schedule ? "bias_expand_fwd" : "schedule_fwd", stream);
     if (launch_schedule(a, !p->reuse_schedule, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim),
                         (SchedHeader*)(ws + l.header[0]), (WorkItem*)(ws + l.items[0]), (int32_t*)(ws + l.seq_base[0]),
-                        (SplitItem*)(ws + l.splits), l.slot_cap, ex, stream) != hipSuccess)
+                        (SplitItem*)(ws + l.splits), may_cut ? l.slot_cap : 0, ex, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }
   {
     ProfScope ps("attn_fwd", stream);                      // includes the kernel that adds up the pieces of cut blocks
     if (launch_attn_fwd(a, p->dtype, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
-    if (schedule_may_cut(a, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), p->seq_offsets_host) &&
-        launch_fwd_finish(a, p->dtype, a.header, a.splits, a.partial, stream) != hipSuccess)
-      return HSTU_ERR_LAUNCH;
+    if (may_cut && launch_fwd_finish(a, p->dtype, a.header, a.splits, a.partial, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   return HSTU_OK;
 }
@@ -354,6 +354,8 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   const bool through_ds = l.ds_bytes != 0 && ds_bytes >= l.ds_bytes;
   const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
   const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
+  bool may_cut[2];                                       // as in the forward
+  for (int s = 0; s < 2; ++s) may_cut[s] = schedule_may_cut(a, 1 + s, rows[s], cols[s], p->seq_offsets_host);
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, false);
     ProfScope ps(p->reuse_schedule ? "bias_expand_bwd" : "schedule_bwd", stream);
@@ -361,7 +363,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     WorkItem* const it[2] = {(WorkItem*)(ws + l.items[0]), (WorkItem*)(ws + l.items[1])};
     int32_t* const sb[2] = {(int32_t*)(ws + l.seq_base[0]), (int32_t*)(ws + l.seq_base[1])};
     SplitItem* const sp[2] = {(SplitItem*)(ws + l.splits_dq), (SplitItem*)(ws + l.splits)};
-    const int caps[2] = {l.slot_cap_dq, l.slot_cap};
+    const int caps[2] = {may_cut[0] ? l.slot_cap_dq : 0, may_cut[1] ? l.slot_cap : 0};
     // (the table of dS tiles goes with the lists, whether this call has room for dS or not: a later one that reuses them decides for itself)
     if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, l.ds_table ? (int32_t*)(ws + l.ds_table) : nullptr, ex,
                              stream) != hipSuccess)
@@ -390,7 +392,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     if (e != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   for (int s = 0; s < 2; ++s)
-    if (!schedule_may_cut(a, 1 + s, rows[s], cols[s], p->seq_offsets_host)) headers[s] = nullptr;
+    if (!may_cut[s]) headers[s] = nullptr;
   DbiasJob db = {};
   if (p->d_rab_table) db = {p->rab_bounds, p->num_buckets, p->d_rab_table};
   {

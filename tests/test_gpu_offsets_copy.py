@@ -31,3 +31,22 @@ def test_too_little_room_for_ds_leaves_every_output_untouched(host, device):
     with pytest.raises(hb.HstuError) as e:
         hb.hstu_attn_schedule_stats(prob, ws, True)
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("dim,dtype", [(128, "bf16"), (64, "bf16"), (32, "fp32")])
+def test_longer_blocks_than_the_host_copy_has(dim, dtype):
+    """Host lengths that leave nothing to cut, so that no launch finishes cut blocks, and device lengths whose blocks would be cut: the rows
+    of every block are written."""
+    from paper_2602_16986_amd.runner import DeviceWorkload
+    w = wl.build("copy", [4096] + 15 * [0], 1, dim, dtype, seed=5, backward=True)
+    dw = DeviceWorkload(w)
+    prob = hb.AttnProblem(dw.q, dw.k, dw.v, dw.out, dw.offsets, max_seqlen=w.max_seqlen, seq_offsets_host=offsets_of(16 * [256]),
+                          alpha=w.alpha, inv_n=1.0 / w.N, rab_table=dw.table, rab_bounds=dw.bounds)
+    outs = [torch.full_like(dw.q, float("nan")) for _ in range(4)]
+    hb.hstu_attn_fwd(prob, dw.q, dw.k, dw.v, outs[0], hb.new_workspace(hb.hstu_attn_workspace_bytes(prob, False), "cuda"))
+    ws = hb.new_workspace(hb.hstu_attn_workspace_bytes(prob, True) - (256 if dim == 128 else 0), "cuda")     # (without room for dS)
+    hb.hstu_attn_bwd(prob, dw.q, dw.k, dw.v, dw.dout, *outs[1:], ws)
+    torch.cuda.synchronize()
+    refs = [orc.attn_fwd(w.q, w.k, w.v, w.offsets, **oracle_args(w)), *orc.attn_bwd(w.q, w.k, w.v, w.dout, w.offsets, **oracle_args(w))]
+    for what, got, ref in zip(("A", "dQ", "dK", "dV"), outs, refs):
+        check(what, to_np(got), ref, TOL[dtype])
