@@ -39,3 +39,25 @@ def test_tail_block_edges(dim, dtype, tail, candidates):
         wanted[w.offsets[b] + max(hist - tail, 0):w.offsets[b] + L] = True
     check("A", got[wanted], ref[wanted], TOL[dtype])
     assert np.all(got[~wanted] == 7.0)
+
+
+@pytest.mark.parametrize("dim,dtype", [(128, "bf16"), (32, "fp32")])
+@pytest.mark.parametrize("lengths,tail", [([2600, 300], 700), ([3000, 2500], 500)])
+def test_pieces_that_nearly_fit_their_slots(dim, dtype, lengths, tail):
+    """Pieces of the first length take up to a quarter more slots than there are (114 of 96, 188 of 176); the next length is a quarter more."""
+    from paper_2602_16986_amd.runner import DeviceWorkload
+    w = wl.build("tail-pieces", lengths, 2, dim, dtype, seed=12)
+    dw = DeviceWorkload(w)
+    dw.problem.params.query_tail = tail
+    dw.ws_fwd.fill_(0xFF)
+    dw.out.fill_(7.0)
+    dw.attn_fwd()
+    torch.cuda.synchronize()
+    items = hb.hstu_attn_schedule_stats(dw.problem, dw.ws_fwd)["items"]
+    entries = dw.ws_fwd[256:256 + 32 * items].cpu().numpy().view(np.int32).reshape(-1, 8)
+    assert (entries[:, 4] >= 0).any() and np.all(entries[entries[:, 4] >= 0][:, 3] - entries[entries[:, 4] >= 0][:, 2] <= 10)
+    got = to_np(dw.out)
+    ref = orc.attn_fwd(w.q, w.k, w.v, w.offsets, **oracle_args(w))
+    wanted = np.concatenate([np.arange(L) >= L - tail for L in lengths])
+    check("A", got[wanted], ref[wanted], TOL[dtype])
+    assert np.all(got[~wanted] == 7.0)
