@@ -209,7 +209,15 @@ __global__ __launch_bounds__(512, 1) void fp8_gemm_ksplit_kernel(int64_t M, int 
     }
   };
   // read-back: this wave finishes rows [16 kh, 16 kh + 16) of its pair's block; 8 lanes per row, 8 rows per instruction
-  const int n_begin = blockIdx.y * n_per, n_end = min(n_begin + n_per, N);   // this workgroup's output features
+  // This workgroup's output features are [n_begin, n_begin + n_end).  The operands are moved to the first, so that the chunk loop starts at 0
+  // (a start that the compiler does not know to be a multiple of 64 costs 65,536 rows x 4,096 features 514 us instead of 502; the kernel
+  // above has its registers full, takes the same either way and spills with moved operands).
+  const int n_begin = blockIdx.y * n_per, n_end = min(n_per, N - n_begin);
+  B += (int64_t)n_begin * K;
+  b_scale += n_begin;
+  if (C) C += n_begin;
+  D += n_begin;
+  const int u_end = u_cols - n_begin;                 // (SILU) of those, the ones in front of it go to u_out
   const int er = l >> 3, ec = l & 7;
   u32x4 cpre[2];
   float sa_row[2];
@@ -226,14 +234,14 @@ __global__ __launch_bounds__(512, 1) void fp8_gemm_ksplit_kernel(int64_t M, int 
       if (C && row < M) cpre[i] = *(const u32x4*)(C + row * N + n0 + 8 * ec);
     }
   };
-  for (int i = n_begin + t; i < n_end; i += 512) sbl[i] = b_scale[i];
-  bload(n_begin);
-  cload(n_begin);
+  for (int i = t; i < n_end; i += 512) sbl[i] = b_scale[i];
+  bload(0);
+  cload(0);
   float* my_epi = epi + w * 32 * kEpiPitch;
   const float* pair0 = epi + rb * 32 * kEpiPitch;             // partial sums of the pair's K halves
   const float* pair1 = epi + (4 + rb) * 32 * kEpiPitch;
   const int swz = r & SWZ;
-  for (int n0 = n_begin; n0 < n_end; n0 += kBN) {
+  for (int n0 = 0; n0 < n_end; n0 += kBN) {
     __syncthreads();                                  // fragments and partial sums of the previous chunk are consumed
     bstore();
     __syncthreads();
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(512, 1) void fp8_gemm_ksplit_kernel(int64_t M, int 
         for (int e = 0; e < 8; ++e) o[e] *= __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * o[e]));
       }
       __bf16* dst = D + row * N + n0 + 8 * ec;
-      if constexpr (SILU) { if (n0 < u_cols) dst = u_out + row * u_cols + n0 + 8 * ec; }
+      if constexpr (SILU) { if (n0 < u_end) dst = u_out + row * u_cols + n_begin + n0 + 8 * ec; }
       if (row < M)
         *(u32x4*)dst = (u32x4){pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]), pack_bf16x2(o[6], o[7])};
     }
@@ -297,8 +305,13 @@ __global__ __launch_bounds__(512, 1) void fp8_gemm_ksplit_kernel(int64_t M, int 
 // Features per workgroup.  A workgroup owns 128 token rows; with fewer row blocks than the chip has workgroup slots the output
 // features are divided as well, and every part reads its rows of A again (from the caches; about the time of one chunk).
 // Of the divisions of the chunks into equal parts the one with the least rounds x (chunks + 1) is taken.
-// 16,512 rows (129 row blocks), K = 512: N = 2048 with SiLU 73.6 us undivided, 42.5 in 3 parts; N = 512 with the residual 19.8 us
-// undivided, 16.0 in 3 parts.
+// With a residual, us undivided -> by the rule (-: which does not divide):
+//   rows       K = 512, N = 512   N = 2048        K = 1024, N = 512   N = 2048
+//   4,096      18.0 ->  8.2       64.7 -> 12.3    24.6 ->  8.3        81.6 -> 16.9
+//   16,512     19.7 -> 14.8       66.7 -> 33.8    25.6 -> 25.6        82.6 -> 62.8
+//   32,768     22.3 -> 19.4       96.6 -> 67.5    28.3, -             110, -
+//   65,536     30.9, -            171, -          54.7, -             211, -
+//   100,000    52, -              256  -> 241     117 -> 119          391 -> 390
 int features_per_workgroup(int64_t M, int N, int slots) {
   const int64_t row_blocks = (M + kBM - 1) / kBM;
   const int chunks = N / 64;
