@@ -408,32 +408,41 @@ __global__ __launch_bounds__(64 * W) void gated_norm_bwd_wide_kernel(const NormB
   }
 }
 
+// the sum over the lanes of a wave that are equal mod 4: two rotations inside a row of 16 lanes, then the rows in pairs
+__device__ __forceinline__ float sum_every_4th_lane(float v) {
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xF, 0xF, true));     // row_ror:4
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true));     // row_ror:8
+  const uint32_t a = __builtin_bit_cast(uint32_t, v);
+  const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return __builtin_bit_cast(float, (uint32_t)q[0]) + __builtin_bit_cast(float, (uint32_t)q[1]);
+}
+
 // dgamma[c] = sum over workgroups of partial[blk][0][c]; dbeta likewise from partial[blk][1][c] (not read unless wanted).
 // A few MB at most, so what counts is how many loads are in flight: a workgroup owns 16 columns (a 64-byte segment of every
-// partial row) and walks the rows 256 at a time; a column's sums meet in a fixed tree (lanes, then waves).  With 64 columns
+// partial row) and walks the rows kThreads / 4 at a time; a column's sums meet in a fixed tree (lanes, then waves).  With 64 columns
 // and 16 row groups per workgroup every thread walked 32 (512 features) or 128 (1024) rows one after the other:
 // 512 features 11.2 us, now 4.8; 1024 features 45.3 us, now 8.1.
-constexpr int kColsumThreads = 1024;
-__global__ __launch_bounds__(kColsumThreads) void gated_norm_colsum_kernel(int nblk, int D, const float* __restrict__ partial,
-                                                                           float* __restrict__ dgamma, float* __restrict__ dbeta) {
-  __shared__ f32x4 red[kColsumThreads / 64][4];
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void gated_norm_colsum_kernel(int nblk, int D, const float* __restrict__ partial,
+                                                                     float* __restrict__ dgamma, float* __restrict__ dbeta) {
+  __shared__ f32x4 red[kThreads / 64][4];
   const int tid = threadIdx.x, c4 = tid & 3, lane = tid & 63, wave = tid >> 6;
   const int c = blockIdx.x * 16 + 4 * c4;                  // D is a multiple of 8: 4 columns are all in or all out
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
   if (c < 2 * D) {
 #pragma unroll 4
-    for (int b = tid >> 2; b < nblk; b += kColsumThreads / 4) s += *(const f32x4*)(partial + (int64_t)b * 2 * D + c);
+    for (int b = tid >> 2; b < nblk; b += kThreads / 4) s += *(const f32x4*)(partial + (int64_t)b * 2 * D + c);
   }
 #pragma unroll
-  for (int m = 4; m < 64; m <<= 1)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] += __shfl_xor(s[i], m, 64);
+  for (int i = 0; i < 4; ++i) s[i] = sum_every_4th_lane(s[i]);
   if (lane < 4) red[wave][c4] = s;
   __syncthreads();
   if (tid < 4 && c < 2 * D) {
     f32x4 t = red[0][c4];
 #pragma unroll
-    for (int w = 1; w < kColsumThreads / 64; ++w) t += red[w][c4];
+    for (int w = 1; w < kThreads / 64; ++w) t += red[w][c4];
     float* dst = c < D ? dgamma + c : (dbeta ? dbeta + (c - D) : nullptr);
     if (dst) {
 #pragma unroll
@@ -442,9 +451,15 @@ __global__ __launch_bounds__(kColsumThreads) void gated_norm_colsum_kernel(int n
   }
 }
 
+// No more threads than there are rows to add need, and 256 where the columns alone fill the chip with workgroups.  The whole backward, us with
+// 1,024 threads everywhere -> this way (64 columns x 16 row groups before): 100 rows x 512 features 10.95 -> 10.5 (10.4); 1 row x 4,096 with
+// dbeta 10.8 -> 9.3 (9.2); 100 rows 13.1 -> 12.2 (12.0); 1,000 rows x 512 and more unchanged (11.4; 12.9 before), where 256 threads take 0.1-0.4 longer.
 static hipError_t launch_colsum(int nblk, const NormBwdArgs& p, const float* partial, hipStream_t stream) {
   const int cols = p.dbeta ? 2 * p.D : p.D;
-  hipLaunchKernelGGL(gated_norm_colsum_kernel, dim3((cols + 15) / 16), dim3(kColsumThreads), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
+  const dim3 grid((cols + 15) / 16);
+  if (nblk <= 16) hipLaunchKernelGGL(gated_norm_colsum_kernel<64>, grid, dim3(64), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
+  else if (nblk <= 64 || grid.x > 256) hipLaunchKernelGGL(gated_norm_colsum_kernel<256>, grid, dim3(256), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
+  else hipLaunchKernelGGL(gated_norm_colsum_kernel<1024>, grid, dim3(1024), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
   return hipGetLastError();
 }
 

@@ -450,3 +450,23 @@ def test_inconsistent_device_offsets_compute_nothing(hb):
     assert hb.hstu_attn_schedule_stats(dw.problem, dw.ws_fwd, False)["items"] > 0
     ref = orc.attn_fwd(w.q, w.k, w.v, w.offsets, **oracle_args(w))
     check("A after a rejected batch", to_np(dw.out), ref, TOL[w.dtype])
+
+
+@pytest.mark.parametrize("T,D", [(1, 64), (128, 64), (129, 64), (512, 512), (513, 64), (17, 1024), (65, 1024), (100, 4096), (300, 4096)])
+@pytest.mark.parametrize("with_beta", [False, True])
+def test_norm_backward_column_sums_at_the_edges_of_their_workgroups(hb, T, D, with_beta):
+    """Partial rows to add on both sides of 16 and 64, and columns on both sides of what fills the chip."""
+    rng = np.random.default_rng(T + D)
+    a, u, dy = (rng.standard_normal((T, D), dtype=np.float32) for _ in range(3))
+    gamma, beta = (rng.standard_normal(D, dtype=np.float32) for _ in range(2))
+    dev = [torch.from_numpy(x).cuda() for x in (dy, a, u, gamma)]
+    dbeta_dev = torch.full((D,), float("nan"), device="cuda") if with_beta else None
+    da, du = (torch.empty(T, D, device="cuda") for _ in range(2))
+    dgamma = torch.full((D,), float("nan"), device="cuda")
+    ws = hb.new_workspace(hb.hstu_gated_norm_bwd_workspace_bytes(T, D), "cuda")
+    hb.hstu_gated_norm_bwd(*dev, torch.from_numpy(beta).cuda() if with_beta else None, 1e-5, da, du, dgamma, dbeta_dev, ws)
+    torch.cuda.synchronize()
+    ref = orc.gated_norm_bwd(dy, a, u, gamma, beta if with_beta else None, 1e-5)
+    for what, got, r in zip(("dA", "dU", "dgamma", "dbeta"), (da, du, dgamma, dbeta_dev), ref):
+        if got is not None:
+            check(what, to_np(got), r, TOL["fp32"])
