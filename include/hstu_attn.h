@@ -112,13 +112,15 @@ typedef struct hstu_attn_params {
  * bf16 backward with head_dim 128: the figure ends with room for dS (2 bytes per pair of every 32 x 128 tile that holds a visible
  * pair: 4.2 GB for eight sequences of 8k-16k tokens and 4 heads, dense causal; 1.2 GB under a 1024 + 256 semi-local mask), which
  * the dK/dV pass leaves for the dQ product, up to 16 GiB; a problem that would take more gets none.  hstu_attn_bwd also accepts a
- * workspace without that room (any size from the figure's other parts on) and then recomputes the scores for dQ.  Without a
+ * workspace without that room, any size from hstu_attn_workspace_least_bytes on, and then recomputes the scores for dQ.  Without a
  * host copy of the offsets the room is a bound from total_tokens and max_seqlen.  The backward figure
  * includes fp32 partial-sum slots for key blocks that the scheduler cuts along the query
  * axis (at most 768 x 2 x 128 x head_dim floats, about 100 MB at head_dim 128) and for query blocks that the dQ pass cuts
  * along the key axis (768 x 128 x head_dim floats); the forward figure includes the same kind of slots for its query blocks
  * (50 MB at head_dim 128). */
 size_t hstu_attn_workspace_bytes(const hstu_attn_params* p, int for_backward);
+/* The least that hstu_attn_fwd or hstu_attn_bwd accepts: the same without the room for dS (0.15 GB for the eight sequences above). */
+size_t hstu_attn_workspace_least_bytes(const hstu_attn_params* p, int for_backward);
 
 /* Paper Eq. 3, forward (attention_forward of the appendix pseudocode).
  * q, k, v: inputs [T, H, d]; out: A [T, H, d]; all DEVICE, dtype p->dtype.
@@ -250,8 +252,10 @@ typedef struct hstu_layer_params {
 /* Bytes of device scratch (256-byte aligned) for hstu_layer_fwd (for_backward = 0) or hstu_layer_bwd; 0 for an
  * invalid description.  Forward: X, the projection and Y (T*(E + 5*H*d) bf16), backward: 17 such [T, 512]-sized
  * buffers at E = H*d = 512; both include the attention workspace and 64 MiB offered to the GEMM library.  The backward's figure
- * includes the room for dS of hstu_attn_workspace_bytes, and hstu_layer_bwd too accepts a workspace without it. */
+ * includes the room for dS of hstu_attn_workspace_bytes, and hstu_layer_bwd too accepts a workspace without it, any size from
+ * hstu_layer_workspace_least_bytes on. */
 size_t hstu_layer_workspace_bytes(const hstu_layer_params* p, int for_backward);
+size_t hstu_layer_workspace_least_bytes(const hstu_layer_params* p, int for_backward);
 
 int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u_saved, void* attn_saved, float* mean,
                    float* rstd, void* workspace, size_t workspace_bytes, void* stream);

@@ -70,6 +70,8 @@ def _load() -> ctypes.CDLL:
     lib.hstu_status_string.argtypes = [ctypes.c_int]
     lib.hstu_attn_workspace_bytes.restype = sz
     lib.hstu_attn_workspace_bytes.argtypes = [pp, ctypes.c_int]
+    lib.hstu_attn_workspace_least_bytes.restype = sz
+    lib.hstu_attn_workspace_least_bytes.argtypes = [pp, ctypes.c_int]
     lib.hstu_attn_fwd.restype = ctypes.c_int
     lib.hstu_attn_fwd.argtypes = [pp, vp, vp, vp, vp, vp, sz, vp]
     lib.hstu_attn_bwd.restype = ctypes.c_int
@@ -95,6 +97,8 @@ def _load() -> ctypes.CDLL:
     lp = ctypes.POINTER(HstuLayerParams)
     lib.hstu_layer_workspace_bytes.restype = sz
     lib.hstu_layer_workspace_bytes.argtypes = [lp, ctypes.c_int]
+    lib.hstu_layer_workspace_least_bytes.restype = sz
+    lib.hstu_layer_workspace_least_bytes.argtypes = [lp, ctypes.c_int]
     lib.hstu_layer_fwd.restype = ctypes.c_int
     lib.hstu_layer_fwd.argtypes = [lp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.hstu_layer_bwd.restype = ctypes.c_int
@@ -124,12 +128,12 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
-EXPORTS = ["hstu_attn_workspace_bytes", "hstu_attn_fwd", "hstu_attn_bwd", "hstu_gated_norm_fwd",
+EXPORTS = ["hstu_attn_workspace_bytes", "hstu_attn_workspace_least_bytes", "hstu_attn_fwd", "hstu_attn_bwd", "hstu_gated_norm_fwd",
            "hstu_gated_norm_bwd_workspace_bytes", "hstu_gated_norm_bwd", "hstu_status_string",
            "hstu_gated_norm_bwd_static_max_bytes", "hstu_gated_norm_bwd_static",
            "hstu_attn_schedule_stats", "hstu_profile_enable", "hstu_profile_read",
            "hstu_truncate_offsets", "hstu_truncate_fwd", "hstu_truncate_bwd",
-           "hstu_layer_workspace_bytes", "hstu_layer_fwd", "hstu_layer_bwd", "hstu_layer_gemm_tunings",
+           "hstu_layer_workspace_bytes", "hstu_layer_workspace_least_bytes", "hstu_layer_fwd", "hstu_layer_bwd", "hstu_layer_gemm_tunings",
            "hstu_norm_quant_fp8", "hstu_fp8_gemm_bias2d",
            "hstu_lbsl_weight", "hstu_lbsl_expected_load", "hstu_lbsl_init", "hstu_lbsl_step", "hstu_lbsl_fit_gamma"]
 
@@ -190,6 +194,10 @@ class AttnProblem:
 
 def hstu_attn_workspace_bytes(prob: AttnProblem, for_backward: bool) -> int:
     return int(_lib.hstu_attn_workspace_bytes(prob.ref(), 1 if for_backward else 0))
+
+
+def hstu_attn_workspace_least_bytes(prob: AttnProblem, for_backward: bool) -> int:
+    return int(_lib.hstu_attn_workspace_least_bytes(prob.ref(), 1 if for_backward else 0))
 
 
 def new_workspace(nbytes: int, device) -> torch.Tensor:
@@ -333,6 +341,10 @@ class LayerProblem:
 
 def hstu_layer_workspace_bytes(prob: LayerProblem, for_backward: bool) -> int:
     return int(_lib.hstu_layer_workspace_bytes(prob.ref(), 1 if for_backward else 0))
+
+
+def hstu_layer_workspace_least_bytes(prob: LayerProblem, for_backward: bool) -> int:
+    return int(_lib.hstu_layer_workspace_least_bytes(prob.ref(), 1 if for_backward else 0))
 
 
 def hstu_layer_fwd(prob: LayerProblem, z, out, u_saved, attn_saved, mean, rstd, workspace, stream=None) -> None:

@@ -268,6 +268,10 @@ size_t hstu_attn_workspace_bytes(const hstu_attn_params* p, int for_backward) {
   return l.total + l.ds_bytes;
 }
 
+size_t hstu_attn_workspace_least_bytes(const hstu_attn_params* p, int for_backward) {
+  return validate(p) != HSTU_OK ? 0 : make_layout(p, for_backward).total;
+}
+
 int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const void* v, void* out, void* workspace,
                   size_t workspace_bytes, void* stream_) {
   const int st = validate(p);
@@ -311,10 +315,6 @@ int hstu_attn_bwd(const hstu_attn_params* p, const void* q, const void* k, const
 }
 
 }  // extern "C"
-
-size_t hstu::attn_workspace_least(const hstu_attn_params* p, int for_backward) {
-  return validate(p) != HSTU_OK ? 0 : make_layout(p, for_backward).total;
-}
 
 int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* pre_q,
                                 const void* pre_k, const void* pre_v, int64_t s_pre, const void* dout, void* dq, void* dk,

@@ -123,12 +123,10 @@ hipError_t launch_attn_fwd(const AttnArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_attn_fwd_pipe(const AttnArgs& a, hipStream_t stream);
 // hstu_attn_bwd for operands that are SiLU of pre-activations (bf16 only; pre_* [T, H, D] with row stride s_pre, all three
 // or none): dq, dk, dv leave as the gradients of the pre-activations.  ds: room for dS (256-byte aligned), or nullptr: what the workspace
-// holds behind attn_workspace_least().  Same checks and error codes as hstu_attn_bwd.
+// holds behind hstu_attn_workspace_least_bytes().  Same checks and error codes as hstu_attn_bwd.
 int attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* k, const void* v, const void* pre_q,
                           const void* pre_k, const void* pre_v, int64_t s_pre, const void* dout, void* dq, void* dk, void* dv,
                           void* workspace, size_t workspace_bytes, void* ds, size_t ds_bytes, void* stream);
-// the least that hstu_attn_fwd / hstu_attn_bwd accept (hstu_attn_workspace_bytes: with room for dS), a multiple of 256; 0: invalid description
-size_t attn_workspace_least(const hstu_attn_params* p, int for_backward);
 hipError_t launch_attn_bwd_dq(const AttnArgs& a, int dtype, hipStream_t stream);
 // attn_dq.hip: dQ from the dS that the dK/dV pass left in a.ds (bf16, 128 features; the work list of launch_attn_bwd_dq)
 hipError_t launch_attn_dq_from_ds(const AttnArgs& a, hipStream_t stream);

@@ -51,7 +51,7 @@ LayerLayout make_layer_layout(const hstu_layer_params* p, int for_backward) {
   size_t off = 0;
   // The attention's part, without dS, is the first one: its work lists lie at the same place for every layer of a batch, whatever
   // their embed_dim (reuse_schedule).
-  const size_t least = attn_workspace_least(&a, for_backward);
+  const size_t least = hstu_attn_workspace_least_bytes(&a, for_backward);    // (a multiple of 256)
   l.attn = off; off += least;
   l.gemm = off; off += kGemmWorkspace;
   l.xn = off; off += align_up(T * E * 2);
@@ -92,6 +92,10 @@ size_t hstu_layer_workspace_bytes(const hstu_layer_params* p, int for_backward) 
   const hstu_attn_params a = attn_problem(p);
   if (hstu_attn_workspace_bytes(&a, for_backward) == 0) return 0;
   return make_layer_layout(p, for_backward).most;
+}
+
+size_t hstu_layer_workspace_least_bytes(const hstu_layer_params* p, int for_backward) {
+  return hstu_layer_workspace_bytes(p, for_backward) == 0 ? 0 : make_layer_layout(p, for_backward).total;
 }
 
 int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u_saved, void* attn_saved, float* mean,

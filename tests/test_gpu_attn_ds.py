@@ -65,6 +65,29 @@ def test_backward_through_ds(name):
     check("dtable (no room)", to_np(dw.dtable), ref_table, TOL["bf16"])
 
 
+def test_least_workspace_is_accepted_and_no_less():
+    from paper_2602_16986_amd.runner import DeviceLayer, DeviceWorkload
+    w = workload("window-candidates")
+    dw = DeviceWorkload(w)
+    least = hb.hstu_attn_workspace_least_bytes(dw.problem, True)
+    for what, g, r in zip(("dQ", "dK", "dV"), backward(dw, hb.new_workspace(least, "cuda")),
+                          orc.attn_bwd(w.q, w.k, w.v, w.dout, w.offsets, **oracle_args(w))):
+        check(what, g, r, TOL["bf16"])
+    dl = DeviceLayer(wl.build_layer("least", [300, 129], 2, 128, 256, seed=4))
+    dl.fwd()
+    full = [t.float() for t in dl.bwd()]
+    least_layer = hb.hstu_layer_workspace_least_bytes(dl.problem, True)
+    assert least_layer < dl.ws_bwd.numel()
+    dl.ws_bwd = hb.new_workspace(least_layer, "cuda")
+    for a, b in zip(full, dl.bwd()):
+        scale = float(a.abs().max())
+        assert float((a - b.float()).abs().max()) <= TOL["bf16"] * scale
+    for call, ws in ((lambda ws: backward(dw, ws), least), (lambda ws: (setattr(dl, "ws_bwd", ws), dl.bwd()), least_layer)):
+        with pytest.raises(hb.HstuError) as e:
+            call(hb.new_workspace(ws - 256, "cuda"))
+        assert e.value.status == -4
+
+
 @pytest.mark.parametrize("name", ["tile-edges", "window-and-prefix", "candidates", "one-bucket-tiles"])
 @pytest.mark.parametrize("build_room,use_room,longer", [(False, True, 0), (True, False, 0), (False, True, 3000), (True, True, 3000)])
 def test_lists_of_a_call_with_other_room(name, build_room, use_room, longer):

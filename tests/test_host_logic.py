@@ -113,3 +113,30 @@ def test_public_header_is_plain_c(tmp_path):
     inc = os.path.join(ROOT, "include")
     subprocess.run(["gcc", "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-fsyntax-only", "-I", inc, str(src)], check=True)
     subprocess.run(["g++", "-std=c++11", "-Wall", "-Werror", "-fsyntax-only", "-x", "c++", "-I", inc, str(src)], check=True)
+
+
+@pytest.mark.parametrize("dim,dtype,lengths", [(128, 0, [600, 400]), (128, 0, [16384] * 10), (64, 0, [600, 400]), (32, 1, [600, 400])])
+def test_least_workspace_is_the_full_one_without_the_room_for_ds(dim, dtype, lengths):
+    """hstu_attn_workspace_least_bytes / hstu_layer_workspace_least_bytes against the full figures: they differ by 8 KB per dS tile in a bf16
+    backward with 128 features that stays within 16 GiB, and not otherwise; 0 for an invalid description."""
+    from paper_2602_16986_amd import binding as hb
+    host = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    heads = 8
+    lp = hb.HstuLayerParams()
+    p = lp.attn
+    p.batch, p.num_heads, p.head_dim, p.total_tokens, p.max_seqlen, p.dtype = len(lengths), heads, dim, int(host[-1]), max(lengths), dtype
+    p.row_stride_q = p.row_stride_k = p.row_stride_v = p.row_stride_o = heads * dim
+    p.seq_offsets, p.seq_offsets_host = 256, host.ctypes.data            # (the device copy is never dereferenced by the size query)
+    p.local_window, p.alpha, p.inv_n, lp.embed_dim = -1, 1.0, 1.0, 64
+    tiles = heads * sum(-(-(L - 128 * k) // 32) for L in lengths for k in range(-(-L // 128)))
+    room = tiles * 8192 if (dim, dtype) == (128, 0) and tiles * 8192 <= 1 << 34 else 0
+    assert (room > 0) == (dim == 128 and len(lengths) == 2)
+    for full, least, arg in ((hb._lib.hstu_attn_workspace_bytes, hb._lib.hstu_attn_workspace_least_bytes, p),
+                             (hb._lib.hstu_layer_workspace_bytes, hb._lib.hstu_layer_workspace_least_bytes, lp)):
+        if arg is lp and dtype == 1:
+            assert least(ctypes.byref(arg), 1) == full(ctypes.byref(arg), 1) == 0        # the layer is bf16 only
+            continue
+        assert least(ctypes.byref(arg), 0) == full(ctypes.byref(arg), 0) > 0
+        assert least(ctypes.byref(arg), 1) == full(ctypes.byref(arg), 1) - room > 0
+    p.head_dim = 96
+    assert hb._lib.hstu_attn_workspace_least_bytes(ctypes.byref(p), 1) == hb._lib.hstu_layer_workspace_least_bytes(ctypes.byref(lp), 1) == 0
