@@ -3,6 +3,7 @@
 #include "../../include/hstu_attn.h"
 #include "hstu_common.h"
 #include "hstu_kernels.h"
+#include "hstu_plan.h"
 #include "profile.h"
 
 #include <algorithm>
@@ -39,29 +40,12 @@ struct Layout {           // byte offsets inside a workspace
 // a lot in length, which the same bound covers).
 inline int slot_cap_for(int max_items) { return max_items < 384 ? 2 * max_items : 768; }
 
-// dS tiles (32 queries x 128 keys) that the dK/dV pass can leave for the dQ product: an upper bound over all heads.  From the host
-// copy of the lengths where there is one, else from the longest sequence; candidates (their counts are known on the device only) can
-// add whole columns for the key blocks that the window in front of position n reaches.
-int64_t ds_tiles_bound(const hstu_attn_params* p) {
-  const int64_t K1 = p->local_window < (1 << 28) ? p->local_window : (1 << 28), K2 = p->global_prefix < (1 << 28) ? p->global_prefix : (1 << 28);
-  const int64_t wide = K1 >= 0 ? (K1 + 158) / 32 : 0, cand_blocks = p->num_targets && K1 >= 0 ? K1 / 128 + 2 : 0;
-  auto of = [&](int64_t L) -> int64_t {
-    const int64_t nq = (L + 31) / 32, nk = (L + 127) / 128;
-    const int64_t dense = nk * nq - 2 * nk * (nk - 1);
-    if (K1 < 0) return dense;
-    const int64_t pre = std::min(nk, (K2 + 127) / 128);
-    return std::min(dense, pre * nq - 2 * pre * (pre - 1) + (nk - pre) * wide + std::min(nk, cand_blocks) * nq);
-  };
-  int64_t tiles = 0;
-  if (p->seq_offsets_host) {
-    for (int b = 0; b < p->batch; ++b) tiles += of((int64_t)p->seq_offsets_host[b + 1] - p->seq_offsets_host[b]);
-  } else {
-    const int64_t most = std::min(p->max_seqlen, p->total_tokens), blocks = (int64_t)p->total_tokens / 128 + p->batch;
-    const int64_t nq = (most + 31) / 32, nk = (most + 127) / 128;
-    tiles = blocks * (2 * nk + 2);
-    if (K1 >= 0) tiles = std::min(tiles, p->batch * (std::min(nk, (K2 + 127) / 128) + std::min(nk, cand_blocks)) * nq + blocks * wide);
-  }
-  return tiles * p->num_heads;
+// Sequences are shorter than 2^24 tokens: windows beyond 2^28 mean the same and keep the kernels' index sums inside int32.
+inline int window_of(int32_t w) { return w < 0 ? -1 : (w < (1 << 28) ? w : (1 << 28)); }
+
+PlanBatch plan_of(const hstu_attn_params* p) {
+  return {p->batch, p->num_heads, p->total_tokens, p->max_seqlen, window_of(p->local_window), window_of(p->global_prefix), p->num_targets != nullptr,
+          p->seq_offsets_host};
 }
 // 1/18 of the card's memory: eight sequences of 16k tokens with eight heads under the dense mask; beyond it the two passes stay
 // independent of each other (dQ recomputes S and dP).
@@ -112,7 +96,7 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     off += align_up((size_t)l.slot_cap_dq * dq_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
     l.dbias = off;                                     // per-distance sums of dS for the bias-table gradient, then the bucket ends per distance
     off += align_up((size_t)(dbias_copies_for(p) * p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
-    const int64_t bytes = ds ? ds_tiles_bound(p) * kDsTileBytes : 0;
+    const int64_t bytes = ds ? ds_tiles_bound(plan_of(p)) * kDsTileBytes : 0;
     if (bytes <= kDsMaxBytes) l.ds_bytes = (size_t)bytes;
   }
   l.total = off;
@@ -163,9 +147,8 @@ AttnArgs make_args(const hstu_attn_params* p, const void* q, const void* k, cons
   a.sq = p->row_stride_q; a.sk = p->row_stride_k; a.sv = p->row_stride_v; a.so = p->row_stride_o;
   a.offsets = p->seq_offsets; a.num_targets = p->num_targets;
   a.B = p->batch; a.H = p->num_heads; a.D = p->head_dim; a.T = p->total_tokens; a.max_seqlen = p->max_seqlen;
-  // sequences are shorter than 2^24 tokens: windows beyond 2^28 mean the same and keep the kernels' index sums inside int32
-  a.K1 = p->local_window < 0 ? -1 : (p->local_window < (1 << 28) ? p->local_window : (1 << 28));
-  a.K2 = p->global_prefix < (1 << 28) ? p->global_prefix : (1 << 28);
+  a.K1 = window_of(p->local_window);
+  a.K2 = window_of(p->global_prefix);
   a.alpha = p->alpha; a.inv_n = p->inv_n;
   a.query_tail = p->query_tail > 0 ? p->query_tail : 0;
   return a;
@@ -292,7 +275,7 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
   a.splits = (const SplitItem*)(ws + l.splits);
   a.partial = (float*)(ws + l.partial);
   // (a list is cut only where the launch that finishes cut blocks follows: lengths on the device may be longer than the host's copy says)
-  const bool may_cut = schedule_may_cut(a, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), p->seq_offsets_host);
+  const bool may_cut = schedule_may_cut(plan_of(p), a.query_tail, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim));
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, true);
     ProfScope ps(p->reuse_schedule ? "bias_expand_fwd" : "schedule_fwd", stream);
@@ -355,7 +338,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
   const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
   bool may_cut[2];                                       // as in the forward
-  for (int s = 0; s < 2; ++s) may_cut[s] = schedule_may_cut(a, 1 + s, rows[s], cols[s], p->seq_offsets_host);
+  for (int s = 0; s < 2; ++s) may_cut[s] = schedule_may_cut(plan_of(p), 0, 1 + s, rows[s], cols[s]);
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, false);
     ProfScope ps(p->reuse_schedule ? "bias_expand_bwd" : "schedule_bwd", stream);

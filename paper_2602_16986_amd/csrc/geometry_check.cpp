@@ -7,9 +7,13 @@
 //   - classify_tile says Full only if all pairs of the 32x32 block are visible history pairs with
 //     distance i - j, and Empty only if none is visible;
 //   otherwise a non-zero code naming the violated property.
+//   plan_check(...) does the same for the bounds of hstu_plan.h on one batch: the room for dS holds the tiles of the dK/dV list, with the
+//   host copy of the offsets and without it; the query tiles of a key block are consecutive (the dQ product addresses dS by that); and a
+//   list in which the scheduler cuts a block is one that schedule_may_cut() names.
 #include <vector>
 
 #include "hstu_geometry.h"
+#include "hstu_plan.h"
 
 using namespace hstu;
 
@@ -64,6 +68,54 @@ extern "C" int geometry_check(int L, int M, int K1, int K2, int block_rows, int 
         }
       if (kind == kTileFull && nbad) return 70;
       if (kind == kTileEmpty && nvis) return 80;
+    }
+  return 0;
+}
+
+// targets: nullptr or the candidates of every sequence; slack: by how much max_seqlen exceeds the longest one
+extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets, int H, int K1, int K2, int query_tail, int slack) {
+  std::vector<int32_t> offsets(B + 1, 0);
+  int longest = 0;
+  for (int b = 0; b < B; ++b) {
+    offsets[b + 1] = offsets[b] + lengths[b];
+    longest = imax(longest, lengths[b]);
+  }
+  const PlanBatch with = {B, H, offsets[B], longest + slack, K1, K2, targets != nullptr, offsets.data()};
+  PlanBatch without = with;
+  without.host_offsets = nullptr;
+  auto geom = [&](int b) { return SeqGeom{lengths[b], lengths[b] - (targets ? targets[b] : 0), K1, K2}; };
+
+  int64_t ds = 0;
+  for (int b = 0; b < B; ++b)
+    for (int k0 = 0; k0 < lengths[b]; k0 += 128) {
+      const TileRanges t = row_tile_ranges(geom(b), k0, imin(k0 + 128, lengths[b]) - 1, 32);
+      for (int i = 1; i < t.count(); ++i)
+        if (t.at(i) != t.at(0) + i) return 1;
+      ds += (int64_t)t.count() * H;
+    }
+  if (ds > ds_tiles_bound(with)) return 2;
+  if (ds > ds_tiles_bound(without)) return 3;
+
+  const int parts[3] = {kFwdTargetChunks, kDqTargetChunks, kTargetChunks};
+  for (int which = 0; which < 3; ++which)
+    for (int tile = 32; tile <= 64; tile += 32) {
+      const int tail = which == 0 ? query_tail : 0;
+      int64_t all = 0;
+      int most = 0;
+      for (int b = 0; b < B; ++b) {
+        const SeqGeom g = geom(b);
+        for (int r0 = tail_origin(g.n, tail); r0 < g.L; r0 += 128) {
+          const int r1 = imin(r0 + 128, g.L) - 1;
+          const int cost = (which == 2 ? row_tile_ranges(g, r0, r1, tile) : tile_ranges(g, r0, r1, tile)).count();
+          all += (int64_t)cost * H;
+          most = imax(most, cost);
+        }
+      }
+      // the scheduler's first piece size; with a tail its share is the key blocks'
+      const double share = 1.0 / (tail > 0 ? kTargetChunks : parts[which]);
+      const int64_t chunk = std::max((int64_t)kMinChunk, (int64_t)std::ceil((double)all * share));
+      if (most > 2 * chunk && !schedule_may_cut(with, tail, which, 128, tile)) return 10 + which;
+      if (most > 2 * chunk && !schedule_may_cut(without, tail, which, 128, tile)) return 20 + which;
     }
   return 0;
 }

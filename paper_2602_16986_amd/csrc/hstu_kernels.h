@@ -105,10 +105,6 @@ hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int ti
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
                                 const int slot_cap[2], int32_t* ds_table, const ExpandJob& ex, hipStream_t stream);
-// false: no list that the scheduler can build for this problem has a cut block (host arithmetic on bounds; host_offsets may be
-// nullptr).  which: 0 forward, 1 dQ list, 2 dK/dV list.
-bool schedule_may_cut(const AttnArgs& a, int which, int block_rows, int tile_cols, const int32_t* host_offsets);
-
 int schedule_sorted_pairs();              // lists of up to this many (sequence, block) pairs are sorted
 
 // attn_core.hip

@@ -1,0 +1,78 @@
+// Host arithmetic that a launch is planned with before the device has seen the offsets: bounds on what the scheduler will make of a batch.
+// Plain C++ on plain values, so that the host-side check of the tiling logic compiles the same header.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace hstu {
+
+constexpr int kMinChunk = 8;         // a long block is cut into pieces of at least this many tiles ...
+constexpr int kTargetChunks = 2048;  // ... and, key blocks, of about 1/2048 of all scheduled tiles (4 per workgroup slot of the chip)
+constexpr int kFwdTargetChunks = 1536;   // forward lists: 2 x chunk = one slot's share when 768 workgroups are resident
+constexpr int kDqTargetChunks = 1024;    // dQ lists: the same with 512 resident workgroups
+
+struct PlanBatch {
+  int batch, heads, total_tokens, max_seqlen;
+  int K1, K2;                        // of SeqGeom, both below 2^28
+  bool candidates;                   // their counts are known on the device only
+  const int32_t* host_offsets;       // or nullptr
+};
+
+// dS tiles (32 queries x 128 keys) that the dK/dV pass can leave for the dQ product: an upper bound over all heads.  From the host
+// copy of the lengths where there is one, else from the longest sequence; candidates can add whole columns for the key blocks that the
+// window in front of position n reaches.
+inline int64_t ds_tiles_bound(const PlanBatch& p) {
+  const int64_t K1 = p.K1, K2 = p.K2;
+  const int64_t wide = K1 >= 0 ? (K1 + 158) / 32 : 0, cand_blocks = p.candidates && K1 >= 0 ? K1 / 128 + 2 : 0;
+  auto of = [&](int64_t L) -> int64_t {
+    const int64_t nq = (L + 31) / 32, nk = (L + 127) / 128;
+    const int64_t dense = nk * nq - 2 * nk * (nk - 1);
+    if (K1 < 0) return dense;
+    const int64_t pre = std::min(nk, (K2 + 127) / 128);
+    return std::min(dense, pre * nq - 2 * pre * (pre - 1) + (nk - pre) * wide + std::min(nk, cand_blocks) * nq);
+  };
+  int64_t tiles = 0;
+  if (p.host_offsets) {
+    for (int b = 0; b < p.batch; ++b) tiles += of((int64_t)p.host_offsets[b + 1] - p.host_offsets[b]);
+  } else {
+    const int64_t most = std::min(p.max_seqlen, p.total_tokens), blocks = (int64_t)p.total_tokens / 128 + p.batch;
+    const int64_t nq = (most + 31) / 32, nk = (most + 127) / 128;
+    tiles = blocks * (2 * nk + 2);
+    if (K1 >= 0) tiles = std::min(tiles, p.batch * (std::min(nk, (K2 + 127) / 128) + std::min(nk, cand_blocks)) * nq + blocks * wide);
+  }
+  return tiles * p.heads;
+}
+
+// Most batches are cut nowhere, and a launch that would add up pieces costs 4.5 us for finding that out.  A block is cut
+// when it is longer than 2 x chunk, chunk >= kMinChunk and >= share x (all tiles).  The longest block is bounded by the longest
+// sequence and the mask, the tiles from below by the visible pairs, which takes the lengths: without a host copy of the offsets
+// only kMinChunk counts, and so it does with candidates (their counts are known on the device only) or a query tail.
+// which: 0 forward, 1 dQ list, 2 dK/dV list.  false: no list that the scheduler can build for this problem has a cut block.
+inline bool schedule_may_cut(const PlanBatch& p, int query_tail, int which, int block_rows, int tile_cols) {
+  const bool key_major = which == 2, by_position = !p.candidates && query_tail == 0;
+  const double share = 1.0 / (which == 0 ? kFwdTargetChunks : which == 1 ? kDqTargetChunks : kTargetChunks);
+  double longest = p.max_seqlen, pairs = 0.0;
+  if (p.host_offsets) {
+    longest = 0.0;
+    for (int b = 0; b < p.batch; ++b) {
+      const double L = p.host_offsets[b + 1] - p.host_offsets[b];
+      longest = L > longest ? L : longest;
+      pairs += p.K1 < 0 || L <= p.K1 ? 0.5 * L * L : p.K1 * (L - 0.5 * p.K1);       // (those of a global prefix left out)
+    }
+  }
+  double most = std::ceil(longest / tile_cols);          // tiles of the longest block
+  if (p.K1 >= 0 && by_position && !(key_major && p.K2 > 0)) {
+    const double band = std::floor((double)(block_rows + p.K1) / tile_cols) + 2, prefix = key_major ? 0 : std::ceil((double)p.K2 / tile_cols);
+    if (band + prefix < most) most = band + prefix;
+  }
+  double chunk = kMinChunk;
+  if (by_position) {
+    const double tiles = std::ceil(share * pairs * p.heads / ((double)block_rows * tile_cols) * (1 - 1e-9));
+    if (tiles > chunk) chunk = tiles;
+  }
+  return most > 2 * chunk;
+}
+
+}  // namespace hstu

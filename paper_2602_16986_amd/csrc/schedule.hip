@@ -25,6 +25,7 @@
 
 #include "hstu_common.h"
 #include "hstu_kernels.h"
+#include "hstu_plan.h"
 
 namespace hstu {
 namespace {
@@ -33,10 +34,6 @@ constexpr int kSchedThreads = 1024;
 constexpr int kSchedWaves = kSchedThreads / 64;
 constexpr int kSortMax = 8192;       // lists of up to this many (sequence, block) pairs are sorted by cost in LDS
 constexpr int kSeqCache = 1024;      // batches up to this size keep their block prefix sums and lengths in LDS
-constexpr int kMinChunk = 8;         // a long key block is cut into pieces of at least this many tiles ...
-constexpr int kTargetChunks = 2048;  // ... and of about 1/2048 of all scheduled tiles (4 per workgroup slot of the chip)
-constexpr int kFwdTargetChunks = 1536;   // forward lists: 2 x chunk = one slot's share when 768 workgroups are resident
-constexpr int kDqTargetChunks = 1024;    // dQ lists: the same with 512 resident workgroups
 constexpr int kDigitBits = 6, kDigits = 1 << kDigitBits;   // radix sort: one digit per pass, one counter per lane of a wave
 constexpr int kKeyBits = 12;         // costs are sorted exactly up to 4,095 tiles, by 4,096 equal classes beyond
 constexpr int kCountPitch = kSchedWaves + 1;
@@ -464,34 +461,5 @@ hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_r
 }
 
 int schedule_sorted_pairs() { return kSortMax; }
-
-// Most batches are cut nowhere, and a launch that would add up pieces costs 4.5 us for finding that out.  A block is cut
-// when it is longer than 2 x chunk, chunk >= kMinChunk and >= share x (all tiles).  The longest block is bounded by the longest
-// sequence and the mask, the tiles from below by the visible pairs, which takes the lengths: without a host copy of the offsets
-// only kMinChunk counts, and so it does with candidates (their counts are known on the device only) or a query tail.
-bool schedule_may_cut(const AttnArgs& a, int which, int block_rows, int tile_cols, const int32_t* host_offsets) {
-  const bool key_major = which == 2, by_position = a.num_targets == nullptr && a.query_tail == 0;
-  const double share = 1.0 / (which == 0 ? kFwdTargetChunks : which == 1 ? kDqTargetChunks : kTargetChunks);
-  double longest = a.max_seqlen, pairs = 0.0;
-  if (host_offsets) {
-    longest = 0.0;
-    for (int b = 0; b < a.B; ++b) {
-      const double L = host_offsets[b + 1] - host_offsets[b];
-      longest = L > longest ? L : longest;
-      pairs += a.K1 < 0 || L <= a.K1 ? 0.5 * L * L : a.K1 * (L - 0.5 * a.K1);       // (those of a global prefix left out)
-    }
-  }
-  double most = ceil(longest / tile_cols);               // tiles of the longest block
-  if (a.K1 >= 0 && by_position && !(key_major && a.K2 > 0)) {
-    const double band = floor((double)(block_rows + a.K1) / tile_cols) + 2, prefix = key_major ? 0 : ceil((double)a.K2 / tile_cols);
-    if (band + prefix < most) most = band + prefix;
-  }
-  double chunk = kMinChunk;
-  if (by_position) {
-    const double tiles = ceil(share * pairs * a.H / ((double)block_rows * tile_cols) * (1 - 1e-9));
-    if (tiles > chunk) chunk = tiles;
-  }
-  return most > 2 * chunk;
-}
 
 }  // namespace hstu

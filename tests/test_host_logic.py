@@ -21,6 +21,8 @@ def geom(tmp_path_factory):
     lib = ctypes.CDLL(so)
     lib.geometry_check.restype = ctypes.c_int
     lib.geometry_check.argtypes = [ctypes.c_int] * 6
+    lib.plan_check.restype = ctypes.c_int
+    lib.plan_check.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p] + [ctypes.c_int] * 5
     return lib
 
 
@@ -47,6 +49,24 @@ def test_tile_enumeration_random(geom):
         br, bn = [(256, 64), (128, 64), (128, 32)][int(rng.integers(0, 3))]
         rc = geom.geometry_check(L, M, K1, K2, br, bn)
         assert rc == 0, f"property {rc} violated for L={L} M={M} K1={K1} K2={K2} rows={br} BN={bn}"
+
+
+def test_bounds_that_launches_are_planned_with(geom):
+    rng = np.random.default_rng(1)
+    for _ in range(4000):
+        B = int(rng.integers(1, 20))
+        top = int(rng.choice([1, 40, 129, 300, 2000, 20000]))
+        lengths = rng.integers(0, top + 1, B).astype(np.int32)
+        if rng.random() < 0.2:
+            lengths[:] = top
+        targets = (rng.random(B) * rng.choice([0.1, 1.0]) * (lengths + 1)).astype(np.int32) if rng.random() < 0.5 else None
+        H = int(rng.choice([1, 2, 8, 64]))
+        K1 = int(rng.choice([-1, -1, 0, 1, 5, 64, 97, 128, 1000, 5000, 1 << 28]))
+        K2 = int(rng.choice([0, 1, 31, 128, 129, 700, 1 << 28]))
+        tail = int(rng.choice([0, 1, 33, 500]))
+        slack = int(rng.choice([0, 0, 1, 5000]))
+        rc = geom.plan_check(B, lengths.ctypes.data, None if targets is None else targets.ctypes.data, H, K1, K2, tail, slack)
+        assert rc == 0, f"property {rc} violated for {lengths.tolist()} targets={None if targets is None else targets.tolist()} H={H} K1={K1} K2={K2} tail={tail} slack={slack}"
 
 
 def test_library_exports_every_declared_symbol():
