@@ -133,3 +133,18 @@ def test_room_for_other_lengths_computes_nothing():
     hb.hstu_attn_bwd(prob, q, q, q, q, dq, dk, dv, ws)
     torch.cuda.synchronize()
     assert all(torch.all(t == 5.0) for t in (dq, dk, dv))
+
+
+@pytest.mark.parametrize("dim,dtype,room", [(128, "bf16", True), (128, "bf16", False), (64, "bf16", False), (32, "fp32", False)])
+def test_bias_gradient_with_one_copy_of_the_sums(dim, dtype, room):
+    """max_seqlen so large that the sums per distance are kept once for the chip instead of once per die."""
+    from paper_2602_16986_amd.runner import DeviceWorkload
+    w = wl.build("one-copy", [700, 301, 64], 2, dim, dtype, seed=9, K1=400, K2=30, backward=True, num_targets=np.array([40, 0, 64], np.int32))
+    dw = DeviceWorkload(w, bias_grad=True)
+    dw.problem.params.max_seqlen = 300000
+    size = hb.hstu_attn_workspace_bytes(dw.problem, True) if room else hb.hstu_attn_workspace_least_bytes(dw.problem, True)
+    dw.dtable.fill_(float("nan"))
+    got = backward(dw, hb.new_workspace(size, "cuda"))
+    for what, g, r in zip(("dQ", "dK", "dV"), got, orc.attn_bwd(w.q, w.k, w.v, w.dout, w.offsets, **oracle_args(w))):
+        check(what, g, r, TOL[dtype])
+    check("dtable", to_np(dw.dtable), orc.attn_bwd_bias(w.q, w.k, w.v, w.dout, w.offsets, **oracle_args(w)), TOL[dtype])
