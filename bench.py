@@ -288,7 +288,8 @@ def bench_layer(args):
                 kern.setdefault(f"{tag}:{name}", []).append(ms)
     hb.hstu_profile_enable(False)
     kern = {k: float(np.mean(v)) for k, v in kern.items()}
-    algo = {"fwd:attn_fwd": 4.0, "bwd:attn_bwd_dq": 6.0, "bwd:attn_bwd_dkdv": 8.0}
+    useful_d, _ = pass_flops(hb.hstu_layer_workspace_bytes(dl.problem, True) > hb.hstu_layer_workspace_least_bytes(dl.problem, True))
+    algo = {"fwd:attn_fwd": useful_d["attn_fwd"], "bwd:attn_bwd_dq": useful_d["attn_bwd_dq"], "bwd:attn_bwd_dkdv": useful_d["attn_bwd_dkdv"]}
     dom = max(algo, key=lambda k: kern[k])
     achieved = algo[dom] * c.d * fl["pairs"] / (kern[dom] * 1e-3) / 1e12
     e = 2 * c.T
@@ -313,6 +314,17 @@ def bench_layer(args):
            "saved_bytes": {"rematerialised": e * (c.E + 2 * HD) + 8 * c.T,
                            "everything_kept": e * (2 * c.E + 4 * HD + 4 * HD + 2 * HD) + 8 * c.T}}
     print(json.dumps(out))
+
+
+def pass_flops(through_ds):
+    """Useful and executed FLOPs per unmasked pair, in units of d, of the attention passes.  Of the 10 d that the backward owes (S, dP, dV, dK,
+    dQ) the dK/dV pass computes 8 d and hands dS on to the dQ product, 2 d, where the workspace has room for dS.  Without it both passes
+    compute S and dP: the dK/dV pass is then credited with dV, dK and half of them (6 of the 8 d it executes), the dQ pass with dQ and the
+    other half (4 of 6 d).  The forward has its 4 d."""
+    if through_ds:
+        useful = {"attn_fwd": 4.0, "attn_bwd_dq": 2.0, "attn_bwd_dkdv": 8.0}
+        return useful, useful
+    return ({"attn_fwd": 4.0, "attn_bwd_dq": 4.0, "attn_bwd_dkdv": 6.0}, {"attn_fwd": 4.0, "attn_bwd_dq": 6.0, "attn_bwd_dkdv": 8.0})
 
 
 def other_configs(args, torch, hb, flops, workloads, DeviceWorkload, peak):
@@ -411,16 +423,8 @@ def main():
     value = useful / (ms_step * 1e-3) / 1e12
     peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_FP32_TFLOPS
 
-    # Roofline of the dominant kernel, in USEFUL FLOPs: of the 10 d the backward owes per unmasked pair (S, dP, dV, dK,
-    # dQ) the dK/dV pass computes 8 d and hands dS on to the dQ product, 2 d (bf16 with 128 features).  Where the two passes are
-    # independent both compute S and dP: the dK/dV pass is then credited with dV, dK and half of them (6 of the 8 d it executes), the
-    # dQ pass with dQ and the other half (4 of 6 d).  The forward has its 4 d.  What the passes execute is reported beside it.
-    if w.dtype == "bf16" and w.d == 128:
-        useful_d = {"attn_fwd": 4.0, "attn_bwd_dq": 2.0, "attn_bwd_dkdv": 8.0}
-        executed_d = useful_d
-    else:
-        useful_d = {"attn_fwd": 4.0, "attn_bwd_dq": 4.0, "attn_bwd_dkdv": 6.0}
-        executed_d = {"attn_fwd": 4.0, "attn_bwd_dq": 6.0, "attn_bwd_dkdv": 8.0}
+    # roofline of the dominant kernel, in useful FLOPs; what the passes execute is reported beside it
+    useful_d, executed_d = pass_flops(hb.hstu_attn_workspace_bytes(dw.problem, True) > hb.hstu_attn_workspace_least_bytes(dw.problem, True))
     dom = max((k for k in kern if k in useful_d), key=lambda k: kern[k])
     achieved = useful_d[dom] * w.d * fl["pairs"] / (kern[dom] * 1e-3) / 1e12
     roofline = {"kernel": dom, "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
