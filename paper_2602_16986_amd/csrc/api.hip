@@ -47,8 +47,8 @@ PlanBatch plan_of(const hstu_attn_params* p) {
   return {p->batch, p->num_heads, p->total_tokens, p->max_seqlen, window_of(p->local_window), window_of(p->global_prefix), p->num_targets != nullptr,
           p->seq_offsets_host};
 }
-// 1/18 of the card's memory: eight sequences of 16k tokens with eight heads under the dense mask; beyond it the two passes stay
-// independent of each other (dQ recomputes S and dP).
+// 1/18 of the card's memory: seven sequences of 16,384 tokens with eight heads under the dense mask (14.1 GiB; eight need 16.1); beyond it
+// the two passes stay independent of each other (dQ recomputes S and dP).
 constexpr int64_t kDsMaxBytes = (int64_t)16 << 30;
 
 // One schedule for the forward; two (dQ pass, dK/dV pass) for the backward.

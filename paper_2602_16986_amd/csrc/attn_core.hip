@@ -189,12 +189,6 @@ __device__ __forceinline__ void key_diag_all(std::integer_sequence<int, R...>, c
 // rows once the bias strip is addressed with the row's effective position (query-stationary passes) or anchored at n
 // for a tile of candidate queries (dK/dV pass).  Batches without candidates run the instantiation without it (a few
 // scalar instructions per tile less).
-// d/dt [t sigmoid(t)]
-__device__ __forceinline__ float dsilu(float t) {
-  const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-kLog2e * t));
-  return sg * (1.0f + t * (1.0f - sg));
-}
-
 template <typename E, int D, int MODE, int NWAVES, bool DBIAS = false, bool CAND = false, bool DS = false>
 __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) void attn_kernel(const AttnArgs a) {
   static_assert(!DBIAS || MODE == kBwdDQ || DS, "the bias gradient rides with the dQ pass, or with the dK/dV pass that hands dS on");
@@ -623,24 +617,20 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     };
 
     bool done = false;
-    if constexpr (MODE != kFwd && C::kBf16 && NSB == 2 && D == 128) {
+    if constexpr (MODE == kBwdDQ && C::kBf16 && NSB == 2 && D == 128) {
       if (kind == kTileFull) {
-        // Software-pipelined backward for fully visible tiles: the pointwise
+        // Software-pipelined dQ pass for fully visible tiles: the pointwise
         // work of one 32-row sub-block (SiLU, its derivative, packing) is issued between the matrix
         // instructions that do not depend on it:
-        //   S,dP(0) | S,dP(1) + pointwise(0) | outputs(0) + pointwise(1) | outputs(1)
-        // outputs = dQ^T += K^T dS^T (dQ pass) or dK^T += Q^T dS, dV^T += dO^T P (dK/dV pass).
+        //   S,dP(0) | S,dP(1) + pointwise(0) | dQ(0) + pointwise(1) | dQ(1), with dQ^T += K^T dS^T.
         static_assert(C::kDma, "256-byte-row tiles only");
         const float* strip = (const float*)(smem + C::STRIP_BASE + stage * C::STRIP_BYTES) + strip_lane;
         // score fragment n: tensor n%2 (S then dP), sub-block n/16, k-step (n/2)%8
         auto rowfrag = [&](int n) -> bf16x8 { return rowfrag_at(n & 1, n >> 4, (n >> 1) & 7); };
-        // output fragment n: sub-block n / (8*NOUT), then (k-step, feature block) major, output minor
-        auto trfrag = [&](int n) -> bf16x8 {
-          const int r = n % (8 * C::NOUT), step = r / C::NOUT;
-          return trfrag_at(r % C::NOUT, n / (8 * C::NOUT), step / C::OB, step % C::OB);
-        };
+        // output fragment n: sub-block n / 8, then k-step, then feature block
+        auto trfrag = [&](int n) -> bf16x8 { return trfrag_at(0, n / 8, n % 8 / C::OB, n % C::OB); };
         f32x16 sv[2], dp[2];
-        uint32_t pds[2][8], pp[2][8];
+        uint32_t pds[2][8];
         float dsf[DBQ ? 2 : 1][16];                                      // dS in fp32 for the bias gradient
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
@@ -657,17 +647,16 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
 #pragma unroll
           for (int r = 0; r < 16; ++r) dp[sb][r] = 0.f;
         }
-        // elements 2m, 2m+1 of sub-block sb -> packed pairs of dS (and of P for the dK/dV pass);
+        // elements 2m, 2m+1 of sub-block sb -> a packed pair of dS
         auto pointwise = [&](int sb, int m) {
           const float s0v = sv[sb][2 * m], s1v = sv[sb][2 * m + 1];
           const float g0 = sigmoid_l2(s0v), g1 = sigmoid_l2(s1v);
           const float p0v = s0v * g0, p1v = s1v * g1;
           const float ds0 = dp[sb][2 * m] * dsilu_l2(p0v, g0), ds1 = dp[sb][2 * m + 1] * dsilu_l2(p1v, g1);
           pds[sb][m] = pack_bf16x2(ds0, ds1);
-          if constexpr (MODE == kBwdDKDV) pp[sb][m] = pack_bf16x2(p0v, p1v);
           if constexpr (DBQ) { dsf[sb][2 * m] = ds0; dsf[sb][2 * m + 1] = ds1; }
         };
-        constexpr int PF = (MODE == kBwdDQ) ? 2 : 4;                      // the dQ pass runs two waves per SIMD: 256 registers
+        constexpr int PF = 2;                                             // two waves per SIMD: 256 registers
         bf16x8 fr[PF];
 #pragma unroll
         for (int i = 0; i < PF; ++i) fr[i] = rowfrag(i);
@@ -686,20 +675,18 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
         if constexpr (DBQ) {                                            // fully visible tile: history rows, distance x - y
           dist_sum(dsf[0], 0, xw0 - y0, one_bucket(xw0 - y0));
         }
-        constexpr int NO = 16 * C::NOUT;                                  // output products of the tile
 #pragma unroll
         for (int i = 0; i < PF; ++i) fr[i] = trfrag(i);
 #pragma unroll
-        for (int n = 0; n < NO; ++n) {
+        for (int n = 0; n < 16; ++n) {
           const bf16x8 fa = fr[n % PF];
-          if (n + PF < NO) fr[n % PF] = trfrag(n + PF);
+          if (n + PF < 16) fr[n % PF] = trfrag(n + PF);
           __builtin_amdgcn_sched_barrier(0);
-          const int sb = n / (8 * C::NOUT), r = n % (8 * C::NOUT), step = r / C::NOUT, o = r % C::NOUT;
-          const int ks2 = step / C::OB, ob = step % C::OB;
-          const uint32_t* pk = (o == 0) ? pds[sb] : pp[sb];
+          const int sb = n / 8, ks2 = n % 8 / C::OB, ob = n % C::OB;
+          const uint32_t* pk = pds[sb];
           const bf16x8 pb = __builtin_bit_cast(bf16x8, (u32x4){pk[4 * ks2], pk[4 * ks2 + 1], pk[4 * ks2 + 2], pk[4 * ks2 + 3]});
-          out[o][ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, pb, out[o][ob], 0, 0, 0);
-          if (sb == 0 && o == C::NOUT - 1) pointwise(1, step);
+          out[0][ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, pb, out[0][ob], 0, 0, 0);
+          if (sb == 0) pointwise(1, n);
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (DBQ) {
@@ -1201,10 +1188,10 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
 //     query axis;
 //   - bias-table gradient: dtable[h, c] = inv_n * sum of the per-distance sums over the distances of bucket c
 //     (bounds[c] <= x < bounds[c+1], x < bias_stride), a fixed-order tree per (bucket, head).
-// A unit of work is a quarter of one output of a cut block (32 rows), or one (bucket, head); workgroups take units
-// round-robin.  Nothing but latency bounds it: a thread has the loads of 4 rows x 2 pieces in flight (64 prefix blocks of the
-// semi-local 8k-16k workload, 8 pieces of 128 KB each: 25 us with one load in flight and 16
-// rows per workgroup, 15.6 now).  One launch for both passes and the table's gradient: the backward of an ordinary batch had 23 us in three.
+// A unit of work is 4 KB of one output of a cut block (kUnitRows rows: 8 of 128 features, 16 of 64, 32 of 32), or one (bucket, head);
+// workgroups take units round-robin.  Nothing but latency bounds it: a thread owns 16 bytes of one row and has those of kPiecesAhead = 8
+// pieces in flight (64 prefix blocks of the semi-local 8k-16k workload, 8 pieces of 128 KB each: 16 us; 25 with one load in flight and 16
+// rows per workgroup).  One launch for both passes and the table's gradient: the backward of an ordinary batch had 23 us in three.
 enum { kFinishDKDV = 0, kFinishFwd = 1, kFinishDQ = 2 };
 constexpr int kFinishThreads = 256, kBlockRows = 128, kPiecesAhead = 8;
 constexpr int finish_units(int D) { return kBlockRows * D / (4 * kFinishThreads); }     // units per output of a block
@@ -1216,7 +1203,7 @@ __device__ __forceinline__ void finish_unit(const AttnArgs& a, const FinishJob& 
   const int xb = it.rb_h >> 8, h = it.rb_h & 255;
   const int o = unit / kUnits, r0 = (unit % kUnits) * kUnitRows + (int)threadIdx.x / VPR, c4 = (int)threadIdx.x % VPR;
   const int x0 = xb * kBlockRows + (job.what == kFinishFwd ? tail_origin(it.hist, a.query_tail) : 0);
-  if (x0 + unit % kUnits * kUnitRows >= it.len) return;                  // 32 rows past the end (their waves left nothing)
+  if (x0 + unit % kUnits * kUnitRows >= it.len) return;                  // rows past the end (whole waves of them left nothing)
   const int64_t piece = (job.what == kFinishDKDV ? 2 : 1) * kBlockRows * VPR;
   const f32x4* src = (const f32x4*)job.partial + it.first_slot * piece + (int64_t)(o * kBlockRows + r0) * VPR + c4;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};

@@ -23,11 +23,6 @@ constexpr int kBX = 128, kBN = 64, kD = 128, kWaves = 4;
 constexpr int kTileK = kBN * kD * 2, kTileDs = kBX * kBN * 2, kStage = kTileK + kTileDs;
 constexpr int kSmem = 2 * kStage;
 
-__device__ __forceinline__ float dsilu_of(float t) {
-  const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * t));
-  return sg * (1.0f + t * (1.0f - sg));
-}
-
 __global__ __launch_bounds__(64 * kWaves, 2) void attn_dq_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   typedef __attribute__((address_space(3))) void* lds_void;
@@ -175,8 +170,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_dq_kernel(const AttnArgs 
       float v0 = out[ob][4 * q4] * scale, v1 = out[ob][4 * q4 + 1] * scale, v2 = out[ob][4 * q4 + 2] * scale, v3 = out[ob][4 * q4 + 3] * scale;
       if (pre) {
         const u32x2 t = *(const u32x2*)(pre + f);
-        v0 *= dsilu_of(__uint_as_float(t[0] << 16)); v1 *= dsilu_of(__uint_as_float(t[0] & 0xFFFF0000u));
-        v2 *= dsilu_of(__uint_as_float(t[1] << 16)); v3 *= dsilu_of(__uint_as_float(t[1] & 0xFFFF0000u));
+        v0 *= dsilu(__uint_as_float(t[0] << 16)); v1 *= dsilu(__uint_as_float(t[0] & 0xFFFF0000u));
+        v2 *= dsilu(__uint_as_float(t[1] << 16)); v3 *= dsilu(__uint_as_float(t[1] & 0xFFFF0000u));
       }
       *(u32x2*)(dst + f) = (u32x2){pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
     }
