@@ -28,7 +28,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 
 
 TRAFFIC_SOURCES = ("attn_core.hip", "attn_fwd_pipe.hip", "attn_dq.hip", "gated_norm.hip", "schedule.hip", "api.hip", "hstu_common.h", "hstu_geometry.h",
-                   "hstu_kernels.h")
+                   "hstu_kernels.h", "hstu_plan.h")
 
 
 def kernel_sources_hash():
