@@ -81,8 +81,8 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
                   (int64_t)p->total_tokens / 128 + p->batch <= schedule_sorted_pairs();
   if (for_backward) { l.splits_dq = off; off += align_up((size_t)(l.slot_cap_dq / 2 + 1) * sizeof(SplitItem)); }
   if (ds) { l.ds_table = off; off += align_up(((size_t)p->total_tokens / 128 + p->batch) * 16); }
-  l.bias = off;
-  off += align_up((size_t)p->num_heads * ((size_t)p->max_seqlen + 1) * sizeof(float));
+  l.bias = off + kBiasPad * sizeof(float);
+  off += align_up(((size_t)p->num_heads * ((size_t)p->max_seqlen + 1 + kBiasPad) + kBiasPad) * sizeof(float));
   l.seed = off;                                        // score seeds by distance (bias + mask) of the pipelined kernels
   off += align_up((size_t)kSeedVariants * p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float));
   if (!for_backward) {
@@ -159,6 +159,7 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   ExpandJob ex = {};
   a.bias = nullptr;
   a.bias_stride = p->max_seqlen + 1;
+  a.bias_pitch = a.bias_stride + kBiasPad;
   a.seed = nullptr;
   ex.table = p->rab_table; ex.bounds = p->rab_bounds; ex.num_buckets = p->num_buckets;
   if (p->dtype == HSTU_BF16 && p->head_dim == 128 && for_forward) {   // the pipelined forward takes bias and mask from the seed tables
@@ -171,6 +172,7 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   if (!p->rab_table) return ex;
   ex.bias = (float*)(ws + l.bias);
   ex.bias_len = a.bias_stride;
+  ex.bias_pitch = a.bias_pitch;
   a.bias = ex.bias;
   if (!for_forward && p->d_rab_table) {               // only the bias-table gradient needs the bucket ends and the sums per distance
     a.dbias_copies = dbias_copies_for(p);

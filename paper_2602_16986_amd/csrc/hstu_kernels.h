@@ -46,8 +46,8 @@ struct AttnArgs {
   int32_t B, H, D, T, max_seqlen;
   int32_t K1, K2;
   float alpha, inv_n;
-  const float* bias;                // expanded table [H, bias_stride] indexed by distance, or nullptr
-  int32_t bias_stride;
+  const float* bias;                // expanded table indexed by distance, or nullptr: bias_stride entries per head, heads bias_pitch apart, kBiasPad zeros
+  int32_t bias_stride, bias_pitch;  // in front of each and behind the last
   const SchedHeader* header;
   const WorkItem* items;
   int32_t max_items;
@@ -81,6 +81,7 @@ struct AttnArgs {
   SchedHeader* ds_lists[2];
 };
 constexpr int kDsTileBytes = 32 * 128 * 2;
+constexpr int kBiasPad = 128;
 constexpr int kDbiasCopies = 8;          // one per die
 constexpr int kSeedVariants = 2;
 inline int seed_dmax_for(int max_seqlen) { return max_seqlen + 128; }
@@ -90,7 +91,7 @@ inline int seed_len_for(int max_seqlen) { return (seed_dmax_for(max_seqlen) + 1 
 // Tables that an attention pass reads, filled in the scheduler's launch.
 struct ExpandJob {
   const float* table; const int32_t* bounds; int num_buckets;   // bias table [H, num_buckets] or nullptr
-  float* bias; int bias_len;                                    // optional: AttnArgs::bias [H, bias_len]
+  float* bias; int bias_len, bias_pitch;                        // optional: AttnArgs::bias
   int32_t* bucket_end;                                          // optional, with bias: [bias_len], the first distance of the next bucket
   float* seed; int seed_len, seed_dmax;                         // optional: AttnArgs::seed (table may be nullptr: no bias)
   float* zero; int64_t zero_count;                              // optional: floats to clear

@@ -387,6 +387,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
 // Thread `id` of `n` threads fills its share of the tables:
 //   bias[h, x] = log2(e) * table[h, bucket(x)], bucket(x) = max{c : bounds[c] <= x}, for x in [0, bias_len): the attention kernels
 //   keep their scores in units of ln 2; bucket_end[x]: where the next bucket starts;
+//   and the zeros around every head's row;
 //   seed[v][h][i] (AttnArgs::seed), d = seed_dmax - i;
 //   and clears the per-distance sums of the bias gradient.
 __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen, int id, int n) {
@@ -400,9 +401,10 @@ __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen,
   };
   for (int x = id; j.bias && x < j.bias_len; x += n) {
     const int c = bucket(x);
-    for (int h = 0; h < H; ++h) j.bias[(size_t)h * j.bias_len + x] = j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f;
+    for (int h = 0; h < H; ++h) j.bias[(size_t)h * j.bias_pitch + x] = j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f;
     if (j.bucket_end) j.bucket_end[x] = c + 1 < j.num_buckets ? j.bounds[c + 1] : 0x7FFFFFFF;
   }
+  for (int i = id; j.bias && i < (H + 1) * kBiasPad; i += n) j.bias[(int64_t)(i / kBiasPad) * j.bias_pitch - kBiasPad + i % kBiasPad] = 0.f;
   for (int i = id; j.seed && i < j.seed_len; i += n) {
     const int d = j.seed_dmax - i;
     const int c = j.table ? bucket(d < 0 ? 0 : (d > max_seqlen ? max_seqlen : d)) : 0;    // distances beyond any real pair take the last real one's bias
