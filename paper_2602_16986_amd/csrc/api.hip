@@ -162,7 +162,7 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   a.bias_pitch = a.bias_stride + kBiasPad;
   a.seed = nullptr;
   ex.table = p->rab_table; ex.bounds = p->rab_bounds; ex.num_buckets = p->num_buckets;
-  if (p->dtype == HSTU_BF16 && p->head_dim == 128 && for_forward) {   // the pipelined forward takes bias and mask from the seed tables
+  if (p->dtype == HSTU_BF16 && for_forward) {         // the pipelined forward takes bias and mask from the seed tables
     ex.seed = (float*)(ws + l.seed);                                       // (that kernel needs no other table)
     ex.seed_len = seed_len_for(p->max_seqlen);
     ex.seed_dmax = seed_dmax_for(p->max_seqlen);

@@ -1,6 +1,6 @@
 // Fused jagged HSTU attention kernels for gfx950 (MI355X): forward, dQ pass and dK/dV pass.
 //
-// One templated kernel covers the three passes because they share one shape.  A workgroup
+// One templated kernel covers the three passes because they share one shape (the forward here is the fp32 one: attn_fwd_pipe.hip has bf16).  A workgroup
 // owns a block of "stationary" rows x of one (sequence, head) and streams tiles of the other
 // side y through LDS, visiting only tiles that hold a visible pair (tile_ranges /
 // row_tile_ranges):
@@ -58,12 +58,11 @@ struct Cfg {
   // registers and half the LDS, i.e. two workgroups per compute unit like the other passes.
   static constexpr bool kStatLds = kBf16 && D == 128 && MODE == kBwdDKDV;
   // dQ pass with 64 features: 32-row tiles fit 168 registers and three workgroups per compute unit; 8 x 8k-16k semi-local 304 -> 290 us, short ragged histories 117 -> 108.
-  // (32 features take 64-row tiles at two workgroups: 211 us against 233 with 32-row ones at three; the narrow forwards are
-  // equal or slower with 32-row tiles.)
-  static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && D == 64 && MODE == kBwdDQ;
+  // (32 features fit as many with 64-row tiles: 211 us against 233 with 32-row ones.)
+  static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && D != 128 && MODE == kBwdDQ;
   // dK/dV pass: 32-row tiles for every width.  With 64 features a 64-row tile took more than 256 registers, one workgroup per compute
   // unit: 8 x 8k-16k dense 2.49 ms, 1.85 when made to fit (29 registers spilled), 1.54 with 32-row tiles; 32 features 0.29 -> 0.23 semi-local.
-  static constexpr int BN = kBf16 ? ((MODE == kBwdDKDV || kThreePerCu) ? 32 : 64) : 32;  // streamed rows per LDS tile
+  static constexpr int BN = kBf16 ? ((MODE == kBwdDKDV || D == 64) ? 32 : 64) : 32;  // streamed rows per LDS tile
   static constexpr int NT = 64 * NWAVES;
   static constexpr int ROW_BYTES = D * (int)sizeof(E);
   // LDS tiles are read two ways: 16-byte reads with one streamed row per lane (score products)
@@ -86,7 +85,7 @@ struct Cfg {
   static constexpr bool kTwoPerCu = kBf16 && NWAVES == 4;
   static constexpr int kWgPerCu = kThreePerCu ? 3 : (kTwoPerCu ? 2 : 1);
   static constexpr int PAD0 = !kBf16 ? 16 : (kSwz0 ? 0 : (kBoth0 ? 80 : 16));
-  static constexpr int PAD1 = !kBf16 ? 16 : (kSwz1 ? 0 : (kBoth1 ? 80 : (MODE == kFwd ? 64 : 16)));
+  static constexpr int PAD1 = !kBf16 ? 16 : (kSwz1 ? 0 : (kBoth1 ? 80 : 16));
   static constexpr int STRIDE0 = ROW_BYTES + PAD0, STRIDE1 = ROW_BYTES + PAD1;   // LDS row strides, bytes
   static constexpr int TILE0 = BN * STRIDE0, TILE1 = BN * STRIDE1;
   static constexpr int STAGE_BYTES = TILE0 + TILE1;
@@ -558,7 +557,6 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
   HSTU_TLB(1);
 
   const bool stat_hist = min(xw0 + 32, L) - 1 < g.n;  // this wave's stationary rows are all history rows
-  constexpr int SBG = (MODE == kFwd && NSB >= 2) ? 2 : 1;   // sub-blocks whose products are interleaved
   for (int t = t_begin; t < ntiles; ++t) {
     const int yt = nx_yt;                                    // set_next() of the previous round (or of the prologue) named this tile
     const int stage = (t - t_begin) & 1;
@@ -821,9 +819,9 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     }
     if (kind != kTileEmpty && !done) {                                   // wave-uniform
 #pragma unroll
-      for (int sg = 0; sg < NSB; sg += SBG) {
-        // ---- scores of SBG sub-blocks at once: independent accumulators keep the matrix pipe fed
-        f32x16 sc1[SBG], sc2[SBG];
+      for (int sg = 0; sg < NSB; ++sg) {
+        // ---- scores
+        f32x16 sc1, sc2;
         // Mixed tile whose (existing) query rows are all history rows: every visible pair has distance i - j >= 0, which is
         // what the strip is indexed by, so the scores are seeded like a full tile's and only the mask is applied
         // per element (no table gathers, whose wait would also wait for the tile being fetched).
@@ -838,55 +836,41 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           // entry BX - 1 - (x - x0) of the strip anchored at n (strip_lane also carries this lane's 4 hf register offset)
           const float bias_c = *((const float*)(smem + C::STRIP_BASE + stage * C::STRIP_BYTES) + strip_lane - 4 * hf);
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sc1[u][r] = bias_c;
+          for (int r = 0; r < 16; ++r) sc1[r] = bias_c;
         } else if ((kind == kTileFull || seeded) && bias_h) {
           // the distance of every pair that counts is >= 0: seed the accumulators with the bias strip
           const float* strip = (const float*)(smem + C::STRIP_BASE + stage * C::STRIP_BYTES) + strip_lane;
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const f32x4 bv = *(const f32x4*)(strip + (sg + u) * 32 + 8 * q4);
-              sc1[u][4 * q4 + 0] = bv[0]; sc1[u][4 * q4 + 1] = bv[1];
-              sc1[u][4 * q4 + 2] = bv[2]; sc1[u][4 * q4 + 3] = bv[3];
-            }
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4 bv = *(const f32x4*)(strip + sg * 32 + 8 * q4);
+            sc1[4 * q4 + 0] = bv[0]; sc1[4 * q4 + 1] = bv[1];
+            sc1[4 * q4 + 2] = bv[2]; sc1[4 * q4 + 3] = bv[3];
+          }
         } else {
           // (opaque moves: otherwise the compiler clears the registers ahead of the branch, on the strip's path too)
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) asm volatile("v_mov_b32 %0, 0" : "=v"(sc1[u][r]));
+          for (int r = 0; r < 16; ++r) asm volatile("v_mov_b32 %0, 0" : "=v"(sc1[r]));
         }
         if constexpr (MODE != kFwd) {
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sc2[u][r] = 0.f;
+          for (int r = 0; r < 16; ++r) sc2[r] = 0.f;
         }
         if constexpr (C::kBf16) {
           // A-operand fragments are fetched one k-step ahead of the product that consumes them
-          bf16x8 f1[2][SBG], f2[2][SBG], fs[2];
+          bf16x8 f1[2], f2[2], fs[2];
           // stationary operand 1 when it lives in LDS: B fragment of this wave's row x
           auto statfrag = [&](int ks) -> bf16x8 {
             return *(lds_b8)(uintptr_t)(uint32_t)(((kb - stage * C::STAGE_BYTES) ^ (ks << 5)) + C::STAT_BASE + wave * 8192);
           };
           if constexpr (C::kStatLds) fs[0] = statfrag(0);
-#pragma unroll
-          for (int u = 0; u < SBG; ++u) {
-            f1[0][u] = rowfrag_at(0, sg + u, 0);
-            if (MODE != kFwd) f2[0][u] = rowfrag_at(1, sg + u, 0);
-          }
+          f1[0] = rowfrag_at(0, sg, 0);
+          f2[0] = rowfrag_at(1, sg, 0);
 #pragma unroll
           for (int ks = 0; ks < C::KS; ++ks) {
             if (ks + 1 < C::KS) {
               if constexpr (C::kStatLds) fs[(ks + 1) & 1] = statfrag(ks + 1);
-#pragma unroll
-              for (int u = 0; u < SBG; ++u) {
-                f1[(ks + 1) & 1][u] = rowfrag_at(0, sg + u, ks + 1);
-                if (MODE != kFwd) f2[(ks + 1) & 1][u] = rowfrag_at(1, sg + u, ks + 1);
-              }
+              f1[(ks + 1) & 1] = rowfrag_at(0, sg, ks + 1);
+              f2[(ks + 1) & 1] = rowfrag_at(1, sg, ks + 1);
             }
             if constexpr (C::KS % C::CPT == 0) {
               if (sg == 0 && ks % (C::KS / C::CPT) == 0) gload_piece(ks / (C::KS / C::CPT), stage ^ 1);
@@ -894,55 +878,46 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
               if (sg == 0 && ks == 0) gload(stage ^ 1);
             }
             __builtin_amdgcn_sched_barrier(0);                           // keep the fetches ahead of the products
-#pragma unroll
-            for (int u = 0; u < SBG; ++u) {
-              sc1[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks & 1][u], res[0][ks], sc1[u], 0, 0, 0);
-              if constexpr (MODE != kFwd) {
-                if constexpr (C::kStatLds) sc2[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks & 1][u], fs[ks & 1], sc2[u], 0, 0, 0);
-                else sc2[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks & 1][u], res[1][ks], sc2[u], 0, 0, 0);
-              }
-            }
+            sc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks & 1], res[0][ks], sc1, 0, 0, 0);
+            if constexpr (C::kStatLds) sc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks & 1], fs[ks & 1], sc2, 0, 0, 0);
+            else sc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[ks & 1], res[1][ks], sc2, 0, 0, 0);
           }
         } else {
           if (sg == 0) gload(stage ^ 1);
 #pragma unroll
-          for (int ks = 0; ks < C::KS; ++ks)
-#pragma unroll
-            for (int u = 0; u < SBG; ++u) {
-              const int roff = ((sg + u) * 32 + l32) * C::STRIDE0 + (2 * ks + hf) * 4;   // STRIDE0 == STRIDE1 in fp32
-              sc1[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float*)(y1s + roff), res[0][ks], sc1[u], 0, 0, 0);
-              if constexpr (MODE != kFwd)
-                sc2[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float*)(y2s + roff), res[1][ks], sc2[u], 0, 0, 0);
-            }
+          for (int ks = 0; ks < C::KS; ++ks) {
+            const int roff = (sg * 32 + l32) * C::STRIDE0 + (2 * ks + hf) * 4;   // STRIDE0 == STRIDE1 in fp32
+            sc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float*)(y1s + roff), res[0][ks], sc1, 0, 0, 0);
+            if constexpr (MODE != kFwd)
+              sc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float*)(y2s + roff), res[1][ks], sc2, 0, 0, 0);
+          }
         }
 
         // ---- pointwise: SiLU (forward) or its derivative times dP (backward), mask in registers
-        float c1[SBG][16], c2[SBG][16];
+        float c1[16], c2[16];
         if (kind == kTileFull) {
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float sv = sc1[u][r];
-              const float sig = sigmoid_l2(sv);
-              if (MODE == kFwd) {
-                c1[u][r] = sv * sig;
-              } else {
-                c1[u][r] = sc2[u][r] * dsilu_l2(sv * sig, sig);
-                c2[u][r] = sv * sig;
-              }
+          for (int r = 0; r < 16; ++r) {
+            const float sv = sc1[r];
+            const float sig = sigmoid_l2(sv);
+            if (MODE == kFwd) {
+              c1[r] = sv * sig;
+            } else {
+              c1[r] = sc2[r] * dsilu_l2(sv * sig, sig);
+              c2[r] = sv * sig;
             }
+          }
         } else {
           // one score of the mixed path: t = score in ln 2 units, vis = pair visible
-          auto mixed = [&](int u, int r, float t, bool vis) {
+          auto mixed = [&](int r, float t, bool vis) {
             const float sig = sigmoid_l2(t);
             const float p = t * sig;
             if (MODE == kFwd) {
-              c1[u][r] = vis ? p : 0.f;
+              c1[r] = vis ? p : 0.f;
             } else {
-              const float ds = sc2[u][r] * dsilu_l2(p, sig);
-              c1[u][r] = vis ? ds : 0.f;
-              c2[u][r] = vis ? p : 0.f;
+              const float ds = sc2[r] * dsilu_l2(p, sig);
+              c1[r] = vis ? ds : 0.f;
+              c2[r] = vis ? p : 0.f;
             }
           };
           if (CANDK && seeded && cand_tile) {
@@ -950,9 +925,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             const bool key_vis = x_ok && (g.K1 < 0 || g.n - x < g.K1 || x < g.K2);
             const int up = key_vis ? L - 1 - y0 - 4 * hf : -1;
 #pragma unroll
-            for (int u = 0; u < SBG; ++u)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) mixed(u, r, sc1[u][r], (sg + u) * 32 + 8 * (r >> 2) + (r & 3) <= up);
+            for (int r = 0; r < 16; ++r) mixed(r, sc1[r], sg * 32 + 8 * (r >> 2) + (r & 3) <= up);
           } else if (seeded && MODE == kBwdDKDV) {
             // History rows only, seen from key x: the queries y >= x with y - x < K1 (any y >= x for a key of the global
             // prefix or a dense mask), and y < L.  Query = y0 + c + 4 hf, c a compile-time constant per register.
@@ -964,22 +937,16 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             const bool need_up = y0 + C::BN > L || (g.K1 >= 0 && kfirst <= xw0 + 31 && y0 + C::BN - 1 - kfirst >= g.K1);
             if (need_lo && !need_up) {
 #pragma unroll
-              for (int u = 0; u < SBG; ++u)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mixed(u, r, sc1[u][r], (sg + u) * 32 + 8 * (r >> 2) + (r & 3) >= lo);
+              for (int r = 0; r < 16; ++r) mixed(r, sc1[r], sg * 32 + 8 * (r >> 2) + (r & 3) >= lo);
             } else if (need_up && !need_lo) {
 #pragma unroll
-              for (int u = 0; u < SBG; ++u)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mixed(u, r, sc1[u][r], (sg + u) * 32 + 8 * (r >> 2) + (r & 3) <= up);
+              for (int r = 0; r < 16; ++r) mixed(r, sc1[r], sg * 32 + 8 * (r >> 2) + (r & 3) <= up);
             } else {
 #pragma unroll
-              for (int u = 0; u < SBG; ++u)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                  const int c = (sg + u) * 32 + 8 * (r >> 2) + (r & 3);
-                  mixed(u, r, sc1[u][r], c >= lo && c <= up);
-                }
+              for (int r = 0; r < 16; ++r) {
+                const int c = sg * 32 + 8 * (r >> 2) + (r & 3);
+                mixed(r, sc1[r], c >= lo && c <= up);
+              }
             }
           } else if (seeded) {
             // History rows only: row x sees the keys y <= x with x - y < K1 or y < K2.  Relative to the tile's first key and
@@ -994,70 +961,59 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             const bool need_pre = need_lo && g.K2 > y0;
             if (!need_lo) {
 #pragma unroll
-              for (int u = 0; u < SBG; ++u)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mixed(u, r, sc1[u][r], (sg + u) * 32 + 8 * (r >> 2) + (r & 3) <= up);
+              for (int r = 0; r < 16; ++r) mixed(r, sc1[r], sg * 32 + 8 * (r >> 2) + (r & 3) <= up);
             } else if (!need_pre) {
 #pragma unroll
-              for (int u = 0; u < SBG; ++u)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                  const int c = (sg + u) * 32 + 8 * (r >> 2) + (r & 3);
-                  mixed(u, r, sc1[u][r], c <= up && c >= lo);
-                }
+              for (int r = 0; r < 16; ++r) {
+                const int c = sg * 32 + 8 * (r >> 2) + (r & 3);
+                mixed(r, sc1[r], c <= up && c >= lo);
+              }
             } else {
 #pragma unroll
-              for (int u = 0; u < SBG; ++u)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                  const int c = (sg + u) * 32 + 8 * (r >> 2) + (r & 3);
-                  mixed(u, r, sc1[u][r], c <= up && (c >= lo || c < pre));
-                }
+              for (int r = 0; r < 16; ++r) {
+                const int c = sg * 32 + 8 * (r >> 2) + (r & 3);
+                mixed(r, sc1[r], c <= up && (c >= lo || c < pre));
+              }
             }
           } else {
 #pragma unroll
-            for (int u = 0; u < SBG; ++u)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const int y = y0 + (sg + u) * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-                int delta;
-                const bool vis = (MODE == kBwdDKDV) ? visible(g, y, x, delta) : visible(g, x, y, delta);
-                float bv = 0.f;
-                if (bias_h) bv = bias_h[vis ? delta : 0];
-                mixed(u, r, sc1[u][r] + bv, vis);
-              }
+            for (int r = 0; r < 16; ++r) {
+              const int y = y0 + sg * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
+              int delta;
+              const bool vis = (MODE == kBwdDKDV) ? visible(g, y, x, delta) : visible(g, x, y, delta);
+              float bv = 0.f;
+              if (bias_h) bv = bias_h[vis ? delta : 0];
+              mixed(r, sc1[r] + bv, vis);
+            }
           }
         }
 
         if constexpr (DBQ) {
+          float hv[16];
 #pragma unroll
-          for (int u = 0; u < SBG; ++u) {
-            float hv[16];
+          for (int r = 0; r < 16; ++r) hv[r] = x < g.n ? c1[r] : 0.f;
+          if (xw0 + 31 >= g.n) {
+            // candidate rows stand at position n: one distance per key (their own key: distance 0), summed over the rows
+            float cv[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) hv[r] = x < g.n ? c1[u][r] : 0.f;
-            if (xw0 + 31 >= g.n) {
-              // candidate rows stand at position n: one distance per key (their own key: distance 0), summed over the rows
-              float cv[16];
-#pragma unroll
-              for (int r = 0; r < 16; ++r) cv[r] = x < g.n ? 0.f : c1[u][r];
-              const float v = row_sums(cv, i16);
-              const int y = y0 + (sg + u) * 32 + 8 * (i16 >> 2) + 4 * hf + (i16 & 3);
-              if (v != 0.f) atomicAdd(dist_h + max(g.n - y, 0), v);
-            }
-            const int w0 = xw0 - y0 - 32 * (sg + u);
-            if (xw0 < g.n) dist_sum(hv, sg + u, w0, kind == kTileFull ? one_bucket(w0) : 0);
+            for (int r = 0; r < 16; ++r) cv[r] = x < g.n ? 0.f : c1[r];
+            const float v = row_sums(cv, i16);
+            const int y = y0 + sg * 32 + 8 * (i16 >> 2) + 4 * hf + (i16 & 3);
+            if (v != 0.f) atomicAdd(dist_h + max(g.n - y, 0), v);
           }
+          const int w0 = xw0 - y0 - 32 * sg;
+          if (xw0 < g.n) dist_sum(hv, sg, w0, kind == kTileFull ? one_bucket(w0) : 0);
         }
         if constexpr (DBK) {
           // candidate queries stand at position n: one distance per key (their own key: distance 0)
           float hv[16];
           const int nh = g.n - y0 - 4 * hf;                                  // c < nh  <=>  history query
 #pragma unroll
-          for (int r = 0; r < 16; ++r) hv[r] = 8 * (r >> 2) + (r & 3) < nh ? c1[0][r] : 0.f;
+          for (int r = 0; r < 16; ++r) hv[r] = 8 * (r >> 2) + (r & 3) < nh ? c1[r] : 0.f;
           if (CANDK && y0 + C::BN > g.n) {
             float cand = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) cand += 8 * (r >> 2) + (r & 3) < nh ? 0.f : c1[0][r];
+            for (int r = 0; r < 16; ++r) cand += 8 * (r >> 2) + (r & 3) < nh ? 0.f : c1[r];
             if (cand != 0.f) atomicAdd(dist_h + (x < g.n ? g.n - x : 0), cand);
           }
           if (y0 < g.n) dist_sum(hv, 0, y0 - xw0, 0);
@@ -1068,61 +1024,54 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           // transpose load: within a group of 16 lanes, lane 4r+c supplies the address of 4 features
           // (4c..4c+3) of streamed row r and lane i receives feature i of rows 0..3.  The 8 k-slots of
           // this lane in k-step ks2 are streamed rows ks2*16 + 4*hf + {0..3} and + 8 + {0..3}.
-          constexpr int NSTEP = SBG * 2 * C::OB;                          // (sub-block, k-step, feature block)
-          constexpr int TSRC = (MODE == kFwd) ? 1 : 0;                    // V (forward), K (dQ), Q (dK)
-          auto fetch = [&](int step, int tensor) -> bf16x8 {
-            return trfrag_at(tensor, sg + step / (2 * C::OB), (step / C::OB) & 1, step % C::OB);
-          };
-          uint32_t pk1[SBG][8], pk2[SBG][8];
+          constexpr int NSTEP = 2 * C::OB;                                // (k-step, feature block)
+          auto fetch = [&](int step, int tensor) -> bf16x8 { return trfrag_at(tensor, sg, step / C::OB, step % C::OB); };      // tensor 0: K (dQ), Q (dK); 1: dO (dV)
+          uint32_t pk1[8], pk2[8];
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-              pk1[u][m] = pack_bf16x2(c1[u][2 * m], c1[u][2 * m + 1]);
-              if (MODE == kBwdDKDV) pk2[u][m] = pack_bf16x2(c2[u][2 * m], c2[u][2 * m + 1]);
-            }
+          for (int m = 0; m < 8; ++m) {
+            pk1[m] = pack_bf16x2(c1[2 * m], c1[2 * m + 1]);
+            if (MODE == kBwdDKDV) pk2[m] = pack_bf16x2(c2[2 * m], c2[2 * m + 1]);
+          }
           if constexpr (DS) {
-            static_assert(SBG == 1 && NSB == 1, "one sub-block per tile");
-            ds_store(0, pk1[0][0], pk1[0][1], pk1[0][2], pk1[0][3]);
-            ds_store(1, pk1[0][4], pk1[0][5], pk1[0][6], pk1[0][7]);
+            static_assert(NSB == 1, "one sub-block per tile");
+            ds_store(0, pk1[0], pk1[1], pk1[2], pk1[3]);
+            ds_store(1, pk1[4], pk1[5], pk1[6], pk1[7]);
           }
           bf16x8 a1[2], a2[2];
-          a1[0] = fetch(0, TSRC);
+          a1[0] = fetch(0, 0);
           if (MODE == kBwdDKDV) a2[0] = fetch(0, 1);
 #pragma unroll
           for (int step = 0; step < NSTEP; ++step) {
             if (step + 1 < NSTEP) {
-              a1[(step + 1) & 1] = fetch(step + 1, TSRC);
+              a1[(step + 1) & 1] = fetch(step + 1, 0);
               if (MODE == kBwdDKDV) a2[(step + 1) & 1] = fetch(step + 1, 1);
             }
             __builtin_amdgcn_sched_barrier(0);
-            const int u = step / (2 * C::OB), ks2 = (step / C::OB) & 1, ob = step % C::OB;
-            const bf16x8 b1 = __builtin_bit_cast(bf16x8, (u32x4){pk1[u][4 * ks2], pk1[u][4 * ks2 + 1], pk1[u][4 * ks2 + 2], pk1[u][4 * ks2 + 3]});
+            const int ks2 = step / C::OB, ob = step % C::OB;
+            const bf16x8 b1 = __builtin_bit_cast(bf16x8, (u32x4){pk1[4 * ks2], pk1[4 * ks2 + 1], pk1[4 * ks2 + 2], pk1[4 * ks2 + 3]});
             out[0][ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[step & 1], b1, out[0][ob], 0, 0, 0);
             if constexpr (MODE == kBwdDKDV) {                            // dV^T += dO^T P
-              const bf16x8 b2 = __builtin_bit_cast(bf16x8, (u32x4){pk2[u][4 * ks2], pk2[u][4 * ks2 + 1], pk2[u][4 * ks2 + 2], pk2[u][4 * ks2 + 3]});
+              const bf16x8 b2 = __builtin_bit_cast(bf16x8, (u32x4){pk2[4 * ks2], pk2[4 * ks2 + 1], pk2[4 * ks2 + 2], pk2[4 * ks2 + 3]});
               out[1][ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2[step & 1], b2, out[1][ob], 0, 0, 0);
             }
           }
         } else {
 #pragma unroll
-          for (int u = 0; u < SBG; ++u)
+          for (int ks2 = 0; ks2 < 16; ++ks2) {
+            // k-step ks2 contracts the two streamed rows 8*(ks2/4) + ks2%4 (+4 for the upper half-wave)
+            const int trow = sg * 32 + 8 * (ks2 >> 2) + 4 * hf + (ks2 & 3);
 #pragma unroll
-            for (int ks2 = 0; ks2 < 16; ++ks2) {
-              // k-step ks2 contracts the two streamed rows 8*(ks2/4) + ks2%4 (+4 for the upper half-wave)
-              const int trow = (sg + u) * 32 + 8 * (ks2 >> 2) + 4 * hf + (ks2 & 3);
-#pragma unroll
-              for (int ob = 0; ob < C::OB; ++ob) {
-                const int off = trow * C::STRIDE0 + (ob * 32 + l32) * 4;
-                const unsigned char* src0 = (MODE == kFwd) ? y2s : y1s;
-                const float af = *(const float*)(src0 + off);
-                out[0][ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(af, c1[u][ks2], out[0][ob], 0, 0, 0);
-                if constexpr (MODE == kBwdDKDV) {
-                  const float af2 = *(const float*)(y2s + off);
-                  out[1][ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(af2, c2[u][ks2], out[1][ob], 0, 0, 0);
-                }
+            for (int ob = 0; ob < C::OB; ++ob) {
+              const int off = trow * C::STRIDE0 + (ob * 32 + l32) * 4;
+              const unsigned char* src0 = (MODE == kFwd) ? y2s : y1s;
+              const float af = *(const float*)(src0 + off);
+              out[0][ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(af, c1[ks2], out[0][ob], 0, 0, 0);
+              if constexpr (MODE == kBwdDKDV) {
+                const float af2 = *(const float*)(y2s + off);
+                out[1][ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(af2, c2[ks2], out[1][ob], 0, 0, 0);
               }
             }
+          }
         }
       }
     }
@@ -1322,12 +1271,12 @@ static hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
 template <int MODE, int NW_BF16, int NW_FP32, bool DBIAS = false, bool CAND = false>
 static hipError_t dispatch(const AttnArgs& a, int dtype, hipStream_t stream) {
   if (dtype == 0) {
-    switch (a.D) {
-      case 32: return launch_one<__bf16, 32, MODE, NW_BF16, DBIAS, CAND>(a, stream);
-      case 64: return launch_one<__bf16, 64, MODE, NW_BF16, DBIAS, CAND>(a, stream);
-      case 128:
-        if constexpr (MODE != kFwd) return launch_one<__bf16, 128, MODE, NW_BF16, DBIAS, CAND>(a, stream);    // (the forward: attn_fwd_pipe.hip)
-        break;
+    if constexpr (MODE != kFwd) {                          // (the forward: attn_fwd_pipe.hip)
+      switch (a.D) {
+        case 32: return launch_one<__bf16, 32, MODE, NW_BF16, DBIAS, CAND>(a, stream);
+        case 64: return launch_one<__bf16, 64, MODE, NW_BF16, DBIAS, CAND>(a, stream);
+        case 128: return launch_one<__bf16, 128, MODE, NW_BF16, DBIAS, CAND>(a, stream);
+      }
     }
   } else {
     switch (a.D) {
@@ -1349,11 +1298,11 @@ int fwd_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kFwdWavesBf16 : k
 int dq_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDqWavesBf16 : kDqWavesFp32); }
 int dkv_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDkvWavesBf16 : kDkvWavesFp32); }
 int stream_tile_rows(int dtype, int D) { return dtype == 0 && D != 64 ? 64 : 32; }
-int fwd_tile_rows(int dtype, int D) { return dtype == 0 ? (D == 128 ? 32 : 64) : 32; }
+int fwd_tile_rows(int, int) { return 32; }
 int dkv_tile_rows(int, int) { return 32; }
 
 hipError_t launch_attn_fwd(const AttnArgs& a, int dtype, hipStream_t stream) {
-  if (dtype == 0 && a.D == 128) return launch_attn_fwd_pipe(a, stream);
+  if (dtype == 0) return launch_attn_fwd_pipe(a, stream);
   if (a.num_targets) return dispatch<kFwd, kFwdWavesBf16, kFwdWavesFp32, false, true>(a, dtype, stream);
   return dispatch<kFwd, kFwdWavesBf16, kFwdWavesFp32>(a, dtype, stream);
 }

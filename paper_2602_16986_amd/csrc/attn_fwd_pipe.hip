@@ -1,7 +1,7 @@
-// Forward attention for bf16 with 128 features per head: the tile loop as a software pipeline inside every wave.
+// Forward attention for bf16 (32, 64 or 128 features per head): the tile loop as a software pipeline inside every wave.
 //
-// Computes for this width what attn_kernel<..., forward, ...> computes for the others (paper Eq. 3 under the masks of Section 4.2.1, same work items, same
-// LDS tile format), with the instruction stream arranged for the way a gfx950 SIMD issues.  Measured on the part: a
+// Computes what attn_kernel<float, ..., forward, ...> computes for fp32 (paper Eq. 3 under the masks of Section 4.2.1, same work items),
+// with the instruction stream arranged for the way a gfx950 SIMD issues.  Measured on the part: a
 // matrix instruction hides vector instructions only when they follow it in the SAME wave (a second wave's vector work
 // does not overlap with this wave's matrix work), and every instruction a wave issues, scalar ones included, delays its
 // next matrix instruction.  So:
@@ -11,7 +11,10 @@
 //      step s, second half (8 slots):  O += V(s-1)^T P(s-1), keys 0..15 then 16..31       |  SiLU of keys 0..15 of sub-block s
 //    P(s-1) is complete exactly when its second product starts; a slot carries one matrix instruction, one SiLU (exp2,
 //    add, rcp, mul) per lane and half a bf16 packing, the SiLU as a rolling pipeline over the slots so that nothing waits
-//    for the transcendental in front of it.
+//    for the transcendental in front of it.  With 64 features a half-step has 4 slots of two SiLU each, with 32 two of four: the
+//    pointwise work bounds those.  8 x 8k-16k tokens, 4 heads, dense / 1024 + 256 semi-local: 64 features 870 -> 624 / 227 -> 163 us,
+//    32 features semi-local 158 -> 125; the last 64 rows and 32-128 candidates of each, 64 features, 69 -> 46 us (before: element-wise masks and the
+//    pointwise work of a tile behind its score products).  Four or five workgroups per compute unit measure the same there as three.
 // 2. The mask costs nothing in the loop: the score accumulators are SEEDED with a function of the distance
 //    position - key (AttnArgs::seed): the relative bias where the key is visible, -1e30 where it is not (later keys;
 //    keys beyond the local band).  Such a score stays at -1e30 through the product, exp2(1e30) = inf, rcp(inf) = 0 and
@@ -33,19 +36,34 @@
 namespace hstu {
 namespace {
 
-constexpr int kBX = 128, kBN = 32, kWaves = 4, kThreads = 64 * kWaves, kD = 128;
-constexpr int kTile = kBN * 256;                                       // one 32-row tile of 256-byte rows
+constexpr int kBX = 128, kBN = 32, kWaves = 4, kThreads = 64 * kWaves;
 // Seed strip of one (block, sub-block): the kBX + kBN - 1 distances a sub-block needs, in 4 copies shifted by one entry so
 // that a lane fetches 4 consecutive entries with one aligned 16-byte read.  Wave c loads copy c with one 16-byte-per-lane
 // load (entries 4 l .. 4 l + 3 from lane l; the seed table is stored by descending distance for this).  Copies are 1088
 // bytes apart: 1 KB that the load fills plus 64 bytes that put the 16 reads of a quarter-wave on 16 different bank groups.
 constexpr int kStripCopy = 1088, kStripBytes = 4 * kStripCopy;
-constexpr int kKBase = 0, kVBase = 2 * kTile, kStripBase = 4 * kTile;
-// The last kQLds of the 8 Q fragments of a lane wait in LDS (16 bytes per lane and fragment) instead of in registers: that
-// is what lets three workgroups share a compute unit (168 registers per lane).
-constexpr int kQLds = 2;
-constexpr int kQBase = kStripBase + 2 * kStripBytes;
-constexpr int kSmemBytes = kQBase + kQLds * kThreads * 16;
+// What follows from the number of features.
+template <int D>
+struct Pipe {
+  static constexpr int kRow = 2 * D, kTile = kBN * kRow;                // bytes of a row of K or V, and of a 32-row tile
+  static constexpr int kSteps = D / 16, kBlocks = D / 32;               // k-steps of a score product (slots of a half-step), 32-feature output blocks
+  static constexpr int kScores = 8 / kSteps;                            // scores whose SiLU rides in a slot
+  // Loads of a tile: kRowsPer rows per wave-level load.  Two per wave with 128 features, one with 64; with 32 the first two waves load
+  // the tile and the others' loads (the waits count loads) have an empty range and a place of their own to put zeros.
+  static constexpr int kRowsPer = 1024 / kRow, kPieces = D == 128 ? 2 : 1, kLoaders = D == 32 ? 2 : kWaves;
+  // The last kQLds of the 8 Q fragments of a lane wait in LDS (16 bytes per lane and fragment) instead of in registers: that
+  // is what lets three workgroups of the widest kernel share a compute unit (168 registers per lane).
+  static constexpr int kQLds = D == 128 ? 2 : 0;
+  static constexpr int kWgPerCu = D == 128 ? 3 : 4;
+  static constexpr int kKBase = 0, kVBase = 2 * kTile, kStripBase = 4 * kTile, kQBase = kStripBase + 2 * kStripBytes;
+  static constexpr int kIdle = kQBase + kQLds * kThreads * 16;          // where the loads of waves that load nothing land
+  static constexpr int kSmemBytes = kIdle + (kLoaders < kWaves ? 1024 : 0);
+  // Row r keeps its 16-byte chunk c at chunk c ^ swizzle(r), so that 16 rows read at one chunk, and 4 rows read at 4 chunks (transpose
+  // loads), lie in 16 different groups of 4 banks each.
+  static __device__ __forceinline__ int swizzle(int r) {
+    return D == 128 ? 4 * (r & 3) + ((r >> 2) & 3) : D == 64 ? 4 * ((r >> 1) & 1) + ((r >> 2) & 3) : (r >> 2) & 3;
+  }
+};
 #ifndef HSTU_FP_PF
 #define HSTU_FP_PF 1
 #endif
@@ -91,9 +109,12 @@ typedef __attribute__((address_space(3))) const bf16x8* lds_b8;
 typedef __attribute__((address_space(3))) const f32x4* lds_f4;
 
 template <int N> using IC = std::integral_constant<int, N>;
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }      // at most N still fly
 
-template <bool CAND>
-__global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnArgs a) {
+template <int D, bool CAND>
+__global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_kernel(const AttnArgs a) {
+  using W = Pipe<D>;
+  constexpr int kTile = W::kTile, kSteps = W::kSteps, kBlocks = W::kBlocks, kQLds = W::kQLds, kPieces = W::kPieces;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   const int wg = blockIdx.x;
   const int xcd = wg % kNumXcd, slot_id = wg / kNumXcd;
@@ -123,26 +144,26 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   const bool x_ok = x < L;
   const int q0 = a.query_tail > 0 ? max(g.n - a.query_tail, 0) : 0;    // rows before q0 are not written
 
-  const int64_t hoff = (int64_t)h * kD;
+  const int64_t hoff = (int64_t)h * D;
   const __bf16* Qp = (const __bf16*)a.q + seq0 * a.sq + hoff;
   const __bf16* Kp = (const __bf16*)a.k + seq0 * a.sk + hoff;
   const __bf16* Vp = (const __bf16*)a.v + seq0 * a.sv + hoff;
 
   // ---- this lane's query row as B operands of the score product, times alpha log2 e (scores in units of ln 2)
   const float score_scale = kLog2e * a.alpha;
-  bf16x8 qf[8];
+  bf16x8 qf[kSteps];
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
+  for (int ks = 0; ks < kSteps; ++ks) {
     u32x4 raw = {0u, 0u, 0u, 0u};
     if (x_ok) raw = *(const u32x4*)(Qp + (int64_t)x * a.sq + ks * 16 + hf * 8);
     qf[ks] = __builtin_bit_cast(bf16x8, raw);
   }
   typedef __attribute__((address_space(3))) bf16x8* lds_b8w;
-  const int qaddr = (int)(uint32_t)(uintptr_t)(lds_void)smem + kQBase + tid * 16;
+  const int qaddr = (int)(uint32_t)(uintptr_t)(lds_void)smem + W::kQBase + tid * 16;
   // (first use in the prologue, after the first sub-blocks' loads are issued: the two round trips to memory overlap)
   auto finish_q = [&]() {
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < kSteps; ++ks) {
       u32x4 raw = __builtin_bit_cast(u32x4, qf[ks]);
 #pragma unroll
       for (int w = 0; w < 4; ++w)
@@ -151,14 +172,14 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
       qf[ks] = __builtin_bit_cast(bf16x8, raw);
     }
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));    // landed before the loop: nothing in it may wait on them
+    for (int ks = 0; ks < kSteps; ++ks) asm volatile("" : "+v"(qf[ks]));    // landed before the loop: nothing in it may wait on them
 #pragma unroll
-    for (int i = 0; i < kQLds; ++i) *(lds_b8w)(uintptr_t)(uint32_t)(qaddr + i * kThreads * 16) = qf[8 - kQLds + i];
+    for (int i = 0; i < kQLds; ++i) *(lds_b8w)(uintptr_t)(uint32_t)(qaddr + i * kThreads * 16) = qf[kSteps - kQLds + i];
   };
 
-  f32x16 out[4];
+  f32x16 out[kBlocks];
 #pragma unroll
-  for (int ob = 0; ob < 4; ++ob)
+  for (int ob = 0; ob < kBlocks; ++ob)
 #pragma unroll
     for (int r = 0; r < 16; ++r) out[ob][r] = 0.f;
 
@@ -199,10 +220,12 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
 
   // ---- global -> LDS: raw buffer loads with the LDS destination in M0 (lane l lands at M0 + 16 l)
   const uint32_t rowbK = (uint32_t)(a.sk * 2), rowbV = (uint32_t)(a.sv * 2);
-  const int dma_chunk = (lane & 15) ^ (4 * (lane >> 4) + (wave & 3));
-  uint32_t voffK = __umul24((uint32_t)(lane >> 4), rowbK) + (uint32_t)(dma_chunk * 16);
-  uint32_t voffV = __umul24((uint32_t)(lane >> 4), rowbV) + (uint32_t)(dma_chunk * 16);
-  // the second 4-row group of a wave (16 rows further down) uses the same descriptor with a lane offset 16 rows larger
+  const bool loader = W::kLoaders == kWaves || wave < W::kLoaders;
+  const int dma_row = lane / (64 / W::kRowsPer);                        // of the wave's rows of a tile
+  const int dma_chunk = (lane % (64 / W::kRowsPer)) ^ W::swizzle(W::kRowsPer * wave + dma_row);
+  uint32_t voffK = __umul24((uint32_t)dma_row, rowbK) + (uint32_t)(dma_chunk * 16);
+  uint32_t voffV = __umul24((uint32_t)dma_row, rowbV) + (uint32_t)(dma_chunk * 16);
+  // the second group of rows of a wave (128 features: 16 rows further down) uses the same descriptor with a lane offset 16 rows larger
   uint32_t voffK1 = voffK + 16u * rowbK, voffV1 = voffV + 16u * rowbV;
   uint32_t voffS = 16u * (uint32_t)lane + 4u * (uint32_t)wave;           // this wave loads copy `wave` of the strip
   asm volatile("" : "+v"(voffK), "+v"(voffV), "+v"(voffK1), "+v"(voffV1), "+v"(voffS));
@@ -215,7 +238,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   // (M0 = a per-wave base + a constant: one scalar instruction; one idle cycle between the write of M0 and its use)
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void)smem;
   const uint32_t m0_rows = smem_base + (uint32_t)wave * 1024u;
-  const uint32_t m0_strip = smem_base + (uint32_t)kStripBase + (uint32_t)wave * (uint32_t)kStripCopy;
+  const uint32_t m0_strip = smem_base + (uint32_t)W::kStripBase + (uint32_t)wave * (uint32_t)kStripCopy;
   auto dma16 = [&](i32x4 rs, uint32_t voff, uint32_t m0_base, uint32_t dst_off) {
     asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
                  :: "s"(m0_base), "s"(dst_off), "v"(voff), "s"(rs) : "memory", "m0", "scc");
@@ -230,7 +253,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   auto src_of = [&](int idx) -> Src {
     const bool valid = idx < n;
     const int yt = valid ? tile_of(idx) : 0;
-    const int yrow = yt * kBN + 4 * wave;
+    const int yrow = yt * kBN + W::kRowsPer * wave;
     const int left = valid ? L - yrow : 0;
     const bool band = g.K1 >= 0 && yt >= tr.b0 && yt < tr.b1;
     Src r;
@@ -256,26 +279,31 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
     r.yt = yt;
     return r;
   };
-  // piece c (0, 1): the 4-row group 4 c + wave of the tile
-  auto load_k = [&](const Src& sr, int stage, int c) { dma16(make_rsrc(sr.k.addr, (uint32_t)max(sr.k.left, 0) * rowbK), c ? voffK1 : voffK, m0_rows, (uint32_t)(kKBase + stage * kTile + 4096 * c)); };
-  auto load_vd = [&](const Rows& vd, int stage, int c) { dma16(make_rsrc(vd.addr, (uint32_t)max(vd.left, 0) * rowbV), c ? voffV1 : voffV, m0_rows, (uint32_t)(kVBase + stage * kTile + 4096 * c)); };
+  // piece c of a wave: the rows 16 c + kRowsPer * wave .. of the tile
+  auto load_rows = [&](const Rows& r, uint32_t rowb, uint32_t voff, int base, int stage, int c) {
+    const uint32_t bytes = loader ? (uint32_t)max(r.left, 0) * rowb : 0u;
+    if (W::kLoaders == kWaves || loader) dma16(make_rsrc(r.addr, bytes), voff, m0_rows, (uint32_t)(base + stage * kTile + 4096 * c));
+    else dma16(make_rsrc(r.addr, bytes), voff, smem_base, (uint32_t)W::kIdle);
+  };
+  auto load_k = [&](const Src& sr, int stage, int c) { load_rows(sr.k, rowbK, c ? voffK1 : voffK, W::kKBase, stage, c); };
+  auto load_vd = [&](const Rows& vd, int stage, int c) { load_rows(vd, rowbV, c ? voffV1 : voffV, W::kVBase, stage, c); };
   auto load_v = [&](const Src& sr, int stage, int c) { load_vd(sr.v, stage, c); };
   auto load_strip = [&](const Src& sr, int stage) { dma16(make_rsrc(sr.seed, sr.seed_bytes), voffS + sr.s_off, m0_strip, (uint32_t)(stage * kStripBytes)); };
 
   // ---- LDS fragment addresses of stage 0 (the stage and the position inside the tile are immediate offsets).
-  // Row r stores its logical 16-byte chunk c at chunk c ^ (4 (r % 4) + (r / 4) % 4).
-  const int zl = 4 * (l32 & 3) + ((l32 >> 2) & 3);
-  const int kb = (int)smem_base + kKBase + l32 * 256 + ((hf ^ (zl & 1)) << 4) + ((zl >> 1) << 5);
+  const int zl = W::swizzle(l32);
+  const int kb = (int)smem_base + W::kKBase + l32 * W::kRow + ((hf ^ (zl & 1)) << 4) + ((zl >> 1) << 5);
+  // (rows 4 hf + i16 / 4 + 8 hi of a 16-row group, chunks 4 ob + vchunk: the swizzle's low two bits are hf + 2 hi)
   const int vchunk = 2 * (grp16 & 1) + ((i16 & 3) >> 1), vbyte = 8 * (i16 & 1);
-  const int tb = (int)smem_base + kVBase + (4 * hf + (i16 >> 2)) * 256 + ((i16 >> 2) << 6) + ((vchunk ^ hf) << 4) + vbyte;
-  int kaddr[8], vaddr[8];
+  const int tb = (int)smem_base + W::kVBase + (4 * hf + (i16 >> 2)) * W::kRow + ((W::swizzle(i16 >> 2) >> 2) << 6) + ((vchunk ^ hf) << 4) + vbyte;
+  int kaddr[kSteps], vaddr[2 * kBlocks];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < kSteps; ++i) {
     kaddr[i] = kb ^ (i << 5);                                          // k-step i of a score product
     vaddr[i] = tb ^ (((i >> 1) << 6) | ((i & 1) << 5));                // feature block i / 2, rows +0 (i even) or +8 (i odd)
     asm volatile("" : "+v"(kaddr[i]), "+v"(vaddr[i]));
   }
-  const int saddr = (int)smem_base + kStripBase + (strip_s0 & 3) * kStripCopy + (strip_s0 & ~3) * 4;
+  const int saddr = (int)smem_base + W::kStripBase + (strip_s0 & 3) * kStripCopy + (strip_s0 & ~3) * 4;
   auto kfrag = [&](int stage, int ks) -> bf16x8 {
     if constexpr (kNoLdsK) return undefined_value<bf16x8>();
     if constexpr ((HSTU_FWD_ABLATE & 128) != 0) {
@@ -288,8 +316,8 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   // A operand of an output product: features 32 ob .. 32 ob + 31 (rows) x keys 16 ks2 + 4 hf + {0..3}, + 8 + {0..3}
   auto vfrag = [&](int stage, int ks2, int ob) -> bf16x8 {
     if constexpr (kNoLdsV) return undefined_value<bf16x8>();
-    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)(vaddr[2 * ob] + stage * kTile + ks2 * 4096));
-    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)(vaddr[2 * ob + 1] + stage * kTile + ks2 * 4096 + 2048));
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)(vaddr[2 * ob] + stage * kTile + ks2 * 16 * W::kRow));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)(vaddr[2 * ob + 1] + stage * kTile + (ks2 * 16 + 8) * W::kRow));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
@@ -331,13 +359,15 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   Src cur = src_of(0);
   Rows vdesc0 = cur.v, vdesc1;                                         // V of sub-blocks s and s + 1
   const int yt_first = cur.yt;
-  load_k(cur, 0, 0); load_k(cur, 0, 1); load_strip(cur, 0);
+  for (int c = 0; c < kPieces; ++c) load_k(cur, 0, c);
+  load_strip(cur, 0);
   cur = next_src(cur, 1);
   vdesc1 = cur.v;
-  load_k(cur, 1, 0); load_k(cur, 1, 1); load_strip(cur, 1);
+  for (int c = 0; c < kPieces; ++c) load_k(cur, 1, c);
+  load_strip(cur, 1);
   {                                                                     // V stage 1 is read by step 0 ("sub-block -1"): zeros
     const Src none = src_of(n);
-    load_v(none, 1, 0); load_v(none, 1, 1);
+    for (int c = 0; c < kPieces; ++c) load_v(none, 1, c);
   }
   finish_q();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -372,58 +402,60 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
     constexpr bool PATCH = decltype(patch_c)::value;
     // ---------------- first half: S(s) products, SiLU of keys 16..31 of s - 1
     bf16x8 kf[kPF + 1], vf[kPF + 1];                                    // fragments are fetched kPF slots ahead of their product
-    bf16x8 qx[kQLds];
+    bf16x8 qx[kQLds > 0 ? kQLds : 1];
 #pragma unroll
     for (int i = 0; i < kPF; ++i) kf[i] = kfn[i];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < 2 && !kNoDma) load_vd(vdesc0, P, i);
-      if (i >= 8 - kQLds - 2 && i < 8 - 2) qx[i - (8 - kQLds - 2)] = *(lds_b8)(uintptr_t)(uint32_t)(qaddr + (i - (8 - kQLds - 2)) * kThreads * 16);
-      if (i + kPF < 8) kf[(i + kPF) % (kPF + 1)] = kfrag(P, i + kPF);
-      else vf[(i + kPF - 8) % (kPF + 1)] = vfrag(P ^ 1, (i + kPF - 8) >> 2, (i + kPF - 8) & 3);
+    for (int i = 0; i < kSteps; ++i) {
+      if (i < kPieces && !kNoDma) load_vd(vdesc0, P, i);
+      if (kQLds > 0 && i >= kSteps - kQLds - 2 && i < kSteps - 2) qx[i - (kSteps - kQLds - 2)] = *(lds_b8)(uintptr_t)(uint32_t)(qaddr + (i - (kSteps - kQLds - 2)) * kThreads * 16);
+      if (i + kPF < kSteps) kf[(i + kPF) % (kPF + 1)] = kfrag(P, i + kPF);
+      else vf[(i + kPF - kSteps) % (kPF + 1)] = vfrag(P ^ 1, (i + kPF - kSteps) / kBlocks, (i + kPF - kSteps) % kBlocks);
       __builtin_amdgcn_sched_barrier(0);
-      sacc[P] = mfma(kf[i % (kPF + 1)], i < 8 - kQLds ? qf[i] : qx[i - (8 - kQLds)], sacc[P]);
+      sacc[P] = mfma(kf[i % (kPF + 1)], i < kSteps - kQLds ? qf[i] : qx[kQLds > 0 ? i - (kSteps - kQLds) : 0], sacc[P]);
       __builtin_amdgcn_sched_barrier(0);
-      {
-        const float pp = silu_roll(sacc[P ^ 1][8 + i]);                 // finishes the previous score (keys 16.. of s - 1, or key 15 of its first half)
-        if (i == 0) { plo[P ^ 1][3] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(plo[P ^ 1][3])); }
-        else if (i & 1) st_p = pp;
-        else { phi[(i - 1) >> 1] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(phi[(i - 1) >> 1])); }
+#pragma unroll
+      for (int e = i * W::kScores; e < (i + 1) * W::kScores; ++e) {
+        const float pp = silu_roll(sacc[P ^ 1][8 + e]);                 // finishes the previous score (keys 16.. of s - 1, or key 15 of its first half)
+        if (e == 0) { plo[P ^ 1][3] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(plo[P ^ 1][3])); }
+        else if (e & 1) st_p = pp;
+        else { phi[(e - 1) >> 1] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(phi[(e - 1) >> 1])); }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    asm volatile("s_waitcnt vmcnt(2)" ::: "memory");                    // K(s+1), strip(s+1) landed (V(s) may still fly)
+    wait_loads<kPieces>();                                              // K(s+1), strip(s+1) landed (V(s) may still fly)
     __syncthreads();
 
     // ---------------- second half: O += V(s-1)^T P(s-1), SiLU of keys 0..15 of s
     const int yt_seed = cur.yt;                                         // sub-block s + 1, seeded in this half
     cur = next_src(cur, s + 2);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (j == 4) {                                                     // (the last 8 scores of s - 1 went into P in the first half)
+    for (int j = 0; j < kSteps; ++j) {
+      if (j == kSteps / 2) {                                            // (the last 8 scores of s - 1 went into P in the first half)
         seed(sacc[P ^ 1], P ^ 1);
         if (PATCH) { if (s + 1 >= nfast && s + 1 < n) mask_seed(sacc[P ^ 1], yt_seed); }
       }
-      if (j < 2 && !kNoDma) load_k(cur, P, j);
-      else if (j == 2 && !kNoDma) load_strip(cur, P);
-      if (j + kPF < 8) vf[(j + kPF) % (kPF + 1)] = vfrag(P ^ 1, (j + kPF) >> 2, (j + kPF) & 3);
-      else kfn[j + kPF - 8] = kfrag(P ^ 1, j + kPF - 8);
+      if (j < kPieces && !kNoDma) load_k(cur, P, j);
+      if (j == (kPieces < kSteps ? kPieces : kSteps - 1) && !kNoDma) load_strip(cur, P);
+      if (j + kPF < kSteps) vf[(j + kPF) % (kPF + 1)] = vfrag(P ^ 1, (j + kPF) / kBlocks, (j + kPF) % kBlocks);
+      else kfn[j + kPF - kSteps] = kfrag(P ^ 1, j + kPF - kSteps);
       __builtin_amdgcn_sched_barrier(0);
       {
-        const uint32_t* pk = (j < 4) ? plo[P ^ 1] : phi;
+        const uint32_t* pk = (j < kBlocks) ? plo[P ^ 1] : phi;
         const bf16x8 pb = __builtin_bit_cast(bf16x8, (u32x4){pk[0], pk[1], pk[2], pk[3]});
-        out[j & 3] = mfma(vf[j % (kPF + 1)], pb, out[j & 3]);
+        out[j % kBlocks] = mfma(vf[j % (kPF + 1)], pb, out[j % kBlocks]);
       }
       __builtin_amdgcn_sched_barrier(0);
-      {
-        const float pp = silu_roll(sacc[P][j]);
-        if (j == 0) { phi[3] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(phi[3])); }
-        else if (j & 1) st_p = pp;
-        else { plo[P][(j - 1) >> 1] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(plo[P][(j - 1) >> 1])); }
+#pragma unroll
+      for (int e = j * W::kScores; e < (j + 1) * W::kScores; ++e) {
+        const float pp = silu_roll(sacc[P][e]);
+        if (e == 0) { phi[3] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(phi[3])); }
+        else if (e & 1) st_p = pp;
+        else { plo[P][(e - 1) >> 1] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(plo[P][(e - 1) >> 1])); }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    asm volatile("s_waitcnt vmcnt(3)" ::: "memory");                    // V(s) landed (only the 3 loads of this half may still fly)
+    wait_loads<kPieces + 1>();                                          // V(s) landed (only the loads of this half may still fly)
     __syncthreads();
     vdesc0 = vdesc1; vdesc1 = cur.v;
   };
@@ -434,12 +466,13 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
 #pragma unroll 1
     for (int s = 0; s <= n; ++s) {
       const int p = s & 1;
-      if (!kNoDma) { load_vd(vdesc0, p, 0); load_vd(vdesc0, p, 1); }
-      asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+      for (int c = 0; c < kPieces && !kNoDma; ++c) load_vd(vdesc0, p, c);
+      wait_loads<kPieces>();
       __syncthreads();
       cur = next_src(cur, s + 2);
-      if (!kNoDma) { load_k(cur, p, 0); load_k(cur, p, 1); load_strip(cur, p); }
-      asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+      for (int c = 0; c < kPieces && !kNoDma; ++c) load_k(cur, p, c);
+      if (!kNoDma) load_strip(cur, p);
+      wait_loads<kPieces + 1>();
       __syncthreads();
       vdesc0 = vdesc1; vdesc1 = cur.v;
     }
@@ -462,9 +495,9 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
 
   // ---- epilogue.  Lane x holds features 32 ob + 8 (r / 4) + 4 hf + r % 4.
   if (item.slot >= 0) {                                                 // a piece of a cut block: raw sums, finish_kernel adds them up
-    float* dst = a.partial + ((int64_t)item.slot * kBX + (wave * 32 + l32)) * kD;
+    float* dst = a.partial + ((int64_t)item.slot * kBX + (wave * 32 + l32)) * D;
 #pragma unroll
-    for (int ob = 0; ob < 4; ++ob)
+    for (int ob = 0; ob < kBlocks; ++ob)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
         *(f32x4*)(dst + ob * 32 + 8 * q4 + 4 * hf) =
@@ -476,7 +509,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
   const float scale = a.inv_n * kLn2;
   __bf16* dst = (__bf16*)a.out + (int64_t)(seq0 + x) * a.so + hoff;
 #pragma unroll
-  for (int ob = 0; ob < 4; ++ob)
+  for (int ob = 0; ob < kBlocks; ++ob)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       const int f = ob * 32 + 8 * q4 + 4 * hf;
@@ -491,15 +524,25 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_pipe_kernel(const AttnAr
 
 }  // namespace
 
+template <int D>
+static hipError_t launch_width(const AttnArgs& a, int grid, hipStream_t stream) {
+  const dim3 gd(grid), bd(kThreads);
+  if (a.num_targets) hipLaunchKernelGGL((attn_fwd_pipe_kernel<D, true>), gd, bd, Pipe<D>::kSmemBytes, stream, a);
+  else hipLaunchKernelGGL((attn_fwd_pipe_kernel<D, false>), gd, bd, Pipe<D>::kSmemBytes, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_fwd_pipe(const AttnArgs& a, hipStream_t stream) {
   const int per = kNumXcd * kXcdGroup;
   const int grid = (a.max_items + per - 1) / per * per;
   if (grid == 0) return hipSuccess;
   if (!a.seed) return hipErrorInvalidValue;
-  const dim3 gd(grid), bd(kThreads);
-  if (a.num_targets) hipLaunchKernelGGL((attn_fwd_pipe_kernel<true>), gd, bd, kSmemBytes, stream, a);
-  else hipLaunchKernelGGL((attn_fwd_pipe_kernel<false>), gd, bd, kSmemBytes, stream, a);
-  return hipGetLastError();
+  switch (a.D) {
+    case 32: return launch_width<32>(a, grid, stream);
+    case 64: return launch_width<64>(a, grid, stream);
+    case 128: return launch_width<128>(a, grid, stream);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace hstu
