@@ -27,7 +27,7 @@ inline int dbias_copies_for(const hstu_attn_params* p) {
 }
 
 struct Layout {           // byte offsets inside a workspace
-  size_t header[2], items[2], seq_base[2], bias, seed, splits, partial, splits_dq, partial_dq, dbias, ds_table, total;
+  size_t header[2], items[2], seq_base[2], bias, seed, seed_up, splits, partial, splits_dq, partial_dq, dbias, ds_table, total;
   size_t ds_bytes;        // room for dS that the backward can use behind `total`, or elsewhere; 0: none
   int max_items[2];
   int slot_cap;           // partial-sum slots of the dK/dV pass (key blocks cut along the query axis) or of the forward
@@ -84,7 +84,9 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
   l.bias = off + kBiasPad * sizeof(float);
   off += align_up(((size_t)p->num_heads * ((size_t)p->max_seqlen + 1 + kBiasPad) + kBiasPad) * sizeof(float));
   l.seed = off;                                        // score seeds by distance (bias + mask) of the pipelined kernels
-  off += align_up((size_t)kSeedVariants * p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float));
+  const size_t seed_bytes = align_up((size_t)kSeedVariants * p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float));
+  off += seed_bytes;
+  if (for_backward && p->dtype == HSTU_BF16 && p->head_dim != 128) { l.seed_up = off; off += seed_bytes; }
   if (!for_backward) {
     l.partial = off;
     off += align_up((size_t)l.slot_cap * fwd_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
@@ -162,18 +164,20 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   a.bias_pitch = a.bias_stride + kBiasPad;
   a.seed = nullptr;
   ex.table = p->rab_table; ex.bounds = p->rab_bounds; ex.num_buckets = p->num_buckets;
-  if (p->dtype == HSTU_BF16 && for_forward) {         // the pipelined forward takes bias and mask from the seed tables
-    ex.seed = (float*)(ws + l.seed);                                       // (that kernel needs no other table)
+  const bool seeded = p->dtype == HSTU_BF16 && (for_forward || p->head_dim != 128);
+  if (seeded) {                                        // these kernels take bias and mask from the seed tables
+    ex.seed = (float*)(ws + l.seed);
     ex.seed_len = seed_len_for(p->max_seqlen);
     ex.seed_dmax = seed_dmax_for(p->max_seqlen);
-    a.seed = ex.seed; a.seed_len = ex.seed_len; a.seed_dmax = ex.seed_dmax;
-    return ex;
+    if (!for_forward) ex.seed_up = (float*)(ws + l.seed_up);
+    a.seed = ex.seed; a.seed_up = ex.seed_up; a.seed_len = ex.seed_len; a.seed_dmax = ex.seed_dmax;
   }
   if (!p->rab_table) return ex;
-  ex.bias = (float*)(ws + l.bias);
   ex.bias_len = a.bias_stride;
-  ex.bias_pitch = a.bias_pitch;
-  a.bias = ex.bias;
+  if (!seeded) {
+    a.bias = ex.bias = (float*)(ws + l.bias);
+    ex.bias_pitch = a.bias_pitch;
+  }
   if (!for_forward && p->d_rab_table) {               // only the bias-table gradient needs the bucket ends and the sums per distance
     a.dbias_copies = dbias_copies_for(p);
     const int64_t n = (int64_t)a.dbias_copies * p->num_heads * a.bias_stride;

@@ -23,6 +23,7 @@
 // the second product.  The fp32 instantiation uses v_mfma_f32_32x32x2_f32 the same way.
 #include <type_traits>
 
+#include "dist_sums.h"
 #include "hstu_common.h"
 #include "hstu_kernels.h"
 
@@ -136,55 +137,6 @@ __device__ __forceinline__ float sigmoid_l2(float t) {           // sigmoid(t * 
 }
 // dS / dP = sigmoid (1 + s (1 - sigmoid)) = sigmoid + (t sigmoid) * ln2 (1 - sigmoid)
 __device__ __forceinline__ float dsilu_l2(float tp, float sig) { return fmaf(tp, fmaf(-kLn2, sig, kLn2), sig); }
-
-// Diagonal sums of a 32 x 32 block of dS, shared out over the wave.  Lane l32 of half-wave hf holds, in register R, the streamed row
-// 8 (R / 4) + 4 hf + R % 4 of the block; the sum over the pairs with (streamed row - lane row) = o lands at lane -o mod 64: part 0 of it,
-// plus part 1 of the lane 4 further (the upper half-wave's rows are 4 further).  The rotations shift zeros in, so that a value and what
-// comes around the end of a 16-lane row go to their sums without a select: two adds per register.
-template <int CTRL>
-__device__ __forceinline__ float dpp0(float v) {                         // the value DPP control CTRL brings, 0 where it brings none
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int R>
-__device__ __forceinline__ void key_diag_step(float v, float& x0, float& x1, float& x2) {
-  constexpr int q = R >> 2, rho = 8 * (q & 1) + (R & 3);
-  float& lo = (q >> 1) == 0 ? x0 : x1;
-  float& hi = (q >> 1) == 0 ? x1 : x2;
-  if constexpr (rho == 0) {
-    lo += v;
-  } else {
-    lo += dpp0<0x100 + rho>(v);                                          // row_shl: lane b of a row reads lane b + rho
-    hi += dpp0<0x110 + 16 - rho>(v);                                     // row_shr: ... lane b + rho - 16
-  }
-}
-// Sums of 16 registers over the 16 lanes of a row, handed out: lane i of a row leaves with the sum of register i.
-template <int CTRL, int HALF>
-__device__ __forceinline__ void row_fold(float (&v)[16], bool upper) {
-#pragma unroll
-  for (int r = 0; r < HALF; ++r) {
-    const float keep = upper ? v[r + HALF] : v[r], give = upper ? v[r] : v[r + HALF];
-    v[r] = keep + dpp0<CTRL>(give);
-  }
-}
-__device__ __forceinline__ float row_sums(float (&v)[16], int i16) {
-  row_fold<0x140, 8>(v, i16 & 8);                                        // row_mirror: lane ^ 15
-  row_fold<0x141, 4>(v, i16 & 4);                                        // row_half_mirror: lane ^ 7
-  row_fold<0x1B, 2>(v, i16 & 2);                                         // quad_perm: lane ^ 3
-  row_fold<0xB1, 1>(v, i16 & 1);                                         // quad_perm: lane ^ 1
-  return v[0];
-}
-template <int... R, typename V>
-__device__ __forceinline__ void key_diag_all(std::integer_sequence<int, R...>, const V& vals, float& part0, float& part1) {
-  float x0 = 0.f, x1 = 0.f, x2 = 0.f;
-  (key_diag_step<R>(vals[R], x0, x1, x2), ...);
-  // row g of a half-wave is 16 keys further: its class j meets class j - g of row 0
-  const uint32_t m = __builtin_bit_cast(uint32_t, x1);
-  x0 += __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_permlane16_swap(m, 0u, false, false)[1]);
-  x2 += __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_permlane16_swap(0u, m, false, false)[0]);
-  const auto parts = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x0), __builtin_bit_cast(uint32_t, x2), false, false);
-  part0 = __builtin_bit_cast(float, (uint32_t)parts[0]);                 // queries of the lower half-wave ...
-  part1 = __builtin_bit_cast(float, (uint32_t)parts[1]);                 // ... and of the upper one
-}
 
 // DBIAS (dQ pass, or the dK/dV pass that hands dS on): also sum dS per distance into a.dbias_dist[h, distance]; finish_kernel folds
 // distances into buckets afterwards.
@@ -469,86 +421,10 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       dma16(tile_rsrc(R2, rowb, x0 + 4 * rg), voff, dst);
     }
   }
-  // ---- bias gradient (DBIAS).  A 32 x 32 block of this wave, w0 = the distance of its first pair, holds the 63 distances around w0.
-  // Far from the diagonal they lie in one bucket of the table (the buckets of a log-spaced one are hundreds of distances wide there) and
-  // which distance of a bucket receives a sum does not matter: the block adds the plain sum of its dS, kept per lane until the
-  // bucket is left.  Any other block adds along its diagonals: lane l of `win` collects distance win_w0 + SGN * (l, or l - 64 for the upper
-  // half); the next block is 32 further, so the lower half of the window is complete then and leaves for the table of sums per
-  // distance, and the upper half becomes the lower one.  All of it stays in registers: strips in LDS with one read-add-write per class and
-  // half-wave, and a flush per tile by the workgroup, cost the dQ pass as much again as its products (64 features, 1024 + 256 semi-local,
-  // 8k-16k tokens: 0.31 ms without the gradient, 0.66 with it, 0.43 this way; 0.53 with one copy of the table for all dies).
+  // ---- bias gradient (dist_sums.h)
   constexpr int SGN = MODE == kBwdDKDV ? -1 : 1;           // distance = streamed row - lane row in the dK/dV pass, and the negative in the dQ pass
-  constexpr int kNoWindow = -(1 << 30);
-  constexpr int kLate = DBIAS && !DS ? NSB : 0;            // sums that leave at the start of the next tile: the wait for a tile's loads would wait for them
-  float win = 0.f, run_sum = 0.f, late[NSB];
-  int win_w0 = kNoWindow, run_end = 0, run_w0 = 0, late_w0[NSB];
-#pragma unroll
-  for (int u = 0; u < NSB; ++u) { late[u] = 0.f; late_w0[u] = kNoWindow; }
-  float* const dist_h = DBIAS ? a.dbias_dist + (int64_t)(xcd % a.dbias_copies * a.H + h) * a.bias_stride : nullptr;
-  auto win_out = [&](int w0, float v) {
-    // (the lane's number is made here: as a value that lives through the tile loop it would be spilled, and its reload wait for the tile's loads)
-    int l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    const uint32_t off = (uint32_t)(32 + SGN * ((int)((uint32_t)l << 26) >> 26));
-    if (v != 0.f && (uint32_t)(w0 - 32) + off < (uint32_t)a.bias_stride) atomicAdd(dist_h + (w0 - 32) + off, v);
-  };
-  auto win_flush = [&]() {
-    if (win_w0 != kNoWindow) win_out(win_w0, win);
-    win = 0.f;
-    win_w0 = kNoWindow;
-  };
-  auto run_flush = [&]() {
-    if (run_end != 0) {
-      float v = run_sum;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0 && v != 0.f) atomicAdd(dist_h + run_w0, v);
-    }
-    run_sum = 0.f;
-    run_end = 0;
-  };
-  auto late_out = [&]() {
-#pragma unroll
-    for (int u = 0; u < kLate; ++u) {
-      if (late_w0[u] != kNoWindow) win_out(late_w0[u], late[u]);
-      late_w0[u] = kNoWindow;
-    }
-  };
-  // the end of the bucket that holds all distances of a fully visible block of history rows, 0: they lie in several
-  auto one_bucket = [&](int w0) -> int {
-    const int end = ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.bucket_end)[w0 - 31];
-    return end > w0 + 31 ? end : 0;
-  };
-  // adds the 16 dS of this lane in sub-block `sub` of the tile; end: of one_bucket()
-  auto dist_sum = [&](const auto& vals, int sub, int w0, int end) {
-    if (end != 0) {
-      if (end != run_end) {                                // (distances are walked in order: a bucket that is left does not come back)
-        run_flush();
-        run_end = end;
-        run_w0 = w0 - 31;
-      }
-      float t0 = vals[0], t1 = vals[1];
-#pragma unroll
-      for (int r = 2; r < 16; r += 2) { t0 += vals[r]; t1 += vals[r + 1]; }
-      run_sum += t0 + t1;
-      return;
-    }
-    if (w0 == win_w0 - 32 * SGN) {
-      const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, win), 0u, false, false);
-      const float done = __builtin_bit_cast(float, (uint32_t)halves[0]);
-      if constexpr (kLate > 0) { late[sub] = done; late_w0[sub] = win_w0; } else win_out(win_w0, done);
-      win = __builtin_bit_cast(float, (uint32_t)halves[1]);
-    } else {
-      win_flush();
-    }
-    win_w0 = w0;
-    float part0, part1;
-    key_diag_all(std::make_integer_sequence<int, 16>{}, vals, part0, part1);
-    int l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    win += part0;
-    win += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * l + 16, __builtin_bit_cast(int, part1)));      // (of lane l + 4 mod 64)
-  };
+  DistSums<SGN, DBIAS && !DS ? NSB : 0> dist;
+  if constexpr (DBIAS) dist.init(a, xcd, h);
   set_next(t_begin < ntiles ? tr.at(t_begin) : 0, t_begin < ntiles);
   gload(0);
   finish_resident();
@@ -562,7 +438,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     const int stage = (t - t_begin) & 1;
     const bool has_next = t + 1 < ntiles;
     set_next(has_next ? tr.at(t + 1) : 0, has_next);
-    if constexpr (kLate > 0) late_out();
+    if constexpr (DBIAS && !DS) dist.late_out();
     const unsigned char* y1s = smem + stage * C::STAGE_BYTES;
     const unsigned char* y2s = y1s + C::TILE0;
     const int y0 = yt * C::BN;
@@ -685,7 +561,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (DBQ) {                                            // fully visible tile: history rows, distance x - y
-          dist_sum(dsf[0], 0, xw0 - y0, one_bucket(xw0 - y0));
+          dist.add(dsf[0], 0, xw0 - y0, dist.one_bucket(xw0 - y0));
         }
 #pragma unroll
         for (int i = 0; i < PF; ++i) fr[i] = trfrag(i);
@@ -702,7 +578,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (DBQ) {
-          dist_sum(dsf[1], 1, xw0 - y0 - 32, one_bucket(xw0 - y0 - 32));
+          dist.add(dsf[1], 1, xw0 - y0 - 32, dist.one_bucket(xw0 - y0 - 32));
         }
         done = true;
       }
@@ -721,7 +597,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
       const bool tile_hist_f = min(y0 + C::BN, L) - 1 < g.n;               // candidate queries take the general path
       if (kind == kTileFull && (!CANDK || tile_hist_f)) {
         int one_end = 0;
-        if constexpr (DBK) one_end = one_bucket(y0 - xw0);
+        if constexpr (DBK) one_end = dist.one_bucket(y0 - xw0);
         f32x16 sv, dp;
         if (bias_h) {
           const float* strip = (const float*)(smem + C::STRIP_BASE + stage * C::STRIP_BYTES) + strip_lane;
@@ -813,7 +689,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
           }
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (DBK) dist_sum(dp, 0, y0 - xw0, one_end);
+        if constexpr (DBK) dist.add(dp, 0, y0 - xw0, one_end);
         done = true;
       }
     }
@@ -999,10 +875,10 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             for (int r = 0; r < 16; ++r) cv[r] = x < g.n ? 0.f : c1[r];
             const float v = row_sums(cv, i16);
             const int y = y0 + sg * 32 + 8 * (i16 >> 2) + 4 * hf + (i16 & 3);
-            if (v != 0.f) atomicAdd(dist_h + max(g.n - y, 0), v);
+            if (v != 0.f) atomicAdd(dist.dist_h + max(g.n - y, 0), v);
           }
           const int w0 = xw0 - y0 - 32 * sg;
-          if (xw0 < g.n) dist_sum(hv, sg, w0, kind == kTileFull ? one_bucket(w0) : 0);
+          if (xw0 < g.n) dist.add(hv, sg, w0, kind == kTileFull ? dist.one_bucket(w0) : 0);
         }
         if constexpr (DBK) {
           // candidate queries stand at position n: one distance per key (their own key: distance 0)
@@ -1014,9 +890,9 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             float cand = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) cand += 8 * (r >> 2) + (r & 3) < nh ? 0.f : c1[r];
-            if (cand != 0.f) atomicAdd(dist_h + (x < g.n ? g.n - x : 0), cand);
+            if (cand != 0.f) atomicAdd(dist.dist_h + (x < g.n ? g.n - x : 0), cand);
           }
-          if (y0 < g.n) dist_sum(hv, 0, y0 - xw0, 0);
+          if (y0 < g.n) dist.add(hv, 0, y0 - xw0, 0);
         }
 
         // ---- second products: out^T[feature][x] += Y^T[feature][y] * coeff[y][x]
@@ -1081,7 +957,7 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     __syncthreads();
   }
 
-  if constexpr (DBIAS) { late_out(); win_flush(); run_flush(); }
+  if constexpr (DBIAS) dist.flush();
   HSTU_TLB(2);
   // ---- epilogue: scale once, convert, store.  Lane x holds features ob*32 + 8*(r/4) + 4*hf + r%4.
   {
@@ -1269,15 +1145,9 @@ static hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
 }
 
 template <int MODE, int NW_BF16, int NW_FP32, bool DBIAS = false, bool CAND = false>
-static hipError_t dispatch(const AttnArgs& a, int dtype, hipStream_t stream) {
+static hipError_t dispatch(const AttnArgs& a, int dtype, hipStream_t stream) {       // (bf16: the backward with 128 features)
   if (dtype == 0) {
-    if constexpr (MODE != kFwd) {                          // (the forward: attn_fwd_pipe.hip)
-      switch (a.D) {
-        case 32: return launch_one<__bf16, 32, MODE, NW_BF16, DBIAS, CAND>(a, stream);
-        case 64: return launch_one<__bf16, 64, MODE, NW_BF16, DBIAS, CAND>(a, stream);
-        case 128: return launch_one<__bf16, 128, MODE, NW_BF16, DBIAS, CAND>(a, stream);
-      }
-    }
+    if constexpr (MODE != kFwd) return launch_one<__bf16, 128, MODE, NW_BF16, DBIAS, CAND>(a, stream);
   } else {
     switch (a.D) {
       case 32: return launch_one<float, 32, MODE, NW_FP32, DBIAS, CAND>(a, stream);
@@ -1297,7 +1167,7 @@ static_assert(kFwdWavesBf16 * 32 == kBlockRows && kFwdWavesFp32 * 32 == kBlockRo
 int fwd_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kFwdWavesBf16 : kFwdWavesFp32); }
 int dq_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDqWavesBf16 : kDqWavesFp32); }
 int dkv_block_rows(int dtype, int) { return 32 * (dtype == 0 ? kDkvWavesBf16 : kDkvWavesFp32); }
-int stream_tile_rows(int dtype, int D) { return dtype == 0 && D != 64 ? 64 : 32; }
+int stream_tile_rows(int dtype, int D) { return dtype == 0 && D == 128 ? 64 : 32; }
 int fwd_tile_rows(int, int) { return 32; }
 int dkv_tile_rows(int, int) { return 32; }
 
@@ -1307,6 +1177,7 @@ hipError_t launch_attn_fwd(const AttnArgs& a, int dtype, hipStream_t stream) {
   return dispatch<kFwd, kFwdWavesBf16, kFwdWavesFp32>(a, dtype, stream);
 }
 hipError_t launch_attn_bwd_dq(const AttnArgs& a, int dtype, hipStream_t stream) {
+  if (dtype == 0 && a.D != 128) return launch_attn_bwd_narrow(a, false, stream);
   if (a.dbias_dist && a.num_targets) return dispatch<kBwdDQ, kDqWavesBf16, kDqWavesFp32, true, true>(a, dtype, stream);
   if (a.dbias_dist) return dispatch<kBwdDQ, kDqWavesBf16, kDqWavesFp32, true>(a, dtype, stream);
   if (a.num_targets) return dispatch<kBwdDQ, kDqWavesBf16, kDqWavesFp32, false, true>(a, dtype, stream);
@@ -1324,6 +1195,7 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream) {
 }
 
 hipError_t launch_attn_bwd_dkdv(const AttnArgs& a, int dtype, hipStream_t stream) {
+  if (dtype == 0 && a.D != 128) return launch_attn_bwd_narrow(a, true, stream);
   if (a.ds) {
     if (a.dbias_dist && a.num_targets) return launch_one<__bf16, 128, kBwdDKDV, kDkvWavesBf16, true, true, true>(a, stream);
     if (a.dbias_dist) return launch_one<__bf16, 128, kBwdDKDV, kDkvWavesBf16, true, false, true>(a, stream);

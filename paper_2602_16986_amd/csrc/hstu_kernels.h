@@ -69,6 +69,7 @@ struct AttnArgs {
   // semi-local mask) also has -1e30 for d >= K1.  seed_dmax >= max_seqlen + 128, seed_len >= seed_dmax + 1 + 192.
   const float* seed;
   int32_t seed_len, seed_dmax;
+  const float* seed_up;             // the same by ascending distance, seed_up[i] <-> d = i - kSeedUpZero (narrow backward: keys stationary)
   // Backward, bf16 with 128 features, optional: dS in bf16, handed from the dK/dV pass to the dQ product (attn_dq.hip says in
   // which layout).  ds_table[4 p ..]: of (sequence, key block) pair p of the dK/dV list: its first tile of 32 queries x 128 keys in
   // `ds` over all heads, the first query tile it visits, the number of them; pairs of sequence b start at ds_pair0[b], last block first.
@@ -83,7 +84,7 @@ struct AttnArgs {
 constexpr int kDsTileBytes = 32 * 128 * 2;
 constexpr int kBiasPad = 128;
 constexpr int kDbiasCopies = 8;          // one per die
-constexpr int kSeedVariants = 2;
+constexpr int kSeedVariants = 2, kSeedUpZero = 128;
 inline int seed_dmax_for(int max_seqlen) { return max_seqlen + 128; }
 inline int seed_len_for(int max_seqlen) { return (seed_dmax_for(max_seqlen) + 1 + 192 + 63) / 64 * 64; }
 
@@ -92,8 +93,9 @@ inline int seed_len_for(int max_seqlen) { return (seed_dmax_for(max_seqlen) + 1 
 struct ExpandJob {
   const float* table; const int32_t* bounds; int num_buckets;   // bias table [H, num_buckets] or nullptr
   float* bias; int bias_len, bias_pitch;                        // optional: AttnArgs::bias
-  int32_t* bucket_end;                                          // optional, with bias: [bias_len], the first distance of the next bucket
+  int32_t* bucket_end;                                          // optional: [bias_len], the first distance of the next bucket
   float* seed; int seed_len, seed_dmax;                         // optional: AttnArgs::seed (table may be nullptr: no bias)
+  float* seed_up;                                               // optional, with seed: AttnArgs::seed_up
   float* zero; int64_t zero_count;                              // optional: floats to clear
 };
 // Builds the work list of the forward for blocks of `block_rows` query rows against column tiles of `tile_cols`, and fills the
@@ -116,7 +118,7 @@ int stream_tile_rows(int dtype, int D);   // rows of one streamed LDS tile (dQ p
 int fwd_tile_rows(int dtype, int D);      // ... in the forward
 int dkv_tile_rows(int dtype, int D);      // ... in the dK/dV pass
 hipError_t launch_attn_fwd(const AttnArgs& a, int dtype, hipStream_t stream);
-// attn_fwd_pipe.hip: the forward for bf16 and 128 features per head (same work lists as launch_attn_fwd: 128-row blocks, 32-key tiles)
+// attn_fwd_pipe.hip: the forward for bf16 (same work lists as launch_attn_fwd: 128-row blocks, 32-key tiles)
 hipError_t launch_attn_fwd_pipe(const AttnArgs& a, hipStream_t stream);
 // hstu_attn_bwd for operands that are SiLU of pre-activations (bf16 only; pre_* [T, H, D] with row stride s_pre, all three
 // or none): dq, dk, dv leave as the gradients of the pre-activations.  ds: room for dS (256-byte aligned), or nullptr: what the workspace
@@ -125,6 +127,8 @@ int attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const void* 
                           const void* pre_k, const void* pre_v, int64_t s_pre, const void* dout, void* dq, void* dk, void* dv,
                           void* workspace, size_t workspace_bytes, void* ds, size_t ds_bytes, void* stream);
 hipError_t launch_attn_bwd_dq(const AttnArgs& a, int dtype, hipStream_t stream);
+// attn_bwd_narrow.hip: the dQ pass (key_blocks = false) or the dK/dV pass for bf16 and 32 or 64 features per head
+hipError_t launch_attn_bwd_narrow(const AttnArgs& a, bool key_blocks, hipStream_t stream);
 // attn_dq.hip: dQ from the dS that the dK/dV pass left in a.ds (bf16, 128 features; the work list of launch_attn_bwd_dq)
 hipError_t launch_attn_dq_from_ds(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_attn_bwd_dkdv(const AttnArgs& a, int dtype, hipStream_t stream);

@@ -388,7 +388,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
 //   bias[h, x] = log2(e) * table[h, bucket(x)], bucket(x) = max{c : bounds[c] <= x}, for x in [0, bias_len): the attention kernels
 //   keep their scores in units of ln 2; bucket_end[x]: where the next bucket starts;
 //   and the zeros around every head's row;
-//   seed[v][h][i] (AttnArgs::seed), d = seed_dmax - i;
+//   seed[v][h][i] (AttnArgs::seed), d = seed_dmax - i, and seed_up[v][h][i], d = i - kSeedUpZero;
 //   and clears the per-distance sums of the bias gradient.
 __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen, int id, int n) {
   auto bucket = [&](int x) {
@@ -399,9 +399,9 @@ __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen,
     }
     return lo;
   };
-  for (int x = id; j.bias && x < j.bias_len; x += n) {
+  for (int x = id; (j.bias || j.bucket_end) && x < j.bias_len; x += n) {
     const int c = bucket(x);
-    for (int h = 0; h < H; ++h) j.bias[(size_t)h * j.bias_pitch + x] = j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f;
+    for (int h = 0; j.bias && h < H; ++h) j.bias[(size_t)h * j.bias_pitch + x] = j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f;
     if (j.bucket_end) j.bucket_end[x] = c + 1 < j.num_buckets ? j.bounds[c + 1] : 0x7FFFFFFF;
   }
   for (int i = id; j.bias && i < (H + 1) * kBiasPad; i += n) j.bias[(int64_t)(i / kBiasPad) * j.bias_pitch - kBiasPad + i % kBiasPad] = 0.f;
@@ -412,6 +412,15 @@ __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen,
       const float b = j.table ? j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f : 0.f;
       j.seed[(size_t)h * j.seed_len + i] = d < 0 ? -1e30f : b;
       j.seed[((size_t)H + h) * j.seed_len + i] = (d < 0 || (K1 >= 0 && d >= K1)) ? -1e30f : b;
+    }
+  }
+  for (int i = id; j.seed_up && i < j.seed_len; i += n) {
+    const int d = i - kSeedUpZero;
+    const int c = j.table ? bucket(d < 0 ? 0 : (d > max_seqlen ? max_seqlen : d)) : 0;
+    for (int h = 0; h < H; ++h) {
+      const float b = j.table ? j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f : 0.f;
+      j.seed_up[(size_t)h * j.seed_len + i] = d < 0 ? -1e30f : b;
+      j.seed_up[((size_t)H + h) * j.seed_len + i] = (d < 0 || (K1 >= 0 && d >= K1)) ? -1e30f : b;
     }
   }
   for (int64_t i = id; i < j.zero_count; i += n) j.zero[i] = 0.f;
@@ -430,7 +439,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(const int32_t* 
 int log2_of(int n) { return 31 - __builtin_clz((unsigned)n); }
 
 hipError_t launch(const AttnArgs& a, int njobs, const SchedJob& j0, const SchedJob& j1, const ExpandJob& ex, hipStream_t stream) {
-  int64_t most = ex.bias ? ex.bias_len : 0;
+  int64_t most = ex.bias || ex.bucket_end ? ex.bias_len : 0;
   if (ex.seed && ex.seed_len > most) most = ex.seed_len;
   if (ex.zero_count / 4 > most) most = ex.zero_count / 4;
   int64_t blocks = (most + kSchedThreads - 1) / kSchedThreads;
