@@ -37,8 +37,8 @@ struct Layout {           // byte offsets inside a workspace
 // Slots for the pieces of cut key blocks: at most 768 (about 1.5 per workgroup slot of the chip), never more than
 // twice the number of key blocks, none without a mask that can make a key block long (dense causal and local-only
 // masks never have one block much longer than the rest of its sequence... they may still be cut when sequences differ
-// a lot in length, which the same bound covers).
-inline int slot_cap_for(int max_items) { return max_items < 384 ? 2 * max_items : 768; }
+// a lot in length, which the same bound covers).  fp32 blocks are cut more finely (cut_rule_for).
+inline int slot_cap_for(int max_items, bool fp32) { return std::min((fp32 ? 8 : 2) * max_items, 768); }
 
 // Sequences are shorter than 2^24 tokens: windows beyond 2^28 mean the same and keep the kernels' index sums inside int32.
 inline int window_of(int32_t w) { return w < 0 ? -1 : (w < (1 << 28) ? w : (1 << 28)); }
@@ -63,10 +63,10 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     // the dK/dV list also holds the pieces of cut key blocks; so does the forward list (query blocks longer than a
     // workgroup slot's share of the batch, or the few blocks of a query tail against long histories: their key axis is cut)
     if ((for_backward && s == 1) || !for_backward) {
-      l.slot_cap = slot_cap_for(l.max_items[s]);
+      l.slot_cap = slot_cap_for(l.max_items[s], p->dtype == HSTU_FP32);
       l.max_items[s] += l.slot_cap;
     } else {
-      l.slot_cap_dq = slot_cap_for(l.max_items[s]);
+      l.slot_cap_dq = slot_cap_for(l.max_items[s], p->dtype == HSTU_FP32);
       l.max_items[s] += l.slot_cap_dq;
     }
     l.header[s] = off; off += kAlign;
@@ -281,13 +281,15 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
   a.splits = (const SplitItem*)(ws + l.splits);
   a.partial = (float*)(ws + l.partial);
   // (a list is cut only where the launch that finishes cut blocks follows: lengths on the device may be longer than the host's copy says)
-  const bool may_cut = schedule_may_cut(plan_of(p), a.query_tail, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim));
+  const bool fp32 = p->dtype == HSTU_FP32;
+  const bool may_cut = schedule_may_cut(plan_of(p), a.query_tail, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), fp32,
+                                        p->head_dim);
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, true);
     ProfScope ps(p->reuse_schedule ? "bias_expand_fwd" : "schedule_fwd", stream);
     if (launch_schedule(a, !p->reuse_schedule, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim),
                         (SchedHeader*)(ws + l.header[0]), (WorkItem*)(ws + l.items[0]), (int32_t*)(ws + l.seq_base[0]),
-                        (SplitItem*)(ws + l.splits), may_cut ? l.slot_cap : 0, ex, stream) != hipSuccess)
+                        (SplitItem*)(ws + l.splits), may_cut ? l.slot_cap : 0, fp32, ex, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }
   {
@@ -344,7 +346,8 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   const int rows[2] = {dq_block_rows(p->dtype, p->head_dim), dkv_block_rows(p->dtype, p->head_dim)};
   const int cols[2] = {stream_tile_rows(p->dtype, p->head_dim), dkv_tile_rows(p->dtype, p->head_dim)};
   bool may_cut[2];                                       // as in the forward
-  for (int s = 0; s < 2; ++s) may_cut[s] = schedule_may_cut(plan_of(p), 0, 1 + s, rows[s], cols[s]);
+  const bool fp32 = p->dtype == HSTU_FP32;
+  for (int s = 0; s < 2; ++s) may_cut[s] = schedule_may_cut(plan_of(p), 0, 1 + s, rows[s], cols[s], fp32, p->head_dim);
   {
     const ExpandJob ex = prepare_bias(p, a, ws, l, false);
     ProfScope ps(p->reuse_schedule ? "bias_expand_bwd" : "schedule_bwd", stream);
@@ -354,7 +357,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
     SplitItem* const sp[2] = {(SplitItem*)(ws + l.splits_dq), (SplitItem*)(ws + l.splits)};
     const int caps[2] = {may_cut[0] ? l.slot_cap_dq : 0, may_cut[1] ? l.slot_cap : 0};
     // (the table of dS tiles goes with the lists, whether this call has room for dS or not: a later one that reuses them decides for itself)
-    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, l.ds_table ? (int32_t*)(ws + l.ds_table) : nullptr, ex,
+    if (launch_schedule_pair(a, !p->reuse_schedule, rows, cols, hd, it, sb, sp, caps, fp32, l.ds_table ? (int32_t*)(ws + l.ds_table) : nullptr, ex,
                              stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
   }

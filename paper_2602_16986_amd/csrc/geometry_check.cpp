@@ -96,7 +96,6 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
   if (ds > ds_tiles_bound(with)) return 2;
   if (ds > ds_tiles_bound(without)) return 3;
 
-  const int parts[3] = {kFwdTargetChunks, kDqTargetChunks, kTargetChunks};
   for (int which = 0; which < 3; ++which)
     for (int tile = 32; tile <= 64; tile += 32) {
       const int tail = which == 0 ? query_tail : 0;
@@ -111,11 +110,16 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
           most = imax(most, cost);
         }
       }
-      // the scheduler's first piece size; with a tail its share is the key blocks'
-      const double share = 1.0 / (tail > 0 ? kTargetChunks : parts[which]);
-      const int64_t chunk = std::max((int64_t)kMinChunk, (int64_t)std::ceil((double)all * share));
-      if (most > 2 * chunk && !schedule_may_cut(with, tail, which, 128, tile)) return 10 + which;
-      if (most > 2 * chunk && !schedule_may_cut(without, tail, which, 128, tile)) return 20 + which;
+      for (int rule_of = 0; rule_of < 4; ++rule_of) {      // bf16, and fp32 with 32, 64 and 128 features
+        const bool fp32 = rule_of > 0;
+        const int D = fp32 ? 16 << rule_of : 128;
+        const CutRule rule = cut_rule_for(fp32, D, which, tail > 0);
+        // the scheduler's first piece size
+        const int64_t chunk = std::max((int64_t)rule.min_chunk, (int64_t)std::ceil((double)all * (1.0 / rule.target_chunks)));
+        const bool cut = most > 2 * chunk && most > rule.longest_uncut;
+        if (cut && !schedule_may_cut(with, tail, which, 128, tile, fp32, D)) return 10 + which;
+        if (cut && !schedule_may_cut(without, tail, which, 128, tile, fp32, D)) return 20 + which;
+      }
     }
   return 0;
 }

@@ -102,12 +102,12 @@ struct ExpandJob {
 // tables of `ex`.  lists = false: the tables only.  Blocks much longer than the rest may be cut into pieces that leave
 // partial sums in `slot_cap` slots, listed in `splits`.
 hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
-                           int32_t* seq_base, SplitItem* splits, int slot_cap, const ExpandJob& ex, hipStream_t stream);
+                           int32_t* seq_base, SplitItem* splits, int slot_cap, bool fp32, const ExpandJob& ex, hipStream_t stream);
 // The two lists of the backward pass: [0] query blocks (dQ pass), [1] key blocks (dK/dV pass).  ds_table: AttnArgs::ds_table to fill
 // (with seq_base[1] as AttnArgs::ds_pair0), or nullptr; at most schedule_sorted_pairs() pairs then.
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], int32_t* ds_table, const ExpandJob& ex, hipStream_t stream);
+                                const int slot_cap[2], bool fp32, int32_t* ds_table, const ExpandJob& ex, hipStream_t stream);
 int schedule_sorted_pairs();              // lists of up to this many (sequence, block) pairs are sorted
 
 // attn_core.hip

@@ -13,6 +13,19 @@ constexpr int kTargetChunks = 2048;  // ... and, key blocks, of about 1/2048 of 
 constexpr int kFwdTargetChunks = 1536;   // forward lists: 2 x chunk = one slot's share when 768 workgroups are resident
 constexpr int kDqTargetChunks = 1024;    // dQ lists: the same with 512 resident workgroups
 
+// How a list is cut: blocks of more than 2 x chunk tiles are, into pieces of (at most twice) chunk = 1 / target of all tiles, at least
+// min_chunk; a list whose longest block has no more than longest_uncut tiles is not.  which: 0 forward, 1 dQ list, 2 dK/dV list; a forward over a query tail is cut like key blocks.
+// In fp32 a tile of 32 rows takes the matrix pipe 1-8 us (64 cycles an instruction, D / 2 of them for a 32 x 32 block of scores), up to
+// twice as long as the launch that adds pieces up, and such batches are small, so a block is worth cutting from a few tiles on; 256 workgroups
+// are resident (two per compute unit with 32 features).  Whole step, bf16's rule against this one: one sequence of 487 tokens, 7 heads of 128
+// features 500 -> 234 us, 4 heads of 64 238 -> 101; 900 tokens, 4 heads of 32 159 -> 86; 8 sequences of 400-1,000, 8 heads: 1-4 % less.  Up to 8 tiles of 32
+// features the extra launch costs what the pieces save.
+struct CutRule { int target_chunks, min_chunk, longest_uncut; };
+inline CutRule cut_rule_for(bool fp32, int head_dim, int which, bool query_tail) {
+  if (fp32) return head_dim == 32 ? CutRule{1024, 2, 8} : head_dim == 64 ? CutRule{512, 1, 2} : CutRule{512, 1, 2};
+  return {which == 2 || query_tail ? kTargetChunks : which == 1 ? kDqTargetChunks : kFwdTargetChunks, kMinChunk, 0};
+}
+
 struct PlanBatch {
   int batch, heads, total_tokens, max_seqlen;
   int K1, K2;                        // of SeqGeom, both below 2^28
@@ -46,13 +59,14 @@ inline int64_t ds_tiles_bound(const PlanBatch& p) {
 }
 
 // Most batches are cut nowhere, and a launch that would add up pieces costs 4.5 us for finding that out.  A block is cut
-// when it is longer than 2 x chunk, chunk >= kMinChunk and >= share x (all tiles).  The longest block is bounded by the longest
+// when it is longer than 2 x chunk, chunk >= min_chunk and >= share x (all tiles).  The longest block is bounded by the longest
 // sequence and the mask, the tiles from below by the visible pairs, which takes the lengths: without a host copy of the offsets
-// only kMinChunk counts, and so it does with candidates (their counts are known on the device only) or a query tail.
+// only min_chunk counts, and so it does with candidates (their counts are known on the device only) or a query tail.
 // which: 0 forward, 1 dQ list, 2 dK/dV list.  false: no list that the scheduler can build for this problem has a cut block.
-inline bool schedule_may_cut(const PlanBatch& p, int query_tail, int which, int block_rows, int tile_cols) {
+inline bool schedule_may_cut(const PlanBatch& p, int query_tail, int which, int block_rows, int tile_cols, bool fp32 = false, int head_dim = 128) {
   const bool key_major = which == 2, by_position = !p.candidates && query_tail == 0;
-  const double share = 1.0 / (which == 0 ? kFwdTargetChunks : which == 1 ? kDqTargetChunks : kTargetChunks);
+  const CutRule rule = cut_rule_for(fp32, head_dim, which, query_tail > 0);
+  const double share = 1.0 / rule.target_chunks;
   double longest = p.max_seqlen, pairs = 0.0;
   if (p.host_offsets) {
     longest = 0.0;
@@ -67,12 +81,12 @@ inline bool schedule_may_cut(const PlanBatch& p, int query_tail, int which, int 
     const double band = std::floor((double)(block_rows + p.K1) / tile_cols) + 2, prefix = key_major ? 0 : std::ceil((double)p.K2 / tile_cols);
     if (band + prefix < most) most = band + prefix;
   }
-  double chunk = kMinChunk;
+  double chunk = rule.min_chunk;
   if (by_position) {
     const double tiles = std::ceil(share * pairs * p.heads / ((double)block_rows * tile_cols) * (1 - 1e-9));
     if (tiles > chunk) chunk = tiles;
   }
-  return most > 2 * chunk;
+  return most > 2 * chunk && most > rule.longest_uncut;
 }
 
 }  // namespace hstu

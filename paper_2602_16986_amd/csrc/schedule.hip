@@ -45,7 +45,7 @@ struct SchedJob {
   int query_tail;                     // > 0 (query-major lists only): only the blocks that hold the last query_tail history rows or candidates
   int slot_cap;            // > 0: blocks much longer than the average may be cut along the streamed axis
   int even;                // cut blocks into equal pieces of at most 2 x chunk tiles (else: pieces of chunk tiles)
-  double share;            // chunk = this share of all scheduled tiles (at least kMinChunk)
+  CutRule rule;            // how they are
   SchedHeader* header;
   WorkItem* items;
   int32_t* seq_base;
@@ -237,7 +237,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   // doubles until the slots and the list fit; with a query tail (few blocks, most of them cut) it grows by a quarter once the slots are
   // short by a quarter or less: doubled there, most blocks are no longer than twice a piece and stay whole (16 sequences of 2,000-4,000
   // tokens, 4 heads of 32 features, tail 500: 91 us, 69 this way; n tiles in pieces of n / (slots - blocks), which always fit, 86).
-  int chunk = (int)fmin((double)0x3FFFFFFF, fmax((double)kMinChunk, ceil((double)all_tiles * job.share)));
+  int chunk = (int)fmin((double)0x3FFFFFFF, fmax((double)job.rule.min_chunk, ceil((double)all_tiles * (1.0 / job.rule.target_chunks))));
   // pieces of a block of `cost` tiles and their length: key-major lists take pieces of `chunk` tiles (a block of a global
   // prefix is hundreds of times longer than the rest); query-major lists, where the longest block is a few slot shares at
   // most, take the fewest equal pieces of at most 2 x chunk tiles (every piece costs a partial-sum slot and its traffic)
@@ -264,7 +264,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   int slot0 = 0, rank0 = 0, slots = 0, nsplit = 0, entries = pairs;        // first slot and rank of this thread's pairs among the cut ones; totals
   bool cuts = false;                                       // uniform: some block is cut
 #pragma unroll 1
-  for (int round = 0; job.slot_cap > 0 && max_cost > 2 * chunk; round ^= 1) {
+  for (int round = 0; job.slot_cap > 0 && max_cost > max(2 * chunk, job.rule.longest_uncut); round ^= 1) {
     int my_slots = 0, my_cuts = 0;
 #pragma unroll 1
     for (int idx = own0; idx < own1; ++idx) {
@@ -453,21 +453,20 @@ hipError_t launch(const AttnArgs& a, int njobs, const SchedJob& j0, const SchedJ
 }  // namespace
 
 hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
-                           int32_t* seq_base, SplitItem* splits, int slot_cap, const ExpandJob& ex, hipStream_t stream) {
+                           int32_t* seq_base, SplitItem* splits, int slot_cap, bool fp32, const ExpandJob& ex, hipStream_t stream) {
   // equal pieces of about one workgroup slot's share (768 slots at three workgroups per compute unit); the forward over a
   // query tail takes finer pieces (few blocks, each against a whole history)
   const bool even = a.query_tail == 0;
-  const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), 0, a.query_tail, slot_cap, even ? 1 : 0, 1.0 / (even ? kFwdTargetChunks : kTargetChunks),
-                        header, items, seq_base, splits, nullptr};
+  const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), 0, a.query_tail, slot_cap, even ? 1 : 0, cut_rule_for(fp32, a.D, 0, !even), header, items, seq_base, splits, nullptr};
   return launch(a, lists ? 1 : 0, job, job, ex, stream);
 }
 
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
-                                const int slot_cap[2], int32_t* ds_table, const ExpandJob& ex, hipStream_t stream) {
+                                const int slot_cap[2], bool fp32, int32_t* ds_table, const ExpandJob& ex, hipStream_t stream) {
   // dQ list (query-major): equal pieces of about one slot's share, 512 slots at two workgroups per compute unit
-  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, 1.0 / kDqTargetChunks, header[0], items[0], seq_base[0], splits[0], nullptr};
-  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, 1.0 / kTargetChunks, header[1], items[1], seq_base[1], splits[1], ds_table};
+  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, cut_rule_for(fp32, a.D, 1, false), header[0], items[0], seq_base[0], splits[0], nullptr};
+  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, cut_rule_for(fp32, a.D, 2, false), header[1], items[1], seq_base[1], splits[1], ds_table};
   return launch(a, lists ? 2 : 0, j0, j1, ex, stream);
 }
 
