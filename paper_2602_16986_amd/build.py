@@ -18,10 +18,14 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-ato
          # packed fp32 VALU forms are kept off on the test machines
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# The fp32 kernels need more than 256 registers, and the compiler then prefers accumulation registers for everything a matrix instruction
+# touches: a copy of every score each way, 66-112 registers more, and 146 spilled in the dK/dV pass with 128 features.
+FILE_FLAGS = {"attn_core.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
 
 def _compile(src: str, objdir: str, defines=()) -> str:
     obj = os.path.join(objdir, src.replace(".hip", ".o"))
-    cmd = ["hipcc", *FLAGS, *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = ["hipcc", *FLAGS, *FILE_FLAGS.get(src, []), *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stderr)

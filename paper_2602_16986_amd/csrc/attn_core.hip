@@ -57,7 +57,9 @@ struct Cfg {
   // dK/dV pass with 128 features: the accumulators alone take 128 registers per lane, so the V rows of the
   // workgroup's keys stay in LDS (not in registers) and the streamed tiles are 32 rows; that fits 256
   // registers and half the LDS, i.e. two workgroups per compute unit like the other passes.
-  static constexpr bool kStatLds = kBf16 && D == 128 && MODE == kBwdDKDV;
+  // (fp32 fits its 512 registers either way, 440 this way: 8 sequences of 400-1,000 tokens, 8 heads 203 -> 189 us, 2 of 60-130, 3 heads 31 -> 27.
+  // With the accumulation registers that the compiler prefers, see build.py, it spilled 146 of them: 554 us.)
+  static constexpr bool kStatLds = D == 128 && MODE == kBwdDKDV;
   // dQ pass with 64 features: 32-row tiles fit 168 registers and three workgroups per compute unit; 8 x 8k-16k semi-local 304 -> 290 us, short ragged histories 117 -> 108.
   // (32 features fit as many with 64-row tiles: 211 us against 233 with 32-row ones.)
   static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && D != 128 && MODE == kBwdDQ;
@@ -111,7 +113,7 @@ struct Cfg {
   static constexpr int STRIP_BYTES = 4 * SLEN * 4;
   static constexpr int STRIP_BASE = 2 * STAGE_BYTES;
   static constexpr int STAT_BASE = 2 * STAGE_BYTES + 2 * STRIP_BYTES;
-  static constexpr int STAT_BYTES = kStatLds ? BX * ROW_BYTES : 0;      // stationary operand 1, same swizzle as the tiles
+  static constexpr int STAT_BYTES = kStatLds ? BX * STRIDE1 : 0;        // stationary operand 1, laid out as the tiles are
   static constexpr int SMEM_BYTES = STAT_BASE + STAT_BYTES;             // 2 stages x (2 tensors + strip) [+ stationary rows]
 };
 
@@ -409,7 +411,16 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     }
   };
 
-  if constexpr (C::kStatLds) {
+  if constexpr (C::kStatLds && !C::kBf16) {
+    // lane x puts half of its row (hf) there; only this wave reads its rows back
+#pragma unroll 4
+    for (int c = 0; c < C::CPR / 2; ++c) {
+      const int chunk = hf * (C::CPR / 2) + c;
+      u32x4 raw = {0u, 0u, 0u, 0u};
+      if (x_ok) raw = *(const u32x4*)(R2 + (int64_t)x * sr2 + 4 * chunk);
+      *(u32x4*)(smem + C::STAT_BASE + (wave * 32 + l32) * C::STRIDE1 + 16 * chunk) = raw;
+    }
+  } else if constexpr (C::kStatLds) {
     // this wave's 32 stationary rows of operand 1 (V), straight to LDS; only this wave reads them back
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -765,7 +776,9 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
             const int roff = (sg * 32 + l32) * C::STRIDE0 + (2 * ks + hf) * 4;   // STRIDE0 == STRIDE1 in fp32
             sc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float*)(y1s + roff), res[0][ks], sc1, 0, 0, 0);
             if constexpr (MODE != kFwd)
-              sc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float*)(y2s + roff), res[1][ks], sc2, 0, 0, 0);
+              sc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                  *(const float*)(y2s + roff),
+                  C::kStatLds ? *(const float*)(smem + C::STAT_BASE + (wave * 32 + l32) * C::STRIDE1 + (2 * ks + hf) * 4) : res[C::NREG - 1][ks], sc2, 0, 0, 0);
           }
         }
 
