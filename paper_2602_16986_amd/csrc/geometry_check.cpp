@@ -100,13 +100,14 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
     for (int tile = 32; tile <= 64; tile += 32) {
       const int tail = which == 0 ? query_tail : 0;
       int64_t all = 0;
-      int most = 0;
+      int most = 0, blocks = 0;
       for (int b = 0; b < B; ++b) {
         const SeqGeom g = geom(b);
         for (int r0 = tail_origin(g.n, tail); r0 < g.L; r0 += 128) {
           const int r1 = imin(r0 + 128, g.L) - 1;
           const int cost = (which == 2 ? row_tile_ranges(g, r0, r1, tile) : tile_ranges(g, r0, r1, tile)).count();
           all += (int64_t)cost * H;
+          blocks += H;
           most = imax(most, cost);
         }
       }
@@ -116,7 +117,7 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
         const CutRule rule = cut_rule_for(fp32, D, which, tail > 0);
         // the scheduler's first piece size
         const int64_t chunk = std::max((int64_t)rule.min_chunk, (int64_t)std::ceil((double)all * (1.0 / rule.target_chunks)));
-        const bool cut = most > 2 * chunk && most > rule.longest_uncut;
+        const bool cut = most > 2 * chunk + rule.slack_of(blocks) && most > rule.longest_uncut;
         if (cut && !schedule_may_cut(with, tail, which, 128, tile, fp32, D)) return 10 + which;
         if (cut && !schedule_may_cut(without, tail, which, 128, tile, fp32, D)) return 20 + which;
       }

@@ -231,16 +231,15 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   const int max_cost = __builtin_amdgcn_readlane(row_max(sh.wave_total[2][col]), kSchedWaves - 1);
   const int64_t all_tiles = (int64_t)pair_tiles * H, all_dense = (int64_t)pair_dense * H;
 
-  // 3. Cut blocks that are much longer than a workgroup slot's share into pieces of `chunk` tiles (key-major
-  // lists: the few key blocks of a global prefix are seen by every query of their sequence).  Each piece
+  // 3. Cut blocks that are much longer than a workgroup slot's share (CutRule; the few key blocks of a global prefix are seen by
+  // every query of their sequence).  Each piece
   // becomes an entry of the list and accumulates into a partial-sum slot of its own (one per head).  The piece size
   // doubles until the slots and the list fit; with a query tail (few blocks, most of them cut) it grows by a quarter once the slots are
   // short by a quarter or less: doubled there, most blocks are no longer than twice a piece and stay whole (16 sequences of 2,000-4,000
   // tokens, 4 heads of 32 features, tail 500: 91 us, 69 this way; n tiles in pieces of n / (slots - blocks), which always fit, 86).
   int chunk = (int)fmin((double)0x3FFFFFFF, fmax((double)job.rule.min_chunk, ceil((double)all_tiles * (1.0 / job.rule.target_chunks))));
-  // pieces of a block of `cost` tiles and their length: key-major lists take pieces of `chunk` tiles (a block of a global
-  // prefix is hundreds of times longer than the rest); query-major lists, where the longest block is a few slot shares at
-  // most, take the fewest equal pieces of at most 2 x chunk tiles (every piece costs a partial-sum slot and its traffic)
+  // pieces of a block of `cost` tiles and their length: the fewest equal pieces of at most 2 x chunk tiles (every piece costs a
+  // partial-sum slot and its traffic), or pieces of `chunk` tiles
   auto pieces_of = [&](int cost, int& len) {
     len = cost;
     if (cost <= 2 * chunk) return 1;
@@ -263,8 +262,9 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   }
   int slot0 = 0, rank0 = 0, slots = 0, nsplit = 0, entries = pairs;        // first slot and rank of this thread's pairs among the cut ones; totals
   bool cuts = false;                                       // uniform: some block is cut
+  const bool wanted = job.slot_cap > 0 && max_cost > max(2 * chunk + job.rule.slack_of((long long)pairs * H), job.rule.longest_uncut);
 #pragma unroll 1
-  for (int round = 0; job.slot_cap > 0 && max_cost > max(2 * chunk, job.rule.longest_uncut); round ^= 1) {
+  for (int round = 0; wanted && max_cost > 2 * chunk; round ^= 1) {
     int my_slots = 0, my_cuts = 0;
 #pragma unroll 1
     for (int idx = own0; idx < own1; ++idx) {
@@ -466,7 +466,7 @@ hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_r
                                 const int slot_cap[2], bool fp32, int32_t* ds_table, const ExpandJob& ex, hipStream_t stream) {
   // dQ list (query-major): equal pieces of about one slot's share, 512 slots at two workgroups per compute unit
   const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, cut_rule_for(fp32, a.D, 1, false), header[0], items[0], seq_base[0], splits[0], nullptr};
-  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], 0, cut_rule_for(fp32, a.D, 2, false), header[1], items[1], seq_base[1], splits[1], ds_table};
+  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], fp32 ? 0 : 1, cut_rule_for(fp32, a.D, 2, false), header[1], items[1], seq_base[1], splits[1], ds_table};
   return launch(a, lists ? 2 : 0, j0, j1, ex, stream);
 }
 
