@@ -23,7 +23,7 @@ inline int64_t max_items_for(const hstu_attn_params* p, int block_rows) {
 
 // Copies of the sums per distance: one per die while they stay small (16 MB: clearing and adding them up takes a few microseconds).
 inline int dbias_copies_for(const hstu_attn_params* p) {
-  return (int64_t)kDbiasCopies * p->num_heads * ((int64_t)p->max_seqlen + 1) <= (int64_t)4 << 20 ? kDbiasCopies : 1;
+  return (int64_t)kDbiasCopies * p->num_heads * dbias_pitch_for(p->max_seqlen) <= (int64_t)4 << 20 ? kDbiasCopies : 1;
 }
 
 struct Layout {           // byte offsets inside a workspace
@@ -97,7 +97,7 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     l.partial_dq = off;
     off += align_up((size_t)l.slot_cap_dq * dq_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
     l.dbias = off;                                     // per-distance sums of dS for the bias-table gradient, then the bucket ends per distance
-    off += align_up((size_t)(dbias_copies_for(p) * p->num_heads + 1) * ((size_t)p->max_seqlen + 1) * sizeof(float));
+    off += align_up(((size_t)dbias_copies_for(p) * p->num_heads * dbias_pitch_for(p->max_seqlen) + p->max_seqlen + 1) * sizeof(float));
     const int64_t bytes = ds ? ds_tiles_bound(plan_of(p)) * kDsTileBytes : 0;
     if (bytes <= kDsMaxBytes) l.ds_bytes = (size_t)bytes;
   }
@@ -156,8 +156,8 @@ AttnArgs make_args(const hstu_attn_params* p, const void* q, const void* k, cons
   return a;
 }
 
-// Fills the bias fields of the kernel arguments and describes the tables behind them.
-ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws, const Layout& l, bool for_forward) {
+// Fills the bias fields of the kernel arguments and describes the tables behind them (lead: AttnArgs::dbias_lead).
+ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws, const Layout& l, bool for_forward, int lead) {
   ExpandJob ex = {};
   a.bias = nullptr;
   a.bias_stride = p->max_seqlen + 1;
@@ -180,7 +180,9 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   }
   if (!for_forward && p->d_rab_table) {               // only the bias-table gradient needs the bucket ends and the sums per distance
     a.dbias_copies = dbias_copies_for(p);
-    const int64_t n = (int64_t)a.dbias_copies * p->num_heads * a.bias_stride;
+    a.dbias_pitch = dbias_pitch_for(p->max_seqlen);
+    a.dbias_lead = lead;
+    const int64_t n = (int64_t)a.dbias_copies * p->num_heads * a.dbias_pitch;
     a.dbias_dist = ex.zero = (float*)(ws + l.dbias);
     ex.zero_count = n;
     a.bucket_end = ex.bucket_end = (int32_t*)(ws + l.dbias) + n;
@@ -285,7 +287,7 @@ int hstu_attn_fwd(const hstu_attn_params* p, const void* q, const void* k, const
   const bool may_cut = schedule_may_cut(plan_of(p), a.query_tail, 0, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim), fp32,
                                         p->head_dim);
   {
-    const ExpandJob ex = prepare_bias(p, a, ws, l, true);
+    const ExpandJob ex = prepare_bias(p, a, ws, l, true, 0);
     ProfScope ps(p->reuse_schedule ? "bias_expand_fwd" : "schedule_fwd", stream);
     if (launch_schedule(a, !p->reuse_schedule, fwd_block_rows(p->dtype, p->head_dim), fwd_tile_rows(p->dtype, p->head_dim),
                         (SchedHeader*)(ws + l.header[0]), (WorkItem*)(ws + l.items[0]), (int32_t*)(ws + l.seq_base[0]),
@@ -349,7 +351,7 @@ int hstu::attn_bwd_through_silu(const hstu_attn_params* p, const void* q, const 
   const bool fp32 = p->dtype == HSTU_FP32;
   for (int s = 0; s < 2; ++s) may_cut[s] = schedule_may_cut(plan_of(p), 0, 1 + s, rows[s], cols[s], fp32, p->head_dim);
   {
-    const ExpandJob ex = prepare_bias(p, a, ws, l, false);
+    const ExpandJob ex = prepare_bias(p, a, ws, l, false, through_ds ? kDbiasLead : 0);
     ProfScope ps(p->reuse_schedule ? "bias_expand_bwd" : "schedule_bwd", stream);
     SchedHeader* const hd[2] = {(SchedHeader*)(ws + l.header[0]), (SchedHeader*)(ws + l.header[1])};
     WorkItem* const it[2] = {(WorkItem*)(ws + l.items[0]), (WorkItem*)(ws + l.items[1])};

@@ -1103,12 +1103,12 @@ __device__ void dbias_unit(const AttnArgs& a, const DbiasJob& job, int c, int h)
   __shared__ float red[kFinishThreads / 64];
   const int len = a.bias_stride, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lo = min(job.bounds[c], len), hi = c + 1 < job.num_buckets ? min(job.bounds[c + 1], len) : len;
-  const float* dist = a.dbias_dist + (size_t)h * len;
+  const float* dist = a.dbias_dist + (size_t)h * a.dbias_pitch + a.dbias_lead;
   float acc = 0.f;
   for (int x = lo + (int)threadIdx.x; x < hi; x += kFinishThreads) {
     float v[kDbiasCopies];
 #pragma unroll
-    for (int c8 = 0; c8 < kDbiasCopies; ++c8) v[c8] = c8 < a.dbias_copies ? dist[(size_t)c8 * a.H * len + x] : 0.f;
+    for (int c8 = 0; c8 < kDbiasCopies; ++c8) v[c8] = c8 < a.dbias_copies ? dist[(size_t)c8 * a.H * a.dbias_pitch + x] : 0.f;
 #pragma unroll
     for (int c8 = 0; c8 < kDbiasCopies; ++c8) acc += v[c8];
   }

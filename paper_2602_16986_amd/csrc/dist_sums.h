@@ -83,7 +83,7 @@ struct DistSums {
     run_end = run_w0 = 0;
 #pragma unroll
     for (int u = 0; u < kLate; ++u) { late[u] = 0.f; late_w0[u] = kNoWindow; }
-    dist_h = a.dbias_dist + (int64_t)(xcd % a.dbias_copies * a.H + h) * a.bias_stride;
+    dist_h = a.dbias_dist + (int64_t)(xcd % a.dbias_copies * a.H + h) * a.dbias_pitch + a.dbias_lead;
     bucket_end = a.bucket_end;
     stride = (uint32_t)a.bias_stride;
   }

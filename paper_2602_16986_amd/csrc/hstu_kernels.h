@@ -54,10 +54,11 @@ struct AttnArgs {
   float* partial;                   // dK/dV pass: fp32 partial sums [slot][dK, dV][block row][D] of cut key blocks
   const SplitItem* splits;
   int32_t query_tail;               // forward only, > 0: compute only the last query_tail history rows and the candidates of every sequence
-  // backward, optional: sums of dS per distance [dbias_copies][H, bias_stride] (zeroed by the caller), the workgroups of a die adding to
-  // one copy: with one copy for the chip the dies take turns at a few hundred lines
+  // backward, optional: sums of dS per distance [dbias_copies][H][dbias_pitch] (zeroed by the caller), that of distance d at dbias_lead + d, the
+  // workgroups of a die adding to one copy: with one copy for the chip the dies take turns at a few hundred lines.  Pitch and lead put the 32 distances
+  // that leave a wave at once into one 128-byte line.
   float* dbias_dist;
-  int32_t dbias_copies;
+  int32_t dbias_copies, dbias_pitch, dbias_lead;
   // optional (bf16 backward): q, k, v = SiLU(pre_q / pre_k / pre_v) [T, H, D] with row stride s_pre; dq, dk, dv then leave
   // as the gradients of those pre-activations (multiplied by SiLU' on the way out)
   const void* pre_q; const void* pre_k; const void* pre_v; int64_t s_pre;
@@ -83,6 +84,8 @@ struct AttnArgs {
 };
 constexpr int kDsTileBytes = 32 * 128 * 2;
 constexpr int kBiasPad = 128;
+constexpr int kDbiasLead = 31;           // of the dK/dV pass, whose sums leave for distances 32 k - 31 .. 32 k; the dQ pass has 32 k .. 32 k + 31
+inline int dbias_pitch_for(int max_seqlen) { return (max_seqlen + 1 + kDbiasLead + 31) / 32 * 32; }
 constexpr int kDbiasCopies = 8;          // one per die
 constexpr int kSeedVariants = 2, kSeedUpZero = 128;
 inline int seed_dmax_for(int max_seqlen) { return max_seqlen + 128; }
