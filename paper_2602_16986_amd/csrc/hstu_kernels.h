@@ -56,7 +56,8 @@ struct AttnArgs {
   int32_t query_tail;               // forward only, > 0: compute only the last query_tail history rows and the candidates of every sequence
   // backward, optional: sums of dS per distance [dbias_copies][H][dbias_pitch] (zeroed by the caller), that of distance d at dbias_lead + d, the
   // workgroups of a die adding to one copy: with one copy for the chip the dies take turns at a few hundred lines.  Pitch and lead put the 32 distances
-  // that leave a wave at once into one 128-byte line.
+  // that leave a wave at once into one 128-byte line (with rows of bias_stride floats mostly two, which other waves add to as well: dQ pass with
+  // 64 features, 8k-16k semi-local 368 -> 334 us).
   float* dbias_dist;
   int32_t dbias_copies, dbias_pitch, dbias_lead;
   // optional (bf16 backward): q, k, v = SiLU(pre_q / pre_k / pre_v) [T, H, D] with row stride s_pre; dq, dk, dv then leave
