@@ -60,35 +60,25 @@ struct Cfg {
   // (fp32 fits its 512 registers either way, 440 this way: 8 sequences of 400-1,000 tokens, 8 heads 203 -> 189 us, 2 of 60-130, 3 heads 31 -> 27.
   // With the accumulation registers that the compiler prefers, see build.py, it spilled 146 of them: 554 us.)
   static constexpr bool kStatLds = D == 128 && MODE == kBwdDKDV;
-  // dQ pass with 64 features: 32-row tiles fit 168 registers and three workgroups per compute unit; 8 x 8k-16k semi-local 304 -> 290 us, short ragged histories 117 -> 108.
-  // (32 features fit as many with 64-row tiles: 211 us against 233 with 32-row ones.)
-  static constexpr bool kThreePerCu = kBf16 && NWAVES == 4 && D != 128 && MODE == kBwdDQ;
-  // dK/dV pass: 32-row tiles for every width.  With 64 features a 64-row tile took more than 256 registers, one workgroup per compute
-  // unit: 8 x 8k-16k dense 2.49 ms, 1.85 when made to fit (29 registers spilled), 1.54 with 32-row tiles; 32 features 0.29 -> 0.23 semi-local.
-  static constexpr int BN = kBf16 ? ((MODE == kBwdDKDV || D == 64) ? 32 : 64) : 32;  // streamed rows per LDS tile
+  static constexpr int BN = kBf16 && MODE != kBwdDKDV ? 64 : 32;  // streamed rows per LDS tile
   static constexpr int NT = 64 * NWAVES;
   static constexpr int ROW_BYTES = D * (int)sizeof(E);
   // LDS tiles are read two ways: 16-byte reads with one streamed row per lane (score products)
   // and transpose reads that touch 4 consecutive rows x 64 bytes per 32 lanes (second products).
-  //   tensor 0 (Y1): K in the forward (rows only), K in the dQ pass and Q in the dK/dV pass (both ways)
-  //   tensor 1 (Y2): V in the forward (transposed only), V in the dQ pass (rows only), dO in dK/dV (both)
+  //   tensor 0 (Y1): K in the dQ pass and Q in the dK/dV pass (both ways)
+  //   tensor 1 (Y2): V in the dQ pass (rows only), dO in dK/dV (both)
   // 256-byte bf16 rows are unpadded and store the 16-byte chunks of row r at chunk ^ swz(r),
   // swz(r) = 4*(r%4) + (r/4)%4: 16 consecutive rows then map one logical chunk to 16 different bank
   // groups, and 4 consecutive rows map 4 consecutive chunks to 16 different ones, so both ways of
   // reading are conflict-free.  Such tiles travel from global memory straight into LDS (no register
   // staging): a wave-level 16-byte load places its 64 lanes in 1 KB of consecutive LDS, and each lane
-  // applies the swizzle to its global address instead.  Narrower rows and fp32 are staged through
-  // registers into padded rows: the padding that makes the way(s) a tile is read conflict-free
-  // (16 bytes for row-per-lane reads, 64 for transpose reads, 80 for both).
-  static constexpr bool kBoth0 = MODE != kFwd, kBoth1 = MODE == kBwdDKDV;
-  static constexpr bool kDma = kBf16 && D == 128;
-  static constexpr bool kSwz0 = kDma, kSwz1 = kDma;
+  // applies the swizzle to its global address instead.  fp32 rows are staged through registers into rows padded by 16 bytes.
+  static_assert(!kBf16 || (D == 128 && MODE != kFwd), "the other bf16 kernels: attn_fwd_pipe.hip, attn_bwd_narrow.hip");
+  static constexpr bool kDma = kBf16, kSwz0 = kDma, kSwz1 = kDma;
   // 4-wave bf16 workgroups run two per compute unit (two independent instruction streams per SIMD):
   // 256 registers per lane and half of the 160 KB of LDS each.
-  static constexpr bool kTwoPerCu = kBf16 && NWAVES == 4;
-  static constexpr int kWgPerCu = kThreePerCu ? 3 : (kTwoPerCu ? 2 : 1);
-  static constexpr int PAD0 = !kBf16 ? 16 : (kSwz0 ? 0 : (kBoth0 ? 80 : 16));
-  static constexpr int PAD1 = !kBf16 ? 16 : (kSwz1 ? 0 : (kBoth1 ? 80 : 16));
+  static constexpr int kWgPerCu = kBf16 && NWAVES == 4 ? 2 : 1;
+  static constexpr int PAD0 = kBf16 ? 0 : 16, PAD1 = PAD0;
   static constexpr int STRIDE0 = ROW_BYTES + PAD0, STRIDE1 = ROW_BYTES + PAD1;   // LDS row strides, bytes
   static constexpr int TILE0 = BN * STRIDE0, TILE1 = BN * STRIDE1;
   static constexpr int STAGE_BYTES = TILE0 + TILE1;
@@ -488,30 +478,13 @@ __global__ __launch_bounds__(64 * NWAVES, (Cfg<E, D, MODE, NWAVES>::kWgPerCu)) v
     typedef __attribute__((address_space(3))) const bf16x8* lds_b8;
     // row fragment (A operand of a score product): tensor, 32-row sub-block, k-step
     auto rowfrag_at = [&](int tensor, int sub, int ks) -> bf16x8 {
-      if constexpr (C::kDma) {
-        return *(lds_b8)(uintptr_t)(uint32_t)((kb ^ (ks << 5)) + sub * 8192 + tensor * C::TILE0);
-      } else {
-        return tensor == 0 ? *(const bf16x8*)(y1s + lds_off<C, 0>(sub * 32 + l32, 2 * ks + hf))
-                           : *(const bf16x8*)(y2s + lds_off<C, 1>(sub * 32 + l32, 2 * ks + hf));
-      }
+      return *(lds_b8)(uintptr_t)(uint32_t)((kb ^ (ks << 5)) + sub * 8192 + tensor * C::TILE0);
     };
     // transposed fragment (A operand of an output product): tensor, sub-block, 16-row k-step, feature block
     auto trfrag_at = [&](int tensor, int sub, int ks2, int ob) -> bf16x8 {
-      short4v lo, hi;
-      if constexpr (C::kDma) {
-        const int roff = (sub * 32 + ks2 * 16) * 256 + tensor * C::TILE0;
-        lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)((tb ^ (ob << 6)) + roff));
-        hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)((tb ^ ((ob << 6) | 32)) + roff + 2048));
-      } else {
-        const int trow = sub * 32 + ks2 * 16 + 4 * hf + (i16 >> 2);
-        if (tensor == 0) {
-          lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(y1s + lds_off<C, 0>(trow, 4 * ob + vchunk) + vbyte));
-          hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(y1s + lds_off<C, 0>(trow + 8, 4 * ob + vchunk) + vbyte));
-        } else {
-          lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(y2s + lds_off<C, 1>(trow, 4 * ob + vchunk) + vbyte));
-          hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(y2s + lds_off<C, 1>(trow + 8, 4 * ob + vchunk) + vbyte));
-        }
-      }
+      const int roff = (sub * 32 + ks2 * 16) * 256 + tensor * C::TILE0;
+      const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)((tb ^ (ob << 6)) + roff));
+      const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(uint32_t)((tb ^ ((ob << 6) | 32)) + roff + 2048));
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
 
