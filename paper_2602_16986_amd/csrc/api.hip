@@ -86,7 +86,7 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
   l.seed = off;                                        // score seeds by distance (bias + mask) of the pipelined kernels
   const size_t seed_bytes = align_up((size_t)kSeedVariants * p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float));
   off += seed_bytes;
-  if (for_backward && p->dtype == HSTU_BF16 && p->head_dim != 128) { l.seed_up = off; off += seed_bytes; }
+  if (for_backward && p->dtype == HSTU_BF16 && p->head_dim != 128) { l.seed_up = off; off += align_up((size_t)p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float)); }
   if (!for_backward) {
     l.partial = off;
     off += align_up((size_t)l.slot_cap * fwd_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));

@@ -7,9 +7,12 @@
 //   step s, first half:   S(s) = Y1(s) R1^T, dP(s) = Y2(s) R2^T        |  pointwise work of streamed rows 16..31 of tile s - 1
 //   step s, second half:  output products of tile s - 1                |  pointwise work of streamed rows 0..15 of tile s
 // (dQ pass: R = Q, dO, Y = K, V, output dQ += K^T dS; dK/dV pass: R = K, V, Y = Q, dO, outputs dV += dO^T P, dK += Q^T dS.)
-// The mask costs nothing in the loop, as in attn_fwd_pipe.hip: scores are seeded with bias and mask as a function of the distance, and
-// a score that starts at -1e30 leaves P = -0 and dS / dP = 0.  The dK/dV pass takes the seeds in ascending order.  Tiles whose mask is not a
-// function of the distance (candidate rows; the end of the global prefix) are patched element by element in a second copy of the loop.
+// Scores are seeded with the bias as a function of the distance, the dK/dV pass takes the seeds in ascending order; candidates, which stand
+// at one position, are seeded element by element in a second copy of the loop.  A tile that holds only pairs that the wave's rows may see
+// goes through as it is; in any other the score and dP of masked pairs are replaced between the halves (-1e30 leaves P = -0 and
+// dS / dP = 0), whatever their rows held, and the output products of a tile with no visible pair read zeros instead of its rows: rows that
+// are not finite stay with the tokens that may see them.  (Against a mask in the seeds, which needs finite rows: 8 x 8k-16k, 64 features, semi-local
+// 639 -> 650 us, dense 2,695 -> 2,712; 24 x 1-3,000 semi-local 173 -> 179.)
 //
 // Tiles and seed strips are loaded straight to LDS three steps ahead: those of step s + 3 are issued in step s, have landed and are published
 // at the end of step s + 1, and the first fragments are read at the end of step s + 2; the output products read tile s - 1: five stages.
@@ -29,7 +32,7 @@ constexpr int kStages = 5, kStripStages = 4;
 constexpr int kStripCopy = 1088, kStripBytes = 4 * kStripCopy;         // as in attn_fwd_pipe.hip
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 constexpr float kMasked = -1e30f;
-constexpr int kNoTile = 1 << 28;
+constexpr int kNoTile = 1 << 25;                                        // (beyond any tile, and its first row still an int)
 
 template <int D, int MODE>
 struct Narrow {
@@ -40,7 +43,7 @@ struct Narrow {
   static constexpr int kRowsPer = 1024 / kRow;                                            // rows that one wave-level load brings
   static constexpr bool kSplit = D == 32;              // waves 0 and 1 load Y1, 2 and 3 load Y2 (else every wave 8 rows of each)
   static constexpr int kLoads = kSplit ? 2 : 3;        // per wave and step
-  static constexpr int kStripBase = kStages * kStage, kSmemBytes = kStripBase + kStripStages * kStripBytes;
+  static constexpr int kZero = kStages * kStage, kStripBase = kZero + kOut * kTile, kSmemBytes = kStripBase + kStripStages * kStripBytes;
   static __device__ __forceinline__ int swizzle(int r) { return D == 64 ? 4 * ((r >> 1) & 1) + ((r >> 2) & 3) : (r >> 2) & 3; }   // as Pipe::swizzle
 };
 
@@ -112,42 +115,25 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
 #pragma unroll
       for (int r = 0; r < 16; ++r) out[o][ob][r] = 0.f;
 
-  // ---- the item's tiles, those that need a patch last
+  // ---- the item's tiles; those with a candidate's row are the last ones
   const int xlast = min(x0 + kBX, L) - 1;
   const TileRanges tr = MODE == kDQ ? tile_ranges(g, x0, xlast, kBN) : row_tile_ranges(g, x0, xlast, kBN);
   const int t_begin = item.t0, t_end = max(min(tr.count(), item.t1), item.t0), n = t_end - t_begin;
   const int na = tr.a1 - tr.a0, nb = tr.b1 - tr.b0, nc = tr.c1 - tr.c0;
   const int cand_t0 = (CAND && g.n < L) ? g.n / kBN : kNoTile;         // first tile with a candidate's row
   const int pc = min(max(cand_t0 - tr.a0, 0), na) + min(max(cand_t0 - tr.b0, 0), nb) + min(max(cand_t0 - tr.c0, 0), nc);
-  const int suf0 = min(max(pc, t_begin), t_end);
-  // dQ pass: the key tile that holds the end of the prefix goes to the end of the list; dK/dV pass: a block that holds it patches every tile
+  const int nfast = min(max(pc, t_begin), t_end) - t_begin;
+  auto tile_of = [&](int idx) -> int { return tr.at(t_begin + idx); };
+  const WaveTiles tiles = MODE == kDQ ? key_tiles_of(g, xw0) : query_tiles_of(g, xw0);
   const bool band = g.K1 >= 0;
-  const bool cross = MODE == kDKDV && band && x0 < g.K2 && g.K2 < x0 + kBX;
-  const int straddle_t = (MODE == kDQ && band && (g.K2 % kBN) != 0) ? g.K2 / kBN : -1;
-  const int ps_raw = straddle_t - tr.a0;
-  const bool has_ps = straddle_t >= tr.a0 && straddle_t < tr.a1 && ps_raw >= t_begin && ps_raw < suf0;
-  const int ps = has_ps ? ps_raw : kNoTile;
-  const int nfast = cross ? 0 : (suf0 - t_begin) - (has_ps ? 1 : 0);
-  auto tile_of = [&](int idx) -> int {
-    if (MODE == kDKDV) return tr.at(t_begin + idx);
-    int p;
-    const int nplain = (suf0 - t_begin) - (has_ps ? 1 : 0);
-    if (idx < nplain) { p = t_begin + idx; p += (p >= ps) ? 1 : 0; }
-    else { const int j = idx - nplain; p = (suf0 + j < t_end) ? suf0 + j : ps_raw; }
-    return tr.at(p);
-  };
 
   // ---- seeds
   const int px = (MODE == kDQ && CAND) ? min(x, g.n) : x, x0v = (MODE == kDQ && CAND) ? min(x0, g.n) : x0;
   const int strip_s0 = kBX - 1 - (px - x0v) + 4 * hf;
   const float* seed_h = (MODE == kDQ ? a.seed : a.seed_up) + (int64_t)h * a.seed_len;
   const int seed0 = MODE == kDQ ? a.seed_dmax : kSeedUpZero;            // index of distance 0
-  const int64_t seed_var1 = (int64_t)a.H * a.seed_len;
-  // dK/dV pass: one table per block (keys of the prefix are not subject to the window); dQ pass: band tiles take the second one
-  const bool block_band = MODE == kDKDV && band && x0 >= g.K2;
   const float bias0 = CAND ? seed_h[seed0] : 0.f;                       // a candidate's own pair
-  float cand_seed = kMasked;                                            // dK/dV pass: of this lane's key for the candidates, all at position n
-  if (CAND && MODE == kDKDV && x < g.n && (!band || g.n - x < g.K1 || x < g.K2)) cand_seed = seed_h[seed0 + g.n - x];
+  const float cand_seed = CAND && MODE == kDKDV && x < g.n ? seed_h[seed0 + g.n - x] : 0.f;      // of this lane's key for the candidates, all at position n
 
   // ---- global -> LDS
   const bool second = W::kSplit && wave >= 2;
@@ -171,7 +157,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(voff), "s"(rs) : "memory", "m0");
   };
   // where a tile sits; one beyond the list has empty ranges (its loads are still issued: the waits count loads)
-  struct Src { uint64_t a1, a2; int left; uint64_t seed; uint32_t s_off; int yt; };
+  struct Src { uint64_t a1, a2; int left; uint32_t s_off; int yt; };
   auto src_of = [&](int idx) -> Src {
     const bool valid = idx < n;
     const int yt = valid ? tile_of(idx) : 0;
@@ -180,8 +166,6 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     r.a1 = base1 + (uint64_t)(uint32_t)yrow * rowb1;
     r.a2 = base2 + (uint64_t)(uint32_t)yrow * rowb2;
     r.left = valid ? L - yrow : -kNoTile;
-    const bool v1 = MODE == kDQ ? band && yt >= tr.b0 && yt < tr.b1 : block_band;
-    r.seed = (uint64_t)(uintptr_t)(seed_h + (v1 ? seed_var1 : 0));
     // strip index s: distance x0v + kBX - 1 - y0 - s (dQ pass), y0 - x0 - (kBX - 1) + s (dK/dV pass)
     r.s_off = 4u * (uint32_t)(MODE == kDQ ? seed0 - (x0v + (kBX - 1) - yt * kBN) : seed0 + yt * kBN - x0 - (kBX - 1));
     r.yt = valid ? yt : kNoTile;
@@ -189,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
   };
   auto next_src = [&](const Src& prev, int idx) -> Src {                // nearly always the next tile of the sequence
     const int yt = idx < n ? tile_of(idx) : kNoTile;
-    if (__builtin_expect(yt != prev.yt + 1 || (MODE == kDQ && band && yt == tr.b0), 0)) return src_of(idx);
+    if (__builtin_expect(yt != prev.yt + 1, 0)) return src_of(idx);
     Src r = prev;
     r.a1 = prev.a1 + kBN * rowb1;
     r.a2 = prev.a2 + kBN * rowb2;
@@ -202,7 +186,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     const uint32_t left = (uint32_t)max(sr.left, 0);
     if (what == 0) dma16(make_rsrc(sr.a1, left * rowb1), voff1, m0_rows + stage_off);
     else if (what == 1 && !W::kSplit) dma16(make_rsrc(sr.a2, left * rowb2), voff2, m0_rows + stage_off + W::kTile);
-    else dma16(make_rsrc(sr.seed, sr.yt == kNoTile ? 0u : (uint32_t)a.seed_len * 4u), voffS + sr.s_off, m0_strip + (uint32_t)(strip_stage * kStripBytes));
+    else dma16(make_rsrc((uint64_t)(uintptr_t)seed_h, sr.yt == kNoTile ? 0u : (uint32_t)a.seed_len * 4u), voffS + sr.s_off, m0_strip + (uint32_t)(strip_stage * kStripBytes));
   };
 
   // ---- LDS fragment addresses, moved from stage to stage by an addition per step
@@ -214,7 +198,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
 #pragma unroll
   for (int i = 0; i < kSteps; ++i) {
     kaddr[i] = kb ^ (i << 5);
-    taddr[i] = (tb ^ (((i >> 1) << 6) | ((i & 1) << 5))) + (kStages - 1) * W::kStage;     // "tile -1"
+    taddr[i] = (tb ^ (((i >> 1) << 6) | ((i & 1) << 5))) + W::kZero;      // "tile -1"
     asm volatile("" : "+v"(kaddr[i]), "+v"(taddr[i]));
   }
   const int saddr = (int)smem_base + W::kStripBase + (strip_s0 & 3) * kStripCopy + (strip_s0 & ~3) * 4;
@@ -231,32 +215,44 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  // Seeds of a tile whose mask is not a function of the distance.  c: a compile-time constant per score register, streamed row y0 + c + 4 hf.
-  auto patch = [&](f32x16& acc, int yt) {
-    const int y0 = yt * kBN + 4 * hf;
-    if constexpr (MODE == kDQ) {
-      const int up = x_ok ? min(px, g.n - 1) - y0 : -1;                 // history keys up to the row's position
-      const int lo = !band ? -(1 << 28) : px - g.K1 + 1 - y0;            // inside the local band
-      const int pre = g.K2 - y0;                                        // inside the global prefix
-      const int selfc = (CAND && x_ok && x >= g.n) ? x - y0 : -1000;    // a candidate sees itself
+  // Below, c is a compile-time constant per score register: streamed row y0 + c with y0 = first row of the tile + 4 hf.
+  // Seeds of a tile with candidates' rows.
+  auto seed_candidates = [&](f32x16& acc, int yt) {
+    const int y0 = yt * kBN + 4 * hf, hist = g.n - y0, selfc = x >= g.n ? x - y0 : -1000;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = 8 * (r >> 2) + (r & 3);
-        float t = c <= up && (c >= lo || c < pre) ? acc[r] : kMasked;
-        if (CAND) t = c == selfc ? bias0 : t;
-        acc[r] = t;
-      }
-    } else {
-      const int up = cross && x >= g.K2 ? x + g.K1 - 1 - y0 : (1 << 28);   // last query inside the window
-      const int hist = g.n - y0, selfc = x - y0;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = 8 * (r >> 2) + (r & 3);
-        float t = c <= up ? acc[r] : kMasked;
-        if (CAND) t = c < hist ? t : (c == selfc ? bias0 : cand_seed);
-        acc[r] = t;
-      }
+    for (int r = 0; r < 16; ++r) {
+      const int c = 8 * (r >> 2) + (r & 3);
+      if (MODE == kDKDV) acc[r] = c < hist ? acc[r] : cand_seed;
+      acc[r] = c == selfc ? bias0 : acc[r];
     }
+  };
+  // Masked pairs of a tile that is not full; returns whether none is visible.
+  auto mask = [&](f32x16& sc, f32x16& dp, int yt) -> bool {
+    const int t0 = yt * kBN;
+    if (tiles.empty(yt)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { sc[r] = kMasked; dp[r] = 0.f; }
+      return true;
+    }
+    int x = xw0 + l32;
+    asm volatile("" : "+v"(x));                                          // (nothing of this is kept in registers through the loop)
+    const bool x_ok = x < L;
+    const int px = (MODE == kDQ && CAND) ? min(x, g.n) : x, y0 = t0 + 4 * hf;
+    const int selfc = CAND && x >= g.n ? x - y0 : -1;                    // a candidate sees itself
+    uint32_t vis;                                                        // bit c: this lane's row sees, or is seen by, streamed row y0 + c
+    if constexpr (MODE == kDQ) {
+      const int last = min(px, g.n - 1) - y0;                           // history keys up to the row's position, inside the window or the prefix
+      vis = ~bits_from(last + 1) & (band ? bits_from(px - g.K1 + 1 - y0) | ~bits_from(g.K2 - y0) : ~0u);
+    } else {
+      const int last = (band && x >= g.K2 ? min(x + g.K1, g.n) : g.n) - 1 - y0;
+      vis = bits_from(x - y0) & ~bits_from(last + 1);
+      if (CAND && x < g.n && (!band || g.n - x < g.K1 || x < g.K2)) vis |= bits_from(g.n - y0) & ~bits_from(L - y0);
+    }
+    if (CAND) vis |= selfc >= 0 && selfc < 32 ? 1u << selfc : 0u;
+    if (!x_ok) vis = 0u;
+    mask_scores(sc, vis, kMasked);
+    mask_scores(dp, vis, 0.f);
+    return false;
   };
   auto seed = [&](f32x16& acc, int strip_stage) {
 #pragma unroll
@@ -297,10 +293,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
   cur = next_src(cur, 2); yt2 = cur.yt;
 #pragma unroll
   for (int what = 0; what < W::kLoads; ++what) load(cur, what, 2 * W::kStage, 2);
-  {                                                                     // "tile -1" is read by step 0: zeros
+  {                                                                     // the zeros that are read in place of a tile with no visible pair, and of "tile -1" in step 0
     Src none = src_of(n);
-    load(none, 0, (kStages - 1) * W::kStage, 3);
-    if (!W::kSplit) load(none, 1, (kStages - 1) * W::kStage, 3);
+    if (kOut == 2 || !second) load(none, 0, W::kZero, 3);
+    if (kOut == 2 && !W::kSplit) load(none, 1, W::kZero, 3);
   }
   finish_rows();
   wait_loads<0>();
@@ -313,7 +309,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
 #pragma unroll
   for (int i = 0; i < kPF; ++i) fr[i] = rowfrag(i);
   seed(sacc[0], 0);
-  if (nfast == 0 && n > 0) patch(sacc[0], yt_first);
+  if (CAND && nfast == 0 && n > 0) seed_candidates(sacc[0], yt_first);
 #pragma unroll
   for (int r = 0; r < 16; ++r) { sacc[1][r] = 0.f; pacc[1][r] = 0.f; }
 #pragma unroll
@@ -343,12 +339,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     }
   };
 
-  // Stage of tile s + 3 and the step of the fragment addresses to the next stage: scalars that go round.
-  int load_stage = 3, row_stage = 0, tr_stage = kStages - 1;
+  // Stages of tiles s + 3 and s, which go round, and where the output products of tile s - 1 read.
+  int load_stage = 3, row_stage = 0, tr_off = W::kZero;
+  int full_end = 0;                                                     // up to here tiles hold only visible pairs of this wave's rows
   int yt_m1 = kNoTile;                                                  // tile s - 1
-  auto step = [&](int s, auto par_c, auto patch_c) {
+  auto step = [&](int s, auto par_c, auto cand_c) {
     constexpr int P = decltype(par_c)::value;
-    constexpr bool PATCH = decltype(patch_c)::value;
+    constexpr bool CAND_TILES = decltype(cand_c)::value;
     if constexpr (DBIAS) dist.late_out();
     cur = next_src(cur, s + 3);
     const uint32_t load_off = (uint32_t)(load_stage * W::kStage);
@@ -370,6 +367,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
       for (int e = i * W::kScores1; e < (i + 1) * W::kScores1; ++e) feed(sacc[P ^ 1][8 + e], pacc[P ^ 1][8 + e], P ^ 1, 6 + e);
       __builtin_amdgcn_sched_barrier(0);
     }
+    int tr_next = row_stage * W::kStage;
+    if (yt0 >= full_end) {                                              // (tiles ascend)
+      full_end = tiles.full_end(yt0);
+      if (yt0 >= full_end && yt0 != kNoTile && mask(sacc[P], pacc[P], yt0)) tr_next = W::kZero;
+    }
     {
       const int next = row_stage == kStages - 1 ? 0 : row_stage + 1, delta = (next - row_stage) * W::kStage;
       row_stage = next;
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     for (int j = 0; j < kSlots2; ++j) {
       if (j == kSlots2 / 2) {
         seed(sacc[P ^ 1], (s + 1) & (kStripStages - 1));
-        if (PATCH) { if (s + 1 >= nfast && s + 1 < n) patch(sacc[P ^ 1], yt1); }
+        if (CAND_TILES) { if (s + 1 >= nfast && s + 1 < n) seed_candidates(sacc[P ^ 1], yt1); }
       }
       constexpr int N = kSlots1 + kSlots2;
       const int f = kSlots1 + j;                                        // slot of the step
@@ -402,8 +404,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
 #pragma unroll
     for (int i = 0; i < kPF; ++i) fr[i] = nfr[i];
     {
-      const int next = tr_stage == kStages - 1 ? 0 : tr_stage + 1, delta = (next - tr_stage) * W::kStage;
-      tr_stage = next;
+      const int delta = tr_next - tr_off;
+      tr_off = tr_next;
 #pragma unroll
       for (int i = 0; i < 2 * kBlocks; ++i) taddr[i] += delta;
       load_stage = load_stage == kStages - 1 ? 0 : load_stage + 1;
@@ -415,16 +417,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     wait_loads<W::kLoads>();                                            // the loads of the step before have landed
     __syncthreads();
   };
-  // steps whose seeded tile needs no patch, in pairs; then the rest (patched tiles and the step that drains the last one)
+  // steps whose seeded tile has no candidate, in pairs; then the rest (tiles with candidates and the step that drains the last one)
   int s = 0;
   for (; s + 2 < nfast; s += 2) {
     step(s, IC<0>{}, std::false_type{});
     step(s + 1, IC<1>{}, std::false_type{});
   }
   for (; s <= n; s += 2) {
-    step(s, IC<0>{}, std::true_type{});
+    step(s, IC<0>{}, std::bool_constant<CAND>{});
     if (s + 1 > n) break;
-    step(s + 1, IC<1>{}, std::true_type{});
+    step(s + 1, IC<1>{}, std::bool_constant<CAND>{});
   }
   if constexpr (DBIAS) dist.flush();
   wait_loads<0>();                                                      // nothing may still be landing in LDS when the wave ends
@@ -472,7 +474,17 @@ template <int D, int MODE, bool CAND, bool DBIAS>
 hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
   auto kern = attn_bwd_narrow_kernel<D, MODE, CAND, DBIAS>;
   constexpr int smem_bytes = Narrow<D, MODE>::kSmemBytes;
-  static_assert(smem_bytes <= 64 * 1024, "within the default limit of dynamic LDS");
+  static_assert(smem_bytes <= 80 * 1024, "two workgroups share a compute unit");
+  if constexpr (smem_bytes > 64 * 1024) {                                // beyond the default limit
+    static bool attr_set[64] = {};                                       // per instantiation and device
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
+    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
+      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes);
+      if (e != hipSuccess) return e;
+      if (dev >= 0 && dev < 64) attr_set[dev] = true;
+    }
+  }
   const int per = kNumXcd * kXcdGroup;
   const int grid = (a.max_items + per - 1) / per * per;
   if (grid == 0) return hipSuccess;

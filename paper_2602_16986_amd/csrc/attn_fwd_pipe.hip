@@ -22,6 +22,10 @@
 //    mask at all (their Q, K, V rows read as zero).  Only the few sub-blocks whose mask is not a function of the
 //    distance (keys on both sides of the end of the global prefix; candidate keys) are patched element by element,
 //    and those are moved to the end of the item's list and run in a second copy of the loop.
+//    That takes K for finite.  With 32 and 64 features (kExact) the scores of masked pairs are replaced after the product, whatever K held, in the
+//    sub-blocks that hold any for the wave's rows, and the output product of one with no visible pair reads zeros instead of V: rows that
+//    are not finite stay with the queries that may see them.  Costs 2-3 % on short or semi-local batches (8 x 8k-16k semi-local, 64
+//    features 193 -> 198 us, dense 807 -> 810).
 // 3. K, V and the seed strip sit in two-stage rings in LDS, filled by direct-to-LDS loads that are issued a whole
 //    half-step before the barrier that publishes them:
 //      first half of step s:  loads V(s);               at its end: K(s+1), strip(s+1) have landed -> barrier
@@ -55,7 +59,9 @@ struct Pipe {
   // is what lets three workgroups of the widest kernel share a compute unit (168 registers per lane).
   static constexpr int kQLds = D == 128 ? 2 : 0;
   static constexpr int kWgPerCu = D == 128 ? 3 : 4;
-  static constexpr int kKBase = 0, kVBase = 2 * kTile, kStripBase = 4 * kTile, kQBase = kStripBase + 2 * kStripBytes;
+  // A tile of zeros for the output products to read in place of V rows of which no pair is visible (kExact).
+  static constexpr bool kExact = D != 128;
+  static constexpr int kKBase = 0, kVBase = 2 * kTile, kZero = 4 * kTile, kStripBase = kZero + (kExact ? kTile : 0), kQBase = kStripBase + 2 * kStripBytes;
   static constexpr int kIdle = kQBase + kQLds * kThreads * 16;          // where the loads of waves that load nothing land
   static constexpr int kSmemBytes = kIdle + (kLoaders < kWaves ? 1024 : 0);
   // Row r keeps its 16-byte chunk c at chunk c ^ swizzle(r), so that 16 rows read at one chunk, and 4 rows read at 4 chunks (transpose
@@ -70,7 +76,7 @@ struct Pipe {
 constexpr int kPF = HSTU_FP_PF;                                         // slots between a fragment's LDS read and its product
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 constexpr float kMasked = -1e30f;
-constexpr int kNoTile = 1 << 28;
+constexpr int kNoTile = 1 << 25;                                        // (beyond any tile, and its first row still an int)
 // Measurement builds only (results are wrong): HSTU_FWD_ABLATE is a bit mask of parts of the tile loop to leave out, to
 // see what each costs in time and in the clock the chip sustains.  1: the global -> LDS loads of the loop; 2: the two
 // transcendentals of SiLU; 4: the LDS reads of K / V fragments and seeds (16 / 32 / 64: those of K / of V / of the seeds
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
   const int cand_t0 = (CAND && g.n < L) ? g.n / kBN : kNoTile;         // first tile with a candidate key
   const int pc = min(max(cand_t0 - tr.a0, 0), na) + min(max(cand_t0 - tr.b0, 0), nb) + min(max(cand_t0 - tr.c0, 0), nc);
   const int suf0 = min(max(pc, t_begin), t_end);                        // the special suffix is [suf0, t_end)
-  const int straddle_t = (g.K1 >= 0 && (g.K2 % kBN) != 0) ? g.K2 / kBN : -1;
+  const int straddle_t = (!W::kExact && g.K1 >= 0 && (g.K2 % kBN) != 0) ? g.K2 / kBN : -1;
   const int ps_raw = straddle_t - tr.a0;                                // its position, if it is on the list
   const bool has_ps = straddle_t >= tr.a0 && straddle_t < tr.a1 && ps_raw >= t_begin && ps_raw < suf0;
   const int ps = has_ps ? ps_raw : kNoTile;
@@ -300,7 +306,7 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
 #pragma unroll
   for (int i = 0; i < kSteps; ++i) {
     kaddr[i] = kb ^ (i << 5);                                          // k-step i of a score product
-    vaddr[i] = tb ^ (((i >> 1) << 6) | ((i & 1) << 5));                // feature block i / 2, rows +0 (i even) or +8 (i odd)
+    vaddr[i] = (tb ^ (((i >> 1) << 6) | ((i & 1) << 5))) + (W::kExact ? kTile : 0);      // feature block i / 2, rows +0 (i even) or +8 (i odd); "sub-block -1"
     asm volatile("" : "+v"(kaddr[i]), "+v"(vaddr[i]));
   }
   const int saddr = (int)smem_base + W::kStripBase + (strip_s0 & 3) * kStripCopy + (strip_s0 & ~3) * 4;
@@ -324,6 +330,7 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
   // Patch of the seeds of a sub-block whose mask is not a function of the distance: element by element, with per-lane
   // bounds on c = key - y0 - 4 hf (a compile-time constant per score register):
   //   visible <=> (c <= up && (c >= lo || c < pre)) || c == selfc
+  constexpr bool kPatches = CAND || !W::kExact;
   auto mask_seed = [&](f32x16& acc, int yt) {
     const int y0 = yt * kBN + 4 * hf;
     const int up = x_ok ? min(px, g.n - 1) - y0 : -1;                  // history keys up to the row's position
@@ -338,6 +345,20 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
       if (CAND) t = (c == selfc) ? bias0 : t;
       acc[r] = t;
     }
+  };
+  // The scores of masked pairs of a sub-block that is not full (kExact); returns whether no pair is visible.
+  const WaveTiles tiles = key_tiles_of(g, xw0);
+  auto mask_tile = [&](f32x16& acc, int yt) -> bool {
+    if (tiles.empty(yt)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = kMasked;
+      return true;
+    }
+    const int y0 = yt * kBN + 4 * hf, last = min(px, g.n - 1) - y0, selfc = CAND && x >= g.n ? x - y0 : -1;
+    uint32_t vis = ~bits_from(last + 1) & (g.K1 < 0 ? ~0u : bits_from(px - g.K1 + 1 - y0) | ~bits_from(g.K2 - y0));      // as in mask_seed: bit c
+    if (CAND) vis |= selfc >= 0 && selfc < 32 ? 1u << selfc : 0u;
+    mask_scores(acc, x_ok ? vis : 0u, kMasked);
+    return false;
   };
 
   // ---- pipeline state
@@ -365,9 +386,9 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
   vdesc1 = cur.v;
   for (int c = 0; c < kPieces; ++c) load_k(cur, 1, c);
   load_strip(cur, 1);
-  {                                                                     // V stage 1 is read by step 0 ("sub-block -1"): zeros
+  {                                                                     // V of "sub-block -1" in step 0 (stage 1; kExact: the tile of zeros)
     const Src none = src_of(n);
-    for (int c = 0; c < kPieces; ++c) load_v(none, 1, c);
+    for (int c = 0; c < kPieces; ++c) load_v(none, W::kExact ? 2 : 1, c);
   }
   finish_q();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -376,7 +397,7 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
 #pragma unroll
   for (int i = 0; i < kPF; ++i) kfn[i] = kfrag(0, i);
   seed(sacc[0], 0);
-  if (nfast == 0 && n > 0) mask_seed(sacc[0], yt_first);
+  if (kPatches && nfast == 0 && n > 0) mask_seed(sacc[0], yt_first);
 #pragma unroll
   for (int r = 0; r < 16; ++r) sacc[1][r] = kMasked;                    // "sub-block -1": contributes nothing
 #pragma unroll
@@ -395,6 +416,8 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
     return pp;
   };
 
+  // kExact: tile of sub-block s; up to which tile all pairs are visible; how far vaddr is from its place (on the tile of zeros: behind both stages)
+  int yt0 = yt_first, full_end = 0, v_off = W::kExact ? kTile : 0;
   // One step: sub-block s enters (score product, SiLU of its first 16 keys), sub-block s - 1 leaves (SiLU of its last 16
   // keys, output product).  P = parity of s.  PATCH: sub-block s + 1, seeded in this step, may need its mask patched.
   auto step = [&](int s, auto par_c, auto patch_c) {
@@ -426,6 +449,14 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
     wait_loads<kPieces>();                                              // K(s+1), strip(s+1) landed (V(s) may still fly)
     __syncthreads();
 
+    int v_next = 0;
+    if constexpr (W::kExact) {
+      if (yt0 >= full_end) {                                            // (sub-blocks ascend)
+        full_end = tiles.full_end(yt0);
+        if (yt0 >= full_end && yt0 != kNoTile && mask_tile(sacc[P], yt0)) v_next = (2 - P) * kTile;
+      }
+    }
+
     // ---------------- second half: O += V(s-1)^T P(s-1), SiLU of keys 0..15 of s
     const int yt_seed = cur.yt;                                         // sub-block s + 1, seeded in this half
     cur = next_src(cur, s + 2);
@@ -433,7 +464,7 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
     for (int j = 0; j < kSteps; ++j) {
       if (j == kSteps / 2) {                                            // (the last 8 scores of s - 1 went into P in the first half)
         seed(sacc[P ^ 1], P ^ 1);
-        if (PATCH) { if (s + 1 >= nfast && s + 1 < n) mask_seed(sacc[P ^ 1], yt_seed); }
+        if (PATCH && kPatches) { if (s + 1 >= nfast && s + 1 < n) mask_seed(sacc[P ^ 1], yt_seed); }
       }
       if (j < kPieces && !kNoDma) load_k(cur, P, j);
       if (j == (kPieces < kSteps ? kPieces : kSteps - 1) && !kNoDma) load_strip(cur, P);
@@ -454,6 +485,14 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
         else { plo[P][(e - 1) >> 1] = pack_bf16x2(st_p, pp); asm volatile("" : "+v"(plo[P][(e - 1) >> 1])); }
       }
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (W::kExact) {
+      yt0 = yt_seed;
+      if (v_next != v_off) {
+#pragma unroll
+        for (int i = 0; i < 2 * kBlocks; ++i) vaddr[i] += v_next - v_off;
+        v_off = v_next;
+      }
     }
     wait_loads<kPieces + 1>();                                          // V(s) landed (only the loads of this half may still fly)
     __syncthreads();

@@ -6,6 +6,8 @@
 //   - every enumerated tile holds at least one visible pair (no fully masked tile is scheduled),
 //   - classify_tile says Full only if all pairs of the 32x32 block are visible history pairs with
 //     distance i - j, and Empty only if none is visible;
+//   - the tiles of 32 that key_tiles_of() and query_tiles_of() call full hold only visible pairs with history keys (of existing rows), run by run, and
+//     classify_tile()'s full ones are among them; those that they call empty hold none, and classify_tile()'s empty ones of history rows are among them;
 //   otherwise a non-zero code naming the violated property.
 //   plan_check(...) does the same for the bounds of hstu_plan.h on one batch: the room for dS holds the tiles of the dK/dV list, with the
 //   host copy of the offsets and without it; the query tiles of a key block are consecutive (the dQ product addresses dS by that); and a
@@ -68,6 +70,32 @@ extern "C" int geometry_check(int L, int M, int K1, int K2, int block_rows, int 
         }
       if (kind == kTileFull && nbad) return 70;
       if (kind == kTileEmpty && nvis) return 80;
+    }
+  for (int w0 = 0; w0 < L; w0 += 32)
+    for (int keys = 0; keys < 2; ++keys) {                   // tiles of keys for query rows w0 .., or of queries for keys w0 ..
+      const WaveTiles t = keys ? key_tiles_of(g, w0) : query_tiles_of(g, w0);
+      std::vector<int> full(lim / 32 + 1, 0);
+      for (int yt = 0; yt < lim / 32; ++yt) {
+        const int y0 = 32 * yt;
+        bool any = false;
+        full[yt] = 1;
+        for (int x = w0; x < w0 + 32 && x < L; ++x)
+          for (int y = y0; y < y0 + 32; ++y) {
+            int delta;
+            const int i = keys ? x : y, j = keys ? y : x;
+            const bool vis = visible(g, i, j, delta);
+            any |= vis;
+            if (j >= g.n || (!keys && i >= g.n) || !vis) full[yt] = 0;
+          }
+        const int kind = keys ? classify_tile(g, w0, w0 + 31, y0, y0 + 31) : classify_tile(g, y0, y0 + 31, w0, w0 + 31, false);
+        if (kind == kTileFull && t.full_end(yt) <= yt) return 90 + keys;
+        if (t.empty(yt) && any) return 92 + keys;
+        const bool history = keys ? imin(w0 + 31, L - 1) < g.n : y0 + 31 < g.n && w0 + 31 < g.n;
+        if (history && kind == kTileEmpty && !t.empty(yt)) return 94 + keys;
+      }
+      for (int yt = 0; yt < lim / 32; ++yt)
+        for (int f = yt; f < t.full_end(yt); ++f)
+          if (f >= lim / 32 || !full[f]) return 96 + keys;
     }
   return 0;
 }

@@ -44,4 +44,17 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, y);
 }
 
+// Bits lo .. 31.
+__device__ __forceinline__ uint32_t bits_from(int lo) { return lo > 31 ? 0u : ~0u << max(lo, 0); }
+
+// Of a 32 x 32 block of scores (register r of a lane: streamed row 8 (r / 4) + r % 4, + 4 in the upper half-wave): `masked` where the row's bit of `vis` is 0,
+// whatever stood there.  In bit operations, three a score at most: comparisons would take a pair of scalar registers each.
+__device__ __forceinline__ void mask_scores(f32x16& v, uint32_t vis, float masked) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const uint32_t m = (uint32_t)((int)(vis << (31 - (8 * (r >> 2) + (r & 3)))) >> 31);
+    v[r] = __uint_as_float((__float_as_uint(v[r]) & m) | (__float_as_uint(masked) & ~m));
+  }
+}
+
 }  // namespace hstu

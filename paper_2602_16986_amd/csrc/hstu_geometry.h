@@ -151,4 +151,40 @@ HSTU_HD int classify_tile(const SeqGeom& g, int w0, int w1, int j0, int j1, bool
   return kTilePartial;
 }
 
+// Of the tiles of 32 that a wave's 32 rows meet: the full ones (all their pairs are visible) and those that may hold a visible pair at all, by number.
+struct WaveTiles {
+  int full_pre, full_lo, full_hi;                            // full: [0, full_pre) and [full_lo, full_hi)
+  int live_pre, live_lo, live_hi, live_end;                  // may be visible: [0, live_pre), [live_lo, live_hi) and from live_end on
+  HSTU_HD int full_end(int yt) const { return yt < full_pre ? full_pre : (yt >= full_lo && yt < full_hi ? full_hi : yt); }     // of the run of full tiles yt is in, or yt
+  HSTU_HD bool empty(int yt) const { return yt >= live_pre && (yt < live_lo || yt >= live_hi) && yt < live_end; }
+};
+// Key tiles for the query rows w0 .. w0 + 31 (w0 a multiple of 32; those of them that exist; a candidate stands at position n, and waves with candidates
+// leave out no later tile).
+HSTU_HD WaveTiles key_tiles_of(const SeqGeom& g, int w0) {
+  const bool band = g.K1 >= 0;
+  const int first = imin(w0, g.n), last = imin(imin(w0 + 31, g.L - 1), g.n), far = 1 << 30;
+  WaveTiles t;
+  t.full_hi = first >> 5;
+  t.full_lo = band ? imax((last - g.K1) >> 5, -1) + 1 : 0;
+  t.full_pre = band ? imin(g.K2 >> 5, t.full_hi) : 0;
+  t.live_pre = band ? (g.K2 + 31) >> 5 : 0;
+  t.live_lo = band ? (first - g.K1 + 1) >> 5 : 0;
+  t.live_hi = imin(w0 + 31, g.L - 1) < g.n ? (w0 >> 5) + 1 : far;
+  if (t.live_pre > t.live_hi) t.live_pre = t.live_hi;
+  t.live_end = far;
+  return t;
+}
+// Query tiles for the keys k0 .. k0 + 31; full ones hold history rows only, and any tile with a candidate may be visible.
+HSTU_HD WaveTiles query_tiles_of(const SeqGeom& g, int k0) {
+  const bool window = g.K1 >= 0 && k0 + 31 >= g.K2, all_window = g.K1 >= 0 && k0 >= g.K2;
+  WaveTiles t;
+  t.full_pre = t.live_pre = 0;
+  t.full_lo = (k0 >> 5) + 1;
+  t.full_hi = window ? imin((k0 + g.K1) >> 5, g.n >> 5) : g.n >> 5;
+  t.live_lo = k0 >> 5;
+  t.live_hi = all_window ? (k0 + g.K1 + 62) >> 5 : 1 << 30;
+  t.live_end = g.n >> 5;
+  return t;
+}
+
 }  // namespace hstu

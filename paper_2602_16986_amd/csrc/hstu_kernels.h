@@ -71,7 +71,7 @@ struct AttnArgs {
   // semi-local mask) also has -1e30 for d >= K1.  seed_dmax >= max_seqlen + 128, seed_len >= seed_dmax + 1 + 192.
   const float* seed;
   int32_t seed_len, seed_dmax;
-  const float* seed_up;             // the same by ascending distance, seed_up[i] <-> d = i - kSeedUpZero (narrow backward: keys stationary)
+  const float* seed_up;             // the first of them by ascending distance, seed_up[i] <-> d = i - kSeedUpZero (narrow backward: keys stationary)
   // Backward, bf16 with 128 features, optional: dS in bf16, handed from the dK/dV pass to the dQ product (attn_dq.hip says in
   // which layout).  ds_table[4 p ..]: of (sequence, key block) pair p of the dK/dV list: its first tile of 32 queries x 128 keys in
   // `ds` over all heads, the first query tile it visits, the number of them; pairs of sequence b start at ds_pair0[b], last block first.

@@ -388,7 +388,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
 //   bias[h, x] = log2(e) * table[h, bucket(x)], bucket(x) = max{c : bounds[c] <= x}, for x in [0, bias_len): the attention kernels
 //   keep their scores in units of ln 2; bucket_end[x]: where the next bucket starts;
 //   and the zeros around every head's row;
-//   seed[v][h][i] (AttnArgs::seed), d = seed_dmax - i, and seed_up[v][h][i], d = i - kSeedUpZero;
+//   seed[v][h][i] (AttnArgs::seed), d = seed_dmax - i, and seed_up[h][i], d = i - kSeedUpZero;
 //   and clears the per-distance sums of the bias gradient.
 __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen, int id, int n) {
   auto bucket = [&](int x) {
@@ -420,7 +420,6 @@ __device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen,
     for (int h = 0; h < H; ++h) {
       const float b = j.table ? j.table[(size_t)h * j.num_buckets + c] * 1.4426950408889634f : 0.f;
       j.seed_up[(size_t)h * j.seed_len + i] = d < 0 ? -1e30f : b;
-      j.seed_up[((size_t)H + h) * j.seed_len + i] = (d < 0 || (K1 >= 0 && d >= K1)) ? -1e30f : b;
     }
   }
   for (int64_t i = id; i < j.zero_count; i += n) j.zero[i] = 0.f;
