@@ -34,12 +34,6 @@ struct Layout {           // byte offsets inside a workspace
   int slot_cap_dq;        // ... of the dQ pass (query blocks of a small batch cut along the key axis)
 };
 
-// Slots for the pieces of cut key blocks: at most 768 (about 1.5 per workgroup slot of the chip), never more than
-// twice the number of key blocks, none without a mask that can make a key block long (dense causal and local-only
-// masks never have one block much longer than the rest of its sequence... they may still be cut when sequences differ
-// a lot in length, which the same bound covers).  fp32 blocks are cut more finely (cut_rule_for).
-inline int slot_cap_for(int max_items, bool fp32) { return std::min((fp32 ? 8 : 2) * max_items, 768); }
-
 // Sequences are shorter than 2^24 tokens: windows beyond 2^28 mean the same and keep the kernels' index sums inside int32.
 inline int window_of(int32_t w) { return w < 0 ? -1 : (w < (1 << 28) ? w : (1 << 28)); }
 
@@ -60,8 +54,7 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
     const int rows = !for_backward ? fwd_block_rows(p->dtype, p->head_dim)
                                    : (s == 0 ? dq_block_rows(p->dtype, p->head_dim) : dkv_block_rows(p->dtype, p->head_dim));
     l.max_items[s] = (int)max_items_for(p, rows);
-    // the dK/dV list also holds the pieces of cut key blocks; so does the forward list (query blocks longer than a
-    // workgroup slot's share of the batch, or the few blocks of a query tail against long histories: their key axis is cut)
+    // a list also holds the pieces of its cut blocks (hstu_plan.h)
     if ((for_backward && s == 1) || !for_backward) {
       l.slot_cap = slot_cap_for(l.max_items[s], p->dtype == HSTU_FP32);
       l.max_items[s] += l.slot_cap;

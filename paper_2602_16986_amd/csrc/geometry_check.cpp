@@ -11,7 +11,7 @@
 //   otherwise a non-zero code naming the violated property.
 //   plan_check(...) does the same for the bounds of hstu_plan.h on one batch: the room for dS holds the tiles of the dK/dV list, with the
 //   host copy of the offsets and without it; the query tiles of a key block are consecutive (the dQ product addresses dS by that); and a
-//   list in which the scheduler cuts a block is one that schedule_may_cut() names.
+//   list in which the scheduler cuts a block is one that schedule_may_cut() names, and where the lengths say it all no other list is.
 #include <vector>
 
 #include "hstu_geometry.h"
@@ -128,26 +128,42 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
     for (int tile = 32; tile <= 64; tile += 32) {
       const int tail = which == 0 ? query_tail : 0;
       int64_t all = 0;
-      int most = 0, blocks = 0;
+      int most = 0;
+      std::vector<int> costs;
       for (int b = 0; b < B; ++b) {
         const SeqGeom g = geom(b);
         for (int r0 = tail_origin(g.n, tail); r0 < g.L; r0 += 128) {
           const int r1 = imin(r0 + 128, g.L) - 1;
-          const int cost = (which == 2 ? row_tile_ranges(g, r0, r1, tile) : tile_ranges(g, r0, r1, tile)).count();
-          all += (int64_t)cost * H;
-          blocks += H;
-          most = imax(most, cost);
+          costs.push_back((which == 2 ? row_tile_ranges(g, r0, r1, tile) : tile_ranges(g, r0, r1, tile)).count());
+          all += (int64_t)costs.back() * H;
+          most = imax(most, costs.back());
         }
       }
-      for (int rule_of = 0; rule_of < 4; ++rule_of) {      // bf16, and fp32 with 32, 64 and 128 features
-        const bool fp32 = rule_of > 0;
-        const int D = fp32 ? 16 << rule_of : 128;
+      for (int rule_of = 0; rule_of < 6; ++rule_of) {      // bf16 and fp32 with 32, 64 and 128 features
+        const bool fp32 = rule_of >= 3;
+        const int D = 32 << rule_of % 3;
         const CutRule rule = cut_rule_for(fp32, D, which, tail > 0);
-        // the scheduler's first piece size
-        const int64_t chunk = std::max((int64_t)rule.min_chunk, (int64_t)std::ceil((double)all * (1.0 / rule.target_chunks)));
-        const bool cut = most > 2 * chunk + rule.slack_of(blocks) && most > rule.longest_uncut;
+        const bool many = targets && (int64_t)costs.size() * H >= kManyBlocks;
+        const int launch = targets && !many ? 0 : rule.launch, least = 2 * rule.min_chunk + rule.launch * (many ? kUnsure : 1);
+        int64_t chunk = std::max((int64_t)rule.min_chunk, (int64_t)std::ceil((double)all * (1.0 / rule.target_chunks)));
+        const int64_t cap = slot_cap_for(((int64_t)offsets[B] / 128 + B) * H, fp32);
+        bool cut = false;
+        while (most > worth_cutting((int)chunk, fp32) + launch && most > least) {                // the piece size grows until the slots fit
+          int64_t slots = 0;
+          const int64_t piece = tail > 0 || (fp32 && which == 2) ? chunk : 2 * chunk;
+          for (int c : costs)
+            if (c > 2 * chunk) slots += (c + piece - 1) / piece;
+          slots *= H;
+          if (slots <= cap) {
+            cut = most > worth_cutting((int)chunk, fp32) + launch + slots / rule.slots_per_tile;
+            break;
+          }
+          chunk += 4 * slots <= (tail > 0 ? 5 : 6) * cap ? std::max(chunk / 4, (int64_t)1) : chunk;
+        }
         if (cut && !schedule_may_cut(with, tail, which, 128, tile, fp32, D)) return 10 + which;
         if (cut && !schedule_may_cut(without, tail, which, 128, tile, fp32, D)) return 20 + which;
+        if (!cut && !targets && tail == 0 && costs.size() <= 1024 && schedule_may_cut(with, tail, which, 128, tile, fp32, D))
+          return 30 + which;                               // the launch that adds pieces up, for a list that is not cut
       }
     }
   return 0;

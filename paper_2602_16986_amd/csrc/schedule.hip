@@ -41,10 +41,11 @@ constexpr int kMaxExpandBlocks = 192;
 
 // One workgroup builds one list; the backward pass has two (dQ blocks and dK/dV blocks) side by side.
 struct SchedJob {
-  int block_shift, tile_shift, key_major;    // rows of a block and of a tile: powers of two
+  int block_shift, tile_shift;        // rows of a block and of a tile: powers of two
+  bool key_major, fp32;
+  bool even;                          // cut blocks into equal pieces of at most 2 x chunk tiles (else: pieces of chunk tiles)
   int query_tail;                     // > 0 (query-major lists only): only the blocks that hold the last query_tail history rows or candidates
   int slot_cap;            // > 0: blocks much longer than the average may be cut along the streamed axis
-  int even;                // cut blocks into equal pieces of at most 2 x chunk tiles (else: pieces of chunk tiles)
   CutRule rule;            // how they are
   SchedHeader* header;
   WorkItem* items;
@@ -231,11 +232,11 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   const int max_cost = __builtin_amdgcn_readlane(row_max(sh.wave_total[2][col]), kSchedWaves - 1);
   const int64_t all_tiles = (int64_t)pair_tiles * H, all_dense = (int64_t)pair_dense * H;
 
-  // 3. Cut blocks that are much longer than a workgroup slot's share (CutRule; the few key blocks of a global prefix are seen by
-  // every query of their sequence).  Each piece
+  // 3. Cut blocks that are much longer than the rest (CutRule; the few key blocks of a global prefix are seen by every query of
+  // their sequence).  Each piece
   // becomes an entry of the list and accumulates into a partial-sum slot of its own (one per head).  The piece size
-  // doubles until the slots and the list fit; with a query tail (few blocks, most of them cut) it grows by a quarter once the slots are
-  // short by a quarter or less: doubled there, most blocks are no longer than twice a piece and stay whole (16 sequences of 2,000-4,000
+  // doubles until the slots and the list fit, and grows by a quarter once the slots are
+  // short by a quarter (with a query tail) or a half: doubled there, most blocks are no longer than twice a piece and stay whole (16 sequences of 2,000-4,000
   // tokens, 4 heads of 32 features, tail 500: 91 us, 69 this way; n tiles in pieces of n / (slots - blocks), which always fit, 86).
   int chunk = (int)fmin((double)0x3FFFFFFF, fmax((double)job.rule.min_chunk, ceil((double)all_tiles * (1.0 / job.rule.target_chunks))));
   // pieces of a block of `cost` tiles and their length: the fewest equal pieces of at most 2 x chunk tiles (every piece costs a
@@ -262,7 +263,10 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   }
   int slot0 = 0, rank0 = 0, slots = 0, nsplit = 0, entries = pairs;        // first slot and rank of this thread's pairs among the cut ones; totals
   bool cuts = false;                                       // uniform: some block is cut
-  const bool wanted = job.slot_cap > 0 && max_cost > max(2 * chunk + job.rule.slack_of((long long)pairs * H), job.rule.longest_uncut);
+  const bool many = num_targets && (long long)pairs * H >= kManyBlocks;
+  const int launch = num_targets && !many ? 0 : job.rule.launch;      // (with candidates it is there in any case)
+  const bool wanted = job.slot_cap > 0 && max_cost > worth_cutting(chunk, job.fp32) + launch &&
+                      max_cost > 2 * job.rule.min_chunk + job.rule.launch * (many ? kUnsure : 1);
 #pragma unroll 1
   for (int round = 0; wanted && max_cost > 2 * chunk; round ^= 1) {
     int my_slots = 0, my_cuts = 0;
@@ -277,10 +281,10 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     rank0 = block_scan(my_cuts, sh.wave_total[4 + 2 * round], nsplit);
     entries = pairs - nsplit + slots;
     if (entries <= kSortMax && (long long)slots * H <= job.slot_cap) {       // uniform: every thread sees the same totals
-      cuts = true;
+      cuts = max_cost > worth_cutting(chunk, job.fp32) + launch + slots * H / job.rule.slots_per_tile;
       break;
     }
-    const bool nearly = tail > 0 && 4 * (long long)slots * H <= 5 * (long long)job.slot_cap;
+    const bool nearly = 4 * (long long)slots * H <= (tail > 0 ? 5 : 6) * (long long)job.slot_cap;
     chunk += nearly ? max(chunk >> 2, 1) : chunk;              // ends: with no pair cut, entries = pairs <= kSortMax
   }
   if (!cuts) { entries = pairs; nsplit = 0; }
@@ -453,19 +457,17 @@ hipError_t launch(const AttnArgs& a, int njobs, const SchedJob& j0, const SchedJ
 
 hipError_t launch_schedule(const AttnArgs& a, bool lists, int block_rows, int tile_cols, SchedHeader* header, WorkItem* items,
                            int32_t* seq_base, SplitItem* splits, int slot_cap, bool fp32, const ExpandJob& ex, hipStream_t stream) {
-  // equal pieces of about one workgroup slot's share (768 slots at three workgroups per compute unit); the forward over a
-  // query tail takes finer pieces (few blocks, each against a whole history)
+  // (the forward over a query tail takes finer pieces: few blocks, each against a whole history)
   const bool even = a.query_tail == 0;
-  const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), 0, a.query_tail, slot_cap, even ? 1 : 0, cut_rule_for(fp32, a.D, 0, !even), header, items, seq_base, splits, nullptr};
+  const SchedJob job = {log2_of(block_rows), log2_of(tile_cols), false, fp32, even, a.query_tail, slot_cap, cut_rule_for(fp32, a.D, 0, !even), header, items, seq_base, splits, nullptr};
   return launch(a, lists ? 1 : 0, job, job, ex, stream);
 }
 
 hipError_t launch_schedule_pair(const AttnArgs& a, bool lists, const int block_rows[2], const int tile_cols[2], SchedHeader* const header[2],
                                 WorkItem* const items[2], int32_t* const seq_base[2], SplitItem* const splits[2],
                                 const int slot_cap[2], bool fp32, int32_t* ds_table, const ExpandJob& ex, hipStream_t stream) {
-  // dQ list (query-major): equal pieces of about one slot's share, 512 slots at two workgroups per compute unit
-  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), 0, 0, slot_cap[0], 1, cut_rule_for(fp32, a.D, 1, false), header[0], items[0], seq_base[0], splits[0], nullptr};
-  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), 1, 0, slot_cap[1], fp32 ? 0 : 1, cut_rule_for(fp32, a.D, 2, false), header[1], items[1], seq_base[1], splits[1], ds_table};
+  const SchedJob j0 = {log2_of(block_rows[0]), log2_of(tile_cols[0]), false, fp32, true, 0, slot_cap[0], cut_rule_for(fp32, a.D, 1, false), header[0], items[0], seq_base[0], splits[0], nullptr};
+  const SchedJob j1 = {log2_of(block_rows[1]), log2_of(tile_cols[1]), true, fp32, !fp32, 0, slot_cap[1], cut_rule_for(fp32, a.D, 2, false), header[1], items[1], seq_base[1], splits[1], ds_table};
   return launch(a, lists ? 2 : 0, j0, j1, ex, stream);
 }
 
