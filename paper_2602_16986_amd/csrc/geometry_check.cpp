@@ -100,6 +100,49 @@ extern "C" int geometry_check(int L, int M, int K1, int K2, int block_rows, int 
   return 0;
 }
 
+// What the scheduler makes of one list (which: 0 forward, 1 dQ, 2 dK/dV): the blocks' costs in natural order (first sequence first, a sequence's last block first), and in
+// out[]: whether blocks are cut, the first and the last piece size, the partial-sum slots, the blocks of all heads that are cut.  Returns the number of blocks of one head.
+struct PlannedList { bool cut; int64_t first, chunk, slots, split; };
+static PlannedList planned(const std::vector<int>& costs, int64_t rows_over_128_and_batch, int H, int which, bool tail, bool candidates, bool fp32, int D) {
+  const CutRule rule = cut_rule_for(fp32, D, which, tail);
+  int64_t all = 0;
+  int most = 0;
+  for (int c : costs) { all += (int64_t)c * H; most = imax(most, c); }
+  const bool many = candidates && (int64_t)costs.size() * H >= kManyBlocks;
+  const int launch = candidates && !many ? 0 : rule.launch, least = 2 * rule.min_chunk + rule.launch * (many ? kUnsure : 1);
+  const int64_t first = std::max((int64_t)rule.min_chunk, (int64_t)std::ceil((double)all * (1.0 / rule.target_chunks)));
+  const int64_t cap = slot_cap_for(rows_over_128_and_batch * H, fp32);
+  PlannedList l = {false, first, first, 0, 0};
+  while (most > worth_cutting((int)l.chunk, fp32) + launch && most > least) {              // the piece size grows until the slots fit
+    const int64_t piece = tail || (fp32 && which == 2) ? l.chunk : 2 * l.chunk;
+    l.slots = l.split = 0;
+    for (int c : costs)
+      if (c > 2 * l.chunk) { l.slots += (c + piece - 1) / piece * H; l.split += H; }
+    if (l.slots <= cap) {
+      l.cut = most > worth_cutting((int)l.chunk, fp32) + launch + l.slots / rule.slots_per_tile;
+      break;
+    }
+    l.chunk += 4 * l.slots <= (tail ? 5 : 6) * cap ? std::max(l.chunk / 4, (int64_t)1) : l.chunk;
+  }
+  return l;
+}
+extern "C" int planned_list(int B, const int32_t* lengths, const int32_t* targets, int H, int K1, int K2, int which, int tile, int fp32, int D, int32_t* costs_out, int64_t* out) {
+  std::vector<int> costs;
+  int64_t rows = 0;
+  for (int b = 0; b < B; ++b) {
+    const SeqGeom g = {lengths[b], lengths[b] - (targets ? targets[b] : 0), K1, K2};
+    rows += g.L;
+    for (int r0 = (g.L - 1) / 128 * 128; g.L > 0 && r0 >= 0; r0 -= 128) {
+      const int r1 = imin(r0 + 128, g.L) - 1;
+      costs.push_back((which == 2 ? row_tile_ranges(g, r0, r1, tile) : tile_ranges(g, r0, r1, tile)).count());
+    }
+  }
+  const PlannedList l = planned(costs, rows / 128 + B, H, which, false, targets != nullptr, fp32 != 0, D);
+  for (size_t i = 0; costs_out && i < costs.size(); ++i) costs_out[i] = costs[i];
+  out[0] = l.cut; out[1] = l.first; out[2] = l.chunk; out[3] = l.slots; out[4] = l.split;
+  return (int)costs.size();
+}
+
 // targets: nullptr or the candidates of every sequence; slack: by how much max_seqlen exceeds the longest one
 extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets, int H, int K1, int K2, int query_tail, int slack) {
   std::vector<int32_t> offsets(B + 1, 0);
@@ -127,39 +170,18 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
   for (int which = 0; which < 3; ++which)
     for (int tile = 32; tile <= 64; tile += 32) {
       const int tail = which == 0 ? query_tail : 0;
-      int64_t all = 0;
-      int most = 0;
       std::vector<int> costs;
       for (int b = 0; b < B; ++b) {
         const SeqGeom g = geom(b);
         for (int r0 = tail_origin(g.n, tail); r0 < g.L; r0 += 128) {
           const int r1 = imin(r0 + 128, g.L) - 1;
           costs.push_back((which == 2 ? row_tile_ranges(g, r0, r1, tile) : tile_ranges(g, r0, r1, tile)).count());
-          all += (int64_t)costs.back() * H;
-          most = imax(most, costs.back());
         }
       }
       for (int rule_of = 0; rule_of < 6; ++rule_of) {      // bf16 and fp32 with 32, 64 and 128 features
         const bool fp32 = rule_of >= 3;
         const int D = 32 << rule_of % 3;
-        const CutRule rule = cut_rule_for(fp32, D, which, tail > 0);
-        const bool many = targets && (int64_t)costs.size() * H >= kManyBlocks;
-        const int launch = targets && !many ? 0 : rule.launch, least = 2 * rule.min_chunk + rule.launch * (many ? kUnsure : 1);
-        int64_t chunk = std::max((int64_t)rule.min_chunk, (int64_t)std::ceil((double)all * (1.0 / rule.target_chunks)));
-        const int64_t cap = slot_cap_for(((int64_t)offsets[B] / 128 + B) * H, fp32);
-        bool cut = false;
-        while (most > worth_cutting((int)chunk, fp32) + launch && most > least) {                // the piece size grows until the slots fit
-          int64_t slots = 0;
-          const int64_t piece = tail > 0 || (fp32 && which == 2) ? chunk : 2 * chunk;
-          for (int c : costs)
-            if (c > 2 * chunk) slots += (c + piece - 1) / piece;
-          slots *= H;
-          if (slots <= cap) {
-            cut = most > worth_cutting((int)chunk, fp32) + launch + slots / rule.slots_per_tile;
-            break;
-          }
-          chunk += 4 * slots <= (tail > 0 ? 5 : 6) * cap ? std::max(chunk / 4, (int64_t)1) : chunk;
-        }
+        const bool cut = planned(costs, (int64_t)offsets[B] / 128 + B, H, which, tail > 0, targets != nullptr, fp32, D).cut;
         if (cut && !schedule_may_cut(with, tail, which, 128, tile, fp32, D)) return 10 + which;
         if (cut && !schedule_may_cut(without, tail, which, 128, tile, fp32, D)) return 20 + which;
         if (!cut && !targets && tail == 0 && costs.size() <= 1024 && schedule_may_cut(with, tail, which, 128, tile, fp32, D))

@@ -8,6 +8,7 @@ import torch
 
 from oracle import hstu_oracle as orc
 from paper_2602_16986_amd import workloads as wl
+from test_gpu_schedule import plan, read_list  # noqa: F401 (a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -176,18 +177,25 @@ def test_layer_chain_small(hb):
 
 
 @pytest.mark.parametrize("B,lo,hi,K1,K2", [
-    (24, 500, 1100, 64, 128),     # a few hundred global-prefix key blocks, each cut into 3-4 pieces
-    (96, 520, 700, 32, 128),      # more cut candidates than partial-sum slots: the piece size grows until they fit
+    (24, 500, 1100, 64, 128),     # the global-prefix key blocks of the longer sequences, cut into 2-3 pieces among some 300 blocks
+    (96, 520, 700, 32, 128),      # a thousand blocks, none of them worth cutting
+    (3, 2800, 3300, -1, 0),       # more pieces than partial-sum slots: the piece size grows until they fit
     (3, 2500, 4000, 96, 300),     # long pieces, ragged prefix (300 keys = 2.3 key blocks)
 ])
-def test_backward_with_cut_key_blocks(hb, B, lo, hi, K1, K2):
+def test_backward_with_cut_key_blocks(hb, plan, B, lo, hi, K1, K2):
     """dK/dV of key blocks that the scheduler cuts along the query axis (keys of the global prefix are seen by
-    every query): pieces leave fp32 partial sums that a combine kernel adds up; compared with the oracle."""
+    every query): pieces leave fp32 partial sums that a combine kernel adds up; compared with the oracle.  The list in the workspace says
+    that the blocks were cut, and that the pieces grew."""
     rng = np.random.default_rng(B * 1000 + K2)
     L = rng.integers(lo, hi + 1, size=B)
     L[1] = 0                                              # an empty sequence in the middle of the list
     w = wl.build(f"cut-B{B}", L, 2, 128, "bf16", rng=rng, K1=K1, K2=K2, backward=True)
-    run_case(w)
+    dw = run_case(w)
+    head, items = read_list(dw.ws_bwd, w.T, B, 2, False, True)
+    _, rule = plan(w.lengths, None, 2, K1, K2, 2, False, 128)
+    pieces = int((items[:, 4] >= 0).sum())
+    assert (head["split"], pieces) == ((rule["split"], rule["slots"]) if rule["cut"] else (0, 0))
+    assert (head["split"] > 0) == (B != 96) and (B != 3 or K1 >= 0 or head["chunk"] == rule["chunk"] > rule["first"])
 
 
 def test_backward_cut_key_blocks_d64_and_fp32(hb):
