@@ -21,9 +21,10 @@ inline int64_t max_items_for(const hstu_attn_params* p, int block_rows) {
   return ((int64_t)p->total_tokens / block_rows + p->batch) * p->num_heads;
 }
 
-// Copies of the sums per distance: one per die while they stay small (16 MB: clearing and adding them up takes a few microseconds).
+// Copies of the sums per distance: one per die while they stay small (16 MB, up to 62 distances a row of padding apart: clearing and adding them up takes a few
+// microseconds).
 inline int dbias_copies_for(const hstu_attn_params* p) {
-  return (int64_t)kDbiasCopies * p->num_heads * dbias_pitch_for(p->max_seqlen) <= (int64_t)4 << 20 ? kDbiasCopies : 1;
+  return (int64_t)kDbiasCopies * p->num_heads * ((int64_t)p->max_seqlen + 1) <= (int64_t)4 << 20 ? kDbiasCopies : 1;
 }
 
 struct Layout {           // byte offsets inside a workspace

@@ -160,3 +160,16 @@ def test_least_workspace_is_the_full_one_without_the_room_for_ds(dim, dtype, len
         assert least(ctypes.byref(arg), 1) == full(ctypes.byref(arg), 1) - room > 0
     p.head_dim = 96
     assert hb._lib.hstu_attn_workspace_least_bytes(ctypes.byref(p), 1) == hb._lib.hstu_layer_workspace_least_bytes(ctypes.byref(lp), 1) == 0
+
+
+@pytest.mark.parametrize("heads,limit", [(8, 65535), (4, 131071), (2, 262143)])
+def test_copies_of_the_distance_sums_up_to_their_limit(heads, limit):
+    """The backward's workspace holds one copy of the per-distance sums per die up to 4 M sums (heads x (max_seqlen + 1) x 8 copies), and one copy beyond: it grows
+    with max_seqlen up to that limit."""
+    import torch
+    from paper_2602_16986_amd import binding as hb
+    q = torch.zeros(1, heads, 64, dtype=torch.bfloat16)
+    offsets = torch.tensor([0, 1], dtype=torch.int32)
+    size = lambda n: hb.hstu_attn_workspace_bytes(hb.AttnProblem(q, q, q, q, offsets, max_seqlen=n), True)
+    assert 0 < size(limit - 100) <= size(limit - 20) <= size(limit)
+    assert size(limit + 1) < size(limit)
