@@ -19,14 +19,20 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-ato
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 # The fp32 kernels need more than 256 registers, and the compiler then prefers accumulation registers for everything a matrix instruction
-# touches: a copy of every score each way, 66-112 registers more, and 146 spilled in the dK/dV pass with 128 features.
+# touches: a copy of every score each way, 66-112 registers more, and 146 spilled in the dK/dV pass with 128 features.  It is an option of the compiler's own
+# making, and the kernels are right without it: a compiler that does not know it leaves it out.
 FILE_FLAGS = {"attn_core.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str, objdir: str, defines=()) -> str:
     obj = os.path.join(objdir, src.replace(".hip", ".o"))
-    cmd = ["hipcc", *FLAGS, *FILE_FLAGS.get(src, []), *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    run = lambda extra: subprocess.run(["hipcc", *FLAGS, *extra, *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj],
+                                       capture_output=True, text=True)
+    extra = FILE_FLAGS.get(src, [])
+    res = run(extra)
+    if extra and res.returncode != 0 and "nknown command line argument" in res.stderr:
+        sys.stderr.write(f"{src}: compiled without {' '.join(extra)}, which this compiler does not know\n")
+        res = run([])
     if res.returncode != 0:
         sys.stderr.write(res.stderr)
         raise RuntimeError(f"hipcc failed for {src}")

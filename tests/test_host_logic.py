@@ -173,3 +173,15 @@ def test_copies_of_the_distance_sums_up_to_their_limit(heads, limit):
     size = lambda n: hb.hstu_attn_workspace_bytes(hb.AttnProblem(q, q, q, q, offsets, max_seqlen=n), True)
     assert 0 < size(limit - 100) <= size(limit - 20) <= size(limit)
     assert size(limit + 1) < size(limit)
+
+
+def test_a_compiler_option_that_is_not_known_is_left_out(tmp_path, monkeypatch, capfd):
+    from paper_2602_16986_amd import build
+    (tmp_path / "one.hip").write_text("int one() { return 1; }\n")
+    monkeypatch.setattr(build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(build, "FILE_FLAGS", {"one.hip": ["-mllvm", "-an-option-of-another-compiler"]})
+    assert os.path.getsize(build._compile("one.hip", str(tmp_path))) > 0
+    assert "-an-option-of-another-compiler" in capfd.readouterr().err
+    (tmp_path / "one.hip").write_text("int one() { return }\n")
+    with pytest.raises(RuntimeError):
+        build._compile("one.hip", str(tmp_path))
