@@ -117,7 +117,7 @@ typedef struct hstu_attn_params {
  * includes fp32 partial-sum slots for key blocks that the scheduler cuts along the query
  * axis (at most 768 x 2 x 128 x head_dim floats, about 100 MB at head_dim 128) and for query blocks that the dQ pass cuts
  * along the key axis (768 x 128 x head_dim floats); the forward figure includes the same kind of slots for its query blocks
- * (50 MB at head_dim 128). */
+ * (50 MB at head_dim 128).  Small batches have fewer: two slots a block of 128 rows and head, eight in fp32. */
 size_t hstu_attn_workspace_bytes(const hstu_attn_params* p, int for_backward);
 /* The least that hstu_attn_fwd or hstu_attn_bwd accepts: the same without the room for dS (0.15 GB for the eight sequences above). */
 size_t hstu_attn_workspace_least_bytes(const hstu_attn_params* p, int for_backward);

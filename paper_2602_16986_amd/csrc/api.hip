@@ -46,6 +46,9 @@ PlanBatch plan_of(const hstu_attn_params* p) {
 // the two passes stay independent of each other (dQ recomputes S and dP).
 constexpr int64_t kDsMaxBytes = (int64_t)16 << 30;
 
+// The pipelined kernels take bias and mask from seed tables, the others the bias from a table of its own.
+inline bool seeded(const hstu_attn_params* p, bool for_backward) { return p->dtype == HSTU_BF16 && (!for_backward || p->head_dim != 128); }
+
 // One schedule for the forward; two (dQ pass, dK/dV pass) for the backward.
 Layout make_layout(const hstu_attn_params* p, int for_backward) {
   Layout l = {};
@@ -75,12 +78,14 @@ Layout make_layout(const hstu_attn_params* p, int for_backward) {
                   (int64_t)p->total_tokens / 128 + p->batch <= schedule_sorted_pairs();
   if (for_backward) { l.splits_dq = off; off += align_up((size_t)(l.slot_cap_dq / 2 + 1) * sizeof(SplitItem)); }
   if (ds) { l.ds_table = off; off += align_up(((size_t)p->total_tokens / 128 + p->batch) * 16); }
-  l.bias = off + kBiasPad * sizeof(float);
-  off += align_up(((size_t)p->num_heads * ((size_t)p->max_seqlen + 1 + kBiasPad) + kBiasPad) * sizeof(float));
-  l.seed = off;                                        // score seeds by distance (bias + mask) of the pipelined kernels
-  const size_t seed_bytes = align_up((size_t)kSeedVariants * p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float));
-  off += seed_bytes;
-  if (for_backward && p->dtype == HSTU_BF16 && p->head_dim != 128) { l.seed_up = off; off += align_up((size_t)p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float)); }
+  if (seeded(p, for_backward)) {                       // score seeds by distance (bias + mask) ...
+    const size_t table = (size_t)p->num_heads * (size_t)seed_len_for(p->max_seqlen) * sizeof(float);
+    l.seed = off; off += align_up(kSeedVariants * table);
+    if (for_backward) { l.seed_up = off; off += align_up(table); }
+  } else {                                             // ... or the bias by distance
+    l.bias = off + kBiasPad * sizeof(float);
+    off += align_up(((size_t)p->num_heads * ((size_t)p->max_seqlen + 1 + kBiasPad) + kBiasPad) * sizeof(float));
+  }
   if (!for_backward) {
     l.partial = off;
     off += align_up((size_t)l.slot_cap * fwd_block_rows(p->dtype, p->head_dim) * p->head_dim * sizeof(float));
@@ -158,8 +163,7 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   a.bias_pitch = a.bias_stride + kBiasPad;
   a.seed = nullptr;
   ex.table = p->rab_table; ex.bounds = p->rab_bounds; ex.num_buckets = p->num_buckets;
-  const bool seeded = p->dtype == HSTU_BF16 && (for_forward || p->head_dim != 128);
-  if (seeded) {                                        // these kernels take bias and mask from the seed tables
+  if (seeded(p, !for_forward)) {
     ex.seed = (float*)(ws + l.seed);
     ex.seed_len = seed_len_for(p->max_seqlen);
     ex.seed_dmax = seed_dmax_for(p->max_seqlen);
@@ -168,7 +172,7 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   }
   if (!p->rab_table) return ex;
   ex.bias_len = a.bias_stride;
-  if (!seeded) {
+  if (!seeded(p, !for_forward)) {
     a.bias = ex.bias = (float*)(ws + l.bias);
     ex.bias_pitch = a.bias_pitch;
   }

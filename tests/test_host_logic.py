@@ -185,3 +185,19 @@ def test_a_compiler_option_that_is_not_known_is_left_out(tmp_path, monkeypatch, 
     (tmp_path / "one.hip").write_text("int one() { return }\n")
     with pytest.raises(RuntimeError):
         build._compile("one.hip", str(tmp_path))
+
+
+@pytest.mark.parametrize("dtype,d,backward,floats", [("bf16", 32, False, 2), ("bf16", 128, False, 2), ("fp32", 64, False, 1), ("bf16", 64, True, 3), ("bf16", 128, True, 1),
+                                                     ("fp32", 128, True, 1)])
+def test_workspace_holds_the_tables_that_are_read(dtype, d, backward, floats):
+    """Per distance and head: two seed tables in the bf16 forwards and a third one by ascending distance in the narrow backward; the bias in fp32 and in the backward with 128
+    features.  A backward has the sums per distance as well (one copy at these lengths) and an int per distance."""
+    import torch
+    from paper_2602_16986_amd import binding as hb
+    H, lo, hi = 4, 1 << 18, (1 << 18) + 64 * 1024
+    q = torch.zeros(1, H, d, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    offsets = torch.tensor([0, 1], dtype=torch.int32)
+    size = lambda n: hb.hstu_attn_workspace_least_bytes(hb.AttnProblem(q, q, q, q, offsets, max_seqlen=n), backward)
+    assert size(lo) > 0
+    expected = 4 * (hi - lo) * (H * (floats + (1 if backward else 0)) + (1 if backward else 0))
+    assert abs(size(hi) - size(lo) - expected) <= 4096
