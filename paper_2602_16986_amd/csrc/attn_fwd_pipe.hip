@@ -24,8 +24,8 @@
 //    and those are moved to the end of the item's list and run in a second copy of the loop.
 //    That takes K for finite.  With 32 and 64 features (kExact) the scores of masked pairs are replaced after the product, whatever K held, in the
 //    sub-blocks that hold any for the wave's rows, and the output product of one with no visible pair reads zeros instead of V: rows that
-//    are not finite stay with the queries that may see them.  Costs 2-3 % on short or semi-local batches (8 x 8k-16k semi-local, 64
-//    features 193 -> 198 us, dense 807 -> 810).
+//    are not finite stay with the queries that may see them.  Such a sub-block takes 0.2 us longer: 64 features, 8 x 8k-16k dense 807 -> 810 us,
+//    semi-local 193 -> 198, 16 x 1,024 dense 31.2 -> 32.3, and where a narrow window leaves hardly any other (2 x 396, K1 = 168) 17.3 -> 19.3.
 // 3. K, V and the seed strip sit in two-stage rings in LDS, filled by direct-to-LDS loads that are issued a whole
 //    half-step before the barrier that publishes them:
 //      first half of step s:  loads V(s);               at its end: K(s+1), strip(s+1) have landed -> barrier

@@ -24,8 +24,8 @@ namespace hstu {
 // launch and slots_per_tile follow from these; bf16 targets put a piece at .46 (forward) or .7 of a unit's share, fp32 ones at one share (a workgroup or two fill a
 // unit).  The rule before (a slot's share; bf16 lists of many blocks uncut up to 60, 20 or 24 tiles more; fp32 from a few tiles on) did not ask how many slots there
 // would be: 32 x 1,000 tokens, one head of 128, 256 + 64 semi-local, backward 68 -> 60 us; the forward of 2 x 1,365-3,018, 8 heads of 64, 41 -> 33; of 4 x 900, 8 heads of 64
-// in fp32 69 -> 55.  Over those batches, geometric mean: forward 1.02 (128), 1.02 (64), 1.02 (32), backward 1.02, 1.01, 1.01, fp32 1.00-1.03 times as fast; single
-// ones 7 % slower (fp32, 4 x 500) to 20 % faster.
+// in fp32 69 -> 55.  Over those batches, geometric mean: bf16 forward 1.02-1.03, backward 1.01-1.02, fp32 1.00-1.03 times as fast; single ones from 9 % slower (forward
+// of 10 x 1,894-4,048 129 -> 141) to 25 % faster.
 struct CutRule { int target_chunks, min_chunk, launch, slots_per_tile; };
 // (in fp32 with a quarter more than 2 x chunk)
 #if defined(__HIPCC__)
