@@ -250,8 +250,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_narrow_kernel(const Attn
     }
     if (CAND) vis |= selfc >= 0 && selfc < 32 ? 1u << selfc : 0u;
     if (!x_ok) vis = 0u;
-    mask_scores(sc, vis, kMasked);
-    mask_scores(dp, vis, 0.f);
+    mask_scores<true>(vis, sc, kMasked, dp);
     return false;
   };
   auto seed = [&](f32x16& acc, int strip_stage) {

@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kThreads, Pipe<D>::kWgPerCu) void attn_fwd_pipe_ker
     const int y0 = yt * kBN + 4 * hf, last = min(px, g.n - 1) - y0, selfc = CAND && x >= g.n ? x - y0 : -1;
     uint32_t vis = ~bits_from(last + 1) & (g.K1 < 0 ? ~0u : bits_from(px - g.K1 + 1 - y0) | ~bits_from(g.K2 - y0));      // as in mask_seed: bit c
     if (CAND) vis |= selfc >= 0 && selfc < 32 ? 1u << selfc : 0u;
-    mask_scores(acc, x_ok ? vis : 0u, kMasked);
+    mask_scores<false>(x_ok ? vis : 0u, acc, kMasked, acc);
     return false;
   };
 

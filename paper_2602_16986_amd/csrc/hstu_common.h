@@ -48,12 +48,16 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ uint32_t bits_from(int lo) { return lo > 31 ? 0u : ~0u << max(lo, 0); }
 
 // Of a 32 x 32 block of scores (register r of a lane: streamed row 8 (r / 4) + r % 4, + 4 in the upper half-wave): `masked` where the row's bit of `vis` is 0,
-// whatever stood there.  In bit operations, three a score at most: comparisons would take a pair of scalar registers each.
-__device__ __forceinline__ void mask_scores(f32x16& v, uint32_t vis, float masked) {
+// whatever stood there; a second block, if there is one, with zeros.  Three bit operations a score: a bit field, v_bfi, v_and.  (The mask is kept
+// from the compiler, which makes comparisons of it: one instruction more, and a pair of scalar registers each.)
+template <bool ZERO>
+__device__ __forceinline__ void mask_scores(uint32_t vis, f32x16& v, float masked, f32x16& zeroed) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const uint32_t m = (uint32_t)((int)(vis << (31 - (8 * (r >> 2) + (r & 3)))) >> 31);
+    uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)vis, 8 * (r >> 2) + (r & 3), 1);
+    asm volatile("" : "+v"(m));
     v[r] = __uint_as_float((__float_as_uint(v[r]) & m) | (__float_as_uint(masked) & ~m));
+    if (ZERO) zeroed[r] = __uint_as_float(__float_as_uint(zeroed[r]) & m);
   }
 }
 
