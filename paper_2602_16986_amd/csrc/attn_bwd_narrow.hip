@@ -12,7 +12,7 @@
 // goes through as it is; in any other the score and dP of masked pairs are replaced between the halves (-1e30 leaves P = -0 and
 // dS / dP = 0), whatever their rows held, and the output products of a tile with no visible pair read zeros instead of its rows: rows that
 // are not finite stay with the tokens that may see them.  (Against a mask in the seeds, which needs finite rows: 8 x 8k-16k, 64 features, semi-local
-// 639 -> 650 us, dense 2,695 -> 2,712; 24 x 1-3,000 semi-local 173 -> 179; 2 x 396, K1 = 168, where hardly a tile is full, 32.9 -> 37.6.)
+// 586 -> 604 us, dense 2,413 -> 2,430; 24 x 1-3,000 semi-local 196 -> 201; 2 x 396, K1 = 168, where hardly a tile is full, 32.6 -> 36.9.)
 //
 // Tiles and seed strips are loaded straight to LDS three steps ahead: those of step s + 3 are issued in step s, have landed and are published
 // at the end of step s + 1, and the first fragments are read at the end of step s + 2; the output products read tile s - 1: five stages.
