@@ -219,8 +219,9 @@ int hstu_truncate_bwd(int32_t batch, int64_t total_tokens, const int32_t* seq_of
  * d_w1 [4*H*d, E], d_gated_norm_w [H*d], d_w2 [E, H*d], all overwritten.  dU, dV, dQ, dK are written
  * straight into the column blocks of one gradient buffer (no concatenation).
  *
- * The four projections run through hipBLASLt (plain library GEMMs); the first call on a device creates a
- * hipBLASLt handle.  The GEMM kernels are chosen once per SHAPE CLASS, which is the layer's dimensions together with
+ * The products over token rows run in this library's own kernels, unless the reduction is 1024 long or more and the product
+ * takes 10^11 multiply-adds or more; those, and the weight gradients of widths that are not multiples of 128, run through hipBLASLt.  The first
+ * such call on a device creates a hipBLASLt handle.  The library's GEMM kernels are chosen once per SHAPE CLASS, which is the layer's dimensions together with
  * the token count T rounded up to a power of two: the first call of a class runs the library's candidate kernels on
  * `stream`, waits for them and keeps the fastest (that call allocates inside the GEMM library, blocks the host and
  * must not be captured into a graph; hstu_layer_gemm_tunings counts these events).  Every later call of the class,

@@ -1,0 +1,353 @@
+// Products of token rows with a weight matrix (the layer's two projections and the gradients of their inputs; paper Eq. 2 and f2 of
+// Eq. 5), bf16 operands, fp32 accumulation, one rounding:
+//   D[m, n] = epilogue( sum_k A[m, k] W[n, k] )     W [N, K] row-major (kGemmNT) or [K, N] row-major (kGemmNN)
+// with the layer's pointwise work in the epilogue: SiLU with the gate's columns sent to a tensor of their own, the pre-activations
+// beside their SiLU, or the residual rows added.
+//
+// A workgroup owns tiles of WM 32 MI token rows x WN 64 columns, one of its WM WN multiplying waves 32 MI x 64 of it; the token rows sit on the
+// accumulators' lane axis, the columns on the register axis.  Both operands arrive in LDS by direct-to-LDS loads, 64 k at a time, one barrier per k-tile.
+// What bounds it, and what follows (87,728 rows, 2048 columns, K = 512, SiLU; the library's two products with it in their epilogue: 294 us):
+// 1. The L2's request rate.  Every load covers whole 128-byte lines: with 32 k at a time, 64-byte halves of lines whose other halves have left the
+//    first-level cache when they are wanted, 303 us.
+// 2. The stores of the output, which a burst of every compute unit at the end of its tile leaves to the memory (without them 185 us).  Memory operations of a wave
+//    complete in order, so a wave that stores cannot wait for a later load without waiting for the stores: four further waves only load, across
+//    tiles (the workgroups are persistent), and run on while the others store.  288 us without them.  Stores are non-temporal (282 without) and leave in whole lines:
+//    the accumulators go through LDS as fp32, 16 rows x 64 columns at a time and wave by wave (no barrier).  252 us with both.
+// 3. Power, then: products and LDS reads alone run at 1.1-1.2 PFLOP/s.
+// A wave's last products of a k-tile follow the barrier that publishes the next one, whose first operands are read in between: 250 us, and 346 instead of 362
+// for 40,000 x 1024 x K = 4096.
+// Rows of 128 bytes (operands with k contiguous) keep 16-byte chunk c of row r at c ^ (r / 2) % 8; rows of W [K, N], read through the LDS transpose loads, at
+// c ^ (4 (r % 4) + (r / 4) % 4): every read is free of bank conflicts, and the swizzle costs nothing because it is applied to the loads' source addresses.
+#include <algorithm>
+
+#include "hstu_common.h"
+#include "hstu_kernels.h"
+
+namespace hstu {
+namespace {
+
+typedef __attribute__((address_space(3))) void* lds_void;
+typedef __attribute__((address_space(3))) short4v* lds_s4;
+typedef __attribute__((address_space(3))) const bf16x8* lds_b8;
+typedef __attribute__((address_space(3))) f32x4* lds_f4;
+
+constexpr int kBK = 64;
+enum { kTile64Deep = 1, kTile64, kTile128Deep, kTile128, kTile192, kTile256 };     // by token rows of a tile; deep: one workgroup per compute unit, more stages
+constexpr uint32_t kOutside = 0x80000000u;               // a lane offset beyond every range: the load returns zeros
+
+// WM x WN waves multiply, kLoaders more only load.
+constexpr int kLoaders = 4;
+template <int WM, int WN, int MI, int STAGES>
+struct Tile {
+  static constexpr int kWaves = WM * WN, kThreads = 64 * (kWaves + kLoaders);
+  static constexpr int kRows = 32 * MI * WM, kCols = 64 * WN;
+  static constexpr int kA = kRows * kBK * 2, kW = kCols * kBK * 2, kStage = kA + kW;
+  static constexpr int kLoadsA = kRows / 8 / kLoaders, kLoadsW = kCols / 8 / kLoaders, kLoads = kLoadsA + kLoadsW;   // wave-level loads (1 KB) of a loader per stage
+  static constexpr int kArea = 32 * 32 * 4;                                                                          // a wave's part of the epilogue's staging
+  static constexpr int kSmem = STAGES * kStage + kWaves * kArea;
+  static constexpr int kWgPerCu = (160 << 10) / kSmem < 2 ? 1 : 2;
+  static constexpr int kWavesPerSimd = (kWaves + kLoaders) / 4 * kWgPerCu;
+  static_assert(kRows % (8 * kLoaders) == 0 && kCols % (8 * kLoaders) == 0, "every loader loads the same number of rows");
+};
+
+__device__ __forceinline__ float silu(float t) { return t * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * t)); }
+
+__device__ __forceinline__ void store8(__bf16* at, const float (&v)[8]) {
+  const u32x4 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+  __builtin_nontemporal_store(o, (u32x4*)at);
+}
+
+template <int WM, int WN, int MI, int STAGES, bool NN, int EPI>
+__global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN, MI, STAGES>::kWavesPerSimd)) void gemm_rows_kernel(const GemmRowsArgs p, int tiles) {
+  using S = Tile<WM, WN, MI, STAGES>;
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hf = lane >> 5, l32 = lane & 31, i16 = lane & 15, grp16 = lane >> 4;
+  const int nk = (p.K + kBK - 1) / kBK;
+  // Workgroups go to the 8 dies round-robin; a die takes a contiguous range of tiles, columns first: the tiles of one range of token rows run
+  // beside each other and the rows come from memory once.
+  const int tiles_n = (p.N + S::kCols - 1) / S::kCols;
+  const int xcd = blockIdx.x % kNumXcd, per_die = (gridDim.x - xcd + kNumXcd - 1) / kNumXcd;
+  int tile = xcd * (tiles / kNumXcd) + min(xcd, tiles % kNumXcd);
+  const int tile_end = tile + tiles / kNumXcd + (xcd < tiles % kNumXcd ? 1 : 0);
+  tile += blockIdx.x / kNumXcd;
+  if (tile >= tile_end) return;
+
+  constexpr int kPitchW = S::kCols * 2;
+  const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void)smem;
+  if (wave >= S::kWaves) {
+    // ---- global -> LDS.  Load c of a loader: rows 8 (lw + kLoaders c) .. + 7 of an operand with k contiguous.  Of W [K, N]: 1 KB of whole rows.
+    constexpr int kRowsPerLoad = 1024 / kPitchW, kChunks = kPitchW / 16;
+    const int lw = wave - S::kWaves;
+    const uint32_t rowa = (uint32_t)(p.lda * 2), roww = (uint32_t)(p.ldw * 2);
+    const uint32_t chunk = (uint32_t)((lane & 7) ^ ((4 * lw + (lane >> 4)) & 7));
+    const uint32_t va = (uint32_t)(8 * lw + (lane >> 3)) * rowa + 16 * chunk;
+    const bool k_tail = (p.K % kBK) != 0;
+    const bool in_tail = (int)(8 * chunk) < p.K % kBK;                            // (of the last k-tile, where that is not whole)
+    const uint32_t vw = (uint32_t)(8 * lw + (lane >> 3)) * roww + 16 * chunk;
+    // A descriptor holds the rows of the tile (rows past it read as zero); k advances in the scalar offset (for W [K, N] the descriptor advances).
+    auto rsrc = [&](uint64_t addr, int left, int most, uint32_t row) -> i32x4 {
+      return (i32x4){(int)(uint32_t)addr, (int)(uint32_t)(addr >> 32), (int)(left > 0 ? (uint32_t)min(left, most) * row : 0u), 0x00020000};
+    };
+    auto dma16 = [&](const i32x4& rs, uint32_t voff, uint32_t soff, uint32_t dst) {
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+    };
+    i32x4 ra, rw;
+    int load_n0 = 0;
+    auto aim = [&](int t) {                                                       // the loads at tile t
+      const int tm = t / tiles_n;
+      const int64_t m0 = (int64_t)tm * S::kRows;
+      load_n0 = (t - tm * tiles_n) * S::kCols;
+      ra = rsrc((uint64_t)(uintptr_t)p.A + (uint64_t)m0 * rowa, (int)min((int64_t)S::kRows, p.M - m0), S::kRows, rowa);
+      if (!NN) rw = rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)load_n0 * roww, p.N - load_n0, S::kCols, roww);
+    };
+    // load c of k-tile `step` into stage s
+    auto issue = [&](int step, int s, int c) {
+      const bool outside = k_tail && step == nk - 1 && !in_tail;
+      const uint32_t dst = smem_base + (uint32_t)(s * S::kStage + lw * 1024), k_off = (uint32_t)step * (2 * kBK);
+      if (c < S::kLoadsA) {
+        dma16(ra, (outside ? kOutside : va) + (uint32_t)(8 * kLoaders * c) * rowa, k_off, dst + (uint32_t)(kLoaders * 1024 * c));
+        return;
+      }
+      const int cw = c - S::kLoadsA;
+      const uint32_t at = dst + (uint32_t)(S::kA + kLoaders * 1024 * cw);
+      if (NN) {
+        const int first = kRowsPerLoad * (lw + kLoaders * cw), row = step * kBK + first;
+        const int r = first + lane / kChunks, ch = (lane % kChunks) ^ (4 * (r & 3) + ((r >> 2) & 3));
+        const uint32_t v = load_n0 + 8 * ch < p.N ? (uint32_t)(lane / kChunks) * roww + 16 * (uint32_t)ch : kOutside;
+        dma16(rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)row * roww + (uint64_t)load_n0 * 2, p.K - row, kRowsPerLoad, roww), v, 0, at);
+      } else {
+        dma16(rw, (outside ? kOutside : vw) + (uint32_t)(8 * kLoaders * cw) * roww, k_off, at);
+      }
+    };
+    // Loads run STAGES - 1 k-tiles ahead of the products, across tiles.  A loader waits for its loads alone: in a wave that stores as well, waiting for a
+    // load means waiting for every store in front of it.
+    int t = tile, step = 0, s = 0, flying = 0;
+    aim(t);
+    auto next = [&]() {
+#pragma unroll
+      for (int c = 0; c < S::kLoads; ++c) issue(step, s, c);
+      ++flying;
+      s = s == STAGES - 1 ? 0 : s + 1;
+      if (++step == nk) {
+        step = 0;
+        t += per_die;
+        if (t < tile_end) aim(t);
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i)
+      if (t < tile_end) next();
+    while (flying > 0) {
+      if (flying == STAGES - 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(S::kLoads * (STAGES - 2)) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+      --flying;
+      if (t < tile_end) next();
+    }
+    return;
+  }
+
+  // ---- LDS -> operands
+  const int wm = wave / WN, wn = wave % WN;
+  const uint32_t row128 = (uint32_t)(l32 * 128 + 16 * (hf ^ ((l32 >> 1) & 7)));   // k-step ks of a tile: chunk ^ 2 ks
+  const uint32_t ta = smem_base + (uint32_t)(wm * 32 * MI * 128) + row128;
+  const uint32_t tw = smem_base + S::kA + (uint32_t)(wn * 64 * 128) + row128;
+  // Transposed (W [K, N]): lanes of a half-wave take rows 8 hf + 0..3 (then + 4) of 16 k; lane l32 ends up with column l32's 8 values of k.
+  const int vchunk = 2 * (grp16 & 1) + ((i16 & 3) >> 1), vbyte = 8 * (i16 & 1), vrow = i16 >> 2;
+  const uint32_t tr = smem_base + S::kA + (uint32_t)((8 * hf + vrow) * kPitchW + vbyte);
+  const uint32_t tr_lo = (uint32_t)(16 * (vchunk ^ (2 * hf) ^ (4 * vrow))), tr_hi = (uint32_t)(16 * (vchunk ^ (2 * hf + 1) ^ (4 * vrow)));
+  auto wfrag = [&](uint32_t stage_off, int ks, int ni) -> bf16x8 {
+    if (NN) {
+      const uint32_t f = (uint32_t)(16 * (8 * wn + 4 * ni));                     // chunk of the fragment's first column
+      const uint32_t at = tr + stage_off + (uint32_t)(ks * 16 * kPitchW);
+      const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_lo ^ f)));
+      const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_hi ^ f) + 4 * kPitchW));
+      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    return *(lds_b8)(uintptr_t)((tw ^ (uint32_t)(32 * ks)) + stage_off + (uint32_t)(ni * 32 * 128));
+  };
+  auto afrag = [&](uint32_t stage_off, int ks, int mi) -> bf16x8 {
+    return *(lds_b8)(uintptr_t)((ta ^ (uint32_t)(32 * ks)) + stage_off + (uint32_t)(mi * 32 * 128));
+  };
+
+  constexpr int kSteps = kBK / 16, kTotal = kSteps * MI;
+  bf16x8 wf[2][2], af[2];
+  uint32_t off = 0;                                                                // of the k-tile's stage
+  auto first_operands = [&]() {
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) wf[0][ni] = wfrag(off, 0, ni);
+    af[0] = afrag(off, 0, 0);
+  };
+  // this wave's reads of its k-tile are done and the loaders' loads of the next one have landed: the barrier frees the one and publishes the other
+  auto turn = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  turn();
+  for (;;) {
+    const int tm = tile / tiles_n;
+    const int64_t m0 = (int64_t)tm * S::kRows;
+    const int n0 = (tile - tm * tiles_n) * S::kCols;
+    const int next = tile + per_die;
+    f32x16 acc[2][MI];
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[ni][mi][r] = 0.f;
+    first_operands();
+    for (int step = 0; step < nk; ++step) {
+      const uint32_t at = off;
+#pragma unroll
+      for (int n = 0; n < kTotal; ++n) {                                           // two products each; the operands of the next one are read first
+        const int ks = n / MI, mi = n % MI;
+        if (n + 1 < kTotal) {
+          af[(n + 1) & 1] = afrag(at, (n + 1) / MI, (n + 1) % MI);
+          if (mi == 0 && ks + 1 < kSteps) {
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) wf[(ks + 1) & 1][ni] = wfrag(at, ks + 1, ni);
+          }
+        } else if (step + 1 < nk || next < tile_end) {
+          turn();
+          off = off == (uint32_t)((STAGES - 1) * S::kStage) ? 0u : off + S::kStage;
+          if (step + 1 < nk) first_operands();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][ni], af[n & 1], acc[ni][mi], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+
+    // ---- epilogue: 16 token rows x 64 columns at a time through the wave's own part of the staging (chunk c of row r at c ^ r)
+    const int rows = (int)min((int64_t)S::kRows, p.M - m0) - 32 * MI * wm;         // of the wave's part of the tile
+    const uint32_t area = smem_base + (uint32_t)(STAGES * S::kStage + wave * S::kArea);
+    const uint32_t put = area + (uint32_t)((l32 & 15) * 256 + 16 * (hf ^ (l32 & 15)));
+    const uint32_t get = area + (uint32_t)((lane >> 3) * 256 + 16 * ((2 * (lane & 7)) ^ (lane >> 3)));     // and 8 rows further: chunk ^ 8
+    const int col = n0 + 64 * wn + 8 * (lane & 7);
+    const bool col_ok = col < p.N;
+    const bool first = EPI != kEpiPlain && EPI != kEpiResidual && col < p.split;   // of the gate
+    const int64_t w0 = m0 + 32 * MI * wm + (lane >> 3);
+    const int64_t ldd = EPI == kEpiSiluSplit && first ? p.ldd0 : p.ldd;
+    __bf16* const d = (EPI == kEpiSiluSplit && first ? (__bf16*)p.D0 : (__bf16*)p.D) + w0 * ldd + col;
+    u32x4 res[2];
+    auto fetch = [&](int part) {
+#pragma unroll
+      for (int it = 0; it < 2; ++it) {
+        const int row = 16 * part + 8 * it;
+        if (col_ok && row + (lane >> 3) < rows) res[it] = *(const u32x4*)((const __bf16*)p.C + (w0 + row) * p.ldc + col);
+      }
+    };
+    if (EPI == kEpiResidual) fetch(0);
+#pragma unroll
+    for (int part = 0; part < 2 * MI; ++part) {
+      const int mi = part / 2;
+      if ((l32 >> 4) == part % 2) {
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *(lds_f4)(uintptr_t)(put ^ (uint32_t)(128 * ni + 32 * q)) =
+                (f32x4){acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]};
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                           // (the wave's own writes: no other wave touches its part)
+#pragma unroll
+      for (int it = 0; it < 2; ++it) {
+        const uint32_t at = (get ^ (uint32_t)(128 * it)) + (uint32_t)(8 * 256 * it);
+        const f32x4 lo = *(lds_f4)(uintptr_t)at, hi = *(lds_f4)(uintptr_t)(at ^ 16);
+        const int row = 16 * part + 8 * it;
+        float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        if (!col_ok || row + (lane >> 3) >= rows) continue;
+        if (EPI == kEpiResidual) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[2 * e] += __uint_as_float(res[it][e] << 16);
+            v[2 * e + 1] += __uint_as_float(res[it][e] & 0xFFFF0000u);
+          }
+        }
+        if (EPI == kEpiSiluSplit) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = silu(v[e]);
+        }
+        store8(d + row * ldd, v);
+        if (EPI == kEpiPreAndSilu && !first) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = silu(v[e]);
+          store8((__bf16*)p.D0 + (w0 + row) * p.ldd0 + col, v);
+        }
+      }
+      if (EPI == kEpiResidual && part + 1 < 2 * MI) fetch(part + 1);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    tile = next;
+    if (tile >= tile_end) return;
+  }
+}
+
+template <int WM, int WN, int MI, int STAGES, bool NN, int EPI>
+hipError_t launch_tile(const GemmRowsArgs& p, hipStream_t stream) {
+  using S = Tile<WM, WN, MI, STAGES>;
+  static bool attr_set[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!attr_set[dev]) {
+    const hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<WM, WN, MI, STAGES, NN, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, S::kSmem);
+    if (e != hipSuccess) return e;
+    attr_set[dev] = true;
+  }
+  const int64_t tiles = ((p.M + S::kRows - 1) / S::kRows) * ((p.N + S::kCols - 1) / S::kCols);
+  if (tiles > INT32_MAX / 2) return hipErrorInvalidValue;
+  const int grid = (int)std::min<int64_t>(tiles, 256 * S::kWgPerCu);
+  hipLaunchKernelGGL((gemm_rows_kernel<WM, WN, MI, STAGES, NN, EPI>), dim3(grid), dim3(S::kThreads), S::kSmem, stream, p, (int)tiles);
+  return hipGetLastError();
+}
+template <bool NN, int EPI>
+hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
+  switch (tile) {
+    case kTile64Deep: return launch_tile<2, 2, 1, 5, NN, EPI>(p, stream);
+    case kTile64: return launch_tile<2, 2, 1, 2, NN, EPI>(p, stream);
+    case kTile128Deep: return launch_tile<2, 2, 2, 4, NN, EPI>(p, stream);
+    case kTile128: return launch_tile<2, 2, 2, 2, NN, EPI>(p, stream);
+    case kTile192: return launch_tile<2, 4, 3, 2, NN, EPI>(p, stream);
+    default: return launch_tile<2, 4, 4, 2, NN, EPI>(p, stream);
+  }
+}
+
+}  // namespace
+
+// The tile with the least time where a compute unit works through its share of the tiles at the tile's rate (PFLOP/s that the kernels reach on
+// many tiles, K = 512: bytes through the L2 per product fall with the tile; the widest one has no registers left to keep residual rows in).  Up to a tile per
+// compute unit, all of a unit's LDS is one workgroup's: more k-tiles in flight.  us for the tiles of 64 (deep), 64, 128 (deep), 128, 192, 256 rows:
+//   6,418 x 2048, K = 512, SiLU             -    23.9    -    22.5  28.4  21.0 *    (two library products: 34)
+//   6,418 x 512, K = 512, W [K, N]          -     8.9   8.3 *  8.1  13.3  16.2      (16)
+//   6,418 x 512, K = 2048, W [K, N]         -    23.7  19.1 * 24.5  36.2  42.1      (23)
+//   20,000 x 512, K = 2048, W [K, N]        -    63.7    -    51.9  41.1 * 48.2      (42)
+//   87,728 x 512, K = 2048, W [K, N]        -   342.6    -   247.8 216.1 194.3 *    (182-197)
+//   1,200 x 512, K = 512, residual         6.1 *  6.3   8.1   8.0  13.0  18.6
+int gemm_rows_tile(int64_t M, int N, int epilogue) {
+  static const struct { int rows, cols, tile, deep; double rate; } kinds[4] = {
+      {64, 128, kTile64, kTile64Deep, 0.50}, {128, 128, kTile128, kTile128Deep, 0.68}, {192, 256, kTile192, kTile192, 0.80}, {256, 256, kTile256, kTile256, 0.87}};
+  int best = 0;
+  double least = 0;
+  for (const auto& k : kinds) {
+    const int64_t tiles = (M + k.rows - 1) / k.rows * ((N + k.cols - 1) / k.cols);
+    const double rate = k.tile == kTile256 && epilogue == kEpiResidual ? 0.70 : k.rate;
+    const double time = (double)((tiles + 255) / 256) * k.rows * k.cols / rate;
+    if (best == 0 || time < least) { least = time; best = tiles <= 256 ? k.deep : k.tile; }
+  }
+  return best;
+}
+
+// With long rows and much work the library's kernels are the faster ones (with SiLU and all: 30,000 rows, widths 1024 and 1024, a layer's forward 429 us with the
+// library, 457 with these; 8,000 rows 141 and 128); between the two lines both are alike.
+bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)M * (double)N * (double)K < 1e11; }
+
+hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile) {
+  if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || p.K % 8 != 0) return hipErrorInvalidValue;
+  if (tile == 0) tile = gemm_rows_tile(p.M, p.N, epilogue);
+  if (op == kGemmNT && epilogue == kEpiSiluSplit) return launch_epi<false, kEpiSiluSplit>(p, tile, stream);
+  if (op == kGemmNT && epilogue == kEpiPreAndSilu) return launch_epi<false, kEpiPreAndSilu>(p, tile, stream);
+  if (op == kGemmNT && epilogue == kEpiResidual) return launch_epi<false, kEpiResidual>(p, tile, stream);
+  if (op == kGemmNN && epilogue == kEpiPlain) return launch_epi<true, kEpiPlain>(p, tile, stream);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace hstu

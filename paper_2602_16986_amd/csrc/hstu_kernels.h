@@ -203,6 +203,22 @@ long gemm_bf16_tunings();
 int gemm_bf16(int op, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, const void* C,
               int64_t ldc, void* D, int64_t ldd, bool d_fp32, void* ws, size_t ws_bytes, hipStream_t stream, bool silu = false);
 
+// gemm_rows.hip: products of token rows with a weight matrix, the layer's pointwise work in the epilogue.
+struct GemmRowsArgs {
+  int64_t M; int32_t N, K;                  // N and K multiples of 8
+  const void* A; int64_t lda;               // [M, K]
+  const void* W; int64_t ldw;               // [N, K] (kGemmNT) or [K, N] (kGemmNN)
+  const void* C; int64_t ldc;               // kEpiResidual: rows added before the one rounding
+  void* D; int64_t ldd;
+  void* D0; int64_t ldd0;                   // second output, see the epilogues
+  int32_t split;                            // column, a multiple of 8
+};
+// kEpiSiluSplit: SiLU; columns before `split` go to D0, the others to D (both at their own column).
+// kEpiPreAndSilu: D gets the product, D0 the SiLU of the columns from `split` on.
+enum { kEpiPlain = 0, kEpiResidual = 1, kEpiSiluSplit = 2, kEpiPreAndSilu = 3 };
+bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K);      // over the library (gemm.hip)
+hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile = 0);   // tile: 0 by size
+
 // fp8_gemm.hip: D[M,N] (bf16) = a_scale[m] b_scale[n] (Aq[M,K] Bq[N,K]^T) + C[M,N] (bf16 or nullptr), E4M3 codes
 bool fp8_gemm_supported(int N, int K);
 hipError_t launch_fp8_gemm_bias2d(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale,

@@ -81,6 +81,11 @@ LayerLayout make_layer_layout(const hstu_layer_params* p, int for_backward) {
 }
 
 inline bool bad16(const void* ptr) { return ((uintptr_t)ptr & 15u) != 0; }
+GemmRowsArgs rows_product(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* D, int64_t ldd) {
+  GemmRowsArgs g = {};
+  g.M = M; g.N = (int32_t)N; g.K = (int32_t)K; g.A = A; g.lda = lda; g.W = W; g.ldw = ldw; g.D = D; g.ldd = ldd;
+  return g;
+}
 inline int gemm_status(int rc) { return rc == 0 ? HSTU_OK : (rc == -2 ? HSTU_ERR_UNSUPPORTED : HSTU_ERR_LAUNCH); }
 
 }  // namespace
@@ -138,6 +143,11 @@ int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u
     ProfScope ps("fp8_gemm_uvqk", stream);
     if (launch_fp8_gemm_silu(T, (int)(4 * HD), (int)E, xn, xscale, p->w1_q, p->w1_scale, act, u_saved, (int)HD, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
+  } else if (gemm_rows_preferred(T, 4 * HD, E)) {  // Eq. 2: [U V Q K] = SiLU(X W1^T), the gate straight to the saved tensor, V, Q, K to their column blocks
+    ProfScope ps("gemm_uvqk", stream);
+    GemmRowsArgs g = rows_product(T, 4 * HD, E, xn, E, p->w1, E, act, 4 * HD);
+    g.D0 = u_saved; g.ldd0 = HD; g.split = (int32_t)HD;
+    if (launch_gemm_rows(g, kGemmNT, kEpiSiluSplit, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
   } else {
     // Eq. 2: [U V Q K] = SiLU(X W1^T), SiLU in the GEMM library's epilogue: the gate's rows of W1 go straight to the saved-U
     // tensor, the V, Q, K rows to their column blocks of the projection buffer.  A library build without such a kernel
@@ -183,6 +193,11 @@ int hstu_layer_fwd(const hstu_layer_params* p, const void* z, void* out, void* u
   }
   {  // f2 and the residual (Eq. 5): out = Y W2^T + Z, the residual as the GEMM's additive operand
     ProfScope ps("gemm_out", stream);
+    if (gemm_rows_preferred(T, E, HD)) {
+      GemmRowsArgs g = rows_product(T, E, HD, y, HD, p->w2, HD, out, E);
+      g.C = z; g.ldc = E;
+      return launch_gemm_rows(g, kGemmNT, kEpiResidual, stream) == hipSuccess ? HSTU_OK : HSTU_ERR_LAUNCH;
+    }
     st = gemm_status(gemm_bf16(kGemmNT, T, E, HD, y, HD, p->w2, HD, z, E, out, E, false, ws + l.gemm, kGemmWorkspace, stream));
     if (st != HSTU_OK) return st;
   }
@@ -226,13 +241,17 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
   __bf16* dxn = (__bf16*)(ws + l.dxn);
   float* partial = (float*)(ws + l.norm_partial);
   void* gws = ws + l.gemm;
-  const bool fp8 = p->w1_q != nullptr;
+  const bool fp8 = p->w1_q != nullptr, own_uvqk = !fp8 && gemm_rows_preferred(T, 4 * HD, E);
   // Ordered by what each step needs, not by the forward's order.
   // No kernel of its own for the SiLU backward: every producer of a projection gradient multiplies by SiLU' as it stores.
   {  // Eq. 5 / f2, out = Y W2^T + Z:  dY = dout W2
     ProfScope ps("gemm_dy", stream);
-    st = gemm_status(gemm_bf16(kGemmNN, T, HD, E, dout, E, p->w2, HD, nullptr, 0, dy, HD, false, gws, kGemmWorkspace, stream));
-    if (st != HSTU_OK) return st;
+    if (gemm_rows_preferred(T, HD, E)) {
+      if (launch_gemm_rows(rows_product(T, HD, E, dout, E, p->w2, HD, dy, HD), kGemmNN, kEpiPlain, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+    } else {
+      st = gemm_status(gemm_bf16(kGemmNN, T, HD, E, dout, E, p->w2, HD, nullptr, 0, dy, HD, false, gws, kGemmWorkspace, stream));
+      if (st != HSTU_OK) return st;
+    }
   }
   {  // Eq. 1 again: the normalised input from the saved statistics (in bf16: the weight gradient needs it in any case)
     ProfScope ps("layer_norm_fwd", stream);
@@ -255,7 +274,12 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
     ProfScope ps("fp8_gemm_uvqk", stream);
     if (launch_fp8_gemm_bias2d(T, (int)(4 * HD), (int)E, dxn, xscale, p->w1_q, p->w1_scale, nullptr, pre, stream) != hipSuccess)
       return HSTU_ERR_LAUNCH;
-  } else {  // rematerialise U, V, Q, K; the pre-activations stay for the SiLU backward
+  } else if (own_uvqk) {  // rematerialise U, V, Q, K; the pre-activations stay for the SiLU backward, V, Q, K leave activated as well (the gate was saved)
+    ProfScope ps("gemm_uvqk", stream);
+    GemmRowsArgs g = rows_product(T, 4 * HD, E, xn, E, p->w1, E, pre, 4 * HD);
+    g.D0 = act; g.ldd0 = 4 * HD; g.split = (int32_t)HD;
+    if (launch_gemm_rows(g, kGemmNT, kEpiPreAndSilu, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+  } else {  // likewise through the library, and a SiLU pass behind the gated norm
     ProfScope ps("gemm_uvqk", stream);
     st = gemm_status(gemm_bf16(kGemmNT, T, 4 * HD, E, xn, E, p->w1, E, nullptr, 0, pre, 4 * HD, false, gws, kGemmWorkspace, stream));
     if (st != HSTU_OK) return st;
@@ -271,7 +295,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
     n.residual = nullptr; n.sres = 0; n.dgamma = d_gated_norm_w; n.dbeta = nullptr;
     if (launch_norm_bwd(n, partial, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
   }
-  {
+  if (!own_uvqk) {
     ProfScope ps("silu_fwd", stream);
     // (V, Q, K only: the gate's activation is the saved tensor, nothing reads it from this buffer)
     if (launch_silu_fwd(T, (int)(4 * HD), pre, act, nullptr, 0, stream, (int)HD) != hipSuccess) return HSTU_ERR_LAUNCH;
@@ -282,8 +306,12 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
   if (st != HSTU_OK) return st;
   {  // pre = X W1^T:  dX = dpre W1,  dW1 = dpre^T X
     ProfScope ps("gemm_dxn", stream);
-    st = gemm_status(gemm_bf16(kGemmNN, T, E, 4 * HD, dact, 4 * HD, p->w1, E, nullptr, 0, dxn, E, false, gws, kGemmWorkspace, stream));
-    if (st != HSTU_OK) return st;
+    if (gemm_rows_preferred(T, E, 4 * HD)) {
+      if (launch_gemm_rows(rows_product(T, E, 4 * HD, dact, 4 * HD, p->w1, E, dxn, E), kGemmNN, kEpiPlain, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+    } else {
+      st = gemm_status(gemm_bf16(kGemmNN, T, E, 4 * HD, dact, 4 * HD, p->w1, E, nullptr, 0, dxn, E, false, gws, kGemmWorkspace, stream));
+      if (st != HSTU_OK) return st;
+    }
   }
   {
     ProfScope ps("gemm_dw1", stream);
