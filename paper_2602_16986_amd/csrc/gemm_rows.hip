@@ -1,6 +1,7 @@
-// Products of token rows with a weight matrix (the layer's two projections and the gradients of their inputs; paper Eq. 2 and f2 of
+// Products over token rows (the layer's two projections, the gradients of their inputs and of their weights; paper Eq. 2 and f2 of
 // Eq. 5), bf16 operands, fp32 accumulation, one rounding:
 //   D[m, n] = epilogue( sum_k A[m, k] W[n, k] )     W [N, K] row-major (kGemmNT) or [K, N] row-major (kGemmNN)
+//   D[m, n] = sum_k A[k, m] W[k, n]                 kGemmTN: k are the token rows, cut into slabs whose fp32 sums leave one by one (gemm_tn.hip)
 // with the layer's pointwise work in the epilogue: SiLU with the gate's columns sent to a tensor of their own, the pre-activations
 // beside their SiLU, or the residual rows added.
 //
@@ -19,6 +20,7 @@
 // Rows of 128 bytes (operands with k contiguous) keep 16-byte chunk c of row r at c ^ (r / 2) % 8; rows of W [K, N], read through the LDS transpose loads, at
 // c ^ (4 (r % 4) + (r / 4) % 4): every read is free of bank conflicts, and the swizzle costs nothing because it is applied to the loads' source addresses.
 #include <algorithm>
+#include <type_traits>
 
 #include "hstu_common.h"
 #include "hstu_kernels.h"
@@ -31,7 +33,7 @@ typedef __attribute__((address_space(3))) short4v* lds_s4;
 typedef __attribute__((address_space(3))) const bf16x8* lds_b8;
 typedef __attribute__((address_space(3))) f32x4* lds_f4;
 
-constexpr int kBK = 64;
+constexpr int kBK = 64;                                  // of a k-tile: 128 bytes
 enum { kTile64Deep = 1, kTile64, kTile128Deep, kTile128, kTile192, kTile256 };     // by token rows of a tile; deep: one workgroup per compute unit, more stages
 constexpr uint32_t kOutside = 0x80000000u;               // a lane offset beyond every range: the load returns zeros
 
@@ -57,33 +59,37 @@ __device__ __forceinline__ void store8(__bf16* at, const float (&v)[8]) {
   __builtin_nontemporal_store(o, (u32x4*)at);
 }
 
-template <int WM, int WN, int MI, int STAGES, bool NN, int EPI>
+template <int WM, int WN, int MI, int STAGES, int OP, int EPI>
 __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN, MI, STAGES>::kWavesPerSimd)) void gemm_rows_kernel(const GemmRowsArgs p, int tiles) {
   using S = Tile<WM, WN, MI, STAGES>;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hf = lane >> 5, l32 = lane & 31, i16 = lane & 15, grp16 = lane >> 4;
-  const int nk = (p.K + kBK - 1) / kBK;
+  constexpr bool kAT = OP == kGemmTN, kWT = OP == kGemmTN || OP == kGemmNN;   // operands with k as their slow axis
   // Workgroups go to the 8 dies round-robin; a die takes a contiguous range of tiles, columns first: the tiles of one range of token rows run
   // beside each other and the rows come from memory once.
   const int tiles_n = (p.N + S::kCols - 1) / S::kCols;
+  const int tiles_slab = kAT ? (int)((p.M + S::kRows - 1) / S::kRows) * tiles_n : 1;               // (kGemmTN: of a slab of the reduction)
+  // k of a tile: all, or the tile's slab
+  auto k_first = [&](int t) -> int64_t { return kAT ? (int64_t)(t / tiles_slab) * p.slab : 0; };
+  auto k_count = [&](int t) -> int64_t { return kAT ? min(p.slab, p.K - k_first(t)) : p.K; };
+  auto k_tiles = [&](int t) -> int { return (int)((k_count(t) + kBK - 1) / kBK); };
   const int xcd = blockIdx.x % kNumXcd, per_die = (gridDim.x - xcd + kNumXcd - 1) / kNumXcd;
   int tile = xcd * (tiles / kNumXcd) + min(xcd, tiles % kNumXcd);
   const int tile_end = tile + tiles / kNumXcd + (xcd < tiles % kNumXcd ? 1 : 0);
   tile += blockIdx.x / kNumXcd;
   if (tile >= tile_end) return;
 
-  constexpr int kPitchW = S::kCols * 2;
+  constexpr int kPitchW = S::kCols * 2, kPitchA = S::kRows * 2;                   // of operands with k as their slow axis
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void)smem;
   if (wave >= S::kWaves) {
     // ---- global -> LDS.  Load c of a loader: rows 8 (lw + kLoaders c) .. + 7 of an operand with k contiguous.  Of W [K, N]: 1 KB of whole rows.
-    constexpr int kRowsPerLoad = 1024 / kPitchW, kChunks = kPitchW / 16;
     const int lw = wave - S::kWaves;
     const uint32_t rowa = (uint32_t)(p.lda * 2), roww = (uint32_t)(p.ldw * 2);
     const uint32_t chunk = (uint32_t)((lane & 7) ^ ((4 * lw + (lane >> 4)) & 7));
     const uint32_t va = (uint32_t)(8 * lw + (lane >> 3)) * rowa + 16 * chunk;
-    const bool k_tail = (p.K % kBK) != 0;
-    const bool in_tail = (int)(8 * chunk) < p.K % kBK;                            // (of the last k-tile, where that is not whole)
+    const int tail = kAT ? 0 : (int)(p.K % kBK);
+    const bool in_tail = (int)(8 * chunk) < tail;                             // (of the last k-tile, where that is not whole)
     const uint32_t vw = (uint32_t)(8 * lw + (lane >> 3)) * roww + 16 * chunk;
     // A descriptor holds the rows of the tile (rows past it read as zero); k advances in the scalar offset (for W [K, N] the descriptor advances).
     auto rsrc = [&](uint64_t addr, int left, int most, uint32_t row) -> i32x4 {
@@ -93,32 +99,42 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
     };
     i32x4 ra, rw;
-    int load_n0 = 0;
+    // Load c of an operand with k as its slow axis: 1 KB of whole rows of the tile's columns; its descriptor advances.
+    auto dma_rows = [&](auto pitch, uint64_t base, uint32_t row_bytes, int step, int64_t left, int cols, int c, uint32_t dst) {
+      constexpr int kPitch = decltype(pitch)::value, kPer = 1024 / kPitch, kChunks = kPitch / 16;
+      const int first = kPer * (lw + kLoaders * c);
+      const int r = first + lane / kChunks, ch = (lane % kChunks) ^ (4 * (r & 3) + ((r >> 2) & 3));
+      const uint32_t v = 8 * ch < cols ? (uint32_t)(lane / kChunks) * row_bytes + 16 * (uint32_t)ch : kOutside;
+      const int64_t row = (int64_t)step * kBK + first;
+      dma16(rsrc(base + (uint64_t)row * row_bytes, (int)min(left - row, (int64_t)kPer), kPer, row_bytes), v, 0, dst);
+    };
+    int load_n0 = 0, load_m0 = 0, nk = 0;
+    int64_t load_k0 = 0, load_k = 0;
     auto aim = [&](int t) {                                                       // the loads at tile t
-      const int tm = t / tiles_n;
+      const int in_slab = kAT ? t % tiles_slab : t, tm = in_slab / tiles_n;
       const int64_t m0 = (int64_t)tm * S::kRows;
-      load_n0 = (t - tm * tiles_n) * S::kCols;
-      ra = rsrc((uint64_t)(uintptr_t)p.A + (uint64_t)m0 * rowa, (int)min((int64_t)S::kRows, p.M - m0), S::kRows, rowa);
-      if (!NN) rw = rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)load_n0 * roww, p.N - load_n0, S::kCols, roww);
+      load_n0 = (in_slab - tm * tiles_n) * S::kCols;
+      nk = k_tiles(t);
+      load_k0 = k_first(t);
+      load_k = k_count(t);
+      if (kAT) load_m0 = (int)m0;
+      else ra = rsrc((uint64_t)(uintptr_t)p.A + (uint64_t)m0 * rowa, (int)min((int64_t)S::kRows, p.M - m0), S::kRows, rowa);
+      if (!kWT) rw = rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)load_n0 * roww, p.N - load_n0, S::kCols, roww);
     };
     // load c of k-tile `step` into stage s
     auto issue = [&](int step, int s, int c) {
-      const bool outside = k_tail && step == nk - 1 && !in_tail;
-      const uint32_t dst = smem_base + (uint32_t)(s * S::kStage + lw * 1024), k_off = (uint32_t)step * (2 * kBK);
+      const bool outside = tail != 0 && step == nk - 1 && !in_tail;
+      const uint32_t dst = smem_base + (uint32_t)(s * S::kStage + lw * 1024), k_off = (uint32_t)step * 128;
       if (c < S::kLoadsA) {
-        dma16(ra, (outside ? kOutside : va) + (uint32_t)(8 * kLoaders * c) * rowa, k_off, dst + (uint32_t)(kLoaders * 1024 * c));
+        const uint32_t at = dst + (uint32_t)(kLoaders * 1024 * c);
+        if (kAT) dma_rows(std::integral_constant<int, kPitchA>{}, (uint64_t)(uintptr_t)p.A + (uint64_t)load_k0 * rowa + (uint64_t)load_m0 * 2, rowa, step, load_k, (int)p.M - load_m0, c, at);
+        else dma16(ra, (outside ? kOutside : va) + (uint32_t)(8 * kLoaders * c) * rowa, k_off, at);
         return;
       }
       const int cw = c - S::kLoadsA;
       const uint32_t at = dst + (uint32_t)(S::kA + kLoaders * 1024 * cw);
-      if (NN) {
-        const int first = kRowsPerLoad * (lw + kLoaders * cw), row = step * kBK + first;
-        const int r = first + lane / kChunks, ch = (lane % kChunks) ^ (4 * (r & 3) + ((r >> 2) & 3));
-        const uint32_t v = load_n0 + 8 * ch < p.N ? (uint32_t)(lane / kChunks) * roww + 16 * (uint32_t)ch : kOutside;
-        dma16(rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)row * roww + (uint64_t)load_n0 * 2, p.K - row, kRowsPerLoad, roww), v, 0, at);
-      } else {
-        dma16(rw, (outside ? kOutside : vw) + (uint32_t)(8 * kLoaders * cw) * roww, k_off, at);
-      }
+      if (kWT) dma_rows(std::integral_constant<int, kPitchW>{}, (uint64_t)(uintptr_t)p.W + (uint64_t)load_k0 * roww + (uint64_t)load_n0 * 2, roww, step, load_k, p.N - load_n0, cw, at);
+      else dma16(rw, (outside ? kOutside : vw) + (uint32_t)(8 * kLoaders * cw) * roww, k_off, at);
     };
     // Loads run STAGES - 1 k-tiles ahead of the products, across tiles.  A loader waits for its loads alone: in a wave that stores as well, waiting for a
     // load means waiting for every store in front of it.
@@ -152,22 +168,23 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   const uint32_t row128 = (uint32_t)(l32 * 128 + 16 * (hf ^ ((l32 >> 1) & 7)));   // k-step ks of a tile: chunk ^ 2 ks
   const uint32_t ta = smem_base + (uint32_t)(wm * 32 * MI * 128) + row128;
   const uint32_t tw = smem_base + S::kA + (uint32_t)(wn * 64 * 128) + row128;
-  // Transposed (W [K, N]): lanes of a half-wave take rows 8 hf + 0..3 (then + 4) of 16 k; lane l32 ends up with column l32's 8 values of k.
+  // Transposed: lanes of a half-wave take rows 8 hf + 0..3 (then + 4) of 16 k; lane l32 ends up with column l32's 8 values of k.
   const int vchunk = 2 * (grp16 & 1) + ((i16 & 3) >> 1), vbyte = 8 * (i16 & 1), vrow = i16 >> 2;
-  const uint32_t tr = smem_base + S::kA + (uint32_t)((8 * hf + vrow) * kPitchW + vbyte);
   const uint32_t tr_lo = (uint32_t)(16 * (vchunk ^ (2 * hf) ^ (4 * vrow))), tr_hi = (uint32_t)(16 * (vchunk ^ (2 * hf + 1) ^ (4 * vrow)));
+  const uint32_t tra = smem_base + (uint32_t)((8 * hf + vrow) * kPitchA + vbyte), trw = smem_base + S::kA + (uint32_t)((8 * hf + vrow) * kPitchW + vbyte);
+  auto transposed = [&](uint32_t at, uint32_t columns, int pitch) -> bf16x8 {     // columns: byte of the fragment's first one in its row
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_lo ^ columns)));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_hi ^ columns) + (uint32_t)(4 * pitch)));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  auto contiguous = [&](uint32_t base, uint32_t at, int ks) -> bf16x8 { return *(lds_b8)(uintptr_t)((base ^ (uint32_t)(32 * ks)) + at); };
   auto wfrag = [&](uint32_t stage_off, int ks, int ni) -> bf16x8 {
-    if (NN) {
-      const uint32_t f = (uint32_t)(16 * (8 * wn + 4 * ni));                     // chunk of the fragment's first column
-      const uint32_t at = tr + stage_off + (uint32_t)(ks * 16 * kPitchW);
-      const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_lo ^ f)));
-      const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_hi ^ f) + 4 * kPitchW));
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
-    return *(lds_b8)(uintptr_t)((tw ^ (uint32_t)(32 * ks)) + stage_off + (uint32_t)(ni * 32 * 128));
+    if constexpr (kWT) return transposed(trw + stage_off + (uint32_t)(ks * 16 * kPitchW), (uint32_t)(16 * (8 * wn + 4 * ni)), kPitchW);
+    else return contiguous(tw, stage_off + (uint32_t)(ni * 32 * 128), ks);
   };
   auto afrag = [&](uint32_t stage_off, int ks, int mi) -> bf16x8 {
-    return *(lds_b8)(uintptr_t)((ta ^ (uint32_t)(32 * ks)) + stage_off + (uint32_t)(mi * 32 * 128));
+    if constexpr (kAT) return transposed(tra + stage_off + (uint32_t)(ks * 16 * kPitchA), (uint32_t)(64 * (MI * wm + mi)), kPitchA);
+    else return contiguous(ta, stage_off + (uint32_t)(mi * 32 * 128), ks);
   };
 
   constexpr int kSteps = kBK / 16, kTotal = kSteps * MI;
@@ -182,10 +199,10 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   auto turn = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
   turn();
   for (;;) {
-    const int tm = tile / tiles_n;
+    const int in_slab = kAT ? tile % tiles_slab : tile, tm = in_slab / tiles_n;
     const int64_t m0 = (int64_t)tm * S::kRows;
-    const int n0 = (tile - tm * tiles_n) * S::kCols;
-    const int next = tile + per_die;
+    const int n0 = (in_slab - tm * tiles_n) * S::kCols;
+    const int next = tile + per_die, nk = k_tiles(tile);
     f32x16 acc[2][MI];
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni)
@@ -224,10 +241,11 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     const uint32_t get = area + (uint32_t)((lane >> 3) * 256 + 16 * ((2 * (lane & 7)) ^ (lane >> 3)));     // and 8 rows further: chunk ^ 8
     const int col = n0 + 64 * wn + 8 * (lane & 7);
     const bool col_ok = col < p.N;
-    const bool first = EPI != kEpiPlain && EPI != kEpiResidual && col < p.split;   // of the gate
+    const bool first = (EPI == kEpiSiluSplit || EPI == kEpiPreAndSilu) && col < p.split;   // of the gate
     const int64_t w0 = m0 + 32 * MI * wm + (lane >> 3);
     const int64_t ldd = EPI == kEpiSiluSplit && first ? p.ldd0 : p.ldd;
     __bf16* const d = (EPI == kEpiSiluSplit && first ? (__bf16*)p.D0 : (__bf16*)p.D) + w0 * ldd + col;
+    float* const sums = (float*)p.D + (kAT ? (int64_t)(tile / tiles_slab) * p.M * p.N : 0) + w0 * ldd + col;          // (kEpiSums)
     u32x4 res[2];
     auto fetch = [&](int part) {
 #pragma unroll
@@ -256,6 +274,11 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
         const int row = 16 * part + 8 * it;
         float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         if (!col_ok || row + (lane >> 3) >= rows) continue;
+        if (EPI == kEpiSums) {
+          *(f32x4*)(sums + row * ldd) = lo;
+          *(f32x4*)(sums + row * ldd + 4) = hi;
+          continue;
+        }
         if (EPI == kEpiResidual) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -282,32 +305,37 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   }
 }
 
-template <int WM, int WN, int MI, int STAGES, bool NN, int EPI>
+template <int WM, int WN, int MI, int STAGES, int OP, int EPI>
 hipError_t launch_tile(const GemmRowsArgs& p, hipStream_t stream) {
   using S = Tile<WM, WN, MI, STAGES>;
   static bool attr_set[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (!attr_set[dev]) {
-    const hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<WM, WN, MI, STAGES, NN, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, S::kSmem);
+    const hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<WM, WN, MI, STAGES, OP, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, S::kSmem);
     if (e != hipSuccess) return e;
     attr_set[dev] = true;
   }
-  const int64_t tiles = ((p.M + S::kRows - 1) / S::kRows) * ((p.N + S::kCols - 1) / S::kCols);
+  const int64_t slabs = OP == kGemmTN ? (p.K + p.slab - 1) / p.slab : 1;
+  const int64_t tiles = ((p.M + S::kRows - 1) / S::kRows) * ((p.N + S::kCols - 1) / S::kCols) * slabs;
   if (tiles > INT32_MAX / 2) return hipErrorInvalidValue;
   const int grid = (int)std::min<int64_t>(tiles, 256 * S::kWgPerCu);
-  hipLaunchKernelGGL((gemm_rows_kernel<WM, WN, MI, STAGES, NN, EPI>), dim3(grid), dim3(S::kThreads), S::kSmem, stream, p, (int)tiles);
+  hipLaunchKernelGGL((gemm_rows_kernel<WM, WN, MI, STAGES, OP, EPI>), dim3(grid), dim3(S::kThreads), S::kSmem, stream, p, (int)tiles);
   return hipGetLastError();
 }
-template <bool NN, int EPI>
+template <int OP, int EPI>
 hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
-  switch (tile) {
-    case kTile64Deep: return launch_tile<2, 2, 1, 5, NN, EPI>(p, stream);
-    case kTile64: return launch_tile<2, 2, 1, 2, NN, EPI>(p, stream);
-    case kTile128Deep: return launch_tile<2, 2, 2, 4, NN, EPI>(p, stream);
-    case kTile128: return launch_tile<2, 2, 2, 2, NN, EPI>(p, stream);
-    case kTile192: return launch_tile<2, 4, 3, 2, NN, EPI>(p, stream);
-    default: return launch_tile<2, 4, 4, 2, NN, EPI>(p, stream);
+  if constexpr (OP == kGemmTN) {
+    return tile == kTile128Deep ? launch_tile<2, 2, 2, 4, OP, EPI>(p, stream) : launch_tile<2, 2, 2, 2, OP, EPI>(p, stream);
+  } else {
+    switch (tile) {
+      case kTile64Deep: return launch_tile<2, 2, 1, 5, OP, EPI>(p, stream);
+      case kTile64: return launch_tile<2, 2, 1, 2, OP, EPI>(p, stream);
+      case kTile128Deep: return launch_tile<2, 2, 2, 4, OP, EPI>(p, stream);
+      case kTile128: return launch_tile<2, 2, 2, 2, OP, EPI>(p, stream);
+      case kTile192: return launch_tile<2, 4, 3, 2, OP, EPI>(p, stream);
+      default: return launch_tile<2, 4, 4, 2, OP, EPI>(p, stream);
+    }
   }
 }
 
@@ -341,12 +369,14 @@ int gemm_rows_tile(int64_t M, int N, int epilogue) {
 bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)M * (double)N * (double)K < 1e11; }
 
 hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile) {
-  if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || p.K % 8 != 0) return hipErrorInvalidValue;
-  if (tile == 0) tile = gemm_rows_tile(p.M, p.N, epilogue);
-  if (op == kGemmNT && epilogue == kEpiSiluSplit) return launch_epi<false, kEpiSiluSplit>(p, tile, stream);
-  if (op == kGemmNT && epilogue == kEpiPreAndSilu) return launch_epi<false, kEpiPreAndSilu>(p, tile, stream);
-  if (op == kGemmNT && epilogue == kEpiResidual) return launch_epi<false, kEpiResidual>(p, tile, stream);
-  if (op == kGemmNN && epilogue == kEpiPlain) return launch_epi<true, kEpiPlain>(p, tile, stream);
+  if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || (op != kGemmTN && p.K % 8 != 0)) return hipErrorInvalidValue;
+  if (op == kGemmTN) tile = (p.M + 127) / 128 * ((p.N + 127) / 128) * ((p.K + p.slab - 1) / p.slab) <= 256 ? kTile128Deep : kTile128;
+  else if (tile == 0) tile = gemm_rows_tile(p.M, p.N, epilogue);
+  if (op == kGemmNT && epilogue == kEpiSiluSplit) return launch_epi<kGemmNT, kEpiSiluSplit>(p, tile, stream);
+  if (op == kGemmNT && epilogue == kEpiPreAndSilu) return launch_epi<kGemmNT, kEpiPreAndSilu>(p, tile, stream);
+  if (op == kGemmNT && epilogue == kEpiResidual) return launch_epi<kGemmNT, kEpiResidual>(p, tile, stream);
+  if (op == kGemmNN && epilogue == kEpiPlain) return launch_epi<kGemmNN, kEpiPlain>(p, tile, stream);
+  if (op == kGemmTN && epilogue == kEpiSums) return launch_epi<kGemmTN, kEpiSums>(p, tile, stream);
   return hipErrorInvalidValue;
 }
 

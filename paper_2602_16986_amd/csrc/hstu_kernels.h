@@ -205,17 +205,19 @@ int gemm_bf16(int op, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
 
 // gemm_rows.hip: products of token rows with a weight matrix, the layer's pointwise work in the epilogue.
 struct GemmRowsArgs {
-  int64_t M; int32_t N, K;                  // N and K multiples of 8
-  const void* A; int64_t lda;               // [M, K]
-  const void* W; int64_t ldw;               // [N, K] (kGemmNT) or [K, N] (kGemmNN)
+  int64_t M; int32_t N; int64_t K;          // multiples of 8: N, and K or (kGemmTN) M
+  const void* A; int64_t lda;               // [M, K]; kGemmTN: [K, M]
+  const void* W; int64_t ldw;               // [N, K] (kGemmNT) or [K, N] (kGemmNN, kGemmTN)
   const void* C; int64_t ldc;               // kEpiResidual: rows added before the one rounding
   void* D; int64_t ldd;
   void* D0; int64_t ldd0;                   // second output, see the epilogues
   int32_t split;                            // column, a multiple of 8
+  int64_t slab;                             // kGemmTN: the reduction is cut every `slab` k, a multiple of 64; slab i writes its sums at D + i M N (fp32)
 };
 // kEpiSiluSplit: SiLU; columns before `split` go to D0, the others to D (both at their own column).
 // kEpiPreAndSilu: D gets the product, D0 the SiLU of the columns from `split` on.
-enum { kEpiPlain = 0, kEpiResidual = 1, kEpiSiluSplit = 2, kEpiPreAndSilu = 3 };
+// kEpiSums: fp32, unrounded.
+enum { kEpiPlain = 0, kEpiResidual = 1, kEpiSiluSplit = 2, kEpiPreAndSilu = 3, kEpiSums = 4 };
 bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K);      // over the library (gemm.hip)
 hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile = 0);   // tile: 0 by size
 

@@ -83,7 +83,7 @@ LayerLayout make_layer_layout(const hstu_layer_params* p, int for_backward) {
 inline bool bad16(const void* ptr) { return ((uintptr_t)ptr & 15u) != 0; }
 GemmRowsArgs rows_product(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* D, int64_t ldd) {
   GemmRowsArgs g = {};
-  g.M = M; g.N = (int32_t)N; g.K = (int32_t)K; g.A = A; g.lda = lda; g.W = W; g.ldw = ldw; g.D = D; g.ldd = ldd;
+  g.M = M; g.N = (int32_t)N; g.K = K; g.A = A; g.lda = lda; g.W = W; g.ldw = ldw; g.D = D; g.ldd = ldd;
   return g;
 }
 inline int gemm_status(int rc) { return rc == 0 ? HSTU_OK : (rc == -2 ? HSTU_ERR_UNSUPPORTED : HSTU_ERR_LAUNCH); }

@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,H,d,E", [
     (1, 1, 32, 8),            # one row, one k-tile of 8
     (63, 1, 64, 72), (65, 3, 64, 328), (129, 1, 32, 136), (255, 5, 64, 200), (257, 2, 128, 1032),
-    (1990, 4, 128, 64), (2049, 4, 128, 136), (4161, 4, 128, 72), (6401, 4, 128, 136)])
+    (1990, 4, 128, 64), (2049, 4, 128, 136), (4161, 4, 128, 72), (6401, 4, 128, 136),
+    # weight gradients of widths that are multiples of 128: one slab of token rows, ragged slabs, more tiles than compute units
+    (7, 1, 128, 128), (130, 2, 128, 384), (1601, 4, 128, 512), (5003, 1, 128, 256), (200, 9, 128, 1152)])
 def test_layer_products_at_tile_edges(hb, T, H, d, E):
     lengths = [60] * (T // 60) + ([T % 60] if T % 60 else [])
     run_case(wl.build_layer(f"products-{T}-{H}-{d}-{E}", lengths, H, d, E, seed=T + E, K1=40, K2=8))
