@@ -13,11 +13,25 @@ constexpr int kRowsPerBlock = 4;        // forward: one wave per row, 4 waves pe
 constexpr int kBwdWaves = 8;            // backward: 8 waves per workgroup, each walking over rows
 constexpr int kMaxBwdBlocks = 512;      // two workgroups per CU; also the number of partial column-sum rows
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
+// A value from another lane of the same row of 16, by DPP (a lane permutation through LDS, which __shfl_xor is, takes some 100 cycles where this takes 8).
+template <int kCtrl> __device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xF, 0xF, true));
 }
+// op over the 64 lanes of a wave, in every lane: neighbours, pairs, quads (mirrored in 8), octets (mirrored in 16), then rows in pairs and halves
+template <typename Op> __device__ __forceinline__ float wave_all(float v, Op op) {
+  v = op(v, dpp<0xB1>(v));                                 // quad_perm 1 0 3 2
+  v = op(v, dpp<0x4E>(v));                                 // quad_perm 2 3 0 1
+  v = op(v, dpp<0x141>(v));                                // row_half_mirror
+  v = op(v, dpp<0x140>(v));                                // row_mirror
+  const uint32_t a = __builtin_bit_cast(uint32_t, v);
+  const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  v = op(__builtin_bit_cast(float, (uint32_t)p[0]), __builtin_bit_cast(float, (uint32_t)p[1]));
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return op(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_all(v, [](float x, float y) { return x + y; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_all(v, [](float x, float y) { return fmaxf(x, y); }); }
 
 // 8 consecutive elements starting at element index e0 of a row, widened to fp32
 template <typename E>
@@ -46,7 +60,6 @@ __device__ __forceinline__ void store8(E* row, int e0, const float (&v)[8]) {
     *(f32x4*)(row + e0 + 4) = (f32x4){v[4], v[5], v[6], v[7]};
   }
 }
-// v[i] *= d/dt [t sigmoid(t)] at t = pre[e0 + i]: the gradient passes back through a SiLU whose input is `pre`
 // 8 consecutive elements as loaded (one 16-byte chunk of bf16, two of fp32), widened when they are used
 template <typename E> struct Raw8;
 template <> struct Raw8<__bf16> { u32x4 w; };
@@ -65,10 +78,11 @@ __device__ __forceinline__ void widen8(const Raw8<float>& r, float (&v)[8]) {
   for (int i = 0; i < 4; ++i) { v[i] = r.lo[i]; v[4 + i] = r.hi[i]; }
 }
 
+// v[i] *= d/dt [t sigmoid(t)] at t = pre[i]: the gradient passes back through a SiLU whose input is `pre`
 template <typename E>
-__device__ __forceinline__ void dsilu8(const E* pre, int e0, float (&v)[8]) {
+__device__ __forceinline__ void dsilu8(const Raw8<E>& pre, float (&v)[8]) {
   float t[8];
-  load8(pre, e0, t);
+  widen8(pre, t);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * t[i]));
@@ -98,7 +112,7 @@ __device__ __forceinline__ void row_stats(const float (&a)[NCH][8], int lane, in
 
 template <typename E, int NCH>
 __global__ __launch_bounds__(64 * kRowsPerBlock) void gated_norm_fwd_kernel(const NormFwdArgs p) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + wave;
   const int D = p.D;
   if (row >= p.T) return;
@@ -106,10 +120,15 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gated_norm_fwd_kernel(cons
   const E* urow = p.u ? (const E*)p.u + row * p.su : nullptr;       // no gate: plain layer norm
   E* yrow = (E*)p.y + row * p.sy;
   float a[NCH][8];
+  constexpr bool kEarly = NCH <= 4;                    // the gate's rows travel with the first loads, not after the reductions (more of them cost occupancy)
+  Raw8<E> ur[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int e0 = (lane + 64 * c) * 8;
-    if (e0 < D) load8(arow, e0, a[c]);
+    if (e0 < D) {
+      load8(arow, e0, a[c]);
+      if (kEarly && urow) ur[c] = load8raw(urow, e0);
+    }
   }
   float mu, rs;
   if (p.stats_in) { mu = p.mean[row]; rs = p.rstd[row]; }           // statistics saved by an earlier pass
@@ -119,7 +138,8 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gated_norm_fwd_kernel(cons
     const int e0 = (lane + 64 * c) * 8;
     if (e0 < D) {
       float uv[8], gv[8], bv[8], out[8];
-      if (urow) load8(urow, e0, uv);
+      if (!kEarly && urow) ur[c] = load8raw(urow, e0);
+      if (urow) widen8(ur[c], uv);
       load8(p.gamma, e0, gv);
       if (p.beta) load8(p.beta, e0, bv);
 #pragma unroll
@@ -141,28 +161,27 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gated_norm_fwd_kernel(cons
 // through memory in 16 bits).  Per row: y as in the kernel above (or, without gamma, the input rows themselves, times the
 // gate if there is one: plain row-wise quantisation, used for the weights), amax = max |y|, scale = amax / 448,
 // code = E4M3(y * (448 / amax)), ties to even.  All of it in fp32, one division per row and one multiplication per element.
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
-  return v;
-}
-
 template <typename E, int NCH>
 __global__ __launch_bounds__(64 * kRowsPerBlock) void norm_quant_fwd_kernel(const NormFwdArgs p, unsigned char* __restrict__ q,
                                                                             int64_t sq, float* __restrict__ qscale) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + wave;
   const int D = p.D;
   if (row >= p.T) return;
   const E* arow = (const E*)p.a + row * p.sa;
   const E* urow = p.u ? (const E*)p.u + row * p.su : nullptr;
   float a[NCH][8];
+  constexpr bool kEarly = NCH <= 4;
+  Raw8<E> ur[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int e0 = (lane + 64 * c) * 8;
 #pragma unroll
     for (int i = 0; i < 8; ++i) a[c][i] = 0.f;
-    if (e0 < D) load8(arow, e0, a[c]);
+    if (e0 < D) {
+      load8(arow, e0, a[c]);
+      if (kEarly && urow) ur[c] = load8raw(urow, e0);
+    }
   }
   float mu = 0.f, rs = 1.f;
   if (p.gamma) row_stats<NCH>(a, lane, D, p.eps, mu, rs);
@@ -172,7 +191,8 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void norm_quant_fwd_kernel(cons
     const int e0 = (lane + 64 * c) * 8;
     if (e0 < D) {
       float uv[8], gv[8], bv[8];
-      if (urow) load8(urow, e0, uv);
+      if (!kEarly && urow) ur[c] = load8raw(urow, e0);
+      if (urow) widen8(ur[c], uv);
       if (p.gamma) load8(p.gamma, e0, gv);
       if (p.beta) load8(p.beta, e0, bv);
 #pragma unroll
@@ -210,109 +230,113 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void norm_quant_fwd_kernel(cons
 
 // Backward.  Per row: ahat = (a - mu) rstd, dn = dy u, dU = dy (ahat gamma + beta), dahat = dn gamma,
 // dA = rstd (dahat - mean(dahat) - ahat mean(dahat ahat)).  Column sums dgamma = sum dn ahat and
-// dbeta = sum dn are kept per lane over the rows a wave visits, combined across the workgroup's
+// dbeta = sum dn (if wanted) are kept per lane over the rows a wave visits, combined across the workgroup's
 // waves in a fixed order through LDS and written as one partial row per workgroup.
-template <typename E, int NCH>
+// Few rows are a chain of latencies: the chunks of a row are fetched together, the reductions are DPP, and the waves' column sums meet in one step.
+// With the gradient's rows fetched behind the first reductions, lane permutations through LDS and the waves' sums added in turn, bf16, us with
+// the column-sum launch, before -> now: 384 features, 6,418 rows 16.7 -> 12.5, 20,000 rows 25.2 -> 19.1, 87,728 rows 80.9 -> 69.2; 512 features
+// 17.4 -> 12.6, 27.5 -> 21.2, 90.6 -> 89.9 (memory).
+template <typename E> struct BwdRow { Raw8<E> a, dy, u; };          // what the reductions need
+template <typename E> struct BwdTail { Raw8<E> pre, res; };         // and what the results need
+template <typename E> constexpr bool kAhead = sizeof(E) == 2;      // a chunk of fp32 is 8 registers: fetched where it is used, nothing ahead
+
+template <typename E>
+__device__ __forceinline__ void fetch_row(const NormBwdArgs& p, int64_t row, int e0, BwdRow<E>& r) {
+  r.a = load8raw((const E*)p.a + row * p.sa, e0);
+  r.dy = load8raw((const E*)p.dy + row * p.sdy, e0);
+  if (p.u) r.u = load8raw((const E*)p.u + row * p.su, e0);
+}
+template <typename E>
+__device__ __forceinline__ void fetch_tail(const NormBwdArgs& p, int64_t row, int e0, BwdTail<E>& r) {
+  if (p.du_pre) r.pre = load8raw((const E*)p.du_pre + row * p.sdu_pre, e0);
+  if (p.residual) r.res = load8raw((const E*)p.residual + row * p.sres, e0);
+}
+
+// BETA: a bias, or its gradient, is there.
+template <typename E, bool BETA>
 __global__ __launch_bounds__(64 * kBwdWaves, 4) void gated_norm_bwd_kernel(const NormBwdArgs p, float* __restrict__ partial) {
-  extern __shared__ float red[];                       // [2][D]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int D = p.D;
-  const float* __restrict__ gamma = p.gamma;
-  const float* __restrict__ beta = p.beta;
-  float gsum[NCH][8], bsum[NCH][8], gv[NCH][8], bv[NCH][8];
+  extern __shared__ __attribute__((aligned(16))) float red[];         // [waves][dgamma, with BETA dbeta][D]
+  constexpr int kSums = BETA ? 2 : 1;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int D = p.D, e0 = lane * 8;
+  const bool on = e0 < D;
+  float gsum[8], bsum[8], gv[8], bv[8];
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int e0 = (lane + 64 * c) * 8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { gsum[c][i] = 0.f; bsum[c][i] = 0.f; gv[c][i] = 0.f; bv[c][i] = 0.f; }
-    if (e0 < D) {
-      load8(gamma, e0, gv[c]);
-      if (beta) load8(beta, e0, bv[c]);
-    }
+  for (int i = 0; i < 8; ++i) { gsum[i] = 0.f; bsum[i] = 0.f; gv[i] = 0.f; bv[i] = 0.f; }
+  if (on) {
+    load8(p.gamma, e0, gv);
+    if (BETA && p.beta) load8(p.beta, e0, bv);
   }
   const int64_t stride = (int64_t)gridDim.x * kBwdWaves;
   for (int64_t row = (int64_t)blockIdx.x * kBwdWaves + wave; row < p.T; row += stride) {
-    const E* arow = (const E*)p.a + row * p.sa;
-    const E* dyrow = (const E*)p.dy + row * p.sdy;
-    const E* urow = p.u ? (const E*)p.u + row * p.su : nullptr;         // no gate: plain layer norm, no dU
-    const E* rrow = p.residual ? (const E*)p.residual + row * p.sres : nullptr;
-    float a[NCH][8];
-    Raw8<E> rraw[NCH];                                 // the residual's rows travel with the first loads, not after the reductions
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int e0 = (lane + 64 * c) * 8;
-      if (e0 < D) {
-        load8(arow, e0, a[c]);
-        if (rrow) rraw[c] = load8raw(rrow, e0);
-      }
+    BwdRow<E> r;
+    BwdTail<E> tail;
+    if (on) {
+      fetch_row(p, row, e0, r);
+      if (kAhead<E>) fetch_tail(p, row, e0, tail);
     }
+    float a[1][8], dah[8];
+    if (on) widen8(r.a, a[0]);
     float mu, rs;
-    row_stats<NCH>(a, lane, D, p.eps, mu, rs);
+    row_stats<1>(a, lane, D, p.eps, mu, rs);
     float m1 = 0.f, m2 = 0.f;
-    float dah[NCH][8];
+    if (on) {
+      float dyv[8], uv[8], duv[8], yv[8];
+      widen8(r.dy, dyv);
+      if (p.u) widen8(r.u, uv);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int e0 = (lane + 64 * c) * 8;
-      if (e0 < D) {
-        float dyv[8], uv[8], duv[8], yv[8];
-        load8(dyrow, e0, dyv);
-        if (urow) load8(urow, e0, uv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float ah = (a[c][i] - mu) * rs;
-          const float dn = urow ? dyv[i] * uv[i] : dyv[i];
-          const float nv = ah * gv[c][i] + bv[c][i];
-          duv[i] = dyv[i] * nv;
-          yv[i] = urow ? nv * uv[i] : nv;
-          gsum[c][i] += dn * ah;
-          bsum[c][i] += dn;
-          dah[c][i] = dn * gv[c][i];
-          m1 += dah[c][i];
-          m2 += dah[c][i] * ah;
-          a[c][i] = ah;
-        }
-        if (urow) {
-          if (p.du_pre) dsilu8((const E*)p.du_pre + row * p.sdu_pre, e0, duv);
-          store8((E*)p.du + row * p.sdu, e0, duv);
-          if (p.y_out) store8((E*)p.y_out + row * p.sy_out, e0, yv);
-        }
+      for (int i = 0; i < 8; ++i) {
+        const float ah = (a[0][i] - mu) * rs;
+        const float dn = p.u ? dyv[i] * uv[i] : dyv[i];
+        const float nv = ah * gv[i] + bv[i];
+        duv[i] = dyv[i] * nv;
+        yv[i] = p.u ? nv * uv[i] : nv;
+        gsum[i] += dn * ah;
+        if (BETA) bsum[i] += dn;
+        dah[i] = dn * gv[i];
+        m1 += dah[i];
+        m2 += dah[i] * ah;
+        a[0][i] = ah;
+      }
+      if (p.u) {                                       // (no gate: plain layer norm, no dU)
+        if (!kAhead<E> && p.du_pre) tail.pre = load8raw((const E*)p.du_pre + row * p.sdu_pre, e0);
+        if (p.du_pre) dsilu8(tail.pre, duv);
+        store8((E*)p.du + row * p.sdu, e0, duv);
+        if (p.y_out) store8((E*)p.y_out + row * p.sy_out, e0, yv);
       }
     }
     m1 = wave_sum(m1) / (float)D;
     m2 = wave_sum(m2) / (float)D;
+    if (on) {
+      float dav[8], rv[8];
+      if (!kAhead<E> && p.residual) tail.res = load8raw((const E*)p.residual + row * p.sres, e0);
+      if (p.residual) widen8(tail.res, rv);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int e0 = (lane + 64 * c) * 8;
-      if (e0 < D) {
-        float dav[8], rv[8];
-        if (rrow) widen8(rraw[c], rv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          dav[i] = rs * (dah[c][i] - m1 - a[c][i] * m2);
-          if (rrow) dav[i] += rv[i];                   // gradient that bypasses the norm (residual connection)
-        }
-        store8((E*)p.da + row * p.sda, e0, dav);
+      for (int i = 0; i < 8; ++i) {
+        dav[i] = rs * (dah[i] - m1 - a[0][i] * m2);
+        if (p.residual) dav[i] += rv[i];               // gradient that bypasses the norm (residual connection)
       }
+      store8((E*)p.da + row * p.sda, e0, dav);
     }
   }
   // fixed-order combination of the waves' column sums
-  for (int w = 0; w < kBwdWaves; ++w) {
-    if (wave == w) {
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int e0 = (lane + 64 * c) * 8;
-        if (e0 < D)
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            red[e0 + i] = (w == 0 ? 0.f : red[e0 + i]) + gsum[c][i];
-            red[D + e0 + i] = (w == 0 ? 0.f : red[D + e0 + i]) + bsum[c][i];
-          }
-      }
+  if (on) {
+    float* mine = red + wave * kSums * D + e0;
+    *(f32x4*)mine = (f32x4){gsum[0], gsum[1], gsum[2], gsum[3]};
+    *(f32x4*)(mine + 4) = (f32x4){gsum[4], gsum[5], gsum[6], gsum[7]};
+    if (BETA) {
+      *(f32x4*)(mine + D) = (f32x4){bsum[0], bsum[1], bsum[2], bsum[3]};
+      *(f32x4*)(mine + D + 4) = (f32x4){bsum[4], bsum[5], bsum[6], bsum[7]};
     }
-    __syncthreads();
   }
+  __syncthreads();
   float* prow = partial + (int64_t)blockIdx.x * 2 * D;
-  for (int i = threadIdx.x; i < 2 * D; i += blockDim.x) prow[i] = red[i];
+  for (int i = threadIdx.x * 4; i < kSums * D; i += blockDim.x * 4) {
+    f32x4 t = *(const f32x4*)(red + i);
+#pragma unroll
+    for (int w = 1; w < kBwdWaves; ++w) t += *(const f32x4*)(red + w * kSums * D + i);
+    *(f32x4*)(prow + i) = t;
+  }
 }
 
 // Backward for rows wider than 512 features: a workgroup of W waves shares one row, every thread owns one 16-byte chunk
@@ -320,9 +344,29 @@ __global__ __launch_bounds__(64 * kBwdWaves, 4) void gated_norm_bwd_kernel(const
 // at the end).  The row statistics cross the waves through LDS with two barriers per row: the sum of a first, then
 // sum (a - mu)^2, sum dahat and sum dahat (a - mu) together (mean(dahat ahat) = rstd times the last one / D).  The slots
 // alternate with the row parity, so a wave that runs ahead never overwrites what a slower one still reads.  One wave per
-// row needed 48 registers per 512 features (and spilled from 2048 features on).
-template <typename E, int W>
-__global__ __launch_bounds__(64 * W) void gated_norm_bwd_wide_kernel(const NormBwdArgs p, float* __restrict__ partial) {
+// row needed 48 registers per 512 features (and spilled from 2048 features on).  What the reductions of the next row need is fetched a row ahead (bf16), 128 registers
+// keep 16 waves on a compute unit, and a wave sums eight and more slots a lane each (48 values in flight spilled at 16 waves).  bf16 without a bias, us with the
+// column-sum launch, before -> now: 1024 features, 6,418 rows 31.9 -> 22.8, 87,728 rows 214 -> 177; 2048 features, 6,418 rows 43.6 -> 32.8; 4096 features,
+// 20,000 rows 218 -> 165; 8192 features 2,029 -> 369; fp32 at 8192 features, 6,418 rows 283 -> 236.
+// The sum of W (up to 16) values in LDS, in every lane: eight and more a value per lane of a row of 16 (48 values in flight spill at W = 16).
+template <int W> __device__ __forceinline__ float sum_slots(const float* slots, int lane) {
+  if constexpr (W <= 4) {
+    float v = slots[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += slots[w];
+    return v;
+  } else {
+    float v = slots[lane & (W - 1)];
+    v += dpp<0xB1>(v);
+    v += dpp<0x4E>(v);
+    v += dpp<0x141>(v);
+    if (W > 8) v += dpp<0x140>(v);
+    return v;
+  }
+}
+
+template <typename E, int W, bool BETA>
+__global__ __launch_bounds__(64 * W, W < 16 && (BETA || !kAhead<E>) ? 3 : 4) void gated_norm_bwd_wide_kernel(const NormBwdArgs p, float* __restrict__ partial) {
   __shared__ float red1[2][W];
   __shared__ float red2[2][3][W];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -333,23 +377,26 @@ __global__ __launch_bounds__(64 * W) void gated_norm_bwd_wide_kernel(const NormB
   for (int i = 0; i < 8; ++i) { gv[i] = 0.f; bv[i] = 0.f; gsum[i] = 0.f; bsum[i] = 0.f; }
   if (on) {
     load8(p.gamma, e0, gv);
-    if (p.beta) load8(p.beta, e0, bv);
+    if (BETA && p.beta) load8(p.beta, e0, bv);
   }
   const float inv_d = 1.0f / (float)D;
   int par = 0;
+  BwdRow<E> r, next;                                   // the next row's chunks are fetched while this one's sums cross the waves
+  if (kAhead<E> && on && blockIdx.x < p.T) fetch_row(p, blockIdx.x, e0, r);
   for (int64_t row = blockIdx.x; row < p.T; row += gridDim.x, par ^= 1) {
-    const E* arow = (const E*)p.a + row * p.sa;
-    const E* dyrow = (const E*)p.dy + row * p.sdy;
-    const E* urow = p.u ? (const E*)p.u + row * p.su : nullptr;         // no gate: plain layer norm, no dU
-    const E* rrow = p.residual ? (const E*)p.residual + row * p.sres : nullptr;
-    float a[8], dn[8], dyv[8], rv[8];
+    BwdTail<E> tail;
+    if (on && kAhead<E>) {
+      fetch_tail(p, row, e0, tail);
+      if (row + gridDim.x < p.T) fetch_row(p, row + gridDim.x, e0, next);
+    } else if (on) {
+      fetch_row(p, row, e0, r);
+    }
+    float a[8], dyv[8], dah[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { a[i] = 0.f; dn[i] = 0.f; dyv[i] = 0.f; rv[i] = 0.f; }
+    for (int i = 0; i < 8; ++i) { a[i] = 0.f; dyv[i] = 0.f; dah[i] = 0.f; }
     if (on) {
-      load8(arow, e0, a);
-      load8(dyrow, e0, dyv);
-      if (urow) load8(urow, e0, dn);
-      if (rrow) load8(rrow, e0, rv);
+      widen8(r.a, a);
+      widen8(r.dy, dyv);
     }
     float s = 0.f;
 #pragma unroll
@@ -357,61 +404,68 @@ __global__ __launch_bounds__(64 * W) void gated_norm_bwd_wide_kernel(const NormB
     s = wave_sum(s);
     if (lane == 0) red1[par][wave] = s;
     __syncthreads();
-    float tot = 0.f;
+    const float mu = sum_slots<W>(red1[par], lane) * inv_d;
+    float q = 0.f, s1 = 0.f, s2 = 0.f;
+    if (on) {
+      float uv[8];
+      if (p.u) widen8(r.u, uv);
 #pragma unroll
-    for (int w = 0; w < W; ++w) tot += red1[par][w];
-    const float mu = tot * inv_d;
-    float q = 0.f, s1 = 0.f, s2 = 0.f, dah[8], uk[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float c = on ? a[i] - mu : 0.f;
-      uk[i] = dn[i];                                   // the gate, for the optional Y output
-      dn[i] = urow ? dyv[i] * dn[i] : dyv[i];
-      dah[i] = dn[i] * gv[i];
-      q += c * c;
-      s1 += dah[i];
-      s2 += dah[i] * c;
-      a[i] = c;
+      for (int i = 0; i < 8; ++i) {
+        const float c = a[i] - mu;
+        dah[i] = (p.u ? dyv[i] * uv[i] : dyv[i]) * gv[i];
+        q += c * c;
+        s1 += dah[i];
+        s2 += dah[i] * c;
+        a[i] = c;
+      }
     }
     q = wave_sum(q); s1 = wave_sum(s1); s2 = wave_sum(s2);
     if (lane == 0) { red2[par][0][wave] = q; red2[par][1][wave] = s1; red2[par][2][wave] = s2; }
     __syncthreads();
-    float tq = 0.f, t1 = 0.f, t2 = 0.f;
-#pragma unroll
-    for (int w = 0; w < W; ++w) { tq += red2[par][0][w]; t1 += red2[par][1][w]; t2 += red2[par][2][w]; }
+    const float tq = sum_slots<W>(red2[par][0], lane), t1 = sum_slots<W>(red2[par][1], lane), t2 = sum_slots<W>(red2[par][2], lane);
     const float rs = 1.0f / sqrtf(tq * inv_d + p.eps);
     const float m1 = t1 * inv_d, m2 = rs * t2 * inv_d;
     if (on) {
-      float duv[8], dav[8], yv[8];
+      float duv[8], dav[8], yv[8], uv[8], rv[8];
+      if (p.u) widen8(r.u, uv);
+      if (!kAhead<E> && p.residual) tail.res = load8raw((const E*)p.residual + row * p.sres, e0);
+      if (p.residual) widen8(tail.res, rv);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float ah = a[i] * rs;
         const float nv = ah * gv[i] + bv[i];
+        const float dn = p.u ? dyv[i] * uv[i] : dyv[i];
         duv[i] = dyv[i] * nv;
-        yv[i] = nv * uk[i];
-        gsum[i] += dn[i] * ah;
-        bsum[i] += dn[i];
-        dav[i] = rs * (dah[i] - m1 - ah * m2) + rv[i];     // rv: gradient that bypasses the norm (residual connection), else 0
+        yv[i] = p.u ? nv * uv[i] : nv;
+        gsum[i] += dn * ah;
+        if (BETA) bsum[i] += dn;
+        dav[i] = rs * (dah[i] - m1 - ah * m2);
+        if (p.residual) dav[i] += rv[i];               // gradient that bypasses the norm (residual connection)
       }
-      if (urow) {
-        if (p.du_pre) dsilu8((const E*)p.du_pre + row * p.sdu_pre, e0, duv);
+      if (p.u) {                                       // (no gate: plain layer norm, no dU)
+        if (!kAhead<E> && p.du_pre) tail.pre = load8raw((const E*)p.du_pre + row * p.sdu_pre, e0);
+        if (p.du_pre) dsilu8(tail.pre, duv);
         store8((E*)p.du + row * p.sdu, e0, duv);
         if (p.y_out) store8((E*)p.y_out + row * p.sy_out, e0, yv);
       }
       store8((E*)p.da + row * p.sda, e0, dav);
     }
+    if (kAhead<E>) r = next;
   }
   if (on) {
     float* prow = partial + (int64_t)blockIdx.x * 2 * D;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { prow[e0 + i] = gsum[i]; prow[D + e0 + i] = bsum[i]; }
+    for (int i = 0; i < 8; ++i) {
+      prow[e0 + i] = gsum[i];
+      if (BETA) prow[D + e0 + i] = bsum[i];
+    }
   }
 }
 
 // the sum over the lanes of a wave that are equal mod 4: two rotations inside a row of 16 lanes, then the rows in pairs
 __device__ __forceinline__ float sum_every_4th_lane(float v) {
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xF, 0xF, true));     // row_ror:4
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true));     // row_ror:8
+  v += dpp<0x124>(v);                                      // row_ror:4
+  v += dpp<0x128>(v);                                      // row_ror:8
   const uint32_t a = __builtin_bit_cast(uint32_t, v);
   const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
   const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]));
@@ -491,22 +545,19 @@ static hipError_t fwd_one(const NormFwdArgs& p, hipStream_t stream) {
 template <typename E, int W>
 static hipError_t bwd_wide(const NormBwdArgs& p, float* partial, hipStream_t stream) {
   const int nblk = gated_norm_bwd_blocks(p.T, p.D);
-  hipLaunchKernelGGL((gated_norm_bwd_wide_kernel<E, W>), dim3(nblk), dim3(64 * W), 0, stream, p, partial);
+  if (p.beta || p.dbeta) hipLaunchKernelGGL((gated_norm_bwd_wide_kernel<E, W, true>), dim3(nblk), dim3(64 * W), 0, stream, p, partial);
+  else hipLaunchKernelGGL((gated_norm_bwd_wide_kernel<E, W, false>), dim3(nblk), dim3(64 * W), 0, stream, p, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_colsum(nblk, p, partial, stream);
 }
 
-template <typename E, int NCH>
+template <typename E>
 static hipError_t bwd_one(const NormBwdArgs& p, float* partial, hipStream_t stream) {
   const int nblk = gated_norm_bwd_blocks(p.T, p.D);
-  auto kern = gated_norm_bwd_kernel<E, NCH>;
-  const size_t smem = (size_t)2 * p.D * sizeof(float);
-  if (smem > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, dim3(nblk), dim3(64 * kBwdWaves), smem, stream, p, partial);
+  const size_t smem = (size_t)kBwdWaves * p.D * sizeof(float);                           // (32 KB at most)
+  if (p.beta || p.dbeta) hipLaunchKernelGGL((gated_norm_bwd_kernel<E, true>), dim3(nblk), dim3(64 * kBwdWaves), 2 * smem, stream, p, partial);
+  else hipLaunchKernelGGL((gated_norm_bwd_kernel<E, false>), dim3(nblk), dim3(64 * kBwdWaves), smem, stream, p, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_colsum(nblk, p, partial, stream);
@@ -575,7 +626,7 @@ hipError_t launch_norm_bwd(const NormBwdArgs& p, float* partial, hipStream_t str
   const int w = bwd_row_waves(p.D);
 #define BWD_WIDE(E)                                        \
   switch (w) {                                             \
-    case 1: return bwd_one<E, 1>(p, partial, stream);      \
+    case 1: return bwd_one<E>(p, partial, stream);         \
     case 2: return bwd_wide<E, 2>(p, partial, stream);     \
     case 4: return bwd_wide<E, 4>(p, partial, stream);     \
     case 8: return bwd_wide<E, 8>(p, partial, stream);     \
