@@ -8,7 +8,7 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 constexpr int kCopyThreads = 256;            // 4 waves
-constexpr int kRowsPerWave = 8;              // consecutive rows handled by one wave per step
+constexpr int kRowsPerWave = 8;              // consecutive rows of more than 512 bytes handled by one wave per step
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
 // out[b + 1] = sum over b' <= b of the kept rows of sequence b'; one workgroup walks the batch in chunks.
@@ -68,6 +68,7 @@ __device__ __forceinline__ void copy_rows(const char* const src[kRowsPerWave], c
   }
 }
 
+// Rows of more than 512 bytes, one per instruction of a wave.
 // y row r of truncated sequence b is x row  offsets[b+1] - (out_offsets[b+1] - r).
 __global__ __launch_bounds__(kCopyThreads) void truncate_gather_kernel(int B, const int32_t* __restrict__ offsets,
                                                                        const int32_t* __restrict__ out_offsets, int64_t row_bytes,
@@ -125,10 +126,121 @@ __global__ __launch_bounds__(kCopyThreads) void truncate_scatter_kernel(int B, i
   }
 }
 
-int copy_grid(int64_t rows) {
-  const int64_t steps = (rows + kRowsPerWave - 1) / kRowsPerWave;
+// The same, by a whole wave: 64 places at a time
+__device__ __forceinline__ int find_with_wave(const int32_t* __restrict__ off, int B, int r, int lane) {
+  int lo = 0, n = B;                         // it is one of the n from lo on
+  while (n > 1) {
+    const int step = (n + 63) >> 6, at = lane * step;
+    const uint64_t le = __ballot(at < n && off[lo + min(at, n - 1)] <= r);
+    const int k = max(63 - __clzll((long long)le), 0);
+    lo += k * step;
+    n = min(step, n - k * step);
+  }
+  return lo;
+}
+
+// Rows of up to 512 bytes.  A step of a wave copies kUnroll groups of rows, a group as many consecutive rows as 16 bytes a lane of one instruction
+// cover.  The sequences around the step's first row sit in the lanes (a: the offsets that the rows are counted in, b: the others), so that finding a
+// group's sequence takes comparisons and no further trip to memory.
+constexpr int kUnroll = 8;
+struct Window { int32_t a, b; int first; bool covers; };
+struct Place { int32_t a0, a1, b0, b1; };    // a sequence in both offsets
+
+__device__ __forceinline__ Window look(const int32_t* __restrict__ oa, const int32_t* __restrict__ ob, int B, int r0, int last, int lane) {
+  Window w;
+  w.first = find_with_wave(oa, B, r0, lane);
+  w.a = oa[min(w.first + lane, B)];
+  w.b = ob[min(w.first + lane, B)];
+  w.covers = last < __builtin_amdgcn_readlane(w.a, 63) || w.first + 63 >= B;
+  return w;
+}
+// The sequence of row r: the same for the group's rows [g0, g1] (all lanes), or the lane's own.
+__device__ __forceinline__ Place place(const Window& w, const int32_t* __restrict__ oa, const int32_t* __restrict__ ob, int B, int g0, int g1, int r,
+                                       int lane) {
+  if (w.covers) {
+    const bool some = w.first + lane < B;    // (sequences without rows share their start with the next one: the last that starts at or before r holds it)
+    const int k0 = max(63 - __clzll((long long)__ballot(some && w.a <= g0)), 0), k1 = max(63 - __clzll((long long)__ballot(some && w.a <= g1)), 0);
+    if (k0 == k1 && k0 < 63)
+      return {__builtin_amdgcn_readlane(w.a, k0), __builtin_amdgcn_readlane(w.a, k0 + 1), __builtin_amdgcn_readlane(w.b, k0), __builtin_amdgcn_readlane(w.b, k0 + 1)};
+    if (k1 < 63) {
+      int k = k0;
+      for (;;) {
+        const int next = __shfl(w.a, k + 1, 64);
+        const bool on = k < k1 && next <= r;
+        if (__ballot(on) == 0) break;
+        k += on;
+      }
+      return {__shfl(w.a, k, 64), __shfl(w.a, k + 1, 64), __shfl(w.b, k, 64), __shfl(w.b, k + 1, 64)};
+    }
+  }
+  int lo = 0, hi = B;                        // off[lo] <= r < off[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (oa[mid] <= r) lo = mid; else hi = mid;
+  }
+  return {oa[lo], oa[lo + 1], ob[lo], ob[lo + 1]};
+}
+
+// GATHER as truncate_gather_kernel, rows counted in out_offsets; else as truncate_scatter_kernel, rows counted in offsets.
+// What bounds it: memory, once every lane has 16 bytes to move.  us, forward / backward, with the kernels above -> here: 439,000 rows of 256 bytes cut to
+// 120,000 28.9 / 77.5 -> 13.9 / 31.7 (4.4 TB/s), of 128 bytes 23 / 72 -> 12 / 20, 779,000 rows of 400 bytes 96 / 169 -> 62 / 96; rows of 1 KiB, which
+// stay with the kernels above, 134 -> 147 backward.
+template <bool GATHER>
+__global__ __launch_bounds__(kCopyThreads) void truncate_copy_kernel(int B, const int32_t* __restrict__ offsets, const int32_t* __restrict__ out_offsets,
+                                                                     int lanes_per_row, const char* __restrict__ src,
+                                                                     int64_t src_stride, char* __restrict__ dst, int64_t dst_stride, int64_t dst_rows) {
+  const int lane = threadIdx.x & 63;
+  const int64_t wave = (int64_t)blockIdx.x * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t waves = (int64_t)gridDim.x * (kCopyThreads / 64);
+  const int32_t* const oa = GATHER ? out_offsets : offsets;
+  const int32_t* const ob = GATHER ? offsets : out_offsets;
+  const int64_t rows = min((int64_t)oa[B], dst_rows);
+  const int per = 64 / lanes_per_row, sub = lane / lanes_per_row, c = (lane - sub * lanes_per_row) * 16;   // rows of a group, this lane's, its bytes
+  for (int64_t r0 = wave * (kUnroll * per); r0 < rows; r0 += waves * (kUnroll * per)) {
+    const Window w = look(oa, ob, B, (int)r0, (int)min(r0 + kUnroll * per, rows) - 1, lane);
+    const char* from[kUnroll];
+    char* to[kUnroll];
+#pragma unroll
+    for (int i = 0; i < kUnroll; ++i) {
+      from[i] = nullptr; to[i] = nullptr;
+      const int64_t g0 = r0 + i * per, g1 = min(g0 + per, rows) - 1, r = g0 + sub;
+      if (g0 >= rows) continue;
+      const Place p = place(w, oa, ob, B, (int)g0, (int)g1, (int)min(r, g1), lane);
+      if (sub >= per || r > g1) continue;
+      if (GATHER) {
+        const int row = p.b1 - (p.a1 - (int)r);
+        if (row >= p.b0 && row < p.b1) from[i] = src + (int64_t)row * src_stride;        // else: offsets that do not belong together
+      } else {
+        const int drop = (p.a1 - p.a0) - (p.b1 - p.b0), pos = (int)r - p.a0;
+        if (pos >= drop && drop >= 0) from[i] = src + (int64_t)(p.b0 + pos - drop) * src_stride;
+      }
+      to[i] = dst + r * dst_stride;
+    }
+    i32x4_t v[kUnroll];
+#pragma unroll
+    for (int i = 0; i < kUnroll; ++i) v[i] = from[i] ? __builtin_nontemporal_load((const i32x4_t*)(from[i] + c)) : i32x4_t{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < kUnroll; ++i)
+      if (to[i]) __builtin_nontemporal_store(v[i], (i32x4_t*)(to[i] + c));
+  }
+}
+
+int copy_grid(int64_t rows, int rows_per_step) {
+  const int64_t steps = (rows + rows_per_step - 1) / rows_per_step;
   const int64_t wgs = (steps + kCopyThreads / 64 - 1) / (kCopyThreads / 64);
   return (int)max((int64_t)1, min(wgs, (int64_t)256 * 32));
+}
+
+// Rows of up to 512 bytes: at least two to an instruction.
+constexpr int64_t kNarrowRow = 512;
+
+template <bool GATHER>
+hipError_t launch_copy(int B, int64_t rows, const int32_t* offsets, const int32_t* out_offsets, int64_t row_bytes, const void* src, int64_t src_stride,
+                       void* dst, int64_t dst_stride, hipStream_t stream) {
+  const int lanes = (int)(row_bytes / 16), grid = copy_grid(rows, kUnroll * (64 / lanes));
+  hipLaunchKernelGGL(truncate_copy_kernel<GATHER>, dim3(grid), dim3(kCopyThreads), 0, stream, B, offsets, out_offsets, lanes, (const char*)src, src_stride,
+                     (char*)dst, dst_stride, rows);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -141,16 +253,22 @@ hipError_t launch_truncate_offsets(int B, int keep, const int32_t* offsets, cons
 
 hipError_t launch_truncate_gather(int B, const int32_t* offsets, const int32_t* out_offsets, int64_t row_bytes, const void* x,
                                   int64_t x_stride, void* y, int64_t y_stride, int64_t y_rows, hipStream_t stream) {
-  hipLaunchKernelGGL(truncate_gather_kernel, dim3(copy_grid(y_rows)), dim3(kCopyThreads), 0, stream, B, offsets, out_offsets,
-                     row_bytes, (const char*)x, x_stride, (char*)y, y_stride, y_rows);
-  return hipGetLastError();
+  if (row_bytes > kNarrowRow) {
+    hipLaunchKernelGGL(truncate_gather_kernel, dim3(copy_grid(y_rows, kRowsPerWave)), dim3(kCopyThreads), 0, stream, B, offsets, out_offsets,
+                       row_bytes, (const char*)x, x_stride, (char*)y, y_stride, y_rows);
+    return hipGetLastError();
+  }
+  return launch_copy<true>(B, y_rows, offsets, out_offsets, row_bytes, x, x_stride, y, y_stride, stream);
 }
 
 hipError_t launch_truncate_scatter(int B, int64_t T, const int32_t* offsets, const int32_t* out_offsets, int64_t row_bytes,
                                    const void* dy, int64_t dy_stride, void* dx, int64_t dx_stride, hipStream_t stream) {
-  hipLaunchKernelGGL(truncate_scatter_kernel, dim3(copy_grid(T)), dim3(kCopyThreads), 0, stream, B, T, offsets, out_offsets,
-                     row_bytes, (const char*)dy, dy_stride, (char*)dx, dx_stride);
-  return hipGetLastError();
+  if (row_bytes > kNarrowRow) {
+    hipLaunchKernelGGL(truncate_scatter_kernel, dim3(copy_grid(T, kRowsPerWave)), dim3(kCopyThreads), 0, stream, B, T, offsets, out_offsets,
+                       row_bytes, (const char*)dy, dy_stride, (char*)dx, dx_stride);
+    return hipGetLastError();
+  }
+  return launch_copy<false>(B, T, offsets, out_offsets, row_bytes, dy, dy_stride, dx, dx_stride, stream);
 }
 
 }  // namespace hstu
