@@ -146,10 +146,16 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without a torch.cuda.Stream around it: 0.3 us instead of 2.8, of a call that enqueues in 3-6.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream or None
+    if stream is not None:
+        return stream.cuda_stream or None
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream or None
+    return _raw_stream(torch.cuda.current_device()) or None
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -264,14 +270,14 @@ def hstu_gated_norm_bwd_static(dy, attn, u, gamma, beta, eps, dattn, du, dgamma,
 
 def _row_geometry(t: torch.Tensor):
     """(row bytes, row stride in bytes) of a tensor of rows (dim 0) that are contiguous inside."""
-    assert t.dim() >= 2, "expected [rows, ...]"
-    inner = int(np.prod(t.shape[1:]))
-    expect = 1
-    for size, stride in zip(reversed(t.shape[1:]), reversed(t.stride()[1:]) if t.numel() else ()):
-        assert size == 1 or stride == expect, "rows must be contiguous inside"
-        expect *= size
-    stride = t.stride(0) if t.shape[0] > 1 else inner
-    return inner * t.element_size(), stride * t.element_size()
+    shape, strides = t.shape, t.stride()
+    assert len(shape) >= 2, "expected [rows, ...]"
+    full, inner = t.numel() > 0, 1
+    for i in range(len(shape) - 1, 0, -1):
+        assert not full or shape[i] == 1 or strides[i] == inner, "rows must be contiguous inside"
+        inner *= shape[i]
+    size = t.element_size()
+    return inner * size, (strides[0] if shape[0] > 1 else inner) * size
 
 
 def hstu_truncate_offsets(seq_offsets, keep: int, num_targets, out_offsets, stream=None) -> None:
