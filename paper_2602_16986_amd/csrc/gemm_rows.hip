@@ -99,50 +99,55 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
     };
     i32x4 ra, rw;
-    // Load c of an operand with k as its slow axis: 1 KB of whole rows of the tile's columns; its descriptor advances.
-    auto dma_rows = [&](auto pitch, uint64_t base, uint32_t row_bytes, int step, int64_t left, int cols, int c, uint32_t dst) {
+    // An operand with k as its slow axis: load c brings 1 KB of whole rows of the tile's columns, a descriptor holds the 64 rows of a k-tile.  A row's swizzle depends
+    // on c through its parity at most.  (A loader's own instructions are what a k-tile of a small tile waits for: nothing is computed per load but a sum.)
+    struct Rows { uint64_t addr; uint32_t voff[2], stride; };
+    auto aim_rows = [&](auto pitch, const void* base, int64_t k0, uint32_t row_bytes, int first_col, int cols, Rows& o) {
       constexpr int kPitch = decltype(pitch)::value, kPer = 1024 / kPitch, kChunks = kPitch / 16;
-      const int first = kPer * (lw + kLoaders * c);
-      const int r = first + lane / kChunks, ch = (lane % kChunks) ^ (4 * (r & 3) + ((r >> 2) & 3));
-      const uint32_t v = 8 * ch < cols ? (uint32_t)(lane / kChunks) * row_bytes + 16 * (uint32_t)ch : kOutside;
-      const int64_t row = (int64_t)step * kBK + first;
-      dma16(rsrc(base + (uint64_t)row * row_bytes, (int)min(left - row, (int64_t)kPer), kPer, row_bytes), v, 0, dst);
+      static_assert(kPer == 2 || kPer == 4, "256 or 512 bytes");
+      o.addr = (uint64_t)(uintptr_t)base + (uint64_t)k0 * row_bytes + (uint64_t)first_col * 2;
+      o.stride = kPer * kLoaders * row_bytes;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int r = kPer * (lw + kLoaders * c) + lane / kChunks, ch = (lane % kChunks) ^ (4 * (r & 3) + ((r >> 2) & 3));
+        o.voff[c] = first_col + 8 * ch < cols ? (uint32_t)(kPer * lw + lane / kChunks) * row_bytes + 16 * (uint32_t)ch : kOutside;
+      }
     };
-    int load_n0 = 0, load_m0 = 0, nk = 0;
-    int64_t load_k0 = 0, load_k = 0;
+    Rows oa, ow;
+    int nk = 0;
+    int64_t load_k = 0;
     auto aim = [&](int t) {                                                       // the loads at tile t
       const int in_slab = kAT ? t % tiles_slab : t, tm = in_slab / tiles_n;
       const int64_t m0 = (int64_t)tm * S::kRows;
-      load_n0 = (in_slab - tm * tiles_n) * S::kCols;
+      const int n0 = (in_slab - tm * tiles_n) * S::kCols;
       nk = k_tiles(t);
-      load_k0 = k_first(t);
       load_k = k_count(t);
-      if (kAT) load_m0 = (int)m0;
+      if constexpr (kAT) aim_rows(std::integral_constant<int, kPitchA>{}, p.A, k_first(t), rowa, (int)m0, (int)p.M, oa);
       else ra = rsrc((uint64_t)(uintptr_t)p.A + (uint64_t)m0 * rowa, (int)min((int64_t)S::kRows, p.M - m0), S::kRows, rowa);
-      if (!kWT) rw = rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)load_n0 * roww, p.N - load_n0, S::kCols, roww);
+      if constexpr (kWT) aim_rows(std::integral_constant<int, kPitchW>{}, p.W, k_first(t), roww, n0, p.N, ow);
+      else rw = rsrc((uint64_t)(uintptr_t)p.W + (uint64_t)n0 * roww, p.N - n0, S::kCols, roww);
     };
-    // load c of k-tile `step` into stage s
-    auto issue = [&](int step, int s, int c) {
+    // k-tile `step` into stage s
+    auto issue = [&](int step, int s) {
       const bool outside = tail != 0 && step == nk - 1 && !in_tail;
       const uint32_t dst = smem_base + (uint32_t)(s * S::kStage + lw * 1024), k_off = (uint32_t)step * 128;
-      if (c < S::kLoadsA) {
-        const uint32_t at = dst + (uint32_t)(kLoaders * 1024 * c);
-        if (kAT) dma_rows(std::integral_constant<int, kPitchA>{}, (uint64_t)(uintptr_t)p.A + (uint64_t)load_k0 * rowa + (uint64_t)load_m0 * 2, rowa, step, load_k, (int)p.M - load_m0, c, at);
-        else dma16(ra, (outside ? kOutside : va) + (uint32_t)(8 * kLoaders * c) * rowa, k_off, at);
-        return;
-      }
-      const int cw = c - S::kLoadsA;
-      const uint32_t at = dst + (uint32_t)(S::kA + kLoaders * 1024 * cw);
-      if (kWT) dma_rows(std::integral_constant<int, kPitchW>{}, (uint64_t)(uintptr_t)p.W + (uint64_t)load_k0 * roww + (uint64_t)load_n0 * 2, roww, step, load_k, p.N - load_n0, cw, at);
-      else dma16(rw, (outside ? kOutside : vw) + (uint32_t)(8 * kLoaders * cw) * roww, k_off, at);
+      const int left = (int)min(load_k - (int64_t)step * kBK, (int64_t)kBK);
+      const i32x4 da = kAT ? rsrc(oa.addr + (uint64_t)step * (kBK * rowa), left, kBK, rowa) : ra;
+      const i32x4 dw = kWT ? rsrc(ow.addr + (uint64_t)step * (kBK * roww), left, kBK, roww) : rw;
+      const uint32_t a0 = outside ? kOutside : va, w0 = outside ? kOutside : vw;
+#pragma unroll
+      for (int c = 0; c < S::kLoadsA; ++c)
+        dma16(da, kAT ? oa.voff[c & 1] + (uint32_t)c * oa.stride : a0 + (uint32_t)(8 * kLoaders * c) * rowa, kAT ? 0u : k_off, dst + (uint32_t)(kLoaders * 1024 * c));
+#pragma unroll
+      for (int c = 0; c < S::kLoadsW; ++c)
+        dma16(dw, kWT ? ow.voff[c & 1] + (uint32_t)c * ow.stride : w0 + (uint32_t)(8 * kLoaders * c) * roww, kWT ? 0u : k_off, dst + (uint32_t)(S::kA + kLoaders * 1024 * c));
     };
     // Loads run STAGES - 1 k-tiles ahead of the products, across tiles.  A loader waits for its loads alone: in a wave that stores as well, waiting for a
     // load means waiting for every store in front of it.
     int t = tile, step = 0, s = 0, flying = 0;
     aim(t);
     auto next = [&]() {
-#pragma unroll
-      for (int c = 0; c < S::kLoads; ++c) issue(step, s, c);
+      issue(step, s);
       ++flying;
       s = s == STAGES - 1 ? 0 : s + 1;
       if (++step == nk) {
