@@ -6,6 +6,7 @@
 // shuffles, everything between the load and the store in registers.
 #include "hstu_common.h"
 #include "hstu_kernels.h"
+#include "partial_sums.h"
 
 namespace hstu {
 
@@ -13,10 +14,6 @@ constexpr int kRowsPerBlock = 4;        // forward: one wave per row, 4 waves pe
 constexpr int kBwdWaves = 8;            // backward: 8 waves per workgroup, each walking over rows
 constexpr int kMaxBwdBlocks = 512;      // two workgroups per CU; also the number of partial column-sum rows
 
-// A value from another lane of the same row of 16, by DPP (a lane permutation through LDS, which __shfl_xor is, takes some 100 cycles where this takes 8).
-template <int kCtrl> __device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xF, 0xF, true));
-}
 // op over the 64 lanes of a wave, in every lane: neighbours, pairs, quads (mirrored in 8), octets (mirrored in 16), then rows in pairs and halves
 template <typename Op> __device__ __forceinline__ float wave_all(float v, Op op) {
   v = op(v, dpp<0xB1>(v));                                 // quad_perm 1 0 3 2
@@ -462,58 +459,21 @@ __global__ __launch_bounds__(64 * W, W < 16 && (BETA || !kAhead<E>) ? 3 : 4) voi
   }
 }
 
-// the sum over the lanes of a wave that are equal mod 4: two rotations inside a row of 16 lanes, then the rows in pairs
-__device__ __forceinline__ float sum_every_4th_lane(float v) {
-  v += dpp<0x124>(v);                                      // row_ror:4
-  v += dpp<0x128>(v);                                      // row_ror:8
-  const uint32_t a = __builtin_bit_cast(uint32_t, v);
-  const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
-  const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]));
-  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
-  return __builtin_bit_cast(float, (uint32_t)q[0]) + __builtin_bit_cast(float, (uint32_t)q[1]);
-}
-
-// dgamma[c] = sum over workgroups of partial[blk][0][c]; dbeta likewise from partial[blk][1][c] (not read unless wanted).
-// A few MB at most, so what counts is how many loads are in flight: a workgroup owns 16 columns (a 64-byte segment of every
-// partial row) and walks the rows kThreads / 4 at a time; a column's sums meet in a fixed tree (lanes, then waves).  With 64 columns
-// and 16 row groups per workgroup every thread walked 32 (512 features) or 128 (1024) rows one after the other:
-// 512 features 11.2 us, now 4.8; 1024 features 45.3 us, now 8.1.
 template <int kThreads>
-__global__ __launch_bounds__(kThreads) void gated_norm_colsum_kernel(int nblk, int D, const float* __restrict__ partial,
-                                                                     float* __restrict__ dgamma, float* __restrict__ dbeta) {
+__global__ __launch_bounds__(kThreads) void gated_norm_colsum_kernel(const ColsumJob job) {
   __shared__ f32x4 red[kThreads / 64][4];
-  const int tid = threadIdx.x, c4 = tid & 3, lane = tid & 63, wave = tid >> 6;
-  const int c = blockIdx.x * 16 + 4 * c4;                  // D is a multiple of 8: 4 columns are all in or all out
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (c < 2 * D) {
-#pragma unroll 4
-    for (int b = tid >> 2; b < nblk; b += kThreads / 4) s += *(const f32x4*)(partial + (int64_t)b * 2 * D + c);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) s[i] = sum_every_4th_lane(s[i]);
-  if (lane < 4) red[wave][c4] = s;
-  __syncthreads();
-  if (tid < 4 && c < 2 * D) {
-    f32x4 t = red[0][c4];
-#pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) t += red[w][c4];
-    float* dst = c < D ? dgamma + c : (dbeta ? dbeta + (c - D) : nullptr);
-    if (dst) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) dst[i] = t[i];
-    }
-  }
+  column_sums<kThreads>(job, blockIdx.x, red);
 }
 
 // No more threads than there are rows to add need, and 256 where the columns alone fill the chip with workgroups.  The whole backward, us with
 // 1,024 threads everywhere -> this way (64 columns x 16 row groups before): 100 rows x 512 features 10.95 -> 10.5 (10.4); 1 row x 4,096 with
 // dbeta 10.8 -> 9.3 (9.2); 100 rows 13.1 -> 12.2 (12.0); 1,000 rows x 512 and more unchanged (11.4; 12.9 before), where 256 threads take 0.1-0.4 longer.
 static hipError_t launch_colsum(int nblk, const NormBwdArgs& p, const float* partial, hipStream_t stream) {
-  const int cols = p.dbeta ? 2 * p.D : p.D;
-  const dim3 grid((cols + 15) / 16);
-  if (nblk <= 16) hipLaunchKernelGGL(gated_norm_colsum_kernel<64>, grid, dim3(64), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
-  else if (nblk <= 64 || grid.x > 256) hipLaunchKernelGGL(gated_norm_colsum_kernel<256>, grid, dim3(256), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
-  else hipLaunchKernelGGL(gated_norm_colsum_kernel<1024>, grid, dim3(1024), 0, stream, nblk, p.D, partial, p.dgamma, p.dbeta);
+  const ColsumJob job = {nblk, p.D, partial, p.dgamma, p.dbeta};
+  const dim3 grid(job.blocks());
+  if (nblk <= 16) hipLaunchKernelGGL(gated_norm_colsum_kernel<64>, grid, dim3(64), 0, stream, job);
+  else if (nblk <= 64 || grid.x > 256) hipLaunchKernelGGL(gated_norm_colsum_kernel<256>, grid, dim3(256), 0, stream, job);
+  else hipLaunchKernelGGL(gated_norm_colsum_kernel<1024>, grid, dim3(1024), 0, stream, job);
   return hipGetLastError();
 }
 
@@ -543,23 +503,23 @@ static hipError_t fwd_one(const NormFwdArgs& p, hipStream_t stream) {
 }
 
 template <typename E, int W>
-static hipError_t bwd_wide(const NormBwdArgs& p, float* partial, hipStream_t stream) {
+static hipError_t bwd_wide(const NormBwdArgs& p, float* partial, hipStream_t stream, bool sums) {
   const int nblk = gated_norm_bwd_blocks(p.T, p.D);
   if (p.beta || p.dbeta) hipLaunchKernelGGL((gated_norm_bwd_wide_kernel<E, W, true>), dim3(nblk), dim3(64 * W), 0, stream, p, partial);
   else hipLaunchKernelGGL((gated_norm_bwd_wide_kernel<E, W, false>), dim3(nblk), dim3(64 * W), 0, stream, p, partial);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !sums) return e;
   return launch_colsum(nblk, p, partial, stream);
 }
 
 template <typename E>
-static hipError_t bwd_one(const NormBwdArgs& p, float* partial, hipStream_t stream) {
+static hipError_t bwd_one(const NormBwdArgs& p, float* partial, hipStream_t stream, bool sums) {
   const int nblk = gated_norm_bwd_blocks(p.T, p.D);
   const size_t smem = (size_t)kBwdWaves * p.D * sizeof(float);                           // (32 KB at most)
   if (p.beta || p.dbeta) hipLaunchKernelGGL((gated_norm_bwd_kernel<E, true>), dim3(nblk), dim3(64 * kBwdWaves), 2 * smem, stream, p, partial);
   else hipLaunchKernelGGL((gated_norm_bwd_kernel<E, false>), dim3(nblk), dim3(64 * kBwdWaves), smem, stream, p, partial);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !sums) return e;
   return launch_colsum(nblk, p, partial, stream);
 }
 
@@ -621,16 +581,17 @@ hipError_t launch_norm_quant_fwd(const NormFwdArgs& p, void* q, int64_t sq, floa
 #undef Q_CALL
 }
 
-hipError_t launch_norm_bwd(const NormBwdArgs& p, float* partial, hipStream_t stream) {
+hipError_t launch_norm_bwd(const NormBwdArgs& p, float* partial, hipStream_t stream, bool sums) {
+  if (p.T <= 0 && !sums) return hipSuccess;
   if (p.T <= 0) return launch_colsum(0, p, partial, stream);   // no rows: the column sums are zero
   const int w = bwd_row_waves(p.D);
 #define BWD_WIDE(E)                                        \
   switch (w) {                                             \
-    case 1: return bwd_one<E>(p, partial, stream);         \
-    case 2: return bwd_wide<E, 2>(p, partial, stream);     \
-    case 4: return bwd_wide<E, 4>(p, partial, stream);     \
-    case 8: return bwd_wide<E, 8>(p, partial, stream);     \
-    default: return bwd_wide<E, 16>(p, partial, stream);   \
+    case 1: return bwd_one<E>(p, partial, stream, sums);         \
+    case 2: return bwd_wide<E, 2>(p, partial, stream, sums);     \
+    case 4: return bwd_wide<E, 4>(p, partial, stream, sums);     \
+    case 8: return bwd_wide<E, 8>(p, partial, stream, sums);     \
+    default: return bwd_wide<E, 16>(p, partial, stream, sums);   \
   }
   if (p.dtype == 0) { BWD_WIDE(__bf16) }
   BWD_WIDE(float)

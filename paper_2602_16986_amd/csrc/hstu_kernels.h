@@ -180,7 +180,15 @@ hipError_t launch_norm_fwd(const NormFwdArgs& p, hipStream_t stream);
 // same rows as launch_norm_fwd (p.y unused; p.gamma == nullptr: no normalisation), written as E4M3 codes q [T, D] (row stride
 // sq bytes) with one fp32 scale per row
 hipError_t launch_norm_quant_fwd(const NormFwdArgs& p, void* q, int64_t sq, float* qscale, hipStream_t stream);
-hipError_t launch_norm_bwd(const NormBwdArgs& p, float* partial, hipStream_t stream);   // partial: gated_norm_bwd_blocks(T, D) x 2 x D floats
+// partial: gated_norm_bwd_blocks(T, D) x 2 x D floats; sums = false: they are left there (launch_layer_sums)
+hipError_t launch_norm_bwd(const NormBwdArgs& p, float* partial, hipStream_t stream, bool sums = true);
+struct ColsumJob {                          // dgamma[c] (dbeta[c]) = sum over nblk rows of partial [nblk][2][D]
+  int nblk, D; const float* partial; float* dgamma; float* dbeta;
+#if defined(__HIPCC__)
+  __host__ __device__
+#endif
+  int blocks() const { return ((dbeta ? 2 * D : D) + 15) / 16; }
+};
 int gated_norm_bwd_blocks(int64_t T, int D);
 hipError_t launch_gated_norm_fwd(int64_t T, int D, int dtype, const void* attn, const void* u, const float* gamma,
                                  const float* beta, float eps, void* y, float* mean, float* rstd, hipStream_t stream);
@@ -229,12 +237,14 @@ hipError_t launch_fp8_gemm_bias2d(int64_t M, int N, int K, const void* A, const 
 hipError_t launch_fp8_gemm_silu(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale,
                                 void* D, void* u_out, int u_cols, hipStream_t stream);
 
-// gemm_tn.hip: C[N1, N2] (fp32) = A[T, N1]^T B[T, N2] (bf16, row strides lda, ldb in elements), reduction cut into slabs
-// of token rows with fp32 partial tiles in `partial` (gemm_tn_workspace_bytes) added in a fixed order.  N1, N2 multiples of 128.
+// gemm_tn.hip: C[N1, N2] (fp32) = A[T, N1]^T B[T, N2] (bf16, row strides lda, ldb in elements), reduction cut into slabs of token rows with fp32 partial
+// tiles in `partial` (gemm_tn_workspace_bytes), which launch_layer_sums adds in a fixed order (none: C is written).  N1, N2 multiples of 128.
+struct SlabJob { int64_t elems4; int nslab; const float* partial; float* C; };
 bool gemm_tn_supported(int N1, int N2);
 size_t gemm_tn_workspace_bytes(int64_t T, int N1, int N2);
 hipError_t launch_gemm_tn(int64_t T, int N1, int N2, const void* A, int64_t lda, const void* B, int64_t ldb, float* C, float* partial,
-                          hipStream_t stream);
+                          SlabJob& sums, hipStream_t stream);
+hipError_t launch_layer_sums(const SlabJob (&slabs)[2], const ColsumJob (&cols)[2], hipStream_t stream);
 
 // truncate.hip (strides and row sizes in bytes, multiples of 16)
 hipError_t launch_truncate_offsets(int B, int keep, const int32_t* offsets, const int32_t* num_targets, int32_t* out,

@@ -16,7 +16,7 @@ constexpr size_t kGemmWorkspace = (size_t)64 << 20;     // scratch offered to th
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct LayerLayout {
-  size_t attn, gemm, norm_partial, xn, pre, act, y, dy, dattn, dact, dxn, qscale, tn_partial, total;
+  size_t attn, gemm, norm_partial[2], xn, pre, act, y, dy, dattn, dact, dxn, qscale, tn_partial[2], total;   // (gated and input norm; d_w1 and d_w2)
   size_t ds, most;         // dS of the attention backward, if there is room for it: up to here
 };
 
@@ -61,19 +61,16 @@ LayerLayout make_layer_layout(const hstu_layer_params* p, int for_backward) {
   if (for_backward) {
     const size_t pe = hstu_gated_norm_bwd_workspace_bytes((int64_t)T, (int32_t)E);
     const size_t ph = hstu_gated_norm_bwd_workspace_bytes((int64_t)T, (int32_t)HD);
-    l.norm_partial = off; off += align_up(pe > ph ? pe : ph);
+    l.norm_partial[0] = off; off += align_up(ph);
+    l.norm_partial[1] = off; off += align_up(pe);
     l.pre = off; off += align_up(T * 4 * HD * 2);
     l.dy = off; off += align_up(T * HD * 2);
     l.dattn = off; off += align_up(T * HD * 2);
     l.dact = off; off += align_up(T * 4 * HD * 2);
     l.dxn = off; off += align_up(T * E * 2);
-    size_t tn = 0;                                     // partial tiles of the two weight-gradient products
-    if (gemm_tn_supported((int)E, (int)HD)) tn = gemm_tn_workspace_bytes((int64_t)T, (int)E, (int)HD);
-    if (gemm_tn_supported((int)(4 * HD), (int)E)) {
-      const size_t t1 = gemm_tn_workspace_bytes((int64_t)T, (int)(4 * HD), (int)E);
-      tn = t1 > tn ? t1 : tn;
-    }
-    l.tn_partial = off; off += align_up(tn);
+    // partial tiles of the two weight-gradient products
+    l.tn_partial[0] = off; off += gemm_tn_supported((int)(4 * HD), (int)E) ? align_up(gemm_tn_workspace_bytes((int64_t)T, (int)(4 * HD), (int)E)) : 0;
+    l.tn_partial[1] = off; off += gemm_tn_supported((int)E, (int)HD) ? align_up(gemm_tn_workspace_bytes((int64_t)T, (int)E, (int)HD)) : 0;
   }
   l.ds = l.total = off;
   l.most = off + (hstu_attn_workspace_bytes(&a, for_backward) - least);
@@ -239,7 +236,10 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
   __bf16* dattn = (__bf16*)(ws + l.dattn);
   __bf16* dact = (__bf16*)(ws + l.dact);
   __bf16* dxn = (__bf16*)(ws + l.dxn);
-  float* partial = (float*)(ws + l.norm_partial);
+  SlabJob slabs[2] = {};                                  // what one launch at the end adds up: the weight gradients' slabs,
+  const ColsumJob cols[2] = {                             // the norms' column sums
+      {gated_norm_bwd_blocks(T, (int)HD), (int)HD, (const float*)(ws + l.norm_partial[0]), d_gated_norm_w, nullptr},
+      {gated_norm_bwd_blocks(T, (int)E), (int)E, (const float*)(ws + l.norm_partial[1]), d_norm_w, nullptr}};
   void* gws = ws + l.gemm;
   const bool fp8 = p->w1_q != nullptr, own_uvqk = !fp8 && gemm_rows_preferred(T, 4 * HD, E);
   // Ordered by what each step needs, not by the forward's order.
@@ -293,7 +293,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
     n.du_pre = pre; n.sdu_pre = 4 * HD;
     n.y_out = y; n.sy_out = HD;                            // Eq. 4 again: Y, for dW2 = dout^T Y further down
     n.residual = nullptr; n.sres = 0; n.dgamma = d_gated_norm_w; n.dbeta = nullptr;
-    if (launch_norm_bwd(n, partial, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+    if (launch_norm_bwd(n, (float*)(ws + l.norm_partial[0]), stream, false) != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   if (!own_uvqk) {
     ProfScope ps("silu_fwd", stream);
@@ -316,7 +316,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
   {
     ProfScope ps("gemm_dw1", stream);
     if (gemm_tn_supported((int)(4 * HD), (int)E)) {
-      if (launch_gemm_tn(T, (int)(4 * HD), (int)E, dact, 4 * HD, xn, E, d_w1, (float*)(ws + l.tn_partial), stream) != hipSuccess)
+      if (launch_gemm_tn(T, (int)(4 * HD), (int)E, dact, 4 * HD, xn, E, d_w1, (float*)(ws + l.tn_partial[0]), slabs[0], stream) != hipSuccess)
         return HSTU_ERR_LAUNCH;
     } else {
       st = gemm_status(gemm_bf16(kGemmTN, 4 * HD, E, T, dact, 4 * HD, xn, E, nullptr, 0, d_w1, E, true, gws, kGemmWorkspace, stream));
@@ -326,7 +326,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
   {  // weight gradients: this library's slab-split kernel when the widths are multiples of 128, else the GEMM library
     ProfScope ps("gemm_dw2", stream);
     if (gemm_tn_supported((int)E, (int)HD)) {
-      if (launch_gemm_tn(T, (int)E, (int)HD, dout, E, y, HD, d_w2, (float*)(ws + l.tn_partial), stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+      if (launch_gemm_tn(T, (int)E, (int)HD, dout, E, y, HD, d_w2, (float*)(ws + l.tn_partial[1]), slabs[1], stream) != hipSuccess) return HSTU_ERR_LAUNCH;
     } else {
       st = gemm_status(gemm_bf16(kGemmTN, E, HD, T, dout, E, y, HD, nullptr, 0, d_w2, HD, true, gws, kGemmWorkspace, stream));
       if (st != HSTU_OK) return st;
@@ -338,7 +338,11 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
     n.T = T; n.D = (int32_t)E; n.dtype = HSTU_BF16; n.dy = dxn; n.sdy = E; n.a = z; n.sa = E; n.u = nullptr; n.su = 0;
     n.gamma = p->norm_w; n.beta = nullptr; n.eps = p->norm_eps; n.da = dz; n.sda = E; n.du = nullptr; n.sdu = 0;
     n.residual = dout; n.sres = E; n.dgamma = d_norm_w; n.dbeta = nullptr;
-    if (launch_norm_bwd(n, partial, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
+    if (launch_norm_bwd(n, (float*)(ws + l.norm_partial[1]), stream, false) != hipSuccess) return HSTU_ERR_LAUNCH;
+  }
+  {
+    ProfScope ps("layer_sums", stream);
+    if (launch_layer_sums(slabs, cols, stream) != hipSuccess) return HSTU_ERR_LAUNCH;
   }
   return HSTU_OK;
 }
