@@ -21,6 +21,9 @@
 // the expansion in it: 10 blocks 4.9 us (11.3 with a comparison sort and 49 KB of unrolled code), 346 blocks of 512-2048-token
 // sequences 8.7 us (18.4 + 5.2 for the expansion's own launch), 690 blocks of 8k-16k tokens 9.4 us (27 + 5); of the last, 1.0 us
 // go to the offsets and their scan, 1.1 to pricing, 1.1 to each pass of the sort, 1.2 to writing the list.
+// Few blocks with many pieces (a query tail) spent their time on rounds of scans for the piece size, on one thread writing all pieces of its block, and on
+// the expansion's searches through the bucket bounds in global memory: tail of a 20,000-token history 11.3 -> 8.0 us, of eight 8k-16k ones 10.7 -> 9.3-10.3, the
+// backward's launch with the gradient's sums to clear 10.0 -> 8.7.
 #include <cmath>
 
 #include "hstu_common.h"
@@ -267,18 +270,29 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   const int launch = num_targets && !many ? 0 : job.rule.launch;      // (with candidates it is there in any case)
   const bool wanted = job.slot_cap > 0 && max_cost > worth_cutting(chunk, job.fp32) + launch &&
                       max_cost > 2 * job.rule.min_chunk + job.rule.launch * (many ? kUnsure : 1);
+  const bool few = pairs <= 64;                            // every wave adds all of them up for itself: no barriers (a thread owns one pair at most)
 #pragma unroll 1
   for (int round = 0; wanted && max_cost > 2 * chunk; round ^= 1) {
     int my_slots = 0, my_cuts = 0;
+    const int at = few ? min(lane, pairs - 1) : own0, to = few ? at + (lane < pairs ? 1 : 0) : own1;
 #pragma unroll 1
-    for (int idx = own0; idx < own1; ++idx) {
+    for (int idx = at; idx < to; ++idx) {
       int len;
       const int pieces = pieces_of((int)costs[idx], len);
       my_slots += pieces > 1 ? pieces : 0;
       my_cuts += pieces > 1 ? 1 : 0;
     }
-    slot0 = block_scan(my_slots, sh.wave_total[3 + 2 * round], slots);
-    rank0 = block_scan(my_cuts, sh.wave_total[4 + 2 * round], nsplit);
+    if (few) {
+      slot0 = wave_scan(my_slots);
+      rank0 = wave_scan(my_cuts);
+      slots = __builtin_amdgcn_readlane(slot0, 63);
+      nsplit = __builtin_amdgcn_readlane(rank0, 63);
+      slot0 -= my_slots;
+      rank0 -= my_cuts;
+    } else {
+      slot0 = block_scan(my_slots, sh.wave_total[3 + 2 * round], slots);
+      rank0 = block_scan(my_cuts, sh.wave_total[4 + 2 * round], nsplit);
+    }
     entries = pairs - nsplit + slots;
     if (entries <= kSortMax && (long long)slots * H <= job.slot_cap) {       // uniform: every thread sees the same totals
       cuts = max_cost > worth_cutting(chunk, job.fp32) + launch + slots * H / job.rule.slots_per_tile;
@@ -297,6 +311,40 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   if (!cuts) {
 #pragma unroll 1
     for (int idx = tid; idx < pairs; idx += kSchedThreads) sh.keys[0][idx] = key_of((int)costs[idx], idx);
+  } else if (few) {                                      // a thread an entry, and a thread a head of a cut block
+    int32_t* const start = (int32_t*)sh.count;           // (free until the sort) a pair's first entry, its rank among the cut ones
+    int32_t* const rank = start + 64;
+    if (tid < pairs) {
+      int len;
+      const bool cut = pieces_of((int)costs[tid], len) > 1;
+      start[tid] = tid - rank0 + slot0;
+      rank[tid] = rank0;
+      sh.slot_c[tid] = cut ? (uint16_t)slot0 : (uint16_t)0xFFFF;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int e = tid; e < entries; e += kSchedThreads) {
+      int lo = 0, hi = pairs;
+#pragma unroll 1
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (start[mid] <= e) lo = mid; else hi = mid;
+      }
+      const int cost = (int)costs[lo], c = e - start[lo];
+      int plen;
+      pieces_of(cost, plen);
+      sh.keys[0][e] = key_of(min(plen, cost - c * plen), e);
+      sh.entry_item[e] = (uint32_t)lo | ((uint32_t)c << 13);
+    }
+#pragma unroll 1
+    for (int i = tid; i < pairs * H; i += kSchedThreads) {
+      const int idx = i / H, h = i - idx * H;
+      int unused;
+      const int pieces = pieces_of((int)costs[idx], unused);
+      if (pieces < 2) continue;
+      const WorkItem it = locate(idx, 1, false, unused);
+      job.splits[rank[idx] * H + h] = SplitItem{it.b, it.rb_h | h, (int)sh.slot_c[idx] * H + h * pieces, pieces, it.seq0, it.len, it.hist, 0};
+    }
   } else {
     int slot = slot0, rank = rank0, e = own0 - rank0 + slot0;
 #pragma unroll 1
@@ -394,12 +442,16 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
 //   and the zeros around every head's row;
 //   seed[v][h][i] (AttnArgs::seed), d = seed_dmax - i, and seed_up[h][i], d = i - kSeedUpZero;
 //   and clears the per-distance sums of the bias gradient.
-__device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen, int id, int n) {
+// The bounds (where they fit) wait in LDS: a search is seven dependent loads, from the caches 3 us.
+__device__ void expand_tables(const ExpandJob& j, int H, int K1, int max_seqlen, int id, int n, int32_t* lds_bounds, int lds_most) {
+  const bool staged = j.num_buckets <= lds_most;
+  for (int c = threadIdx.x; staged && c < j.num_buckets; c += kSchedThreads) lds_bounds[c] = j.bounds[c];
+  __syncthreads();
   auto bucket = [&](int x) {
     int lo = 0, hi = j.num_buckets;                       // bounds[lo] <= x < bounds[hi] (bounds[num_buckets] = +inf)
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
-      if (j.bounds[mid] <= x) lo = mid; else hi = mid;
+      if ((staged ? lds_bounds[mid] : j.bounds[mid]) <= x) lo = mid; else hi = mid;
     }
     return lo;
   };
@@ -436,7 +488,8 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(const int32_t* 
   __shared__ SchedShared sh;
   const int blk = blockIdx.x;
   if (blk < njobs) schedule_list(blk == 0 ? job0 : job1, sh, offsets, num_targets, B, H, K1, K2, T, max_seqlen);
-  else expand_tables(ex, H, K1, max_seqlen, (blk - njobs) * kSchedThreads + threadIdx.x, ((int)gridDim.x - njobs) * kSchedThreads);
+  else expand_tables(ex, H, K1, max_seqlen, (blk - njobs) * kSchedThreads + threadIdx.x, ((int)gridDim.x - njobs) * kSchedThreads,
+                     (int32_t*)sh.keys[0], kSortMax);
 }
 
 int log2_of(int n) { return 31 - __builtin_clz((unsigned)n); }
