@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0
 ROOT = os.path.dirname(os.path.abspath(__file__))
 
 
-TRAFFIC_SOURCES = ("attn_core.hip", "attn_fwd_pipe.hip", "attn_dq.hip", "attn_bwd_narrow.hip", "dist_sums.h", "gated_norm.hip", "schedule.hip", "api.hip",
+TRAFFIC_SOURCES = ("attn_core.hip", "attn_fwd_pipe.hip", "attn_dq.hip", "attn_bwd_narrow.hip", "dist_sums.h", "gated_norm.hip", "partial_sums.h", "schedule.hip", "api.hip",
                    "hstu_common.h", "hstu_geometry.h", "hstu_kernels.h", "hstu_plan.h")
 
 
