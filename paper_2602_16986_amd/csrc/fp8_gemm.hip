@@ -25,13 +25,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBM = 128;            // rows of A per workgroup
 
-// K = 64 * KS; kBN output features per chunk (64: full 128-byte row segments of C and D).  At K = 1024 the resident rows
-// of A take 128 registers per lane and one workgroup runs per compute unit; 32-feature chunks at two workgroups per compute
-// unit spilled and measured 25 % slower.
+// K = 64 * KS, up to 512 (at 1024 the resident rows of A would take 128 registers per lane); kBN output features per chunk (64: full 128-byte row
+// segments of C and D).
 // SILU: the epilogue applies x sigmoid(x) before the rounding (the first projection of the layer, Eq. 2), and output
 // features [0, u_cols) go to u_out [M, u_cols] instead of D (the gate is kept apart from the rest of the projection).
 template <int KS, int kBN, bool SILU>
-__global__ __launch_bounds__(256, KS >= 16 ? 1 : 2) void fp8_gemm_bias2d_kernel(int64_t M, int N, const unsigned char* __restrict__ A,
+__global__ __launch_bounds__(256, 2) void fp8_gemm_bias2d_kernel(int64_t M, int N, const unsigned char* __restrict__ A,
                                                                   const float* __restrict__ a_scale,
                                                                   const unsigned char* __restrict__ B,
                                                                   const float* __restrict__ b_scale, const __bf16* __restrict__ C,
@@ -163,155 +162,14 @@ __global__ __launch_bounds__(256, KS >= 16 ? 1 : 2) void fp8_gemm_bias2d_kernel(
   }
 }
 
-// K = 1024: the resident rows of A would take 128 registers per lane and leave one wave per SIMD.  Here a workgroup has 8
-// waves, two per 32-row block, each holding one half of K (64 registers) and accumulating its half of every dot product.
-// Both waves of a pair leave their raw partial sums in LDS; after a workgroup barrier each reads back 16 of the pair's 32
-// rows in the row-contiguous layout from both areas, adds them, applies the scales and C and stores.  KSW k-steps per wave.
-template <int KSW, bool SILU>
-__global__ __launch_bounds__(512, 1) void fp8_gemm_ksplit_kernel(int64_t M, int N, const unsigned char* __restrict__ A,
-                                                                  const float* __restrict__ a_scale,
-                                                                  const unsigned char* __restrict__ B,
-                                                                  const float* __restrict__ b_scale, const __bf16* __restrict__ C,
-                                                                  __bf16* __restrict__ D, __bf16* __restrict__ u_out, int u_cols, int n_per) {
-  constexpr int K = 128 * KSW, kBN = 64, CPR = K / 16, SWZ = 15, kEpiPitch = kBN + 4, BP = kBN * CPR / 512;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* bl = smem;                           // [kBN][K] weight chunk
-  float* epi = (float*)(smem + kBN * K);              // [8 waves][32][kEpiPitch] raw partial sums
-  float* sbl = epi + 8 * 32 * kEpiPitch;              // [N] weight scales
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, r = l & 31, h = l >> 5;
-  const int rb = w & 3, kh = w >> 2;                  // row block of the workgroup's 128 rows, half of K
-  const int64_t m0 = (int64_t)blockIdx.x * kBM + 32 * rb;
-  const int64_t gm = m0 + r;
-  const bool row_ok = gm < M;
-  i32x8 af[KSW];
-  {
-    const unsigned char* ap = A + gm * K + 64 * KSW * kh + 32 * h;
-#pragma unroll
-    for (int s = 0; s < KSW; ++s) {
-      u32x4 lo = {0u, 0u, 0u, 0u}, hi = {0u, 0u, 0u, 0u};
-      if (row_ok) { lo = *(const u32x4*)(ap + 64 * s); hi = *(const u32x4*)(ap + 64 * s + 16); }
-      af[s] = (i32x8){(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-    }
-  }
-  u32x4 bpre[BP];
-  auto bload = [&](int n0) {
-#pragma unroll
-    for (int i = 0; i < BP; ++i) {
-      const int p = t + 512 * i;
-      bpre[i] = *(const u32x4*)(B + (int64_t)(n0 + p / CPR) * K + 16 * (p % CPR));
-    }
-  };
-  auto bstore = [&]() {
-#pragma unroll
-    for (int i = 0; i < BP; ++i) {
-      const int p = t + 512 * i, n = p / CPR, c = p % CPR;
-      *(u32x4*)(bl + n * K + 16 * (c ^ (n & SWZ))) = bpre[i];
-    }
-  };
-  // read-back: this wave finishes rows [16 kh, 16 kh + 16) of its pair's block; 8 lanes per row, 8 rows per instruction
-  // This workgroup's output features are [n_begin, n_begin + n_end).  The operands are moved to the first, so that the chunk loop starts at 0
-  // (a start that the compiler does not know to be a multiple of 64 costs 65,536 rows x 4,096 features 514 us instead of 502; the kernel
-  // above has its registers full, takes the same either way and spills with moved operands).
-  const int n_begin = blockIdx.y * n_per, n_end = min(n_per, N - n_begin);
-  B += (int64_t)n_begin * K;
-  b_scale += n_begin;
-  if (C) C += n_begin;
-  D += n_begin;
-  const int u_end = u_cols - n_begin;                 // (SILU) of those, the ones in front of it go to u_out
-  const int er = l >> 3, ec = l & 7;
-  u32x4 cpre[2];
-  float sa_row[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int64_t row = m0 + 16 * kh + 8 * i + er;
-    sa_row[i] = row < M ? a_scale[row] : 0.f;
-  }
-  auto cload = [&](int n0) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int64_t row = m0 + 16 * kh + 8 * i + er;
-      cpre[i] = (u32x4){0u, 0u, 0u, 0u};
-      if (C && row < M) cpre[i] = *(const u32x4*)(C + row * N + n0 + 8 * ec);
-    }
-  };
-  for (int i = t; i < n_end; i += 512) sbl[i] = b_scale[i];
-  bload(0);
-  cload(0);
-  float* my_epi = epi + w * 32 * kEpiPitch;
-  const float* pair0 = epi + rb * 32 * kEpiPitch;             // partial sums of the pair's K halves
-  const float* pair1 = epi + (4 + rb) * 32 * kEpiPitch;
-  const int swz = r & SWZ;
-  for (int n0 = 0; n0 < n_end; n0 += kBN) {
-    __syncthreads();                                  // fragments and partial sums of the previous chunk are consumed
-    bstore();
-    __syncthreads();
-    if (n0 + kBN < n_end) bload(n0 + kBN);
-    f32x16 acc[2];
-#pragma unroll
-    for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[jt][q] = 0.f;
-#pragma unroll
-    for (int s = 0; s < KSW; ++s) {
-#pragma unroll
-      for (int jt = 0; jt < 2; ++jt) {
-        const unsigned char* brow = bl + (32 * jt + r) * K;
-        const int c0 = 4 * (KSW * kh + s) + 2 * h;
-        const u32x4 lo = *(const u32x4*)(brow + 16 * (c0 ^ swz));
-        const u32x4 hi = *(const u32x4*)(brow + 16 * ((c0 + 1) ^ swz));
-        const i32x8 bf = (i32x8){(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-        acc[jt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bf, af[s], acc[jt], 0, 0, 0, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(f32x4*)(my_epi + r * kEpiPitch + 32 * jt + 8 * g + 4 * h) =
-            (f32x4){acc[jt][4 * g + 0], acc[jt][4 * g + 1], acc[jt][4 * g + 2], acc[jt][4 * g + 3]};
-    __syncthreads();                                  // both halves of every pair are in LDS
-    const f32x4 sb0 = *(const f32x4*)(sbl + n0 + 8 * ec), sb1 = *(const f32x4*)(sbl + n0 + 8 * ec + 4);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int lr = 16 * kh + 8 * i + er;
-      const int64_t row = m0 + lr;
-      const float* s0 = pair0 + lr * kEpiPitch + 8 * ec;
-      const float* s1 = pair1 + lr * kEpiPitch + 8 * ec;
-      const f32x4 x0 = *(const f32x4*)s0 + *(const f32x4*)s1, x1 = *(const f32x4*)(s0 + 4) + *(const f32x4*)(s1 + 4);
-      float o[8];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[2 * e] = __uint_as_float(cpre[i][e] << 16);
-        o[2 * e + 1] = __uint_as_float(cpre[i][e] & 0xFFFF0000u);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[e] += x0[e] * sa_row[i] * sb0[e];
-        o[4 + e] += x1[e] * sa_row[i] * sb1[e];
-      }
-      if constexpr (SILU) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] *= __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * o[e]));
-      }
-      __bf16* dst = D + row * N + n0 + 8 * ec;
-      if constexpr (SILU) { if (n0 < u_end) dst = u_out + row * u_cols + n_begin + n0 + 8 * ec; }
-      if (row < M)
-        *(u32x4*)dst = (u32x4){pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]), pack_bf16x2(o[6], o[7])};
-    }
-    if (n0 + kBN < n_end) cload(n0 + kBN);
-  }
-}
-
 // Features per workgroup.  A workgroup owns 128 token rows; with fewer row blocks than the chip has workgroup slots the output
 // features are divided as well, and every part reads its rows of A again (from the caches; about the time of one chunk).
 // Of the divisions of the chunks into equal parts the one with the least rounds x (chunks + 1) is taken.
 // With a residual, us undivided -> by the rule (-: which does not divide):
-//   rows       K = 512, N = 512   N = 2048        K = 1024, N = 512   N = 2048
-//   4,096      18.0 ->  8.2       64.7 -> 12.3    24.6 ->  8.3        81.6 -> 16.9
-//   16,512     19.7 -> 14.8       66.7 -> 33.8    25.6 -> 25.6        82.6 -> 62.8
-//   32,768     22.3 -> 19.4       96.6 -> 67.5    28.3, -             110, -
-//   65,536     30.9, -            171, -          54.7, -             211, -
-//   100,000    52, -              256  -> 241     117 -> 119          391 -> 390
+//   rows       K = 512, N = 512   N = 2048
+//   32,768     22.3 -> 19.4       96.6 -> 67.5
+//   65,536     30.9, -            171, -
+//   100,000    52, -              256  -> 241
 int features_per_workgroup(int64_t M, int N, int slots) {
   const int64_t row_blocks = (M + kBM - 1) / kBM;
   const int chunks = N / 64;
@@ -323,26 +181,6 @@ int features_per_workgroup(int64_t M, int N, int slots) {
     if (best == 0 || cost < best) { best = cost; best_per = per; }
   }
   return 64 * best_per;
-}
-
-template <int KSW, bool SILU>
-hipError_t launch_ksplit(int64_t M, int N, const void* A, const float* a_scale, const void* B, const float* b_scale, const void* C,
-                         void* D, void* u_out, int u_cols, hipStream_t stream) {
-  auto kern = fp8_gemm_ksplit_kernel<KSW, SILU>;
-  const size_t smem = (size_t)64 * 128 * KSW + (size_t)8 * 32 * (64 + 4) * sizeof(float) + (size_t)N * sizeof(float);
-  static bool attr_set[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (!attr_set[dev]) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set[dev] = true;
-  }
-  const int n_per = features_per_workgroup(M, N, 256);                  // one workgroup per compute unit
-  const dim3 grid((unsigned)((M + kBM - 1) / kBM), (N + n_per - 1) / n_per);
-  hipLaunchKernelGGL(kern, grid, dim3(512), smem, stream, M, N, (const unsigned char*)A, a_scale, (const unsigned char*)B,
-                     b_scale, (const __bf16*)C, (__bf16*)D, (__bf16*)u_out, u_cols, n_per);
-  return hipGetLastError();
 }
 
 template <int KS, int kBN, bool SILU>
@@ -358,25 +196,39 @@ hipError_t launch_one(int64_t M, int N, const void* A, const float* a_scale, con
     if (e != hipSuccess) return e;
     attr_set[dev] = true;
   }
-  const int n_per = features_per_workgroup(M, N, KS >= 16 ? 256 : 512);
+  const int n_per = features_per_workgroup(M, N, 512);
   const dim3 grid((unsigned)((M + kBM - 1) / kBM), (N + n_per - 1) / n_per);
   hipLaunchKernelGGL(kern, grid, dim3(256), smem, stream, M, N, (const unsigned char*)A, a_scale, (const unsigned char*)B,
                      b_scale, (const __bf16*)C, (__bf16*)D, (__bf16*)u_out, u_cols, n_per);
   return hipGetLastError();
 }
 
+// gemm_rows.hip's tiles for K = 1024, where the resident rows of A would take 128 registers a lane, and for K = 512 while the rows do not fill the chip several times
+// over with workgroups of this kernel.  us, here -> there: K = 1024 (two waves per 32 rows, half of K each, three barriers a chunk): 20,600 x 4096 with SiLU 155 -> 122, 60,000 x 1024 with a
+// residual 118 -> 93, 1,000 x 1024 8.1 -> 6.3;  K = 512: 6,000 x 2048 20.7 -> 14.4, 12,000 x 512 13.3 -> 8.6, 20,600 x 512 17.2 -> 16.4, but a
+// layer of 20,600 rows 160 -> 164-167; 100,000 x 2048 223, 221.
+bool rows_kernel(int64_t M, int K) { return K == 1024 || (K == 512 && M <= 16384); }
+GemmRowsArgs rows_args(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale, void* D) {
+  GemmRowsArgs g = {};
+  g.M = M; g.N = N; g.K = K; g.A = A; g.lda = K; g.W = B; g.ldw = K; g.scale_a = a_scale; g.scale_w = b_scale; g.D = D; g.ldd = N;
+  return g;
+}
+
 }  // namespace
 
-// (the K = 1024 kernel keeps 138 KB + 4 N bytes in LDS)
 bool fp8_gemm_supported(int N, int K) { return (K == 128 || K == 256 || K == 512 || K == 1024) && N >= 64 && N % 64 == 0 && N <= 4096; }
 
 hipError_t launch_fp8_gemm_bias2d(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale,
                                   const void* C, void* D, hipStream_t stream) {
+  if (rows_kernel(M, K)) {
+    GemmRowsArgs g = rows_args(M, N, K, A, a_scale, B, b_scale, D);
+    g.C = C; g.ldc = N;
+    return launch_gemm_rows(g, kGemmFp8, C ? kEpiResidual : kEpiPlain, stream);
+  }
   switch (K) {
     case 128: return launch_one<2, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
     case 256: return launch_one<4, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
     case 512: return launch_one<8, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
-    case 1024: return launch_ksplit<8, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -384,11 +236,15 @@ hipError_t launch_fp8_gemm_bias2d(int64_t M, int N, int K, const void* A, const 
 hipError_t launch_fp8_gemm_silu(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale,
                                 void* D, void* u_out, int u_cols, hipStream_t stream) {
   if (u_cols % 64 != 0 || (u_cols > 0 && !u_out)) return hipErrorInvalidValue;
+  if (rows_kernel(M, K)) {
+    GemmRowsArgs g = rows_args(M, N, K, A, a_scale, B, b_scale, D);
+    g.D0 = u_out; g.ldd0 = u_cols; g.split = u_cols;
+    return launch_gemm_rows(g, kGemmFp8, kEpiSiluSplit, stream);
+  }
   switch (K) {
     case 128: return launch_one<2, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
     case 256: return launch_one<4, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
     case 512: return launch_one<8, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
-    case 1024: return launch_ksplit<8, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -32,6 +32,8 @@ typedef __attribute__((address_space(3))) void* lds_void;
 typedef __attribute__((address_space(3))) short4v* lds_s4;
 typedef __attribute__((address_space(3))) const bf16x8* lds_b8;
 typedef __attribute__((address_space(3))) f32x4* lds_f4;
+typedef __attribute__((address_space(3))) const i32x4* lds_i4;
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kBK = 64;                                  // of a k-tile: 128 bytes
 enum { kTile64Deep = 1, kTile64, kTile128Deep, kTile128, kTile192, kTile256 };     // by token rows of a tile; deep: one workgroup per compute unit, more stages
@@ -65,7 +67,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hf = lane >> 5, l32 = lane & 31, i16 = lane & 15, grp16 = lane >> 4;
-  constexpr bool kAT = OP == kGemmTN, kWT = OP == kGemmTN || OP == kGemmNN;   // operands with k as their slow axis
+  constexpr bool kAT = OP == kGemmTN, kWT = OP == kGemmTN || OP == kGemmNN, kFp8 = OP == kGemmFp8;   // operands with k as their slow axis; E4M3 codes
+  constexpr int kElem = kFp8 ? 1 : 2, kTileK = 128 / kElem;
   // Workgroups go to the 8 dies round-robin; a die takes a contiguous range of tiles, columns first: the tiles of one range of token rows run
   // beside each other and the rows come from memory once.
   const int tiles_n = (p.N + S::kCols - 1) / S::kCols;
@@ -73,7 +76,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   // k of a tile: all, or the tile's slab
   auto k_first = [&](int t) -> int64_t { return kAT ? (int64_t)(t / tiles_slab) * p.slab : 0; };
   auto k_count = [&](int t) -> int64_t { return kAT ? min(p.slab, p.K - k_first(t)) : p.K; };
-  auto k_tiles = [&](int t) -> int { return (int)((k_count(t) + kBK - 1) / kBK); };
+  auto k_tiles = [&](int t) -> int { return (int)((k_count(t) + kTileK - 1) / kTileK); };
   const int xcd = blockIdx.x % kNumXcd, per_die = (gridDim.x - xcd + kNumXcd - 1) / kNumXcd;
   int tile = xcd * (tiles / kNumXcd) + min(xcd, tiles % kNumXcd);
   const int tile_end = tile + tiles / kNumXcd + (xcd < tiles % kNumXcd ? 1 : 0);
@@ -85,11 +88,11 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   if (wave >= S::kWaves) {
     // ---- global -> LDS.  Load c of a loader: rows 8 (lw + kLoaders c) .. + 7 of an operand with k contiguous.  Of W [K, N]: 1 KB of whole rows.
     const int lw = wave - S::kWaves;
-    const uint32_t rowa = (uint32_t)(p.lda * 2), roww = (uint32_t)(p.ldw * 2);
+    const uint32_t rowa = (uint32_t)(p.lda * kElem), roww = (uint32_t)(p.ldw * kElem);
     const uint32_t chunk = (uint32_t)((lane & 7) ^ ((4 * lw + (lane >> 4)) & 7));
     const uint32_t va = (uint32_t)(8 * lw + (lane >> 3)) * rowa + 16 * chunk;
-    const int tail = kAT ? 0 : (int)(p.K % kBK);
-    const bool in_tail = (int)(8 * chunk) < tail;                             // (of the last k-tile, where that is not whole)
+    const int tail = kAT ? 0 : (int)(p.K % kTileK) * kElem;                     // bytes
+    const bool in_tail = (int)(16 * chunk) < tail;                             // (of the last k-tile, where that is not whole)
     const uint32_t vw = (uint32_t)(8 * lw + (lane >> 3)) * roww + 16 * chunk;
     // A descriptor holds the rows of the tile (rows past it read as zero); k advances in the scalar offset (for W [K, N] the descriptor advances).
     auto rsrc = [&](uint64_t addr, int left, int most, uint32_t row) -> i32x4 {
@@ -182,18 +185,31 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_hi ^ columns) + (uint32_t)(4 * pitch)));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto contiguous = [&](uint32_t base, uint32_t at, int ks) -> bf16x8 { return *(lds_b8)(uintptr_t)((base ^ (uint32_t)(32 * ks)) + at); };
-  auto wfrag = [&](uint32_t stage_off, int ks, int ni) -> bf16x8 {
+  // (E4M3: a lane's 32 codes of 64 k are two 16-byte chunks of its row, the same two for both operands, which is all that the product needs)
+  typedef typename std::conditional<kFp8, i32x8, bf16x8>::type Operand;
+  auto contiguous = [&](uint32_t base, uint32_t at, int ks) -> Operand {
+    if constexpr (kFp8) {
+      const i32x4 lo = *(lds_i4)(uintptr_t)((base ^ (uint32_t)(64 * ks)) + at), hi = *(lds_i4)(uintptr_t)((base ^ (uint32_t)(64 * ks + 32)) + at);
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      return *(lds_b8)(uintptr_t)((base ^ (uint32_t)(32 * ks)) + at);
+    }
+  };
+  auto wfrag = [&](uint32_t stage_off, int ks, int ni) -> Operand {
     if constexpr (kWT) return transposed(trw + stage_off + (uint32_t)(ks * 16 * kPitchW), (uint32_t)(16 * (8 * wn + 4 * ni)), kPitchW);
     else return contiguous(tw, stage_off + (uint32_t)(ni * 32 * 128), ks);
   };
-  auto afrag = [&](uint32_t stage_off, int ks, int mi) -> bf16x8 {
+  auto afrag = [&](uint32_t stage_off, int ks, int mi) -> Operand {
     if constexpr (kAT) return transposed(tra + stage_off + (uint32_t)(ks * 16 * kPitchA), (uint32_t)(64 * (MI * wm + mi)), kPitchA);
     else return contiguous(ta, stage_off + (uint32_t)(mi * 32 * 128), ks);
   };
 
-  constexpr int kSteps = kBK / 16, kTotal = kSteps * MI;
-  bf16x8 wf[2][2], af[2];
+  auto product = [&](const Operand& w, const Operand& x, const f32x16& acc) -> f32x16 {
+    if constexpr (kFp8) return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, acc, 0, 0, 0, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x, acc, 0, 0, 0);
+  };
+  constexpr int kSteps = kFp8 ? 2 : 4, kTotal = kSteps * MI;                       // k-steps of a k-tile
+  Operand wf[2][2], af[2];
   uint32_t off = 0;                                                                // of the k-tile's stage
   auto first_operands = [&]() {
 #pragma unroll
@@ -234,7 +250,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][ni], af[n & 1], acc[ni][mi], 0, 0, 0);
+        for (int ni = 0; ni < 2; ++ni) acc[ni][mi] = product(wf[ks & 1][ni], af[n & 1], acc[ni][mi]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -251,15 +267,23 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     const int64_t ldd = EPI == kEpiSiluSplit && first ? p.ldd0 : p.ldd;
     __bf16* const d = (EPI == kEpiSiluSplit && first ? (__bf16*)p.D0 : (__bf16*)p.D) + w0 * ldd + col;
     float* const sums = (float*)p.D + (kAT ? (int64_t)(tile / tiles_slab) * p.M * p.N : 0) + w0 * ldd + col;          // (kEpiSums)
+    f32x4 sb[2];                                                                   // E4M3: the columns' scales, and the rows'
+    float sa[2];
+    if (kFp8 && col_ok) {
+      sb[0] = *(const f32x4*)(p.scale_w + col);
+      sb[1] = *(const f32x4*)(p.scale_w + col + 4);
+    }
     u32x4 res[2];
     auto fetch = [&](int part) {
 #pragma unroll
       for (int it = 0; it < 2; ++it) {
         const int row = 16 * part + 8 * it;
-        if (col_ok && row + (lane >> 3) < rows) res[it] = *(const u32x4*)((const __bf16*)p.C + (w0 + row) * p.ldc + col);
+        if (!col_ok || row + (lane >> 3) >= rows) continue;
+        if (EPI == kEpiResidual) res[it] = *(const u32x4*)((const __bf16*)p.C + (w0 + row) * p.ldc + col);
+        if (kFp8) sa[it] = p.scale_a[w0 + row];
       }
     };
-    if (EPI == kEpiResidual) fetch(0);
+    if (EPI == kEpiResidual || kFp8) fetch(0);
 #pragma unroll
     for (int part = 0; part < 2 * MI; ++part) {
       const int mi = part / 2;
@@ -284,6 +308,10 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
           *(f32x4*)(sums + row * ldd + 4) = hi;
           continue;
         }
+        if (kFp8) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = v[e] * sa[it] * sb[e / 4][e % 4];
+        }
         if (EPI == kEpiResidual) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -302,7 +330,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
           store8((__bf16*)p.D0 + (w0 + row) * p.ldd0 + col, v);
         }
       }
-      if (EPI == kEpiResidual && part + 1 < 2 * MI) fetch(part + 1);
+      if ((EPI == kEpiResidual || kFp8) && part + 1 < 2 * MI) fetch(part + 1);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
     tile = next;
@@ -332,6 +360,9 @@ template <int OP, int EPI>
 hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
   if constexpr (OP == kGemmTN) {
     return tile == kTile128Deep ? launch_tile<2, 2, 2, 4, OP, EPI>(p, stream) : launch_tile<2, 2, 2, 2, OP, EPI>(p, stream);
+  } else if constexpr (OP == kGemmFp8) {
+    return tile == kTile64 ? launch_tile<2, 2, 1, 2, OP, EPI>(p, stream)
+         : tile == kTile128 ? launch_tile<2, 4, 2, 2, OP, EPI>(p, stream) : launch_tile<2, 4, 3, 2, OP, EPI>(p, stream);
   } else {
     switch (tile) {
       case kTile64Deep: return launch_tile<2, 2, 1, 5, OP, EPI>(p, stream);
@@ -369,6 +400,15 @@ int gemm_rows_tile(int64_t M, int N, int epilogue) {
   return best;
 }
 
+// E4M3: tiles of 64 x 128, 128 x 256 and 192 x 256 take 1 : 3.3 : 4.9 (with a residual, whose rows find no registers there, 7.5), the small one 0.7 beside its rounds.  us
+// for the three:  6,000 x 2048, K = 512, SiLU 16.9 17.1 14.4 *;  12,000 x 512, K = 512, residual 8.8 8.6 * 15.2;  20,600 x 4096, K = 1024, SiLU 177 130 122 *;
+// 20,600 x 1024, K = 1024, residual 39.3 34.7 * 44.6;  6,000 x 512, K = 1024, residual 7.9 * 10.5 17.0.
+static int fp8_tile(int64_t M, int N, int epilogue) {
+  auto rounds = [&](int rows, int cols) { return (double)(((M + rows - 1) / rows * ((N + cols - 1) / cols) + 255) / 256); };
+  const double t64 = rounds(64, 128) + 0.7, t128 = 3.3 * rounds(128, 256), t192 = (epilogue == kEpiResidual ? 7.5 : 4.9) * rounds(192, 256);
+  return t64 <= t128 && t64 <= t192 ? kTile64 : t128 <= t192 ? kTile128 : kTile192;
+}
+
 // With long rows and much work the library's kernels are the faster ones (with SiLU and all: 30,000 rows, widths 1024 and 1024, a layer's forward 429 us with the
 // library, 457 with these; 8,000 rows 141 and 128); between the two lines both are alike.
 bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)M * (double)N * (double)K < 1e11; }
@@ -376,11 +416,15 @@ bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (
 hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || (op != kGemmTN && p.K % 8 != 0)) return hipErrorInvalidValue;
   if (op == kGemmTN) tile = (p.M + 127) / 128 * ((p.N + 127) / 128) * ((p.K + p.slab - 1) / p.slab) <= 256 ? kTile128Deep : kTile128;
+  else if (op == kGemmFp8) tile = fp8_tile(p.M, p.N, epilogue);
   else if (tile == 0) tile = gemm_rows_tile(p.M, p.N, epilogue);
   if (op == kGemmNT && epilogue == kEpiSiluSplit) return launch_epi<kGemmNT, kEpiSiluSplit>(p, tile, stream);
   if (op == kGemmNT && epilogue == kEpiPreAndSilu) return launch_epi<kGemmNT, kEpiPreAndSilu>(p, tile, stream);
   if (op == kGemmNT && epilogue == kEpiResidual) return launch_epi<kGemmNT, kEpiResidual>(p, tile, stream);
   if (op == kGemmNN && epilogue == kEpiPlain) return launch_epi<kGemmNN, kEpiPlain>(p, tile, stream);
+  if (op == kGemmFp8 && epilogue == kEpiPlain) return launch_epi<kGemmFp8, kEpiPlain>(p, tile, stream);
+  if (op == kGemmFp8 && epilogue == kEpiResidual) return launch_epi<kGemmFp8, kEpiResidual>(p, tile, stream);
+  if (op == kGemmFp8 && epilogue == kEpiSiluSplit) return launch_epi<kGemmFp8, kEpiSiluSplit>(p, tile, stream);
   if (op == kGemmTN && epilogue == kEpiSums) return launch_epi<kGemmTN, kEpiSums>(p, tile, stream);
   return hipErrorInvalidValue;
 }

@@ -206,7 +206,7 @@ hipError_t launch_silu_bwd(int64_t T, int C, const void* pre, void* dact, hipStr
 // C: optional bf16 [M,N] added to the product (nullptr: none); D bf16 or fp32 (d_fp32); ld*: row strides in elements.
 // silu: SiLU applied to the product in the library's epilogue, before the one rounding to bf16.
 // Returns 0, -1 (library error) or -2 (no kernel for this problem).  gemm_bf16_tunings: how often candidates were timed.
-enum { kGemmNT = 0, kGemmNN = 1, kGemmTN = 2 };
+enum { kGemmNT = 0, kGemmNN = 1, kGemmTN = 2, kGemmFp8 = 3 };       // kGemmFp8 (gemm_rows.hip): kGemmNT on E4M3 codes
 long gemm_bf16_tunings();
 int gemm_bf16(int op, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, const void* C,
               int64_t ldc, void* D, int64_t ldd, bool d_fp32, void* ws, size_t ws_bytes, hipStream_t stream, bool silu = false);
@@ -215,7 +215,8 @@ int gemm_bf16(int op, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
 struct GemmRowsArgs {
   int64_t M; int32_t N; int64_t K;          // multiples of 8: N, and K or (kGemmTN) M
   const void* A; int64_t lda;               // [M, K]; kGemmTN: [K, M]
-  const void* W; int64_t ldw;               // [N, K] (kGemmNT) or [K, N] (kGemmNN, kGemmTN)
+  const void* W; int64_t ldw;               // [N, K] (kGemmNT, kGemmFp8) or [K, N] (kGemmNN, kGemmTN)
+  const float* scale_a; const float* scale_w;   // kGemmFp8: of the M rows and the N columns
   const void* C; int64_t ldc;               // kEpiResidual: rows added before the one rounding
   void* D; int64_t ldd;
   void* D0; int64_t ldd0;                   // second output, see the epilogues
