@@ -268,25 +268,53 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     __bf16* const d = (EPI == kEpiSiluSplit && first ? (__bf16*)p.D0 : (__bf16*)p.D) + w0 * ldd + col;
     float* const sums = (float*)p.D + (kAT ? (int64_t)(tile / tiles_slab) * p.M * p.N : 0) + w0 * ldd + col;          // (kEpiSums)
     f32x4 sb[2];                                                                   // E4M3: the columns' scales, and the rows'
-    float sa[2];
+    constexpr bool kRes = EPI == kEpiResidual;
+    float sa[kRes ? MI : 2];
     if (kFp8 && col_ok) {
       sb[0] = *(const f32x4*)(p.scale_w + col);
       sb[1] = *(const f32x4*)(p.scale_w + col + 4);
     }
-    u32x4 res[2];
+    if (kFp8 && kRes) {                                                            // (of the accumulators' rows)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+        if (32 * mi + l32 < rows) sa[mi] = p.scale_a[m0 + 32 * (MI * wm + mi) + l32];
+    }
+    // Residual rows come kAhead parts early: memory operations complete in order, so waiting for a load waits for the stores before it, and 16 rows in flight per
+    // wave do not cover the latency.  Descriptors drop what lies outside (the row is in the lane's offset, which the range check covers): a branch would keep the
+    // compiler from counting the stores in between.  As many parts as the registers hold.  us, one part -> these: E4M3, K = 1024, 262,144 x 1024 444 -> 430,
+    // 100,000 x 1024 176 -> 171;  a bf16 layer's forward, widths 512, 6,400 rows 74.1 -> 72.8, 87,000 rows 643 -> 633.  Without a residual the rows' scales stay one
+    // part early: all of them at once 851 -> 876 (the forward of 100,000 rows, E = 1024, H D = 512: the stores come in one burst).
+    constexpr int kAhead = !kRes ? 1 : MI == 1 || MI == 4 || (kFp8 && MI == 3) ? 2 : MI == 2 && S::kWavesPerSimd == 4 ? 3 : 4;
+    u32x4 res[kAhead][2];
+    __amdgpu_buffer_rsrc_t rc, rd;
+    const uint32_t vc = col_ok ? (uint32_t)((lane >> 3) * p.ldc + col) * 2 : kOutside, vd = col_ok ? (uint32_t)((lane >> 3) * p.ldd + col) * 2 : kOutside;
+    if (kRes) {
+      const int64_t r0 = m0 + 32 * MI * wm;
+      const int there = max(0, min(rows, 32 * MI));
+      rc = __builtin_amdgcn_make_buffer_rsrc((void*)((const __bf16*)p.C + (there ? r0 * p.ldc : 0)), 0, (int)(there * p.ldc * 2), 0x00020000);
+      rd = __builtin_amdgcn_make_buffer_rsrc((void*)((__bf16*)p.D + (there ? r0 * p.ldd : 0)), 0, (int)(there * p.ldd * 2), 0x00020000);
+    }
     auto fetch = [&](int part) {
 #pragma unroll
       for (int it = 0; it < 2; ++it) {
         const int row = 16 * part + 8 * it;
-        if (!col_ok || row + (lane >> 3) >= rows) continue;
-        if (EPI == kEpiResidual) res[it] = *(const u32x4*)((const __bf16*)p.C + (w0 + row) * p.ldc + col);
-        if (kFp8) sa[it] = p.scale_a[w0 + row];
+        if (kRes) res[part % kAhead][it] = __builtin_amdgcn_raw_buffer_load_b128(rc, (int)(vc + (uint32_t)(row * p.ldc * 2)), 0, 0);
+        else if (kFp8 && col_ok && row + (lane >> 3) < rows) sa[it] = p.scale_a[w0 + row];
       }
     };
-    if (EPI == kEpiResidual || kFp8) fetch(0);
+    if (kRes || kFp8) {
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) fetch(i);
+    }
 #pragma unroll
     for (int part = 0; part < 2 * MI; ++part) {
       const int mi = part / 2;
+      if (kFp8 && kRes && part % 2 == 0) {
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[ni][mi][r] *= sa[mi];
+      }
       if ((l32 >> 4) == part % 2) {
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
@@ -302,7 +330,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
         const f32x4 lo = *(lds_f4)(uintptr_t)at, hi = *(lds_f4)(uintptr_t)(at ^ 16);
         const int row = 16 * part + 8 * it;
         float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        if (!col_ok || row + (lane >> 3) >= rows) continue;
+        if (!kRes && (!col_ok || row + (lane >> 3) >= rows)) continue;
         if (EPI == kEpiSums) {
           *(f32x4*)(sums + row * ldd) = lo;
           *(f32x4*)(sums + row * ldd + 4) = hi;
@@ -310,14 +338,17 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
         }
         if (kFp8) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = v[e] * sa[it] * sb[e / 4][e % 4];
+          for (int e = 0; e < 8; ++e) v[e] = (kRes ? v[e] : v[e] * sa[it]) * sb[e / 4][e % 4];
         }
-        if (EPI == kEpiResidual) {
+        if (kRes) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            v[2 * e] += __uint_as_float(res[it][e] << 16);
-            v[2 * e + 1] += __uint_as_float(res[it][e] & 0xFFFF0000u);
+            v[2 * e] += __uint_as_float(res[part % kAhead][it][e] << 16);
+            v[2 * e + 1] += __uint_as_float(res[part % kAhead][it][e] & 0xFFFF0000u);
           }
+          const u32x4 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+          __builtin_amdgcn_raw_buffer_store_b128(o, rd, (int)(vd + (uint32_t)(row * p.ldd * 2)), 0, 2);     // (non-temporal)
+          continue;
         }
         if (EPI == kEpiSiluSplit) {
 #pragma unroll
@@ -330,7 +361,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
           store8((__bf16*)p.D0 + (w0 + row) * p.ldd0 + col, v);
         }
       }
-      if ((EPI == kEpiResidual || kFp8) && part + 1 < 2 * MI) fetch(part + 1);
+      if ((kRes || kFp8) && part + kAhead < 2 * MI) fetch(part + kAhead);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
     tile = next;
