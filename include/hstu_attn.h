@@ -254,7 +254,8 @@ typedef struct hstu_layer_params {
  * invalid description.  Forward: X, the projection and Y (T*(E + 5*H*d) bf16), backward: 17 such [T, 512]-sized
  * buffers at E = H*d = 512; both include the attention workspace and 64 MiB offered to the GEMM library.  The backward's figure
  * includes the room for dS of hstu_attn_workspace_bytes, and hstu_layer_bwd too accepts a workspace without it, any size from
- * hstu_layer_workspace_least_bytes on. */
+ * hstu_layer_workspace_least_bytes on.  Neither figure falls as total_tokens grows (the rest alike): what is sized for the
+ * largest batch serves every smaller one. */
 size_t hstu_layer_workspace_bytes(const hstu_layer_params* p, int for_backward);
 size_t hstu_layer_workspace_least_bytes(const hstu_layer_params* p, int for_backward);
 

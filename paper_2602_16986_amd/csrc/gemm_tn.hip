@@ -17,6 +17,22 @@ constexpr int kBK = 64;                    // token rows of a k-tile
 
 bool gemm_tn_supported(int N1, int N2) { return N1 >= kTile && N2 >= kTile && N1 % kTile == 0 && N2 % kTile == 0; }
 
+namespace {
+constexpr double kTileUs = 0.72, kSumsUs = 3.5;                    // 64 token rows of a tile; the launch that adds slabs up
+double slab_us(int N1, int N2) { return (double)N1 * N2 * 8 / 5e6; }
+int tiles_of(int N1, int N2) { return (N1 / kTile) * (N2 / kTile); }
+
+// No more slabs than k-tiles, nor than give every compute unit two workgroups; and slabs that take longer to write and read than the whole product never
+// pay.  None of the three falls as T grows: the room for the partial sums is sized by this, so that a workspace for T rows serves fewer rows too.
+int64_t most_slabs(int64_t T, int N1, int N2) {
+  const int tiles = tiles_of(N1, N2);
+  const int64_t k_tiles = (T + kBK - 1) / kBK;
+  const double whole = kTileUs * (double)((tiles + 255) / 256 * k_tiles);
+  const int64_t pay = (int64_t)std::max(1.0, (whole - kSumsUs) / slab_us(N1, N2));
+  return std::min(std::min(k_tiles, pay), (int64_t)std::max(1, 512 / tiles));
+}
+}  // namespace
+
 // The number of slabs with the least time: a compute unit works through its tiles at 0.72 us per 64 token rows, and slabs cost a launch that adds them up and
 // a copy of the output each to write and read.  us of both launches, with a kernel of its own (64 x 64 per wave, tiles staged through registers, 512
 // workgroups) -> here:
@@ -26,14 +42,14 @@ bool gemm_tn_supported(int N1, int N2) { return N1 >= kTile && N2 >= kTile && N1
 //    6,418      32  ->  29         20   -> 16
 //    1,000      18  ->  14         11   -> 11
 int gemm_tn_slabs(int64_t T, int N1, int N2) {
-  const int tiles = (N1 / kTile) * (N2 / kTile);
-  const int64_t most = std::min<int64_t>((T + kBK - 1) / kBK, std::max(1, 512 / tiles));
+  const int tiles = tiles_of(N1, N2);
+  const int64_t most = most_slabs(T, N1, N2);
   int64_t best = 1;
   double least = 0;
   for (int64_t n = 1; n <= most; ++n) {
     const int64_t rows = ((T + n - 1) / n + kBK - 1) / kBK;
-    double us = 0.72 * (double)((tiles * n + 255) / 256 * rows);
-    if (n > 1) us += 3.5 + (double)n * N1 * N2 * 8 / 5e6;
+    double us = kTileUs * (double)((tiles * n + 255) / 256 * rows);
+    if (n > 1) us += kSumsUs + (double)n * slab_us(N1, N2);
     if (n == 1 || us < least) { least = us; best = n; }
   }
   return (int)best;
@@ -44,8 +60,8 @@ int64_t slab_rows(int64_t T, int nslab) { return ((T + nslab - 1) / nslab + kBK 
 }  // namespace
 
 size_t gemm_tn_workspace_bytes(int64_t T, int N1, int N2) {
-  const int nslab = gemm_tn_slabs(T, N1, N2);
-  return nslab == 1 ? 0 : (size_t)nslab * (size_t)N1 * (size_t)N2 * sizeof(float);
+  const int64_t most = most_slabs(T, N1, N2);
+  return most <= 1 ? 0 : (size_t)most * (size_t)N1 * (size_t)N2 * sizeof(float);
 }
 
 hipError_t launch_gemm_tn(int64_t T, int N1, int N2, const void* A, int64_t lda, const void* B, int64_t ldb, float* C, float* partial,
