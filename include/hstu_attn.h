@@ -220,10 +220,11 @@ int hstu_truncate_bwd(int32_t batch, int64_t total_tokens, const int32_t* seq_of
  * straight into the column blocks of one gradient buffer (no concatenation).
  *
  * The products over token rows run in this library's own kernels, unless the reduction is 1024 long or more and the product
- * takes 10^11 multiply-adds or more; those, and the weight gradients of widths that are not multiples of 128, run through hipBLASLt.  The first
- * such call on a device creates a hipBLASLt handle.  The library's GEMM kernels are chosen once per SHAPE CLASS, which is the layer's dimensions together with
- * the token count T rounded up to a power of two: the first call of a class runs the library's candidate kernels on
- * `stream`, waits for them and keeps the fastest (that call allocates inside the GEMM library, blocks the host and
+ * takes 10^11 multiply-adds or more; those, and the weight gradients of widths that are not multiples of 128, run through
+ * hipBLASLt.  The first such call on a device creates a hipBLASLt handle.  Both the route and the GEMM library's kernels go by the
+ * SHAPE CLASS, which is the layer's dimensions together with the token count T rounded up to a power of two (the multiply-adds
+ * that count are those at half of it, below every T of the class): the first call of a class runs the library's candidate
+ * kernels on `stream`, waits for them and keeps the fastest (that call allocates inside the GEMM library, blocks the host and
  * must not be captured into a graph; hstu_layer_gemm_tunings counts these events).  Every later call of the class,
  * whatever its exact T, only builds its descriptors on the host and enqueues.  Not thread-safe.
  * HSTU_ERR_UNSUPPORTED if the library has no kernel for a shape.

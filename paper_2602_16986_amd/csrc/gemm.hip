@@ -46,10 +46,9 @@ bool g_has_handle[64];
 constexpr int kCandidates = 16;   // heuristic answers timed when a class is tuned
 constexpr int kTrialRuns = 3;
 
-int64_t bucket_of(int64_t n) { int64_t b = 1; while (b < n) b <<= 1; return b; }
 // The token count is M for the projections and their input gradients, and the contraction length K for the weight gradients.
 Shape class_of(Shape s) {
-  if (s.op == kGemmTN) s.K = bucket_of(s.K); else s.M = bucket_of(s.M);
+  if (s.op == kGemmTN) s.K = token_class(s.K); else s.M = token_class(s.M);
   return s;
 }
 bool same(const Shape& a, const Shape& b) {

@@ -440,9 +440,13 @@ static int fp8_tile(int64_t M, int N, int epilogue) {
   return t64 <= t128 && t64 <= t192 ? kTile64 : t128 <= t192 ? kTile128 : kTile192;
 }
 
-// With long rows and much work the library's kernels are the faster ones (with SiLU and all: 30,000 rows, widths 1024 and 1024, a layer's forward 429 us with the
-// library, 457 with these; 8,000 rows 141 and 128); between the two lines both are alike.
-bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)M * (double)N * (double)K < 1e11; }
+// With long rows and much work the library's kernels are the faster ones, once they have been chosen for the size.  They are chosen by timing on a class's
+// first call, which blocks, and then serve every count of the class, some of them badly.  So a class goes to the library as a whole, and only if its
+// smallest count is beyond the line: one call leaves nothing to choose for another of its class.  A layer's step with widths of 1024, us, library (chosen for
+// this count) -> here: 30,000 rows 1,939 -> 1,910, 60,000 rows 3,678 -> 3,602, 120,000 rows 7,232 -> 7,205 (forward 1,715 -> 1,746); 26,000 rows, chosen for
+// 24,000, the forward 482 -> 408.  Widths of 2048: 15,000 rows 2,854 -> 2,921, 50,000 rows 9,192 -> 9,689; 8,000 rows, chosen for 6,000, 1,739 -> 1,598, but
+// 7,500 rows, chosen for them, 1,489 -> 1,532.
+bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)(token_class(M) / 2) * (double)N * (double)K < 1e11; }
 
 hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || (op != kGemmTN && p.K % 8 != 0)) return hipErrorInvalidValue;

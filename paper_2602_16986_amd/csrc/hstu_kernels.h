@@ -207,6 +207,8 @@ hipError_t launch_silu_bwd(int64_t T, int C, const void* pre, void* dact, hipStr
 // silu: SiLU applied to the product in the library's epilogue, before the one rounding to bf16.
 // Returns 0, -1 (library error) or -2 (no kernel for this problem).  gemm_bf16_tunings: how often candidates were timed.
 enum { kGemmNT = 0, kGemmNN = 1, kGemmTN = 2, kGemmFp8 = 3 };       // kGemmFp8 (gemm_rows.hip): kGemmNT on E4M3 codes
+// The token counts that share what was chosen for the first of them (gemm.hip): up to the next power of two.
+inline int64_t token_class(int64_t n) { int64_t c = 1; while (c < n) c <<= 1; return c; }
 long gemm_bf16_tunings();
 int gemm_bf16(int op, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, const void* C,
               int64_t ldc, void* D, int64_t ldd, bool d_fp32, void* ws, size_t ws_bytes, hipStream_t stream, bool silu = false);
@@ -227,7 +229,7 @@ struct GemmRowsArgs {
 // kEpiPreAndSilu: D gets the product, D0 the SiLU of the columns from `split` on.
 // kEpiSums: fp32, unrounded.
 enum { kEpiPlain = 0, kEpiResidual = 1, kEpiSiluSplit = 2, kEpiPreAndSilu = 3, kEpiSums = 4 };
-bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K);      // over the library (gemm.hip)
+bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K);      // over the library (gemm.hip): the same for every M of a token_class
 hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile = 0);   // tile: 0 by size
 
 // fp8_gemm.hip: D[M,N] (bf16) = a_scale[m] b_scale[n] (Aq[M,K] Bq[N,K]^T) + C[M,N] (bf16 or nullptr), E4M3 codes

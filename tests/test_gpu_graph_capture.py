@@ -76,8 +76,8 @@ def test_fp8_layer_forward_replays_from_a_graph():
 
 
 def test_bf16_layer_step_replays_from_a_graph():
-    """Forward and backward of the bf16 layer, GEMM library calls included: the plans are made by the eager call, the
-    captured calls only enqueue."""
+    """Forward and backward of the bf16 layer at widths whose products all run in this library's kernels: the captured calls only
+    enqueue (test_gpu_layer_routes.py captures a step with products of the GEMM library)."""
     from paper_2602_16986_amd.runner import DeviceLayer
     dl = DeviceLayer(wl.layer_case("layer-small-sparse-targets"))
     _capture_and_replay(dl.step, [dl.out, dl.dz, dl.d_norm_w, dl.d_w1, dl.d_gated_norm_w, dl.d_w2], dl.device)

@@ -137,7 +137,8 @@ def test_layer_reuses_the_work_lists_of_a_layer_of_another_width(hb, d, lengths,
 
 
 def test_layer_new_token_count_of_a_known_class_tunes_nothing(hb):
-    """The GEMM kernels are chosen once per shape class (layer dimensions, token count rounded up to a power of two).
+    """The GEMM library's kernels are chosen once per shape class (layer dimensions, token count rounded up to a power of two); here
+    those of the weight gradients, whose widths are no multiples of 128 (test_gpu_layer_routes.py has the products over token rows).
     A batch with another token count of the same class must not time candidates again (that would block the host on
     every jagged batch), and its results must still match the oracle."""
     run_case(wl.build_layer("class-a", [300, 0, 150, 210], 2, 64, 320, seed=11, K1=64, K2=16))     # T = 660: class 1024
