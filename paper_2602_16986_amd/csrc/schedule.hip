@@ -21,9 +21,10 @@
 // the expansion in it: 10 blocks 4.9 us (11.3 with a comparison sort and 49 KB of unrolled code), 346 blocks of 512-2048-token
 // sequences 8.7 us (18.4 + 5.2 for the expansion's own launch), 690 blocks of 8k-16k tokens 9.4 us (27 + 5); of the last, 1.0 us
 // go to the offsets and their scan, 1.1 to pricing, 1.1 to each pass of the sort, 1.2 to writing the list.
-// Few blocks with many pieces (a query tail) spent their time on rounds of scans for the piece size, on one thread writing all pieces of its block, and on
-// the expansion's searches through the bucket bounds in global memory: tail of a 20,000-token history 11.3 -> 8.0 us, of eight 8k-16k ones 10.7 -> 9.3-10.3, the
-// backward's launch with the gradient's sums to clear 10.0 -> 8.7.
+// Few blocks with many pieces (a query tail) spent their time on rounds of scans for the piece size and on one thread writing all pieces of its block, and
+// every call on the expansion's searches through the bucket bounds in global memory.  A forward, us, without -> with waves that share the pieces, staged
+// bounds and scans without barriers: tail of one 65,536-token history (1 head) 49.5 -> 37.4, of a 20,000-token one (4 heads) 34.7 -> 31.4, of eight 8k-16k
+// ones 81.5 -> 80.3;  short lists with few pieces: fp32, 426 tokens, 32.3 -> 31.9, 2,733 tokens (32 features) 30.6 -> 30.2.
 #include <cmath>
 
 #include "hstu_common.h"
@@ -270,11 +271,11 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   const int launch = num_targets && !many ? 0 : job.rule.launch;      // (with candidates it is there in any case)
   const bool wanted = job.slot_cap > 0 && max_cost > worth_cutting(chunk, job.fp32) + launch &&
                       max_cost > 2 * job.rule.min_chunk + job.rule.launch * (many ? kUnsure : 1);
-  const bool few = pairs <= 64;                            // every wave adds all of them up for itself: no barriers (a thread owns one pair at most)
+  const bool few = pairs <= 64;                            // every wave adds all of them up for itself, a pair a lane: no barriers
+  const int at = few ? min(lane, pairs) : own0, to = few ? min(lane + 1, pairs) : own1;
 #pragma unroll 1
   for (int round = 0; wanted && max_cost > 2 * chunk; round ^= 1) {
     int my_slots = 0, my_cuts = 0;
-    const int at = few ? min(lane, pairs - 1) : own0, to = few ? at + (lane < pairs ? 1 : 0) : own1;
 #pragma unroll 1
     for (int idx = at; idx < to; ++idx) {
       int len;
@@ -311,50 +312,20 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   if (!cuts) {
 #pragma unroll 1
     for (int idx = tid; idx < pairs; idx += kSchedThreads) sh.keys[0][idx] = key_of((int)costs[idx], idx);
-  } else if (few) {                                      // a thread an entry, and a thread a head of a cut block
-    int32_t* const start = (int32_t*)sh.count;           // (free until the sort) a pair's first entry, its rank among the cut ones
-    int32_t* const rank = start + 64;
-    if (tid < pairs) {
-      int len;
-      const bool cut = pieces_of((int)costs[tid], len) > 1;
-      start[tid] = tid - rank0 + slot0;
-      rank[tid] = rank0;
-      sh.slot_c[tid] = cut ? (uint16_t)slot0 : (uint16_t)0xFFFF;
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int e = tid; e < entries; e += kSchedThreads) {
-      int lo = 0, hi = pairs;
-#pragma unroll 1
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (start[mid] <= e) lo = mid; else hi = mid;
-      }
-      const int cost = (int)costs[lo], c = e - start[lo];
-      int plen;
-      pieces_of(cost, plen);
-      sh.keys[0][e] = key_of(min(plen, cost - c * plen), e);
-      sh.entry_item[e] = (uint32_t)lo | ((uint32_t)c << 13);
-    }
-#pragma unroll 1
-    for (int i = tid; i < pairs * H; i += kSchedThreads) {
-      const int idx = i / H, h = i - idx * H;
-      int unused;
-      const int pieces = pieces_of((int)costs[idx], unused);
-      if (pieces < 2) continue;
-      const WorkItem it = locate(idx, 1, false, unused);
-      job.splits[rank[idx] * H + h] = SplitItem{it.b, it.rb_h | h, (int)sh.slot_c[idx] * H + h * pieces, pieces, it.seq0, it.len, it.hist, 0};
-    }
   } else {
-    int slot = slot0, rank = rank0, e = own0 - rank0 + slot0;
+    int slot = slot0, rank = rank0, e = at - rank0 + slot0;
+    // A pair's pieces and heads are its thread's; with many pieces the waves share those of few pairs (all of them for a few pieces: 0.9 us, the
+    // instructions of 16 waves on 4 SIMDs)
+    const bool share = few && (max_cost >> 5) > chunk;
+    const int first = share ? wave : 0, step = share ? kSchedWaves : 1;
 #pragma unroll 1
-    for (int idx = own0; idx < own1; ++idx) {
+    for (int idx = few && !share && wave > 0 ? to : at; idx < to; ++idx) {
       const int cost = (int)costs[idx];
       int plen;
       const int pieces = pieces_of(cost, plen);
       sh.slot_c[idx] = pieces > 1 ? (uint16_t)slot : (uint16_t)0xFFFF;
 #pragma unroll 1
-      for (int c = 0; c < pieces; ++c) {
+      for (int c = first; c < pieces; c += step) {
         sh.keys[0][e + c] = key_of(min(plen, cost - c * plen), e + c);
         sh.entry_item[e + c] = (uint32_t)idx | ((uint32_t)c << 13);
       }
@@ -362,7 +333,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
         int unused;
         const WorkItem it = locate(idx, 1, false, unused);
 #pragma unroll 1
-        for (int h = 0; h < H; ++h) job.splits[rank * H + h] = SplitItem{it.b, it.rb_h | h, slot * H + h * pieces, pieces, it.seq0, it.len, it.hist, 0};
+        for (int h = first; h < H; h += step) job.splits[rank * H + h] = SplitItem{it.b, it.rb_h | h, slot * H + h * pieces, pieces, it.seq0, it.len, it.hist, 0};
         slot += pieces;
         ++rank;
       }

@@ -61,3 +61,36 @@ def test_pieces_that_nearly_fit_their_slots(dim, dtype, lengths, tail):
     wanted = np.concatenate([np.arange(L) >= L - tail for L in lengths])
     check("A", got[wanted], ref[wanted], TOL[dtype])
     assert np.all(got[~wanted] == 7.0)
+
+
+@pytest.mark.parametrize("lengths,heads,least", [([20000], 1, 70), ([20000], 18, 33), ([9000, 9500], 1, 33), ([700, 5000, 1300], 1, 16), ([1500, 1100], 2, 2)])
+def test_few_blocks_in_many_pieces(lengths, heads, least):
+    """Up to 64 blocks, the longest in more pieces (and heads) than the scheduler has waves to share them, in fewer, or in few: pieces tile every
+    block, and the wanted rows equal a float64 evaluation."""
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    gen, T, d, tail = torch.Generator(device="cuda").manual_seed(13), int(off[-1]), 128, 21
+    q, k, v = (torch.randn(T, heads, d, generator=gen, device="cuda").mul(d ** -0.5).bfloat16() for _ in range(3))
+    out = torch.full_like(q, 7.0)
+    prob = hb.AttnProblem(q, k, v, out, torch.from_numpy(off).cuda(), max_seqlen=max(lengths), seq_offsets_host=off, inv_n=1.0 / max(lengths), query_tail=tail)
+    ws = hb.new_workspace(hb.hstu_attn_workspace_bytes(prob, False), "cuda")
+    ws.fill_(0xFF)
+    hb.hstu_attn_fwd(prob, q, k, v, out, ws)
+    torch.cuda.synchronize()
+    items = ws[256:256 + 32 * hb.hstu_attn_schedule_stats(prob, ws, False)["items"]].cpu().numpy().view(np.int32).reshape(-1, 8)
+    pieces = {}
+    for b, rbh, t0, t1, slot, *_ in items.tolist():
+        pieces.setdefault((b, rbh & 255), []).append((t0, t1, slot))
+    assert len(pieces) == len(lengths) * heads and max(map(len, pieces.values())) >= least
+    for (b, _), p in pieces.items():
+        p.sort()
+        assert p[0][0] == 0 and p[-1][1] >= -(-lengths[b] // 32) and all(x[1] == y[0] for x, y in zip(p, p[1:]))
+        assert all(x[2] >= 0 for x in p) or len(p) == 1
+    slots = [s for p in pieces.values() for _, _, s in p if s >= 0]
+    assert len(slots) == len(set(slots))
+    for b, L in enumerate(lengths):
+        rows, seq = slice(off[b] + L - tail, off[b] + L), slice(off[b], off[b] + L)
+        s = torch.matmul(q[rows].double().transpose(0, 1), k[seq].double().transpose(0, 1).transpose(1, 2).contiguous())
+        seen = torch.arange(L, device="cuda")[None] <= torch.arange(L - tail, L, device="cuda")[:, None]
+        ref = torch.matmul(torch.where(seen, s * torch.sigmoid(s), 0.0) / max(lengths), v[seq].double().transpose(0, 1).contiguous()).transpose(0, 1)
+        check("A", to_np(out[rows]), ref.cpu().numpy(), TOL["bf16"])
+        assert (out[off[b]:off[b] + L - tail] == 7.0).all()
