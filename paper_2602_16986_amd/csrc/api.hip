@@ -162,7 +162,8 @@ ExpandJob prepare_bias(const hstu_attn_params* p, AttnArgs& a, unsigned char* ws
   a.bias_stride = p->max_seqlen + 1;
   a.bias_pitch = a.bias_stride + kBiasPad;
   a.seed = nullptr;
-  ex.table = p->rab_table; ex.bounds = p->rab_bounds; ex.num_buckets = p->num_buckets;
+  ex.table = p->rab_table; ex.bounds = p->rab_bounds;
+  ex.num_buckets = p->rab_table ? p->num_buckets : 0;      // (any number is accepted without a table; the kernel reads that many bounds)
   if (seeded(p, !for_forward)) {
     ex.seed = (float*)(ws + l.seed);
     ex.seed_len = seed_len_for(p->max_seqlen);
