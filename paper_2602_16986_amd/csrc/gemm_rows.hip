@@ -341,6 +341,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
           for (int e = 0; e < 8; ++e) v[e] = (kRes ? v[e] : v[e] * sa[it]) * sb[e / 4][e % 4];
         }
         if (kRes) {
+          // (E4M3: the scaled product is rounded before the residual is added, as in fp8_gemm_bias2d_kernel: a row's results do not depend on how many rows are beside it)
+#pragma clang fp contract(off)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             v[2 * e] += __uint_as_float(res[part % kAhead][it][e] << 16);
