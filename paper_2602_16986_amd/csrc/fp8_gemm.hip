@@ -25,12 +25,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBM = 128;            // rows of A per workgroup
 
-// K = 64 * KS, up to 512 (at 1024 the resident rows of A would take 128 registers per lane); kBN output features per chunk (64: full 128-byte row
-// segments of C and D).
+// K = 64 * KS (at 1024 the resident rows of A take 128 registers per lane and one workgroup runs per compute unit: for few rows only); kBN output features
+// per chunk (64: full 128-byte row segments of C and D).
 // SILU: the epilogue applies x sigmoid(x) before the rounding (the first projection of the layer, Eq. 2), and output
 // features [0, u_cols) go to u_out [M, u_cols] instead of D (the gate is kept apart from the rest of the projection).
 template <int KS, int kBN, bool SILU>
-__global__ __launch_bounds__(256, 2) void fp8_gemm_bias2d_kernel(int64_t M, int N, const unsigned char* __restrict__ A,
+__global__ __launch_bounds__(256, KS >= 16 ? 1 : 2) void fp8_gemm_bias2d_kernel(int64_t M, int N, const unsigned char* __restrict__ A,
                                                                   const float* __restrict__ a_scale,
                                                                   const unsigned char* __restrict__ B,
                                                                   const float* __restrict__ b_scale, const __bf16* __restrict__ C,
@@ -196,18 +196,19 @@ hipError_t launch_one(int64_t M, int N, const void* A, const float* a_scale, con
     if (e != hipSuccess) return e;
     attr_set[dev] = true;
   }
-  const int n_per = features_per_workgroup(M, N, 512);
+  const int n_per = features_per_workgroup(M, N, KS >= 16 ? 256 : 512);
   const dim3 grid((unsigned)((M + kBM - 1) / kBM), (N + n_per - 1) / n_per);
   hipLaunchKernelGGL(kern, grid, dim3(256), smem, stream, M, N, (const unsigned char*)A, a_scale, (const unsigned char*)B,
                      b_scale, (const __bf16*)C, (__bf16*)D, (__bf16*)u_out, u_cols, n_per);
   return hipGetLastError();
 }
 
-// gemm_rows.hip's tiles for K = 1024, where the resident rows of A would take 128 registers a lane, and for K = 512 while the rows do not fill the chip several times
+// gemm_rows.hip's tiles for K = 1024, where the resident rows of A take 128 registers a lane, and for K = 512 while the rows do not fill the chip several times
 // over with workgroups of this kernel.  us, here -> there: K = 1024 (two waves per 32 rows, half of K each, three barriers a chunk): 20,600 x 4096 with SiLU 155 -> 122, 60,000 x 1024 with a
 // residual 118 -> 93, 1,000 x 1024 8.1 -> 6.3;  K = 512: 6,000 x 2048 20.7 -> 14.4, 12,000 x 512 13.3 -> 8.6, 20,600 x 512 17.2 -> 16.4, but a
-// layer of 20,600 rows 160 -> 164-167; 100,000 x 2048 223, 221.
-bool rows_kernel(int64_t M, int K) { return K == 1024 || (K == 512 && M <= 16384); }
+// layer of 20,600 rows 160 -> 164-167; 100,000 x 2048 223, 221.  Few rows are one trip to memory here, and several k-tiles there: with a residual K = 512, 1 row x 512
+// 3.5, there 4.3, 48 rows 4.2, 4.5, 64 rows 4.4, 4.5;  K = 1024, 1 row 4.9, there 5.5, 32 rows 5.4, 5.7, 48 rows 5.9, 5.7.
+bool rows_kernel(int64_t M, int K) { return K == 1024 ? M > 32 : K == 512 && M >= 64 && M <= 16384; }
 GemmRowsArgs rows_args(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale, void* D) {
   GemmRowsArgs g = {};
   g.M = M; g.N = N; g.K = K; g.A = A; g.lda = K; g.W = B; g.ldw = K; g.scale_a = a_scale; g.scale_w = b_scale; g.D = D; g.ldd = N;
@@ -229,6 +230,7 @@ hipError_t launch_fp8_gemm_bias2d(int64_t M, int N, int K, const void* A, const 
     case 128: return launch_one<2, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
     case 256: return launch_one<4, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
     case 512: return launch_one<8, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
+    case 1024: return launch_one<16, 64, false>(M, N, A, a_scale, B, b_scale, C, D, nullptr, 0, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -245,6 +247,7 @@ hipError_t launch_fp8_gemm_silu(int64_t M, int N, int K, const void* A, const fl
     case 128: return launch_one<2, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
     case 256: return launch_one<4, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
     case 512: return launch_one<8, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
+    case 1024: return launch_one<16, 64, true>(M, N, A, a_scale, B, b_scale, nullptr, D, u_out, u_cols, stream);
     default: return hipErrorInvalidValue;
   }
 }
