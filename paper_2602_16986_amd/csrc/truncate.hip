@@ -8,7 +8,7 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 constexpr int kCopyThreads = 256;            // 4 waves
-constexpr int kRowsPerWave = 8;              // consecutive rows of more than 512 bytes handled by one wave per step
+constexpr int kRowsPerWave = 8;              // consecutive rows handled by one wave per step
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
 // out[b + 1] = sum over b' <= b of the kept rows of sequence b'; one workgroup walks the batch in chunks.
@@ -68,7 +68,7 @@ __device__ __forceinline__ void copy_rows(const char* const src[kRowsPerWave], c
   }
 }
 
-// Rows of more than 512 bytes, one per instruction of a wave.
+// Wide rows, and middling numbers of narrow ones (in_steps), one per instruction of a wave.
 // y row r of truncated sequence b is x row  offsets[b+1] - (out_offsets[b+1] - r).
 __global__ __launch_bounds__(kCopyThreads) void truncate_gather_kernel(int B, const int32_t* __restrict__ offsets,
                                                                        const int32_t* __restrict__ out_offsets, int64_t row_bytes,
@@ -231,8 +231,15 @@ int copy_grid(int64_t rows, int rows_per_step) {
   return (int)max((int64_t)1, min(wgs, (int64_t)256 * 32));
 }
 
-// Rows of up to 512 bytes: at least two to an instruction.
+// Rows of up to 512 bytes, at least two to an instruction, where a step's chain of trips to memory is all there is to wait for (one step), or the steps fill the
+// chip.  In between a row an instruction spreads over more waves; and with few rows a sequence, which a step walks through, it takes more rows to pay.  us,
+// row an instruction -> steps: 64 sequences, 27,000 rows of 48 bytes 7.9 -> 5.8, 20,000 sequences, 200,000 rows 45 -> 10, one sequence, 51 rows of 16 bytes 4.7 ->
+// 2.5;  but one sequence, 2,400 rows of 128 bytes 5.1 -> 5.9, 512 sequences, 400 rows of 16 bytes 7.1 -> 10.4, 1,300 rows 6.9 -> 11.5, 5,000 sequences, 7,500 rows 8.0 -> 15.7.
 constexpr int64_t kNarrowRow = 512;
+bool in_steps(int B, int64_t rows, int64_t row_bytes) {
+  if (row_bytes > kNarrowRow) return false;
+  return (rows <= kUnroll * (64 / (row_bytes / 16)) || rows >= 8192) && (rows >= 8 * (int64_t)B || rows >= 65536);
+}
 
 template <bool GATHER>
 hipError_t launch_copy(int B, int64_t rows, const int32_t* offsets, const int32_t* out_offsets, int64_t row_bytes, const void* src, int64_t src_stride,
@@ -253,7 +260,7 @@ hipError_t launch_truncate_offsets(int B, int keep, const int32_t* offsets, cons
 
 hipError_t launch_truncate_gather(int B, const int32_t* offsets, const int32_t* out_offsets, int64_t row_bytes, const void* x,
                                   int64_t x_stride, void* y, int64_t y_stride, int64_t y_rows, hipStream_t stream) {
-  if (row_bytes > kNarrowRow) {
+  if (!in_steps(B, y_rows, row_bytes)) {
     hipLaunchKernelGGL(truncate_gather_kernel, dim3(copy_grid(y_rows, kRowsPerWave)), dim3(kCopyThreads), 0, stream, B, offsets, out_offsets,
                        row_bytes, (const char*)x, x_stride, (char*)y, y_stride, y_rows);
     return hipGetLastError();
@@ -263,7 +270,7 @@ hipError_t launch_truncate_gather(int B, const int32_t* offsets, const int32_t* 
 
 hipError_t launch_truncate_scatter(int B, int64_t T, const int32_t* offsets, const int32_t* out_offsets, int64_t row_bytes,
                                    const void* dy, int64_t dy_stride, void* dx, int64_t dx_stride, hipStream_t stream) {
-  if (row_bytes > kNarrowRow) {
+  if (!in_steps(B, T, row_bytes)) {
     hipLaunchKernelGGL(truncate_scatter_kernel, dim3(copy_grid(T, kRowsPerWave)), dim3(kCopyThreads), 0, stream, B, T, offsets, out_offsets,
                        row_bytes, (const char*)dy, dy_stride, (char*)dx, dx_stride);
     return hipGetLastError();

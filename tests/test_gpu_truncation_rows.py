@@ -1,5 +1,5 @@
-"""Truncation of narrow rows, several of which one instruction moves: row widths that do and do not divide a wave's lanes, batches whose steps cross
-one, a few, or more sequences than a wave holds at a time, empty ones among them.  Bit for bit against the numpy oracle, both directions."""
+"""Truncation of narrow rows, of which one instruction moves one or several by a rule on their number: row widths that do and do not divide a wave's lanes,
+batches whose steps cross one, a few, or more sequences than a wave holds at a time, empty ones among them, on both sides of the rule.  Bit for bit against the numpy oracle, both directions."""
 import numpy as np
 import pytest
 import torch
@@ -13,6 +13,9 @@ BATCHES = {
     "ordinary": lambda rng: rng.integers(0, 300, size=70),
     "tiny": lambda rng: rng.integers(0, 3, size=5000),
     "mostly empty": lambda rng: np.where(rng.random(900) < 0.9, 0, rng.integers(1, 40, size=900)),
+    "long": lambda rng: np.array([9000, 3]),
+    "many tiny": lambda rng: rng.integers(0, 3, size=70000),
+    "many mostly empty": lambda rng: np.where(rng.random(50000) < 0.9, 0, rng.integers(1, 40, size=50000)),
     "empty ends": lambda rng: np.concatenate([np.zeros(130, int), [77, 0, 5], np.zeros(100, int)]),
 }
 
