@@ -419,14 +419,18 @@ hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
 //   20,000 x 512, K = 2048, W [K, N]        -    63.7    -    51.9  41.1 * 48.2      (42)
 //   87,728 x 512, K = 2048, W [K, N]        -   342.6    -   247.8 216.1 194.3 *    (182-197)
 //   1,200 x 512, K = 512, residual         6.1 *  6.3   8.1   8.0  13.0  18.6
-int gemm_rows_tile(int64_t M, int N, int epilogue) {
-  static const struct { int rows, cols, tile, deep; double rate; } kinds[4] = {
-      {64, 128, kTile64, kTile64Deep, 0.50}, {128, 128, kTile128, kTile128Deep, 0.68}, {192, 256, kTile192, kTile192, 0.80}, {256, 256, kTile256, kTile256, 0.87}};
+// From K = 1024 on the small tiles' share of the L2's requests counts for more, and a residual's epilogue for less.  us, by the rates of short K -> of long K: 5,000 x
+// 4096, K = 2048 97 -> 86, 2,500 x 8192, K = 2048 104 -> 90, 10,000 x 2048, K = 8192, W [K, N] 380 -> 329, 30,000 x 1024, K = 2048, residual 145 -> 130.
+int gemm_rows_tile(int64_t M, int N, int64_t K, int epilogue) {
+  static const struct { int rows, cols, tile, deep; double rate, rate_long; } kinds[4] = {{64, 128, kTile64, kTile64Deep, 0.50, 0.40}, {128, 128, kTile128, kTile128Deep, 0.68, 0.62},
+                                                                                          {192, 256, kTile192, kTile192, 0.80, 0.80}, {256, 256, kTile256, kTile256, 0.87, 0.87}};
+  const bool long_k = K >= 1024;
   int best = 0;
   double least = 0;
   for (const auto& k : kinds) {
     const int64_t tiles = (M + k.rows - 1) / k.rows * ((N + k.cols - 1) / k.cols);
-    const double rate = k.tile == kTile256 && epilogue == kEpiResidual ? 0.70 : k.rate;
+    double rate = long_k ? k.rate_long : k.rate;
+    if (k.tile == kTile256 && epilogue == kEpiResidual) rate = long_k ? 0.74 : 0.68;
     const double time = (double)((tiles + 255) / 256) * k.rows * k.cols / rate;
     if (best == 0 || time < least) { least = time; best = tiles <= 256 ? k.deep : k.tile; }
   }
@@ -454,7 +458,7 @@ hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStre
   if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || (op != kGemmTN && p.K % 8 != 0)) return hipErrorInvalidValue;
   if (op == kGemmTN) tile = (p.M + 127) / 128 * ((p.N + 127) / 128) * ((p.K + p.slab - 1) / p.slab) <= 256 ? kTile128Deep : kTile128;
   else if (op == kGemmFp8) tile = fp8_tile(p.M, p.N, epilogue);
-  else if (tile == 0) tile = gemm_rows_tile(p.M, p.N, epilogue);
+  else if (tile == 0) tile = gemm_rows_tile(p.M, p.N, p.K, epilogue);
   if (op == kGemmNT && epilogue == kEpiSiluSplit) return launch_epi<kGemmNT, kEpiSiluSplit>(p, tile, stream);
   if (op == kGemmNT && epilogue == kEpiPreAndSilu) return launch_epi<kGemmNT, kEpiPreAndSilu>(p, tile, stream);
   if (op == kGemmNT && epilogue == kEpiResidual) return launch_epi<kGemmNT, kEpiResidual>(p, tile, stream);
