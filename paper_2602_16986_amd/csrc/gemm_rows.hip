@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gemm_tiles.h"
 #include "hstu_common.h"
 #include "hstu_kernels.h"
 
@@ -36,7 +37,6 @@ typedef __attribute__((address_space(3))) const i32x4* lds_i4;
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kBK = 64;                                  // of a k-tile: 128 bytes
-enum { kTile64Deep = 1, kTile64, kTile128Deep, kTile128, kTile192, kTile256 };     // by token rows of a tile; deep: one workgroup per compute unit, more stages
 constexpr uint32_t kOutside = 0x80000000u;               // a lane offset beyond every range: the load returns zeros
 
 // WM x WN waves multiply, kLoaders more only load.
@@ -284,7 +284,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     // compiler from counting the stores in between.  As many parts as the registers hold.  us, one part -> these: E4M3, K = 1024, 262,144 x 1024 444 -> 430,
     // 100,000 x 1024 176 -> 171;  a bf16 layer's forward, widths 512, 6,400 rows 74.1 -> 72.8, 87,000 rows 643 -> 633.  Without a residual the rows' scales stay one
     // part early: all of them at once 851 -> 876 (the forward of 100,000 rows, E = 1024, H D = 512: the stores come in one burst).
-    constexpr int kAhead = !kRes ? 1 : MI == 1 || MI == 4 || (kFp8 && MI == 3) ? 2 : MI == 2 && S::kWavesPerSimd == 4 ? 3 : 4;
+    constexpr int kAhead = !kRes ? 1 : MI == 1 || MI == 4 ? 2 : MI == 2 && S::kWavesPerSimd == 4 ? 3 : 4;
     u32x4 res[kAhead][2];
     __amdgpu_buffer_rsrc_t rc, rd;
     const uint32_t vc = col_ok ? (uint32_t)((lane >> 3) * p.ldc + col) * 2 : kOutside, vd = col_ok ? (uint32_t)((lane >> 3) * p.ldd + col) * 2 : kOutside;
@@ -394,8 +394,9 @@ hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
   if constexpr (OP == kGemmTN) {
     return tile == kTile128Deep ? launch_tile<2, 2, 2, 4, OP, EPI>(p, stream) : launch_tile<2, 2, 2, 2, OP, EPI>(p, stream);
   } else if constexpr (OP == kGemmFp8) {
-    return tile == kTile64 ? launch_tile<2, 2, 1, 2, OP, EPI>(p, stream)
-         : tile == kTile128 ? launch_tile<2, 4, 2, 2, OP, EPI>(p, stream) : launch_tile<2, 4, 3, 2, OP, EPI>(p, stream);
+    if constexpr (EPI != kEpiResidual)
+      if (tile == kTile192) return launch_tile<2, 4, 3, 2, OP, EPI>(p, stream);
+    return tile == kTile64 ? launch_tile<2, 2, 1, 2, OP, EPI>(p, stream) : launch_tile<2, 4, 2, 2, OP, EPI>(p, stream);
   } else {
     switch (tile) {
       case kTile64Deep: return launch_tile<2, 2, 1, 5, OP, EPI>(p, stream);
@@ -410,42 +411,6 @@ hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
 
 }  // namespace
 
-// The tile with the least time where a compute unit works through its share of the tiles at the tile's rate (PFLOP/s that the kernels reach on
-// many tiles, K = 512: bytes through the L2 per product fall with the tile; the widest one has no registers left to keep residual rows in).  Up to a tile per
-// compute unit, all of a unit's LDS is one workgroup's: more k-tiles in flight.  us for the tiles of 64 (deep), 64, 128 (deep), 128, 192, 256 rows:
-//   6,418 x 2048, K = 512, SiLU             -    23.9    -    22.5  28.4  21.0 *    (two library products: 34)
-//   6,418 x 512, K = 512, W [K, N]          -     8.9   8.3 *  8.1  13.3  16.2      (16)
-//   6,418 x 512, K = 2048, W [K, N]         -    23.7  19.1 * 24.5  36.2  42.1      (23)
-//   20,000 x 512, K = 2048, W [K, N]        -    63.7    -    51.9  41.1 * 48.2      (42)
-//   87,728 x 512, K = 2048, W [K, N]        -   342.6    -   247.8 216.1 194.3 *    (182-197)
-//   1,200 x 512, K = 512, residual         6.1 *  6.3   8.1   8.0  13.0  18.6
-// From K = 1024 on the small tiles' share of the L2's requests counts for more, and a residual's epilogue for less.  us, by the rates of short K -> of long K: 5,000 x
-// 4096, K = 2048 97 -> 86, 2,500 x 8192, K = 2048 104 -> 90, 10,000 x 2048, K = 8192, W [K, N] 380 -> 329, 30,000 x 1024, K = 2048, residual 145 -> 130.
-int gemm_rows_tile(int64_t M, int N, int64_t K, int epilogue) {
-  static const struct { int rows, cols, tile, deep; double rate, rate_long; } kinds[4] = {{64, 128, kTile64, kTile64Deep, 0.50, 0.40}, {128, 128, kTile128, kTile128Deep, 0.68, 0.62},
-                                                                                          {192, 256, kTile192, kTile192, 0.80, 0.80}, {256, 256, kTile256, kTile256, 0.87, 0.87}};
-  const bool long_k = K >= 1024;
-  int best = 0;
-  double least = 0;
-  for (const auto& k : kinds) {
-    const int64_t tiles = (M + k.rows - 1) / k.rows * ((N + k.cols - 1) / k.cols);
-    double rate = long_k ? k.rate_long : k.rate;
-    if (k.tile == kTile256 && epilogue == kEpiResidual) rate = long_k ? 0.74 : 0.68;
-    const double time = (double)((tiles + 255) / 256) * k.rows * k.cols / rate;
-    if (best == 0 || time < least) { least = time; best = tiles <= 256 ? k.deep : k.tile; }
-  }
-  return best;
-}
-
-// E4M3: tiles of 64 x 128, 128 x 256 and 192 x 256 take 1 : 3.3 : 4.9 (with a residual, whose rows find no registers there, 7.5), the small one 0.7 beside its rounds.  us
-// for the three:  6,000 x 2048, K = 512, SiLU 16.9 17.1 14.4 *;  12,000 x 512, K = 512, residual 8.8 8.6 * 15.2;  20,600 x 4096, K = 1024, SiLU 177 130 122 *;
-// 20,600 x 1024, K = 1024, residual 39.3 34.7 * 44.6;  6,000 x 512, K = 1024, residual 7.9 * 10.5 17.0.
-static int fp8_tile(int64_t M, int N, int epilogue) {
-  auto rounds = [&](int rows, int cols) { return (double)(((M + rows - 1) / rows * ((N + cols - 1) / cols) + 255) / 256); };
-  const double t64 = rounds(64, 128) + 0.7, t128 = 3.3 * rounds(128, 256), t192 = (epilogue == kEpiResidual ? 7.5 : 4.9) * rounds(192, 256);
-  return t64 <= t128 && t64 <= t192 ? kTile64 : t128 <= t192 ? kTile128 : kTile192;
-}
-
 // With long rows and much work the library's kernels are the faster ones, once they have been chosen for the size.  They are chosen by timing on a class's
 // first call, which blocks, and then serve every count of the class, some of them badly.  So a class goes to the library as a whole, and only if its
 // smallest count is beyond the line: one call leaves nothing to choose for another of its class.  A layer's step with widths of 1024, us, library (chosen for
@@ -454,11 +419,11 @@ static int fp8_tile(int64_t M, int N, int epilogue) {
 // 7,500 rows, chosen for them, 1,489 -> 1,532.
 bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)(token_class(M) / 2) * (double)N * (double)K < 1e11; }
 
-hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile) {
+hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.N % 8 != 0 || (op != kGemmTN && p.K % 8 != 0)) return hipErrorInvalidValue;
-  if (op == kGemmTN) tile = (p.M + 127) / 128 * ((p.N + 127) / 128) * ((p.K + p.slab - 1) / p.slab) <= 256 ? kTile128Deep : kTile128;
-  else if (op == kGemmFp8) tile = fp8_tile(p.M, p.N, epilogue);
-  else if (tile == 0) tile = gemm_rows_tile(p.M, p.N, p.K, epilogue);
+  const bool residual = epilogue == kEpiResidual;
+  const int tile = op == kGemmTN ? (p.M + 127) / 128 * ((p.N + 127) / 128) * ((p.K + p.slab - 1) / p.slab) <= 256 ? kTile128Deep : kTile128
+                 : op == kGemmFp8 ? fp8_tile(p.M, p.N, residual) : gemm_rows_tile(p.M, p.N, p.K, residual);
   if (op == kGemmNT && epilogue == kEpiSiluSplit) return launch_epi<kGemmNT, kEpiSiluSplit>(p, tile, stream);
   if (op == kGemmNT && epilogue == kEpiPreAndSilu) return launch_epi<kGemmNT, kEpiPreAndSilu>(p, tile, stream);
   if (op == kGemmNT && epilogue == kEpiResidual) return launch_epi<kGemmNT, kEpiResidual>(p, tile, stream);

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "hstu_geometry.h"
+#include "gemm_tiles.h"
 #include "hstu_plan.h"
 
 using namespace hstu;
@@ -189,4 +190,9 @@ extern "C" int plan_check(int B, const int32_t* lengths, const int32_t* targets,
       }
     }
   return 0;
+}
+
+// The tile of a product over token rows, by gemm_rows.hip's own rule: kTile64Deep .. kTile256 (fp8: kTile64, kTile128, kTile192)
+extern "C" int product_tile(long long M, int N, long long K, int residual, int fp8) {
+  return fp8 ? fp8_tile(M, N, residual != 0) : gemm_rows_tile(M, N, K, residual != 0);
 }

@@ -230,7 +230,7 @@ struct GemmRowsArgs {
 // kEpiSums: fp32, unrounded.
 enum { kEpiPlain = 0, kEpiResidual = 1, kEpiSiluSplit = 2, kEpiPreAndSilu = 3, kEpiSums = 4 };
 bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K);      // over the library (gemm.hip): the same for every M of a token_class
-hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream, int tile = 0);   // tile: 0 by size
+hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream);
 
 // fp8_gemm.hip: D[M,N] (bf16) = a_scale[m] b_scale[n] (Aq[M,K] Bq[N,K]^T) + C[M,N] (bf16 or nullptr), E4M3 codes
 bool fp8_gemm_supported(int N, int K);
