@@ -493,8 +493,9 @@ int hstu_gated_norm_bwd_static(int64_t T, int32_t D, int32_t dtype, const void* 
   void* partial = nullptr;
   const int sp = static_scratch(&partial);
   if (sp != HSTU_OK) return sp;
-  // every workgroup overwrites its whole row of partial sums and the column-sum kernel reads only the rows of this
-  // launch, so nothing left by an earlier call is ever read and nothing needs clearing
+  // every workgroup overwrites the columns that are wanted of its row of partial sums (dgamma's, with a bias or its gradient also
+  // dbeta's) and the column-sum kernel reads only those, of the rows of this launch: nothing left by an earlier call is
+  // ever read and nothing needs clearing
   if (launch_gated_norm_bwd(T, D, dtype, dy, attn, u, gamma, beta, eps, dattn, du, dgamma, dbeta, (float*)partial,
                             (hipStream_t)stream) != hipSuccess)
     return HSTU_ERR_LAUNCH;

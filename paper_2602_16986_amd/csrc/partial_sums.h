@@ -33,8 +33,9 @@ __device__ __forceinline__ void column_sums(const ColsumJob& job, int block, f32
   float* const dgamma = job.dgamma; float* const dbeta = job.dbeta;
   const int tid = threadIdx.x, c4 = tid & 3, lane = tid & 63, wave = tid >> 6;
   const int c = block * 16 + 4 * c4;                  // D is a multiple of 8: 4 columns are all in or all out
+  const int cols = dbeta ? 2 * D : D;                 // (of every partial row; the others may never have been written)
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (c < 2 * D) {
+  if (c < cols) {
 #pragma unroll 4
     for (int b = tid >> 2; b < nblk; b += kThreads / 4) s += *(const f32x4*)(partial + (int64_t)b * 2 * D + c);
   }
@@ -42,15 +43,13 @@ __device__ __forceinline__ void column_sums(const ColsumJob& job, int block, f32
   for (int i = 0; i < 4; ++i) s[i] = sum_every_4th_lane(s[i]);
   if (lane < 4) red[wave][c4] = s;
   __syncthreads();
-  if (tid < 4 && c < 2 * D) {
+  if (tid < 4 && c < cols) {
     f32x4 t = red[0][c4];
 #pragma unroll
     for (int w = 1; w < kThreads / 64; ++w) t += red[w][c4];
-    float* dst = c < D ? dgamma + c : (dbeta ? dbeta + (c - D) : nullptr);
-    if (dst) {
+    float* const dst = c < D ? dgamma + c : dbeta + (c - D);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dst[i] = t[i];
-    }
+    for (int i = 0; i < 4; ++i) dst[i] = t[i];
   }
 }
 
