@@ -288,7 +288,8 @@ int64_t hstu_layer_gemm_tunings(void);
  *     d[m, n] = a_scale[m] * b_scale[n] * sum_k a_q[m, k] * b_q[n, k]  +  c[m, n]
  *   a_q: codes [M, K]; b_q: codes [N, K] (weights stored [out, in]); c: bf16 [M, N] or NULL; d: bf16 [M, N]; products
  *   exact, fp32 accumulation, one rounding to bf16.  K in {128, 256, 512, 1024}, N a multiple of 64 (else
- *   HSTU_ERR_UNSUPPORTED); all pointers 16-byte aligned.  c may be d (in-place accumulation).
+ *   HSTU_ERR_UNSUPPORTED); all pointers 16-byte aligned.  c may be d (in-place accumulation).  A row of d does not depend on
+ *   M, bit for bit.
  */
 int hstu_norm_quant_fp8(int64_t T, int32_t D, int32_t dtype, const void* a, const void* u, const float* gamma,
                         const float* beta, float eps, void* q, float* q_scale, float* mean, float* rstd, void* stream);
@@ -368,7 +369,8 @@ int hstu_attn_schedule_stats(const hstu_attn_params* p, const void* workspace, i
  * adds the partial sums of cut blocks and folds the bias-table gradient],
  * "truncate_offsets", "truncate_fwd", "truncate_bwd", and from the layer entry points "layer_norm_fwd",
  * "gemm_uvqk", "silu_fwd", "gemm_out", "gemm_dy", "gemm_dw2", "gemm_dxn", "gemm_dw1", "layer_norm_bwd",
- * and "norm_quant_fp8", "fp8_gemm_bias2d";
+ * "layer_sums" [the norms' column sums and the weight gradients' slabs], with FP8 projections "layer_norm_quant", "fp8_gemm_uvqk",
+ * "gated_norm_quant", "fp8_gemm_out", and "norm_quant_fp8", "fp8_gemm_bias2d";
  * "attn_fwd" includes the kernel that adds the partial sums of cut blocks) and
  * ms[i] = elapsed milliseconds.  HOST arrays.  Not thread-safe; enable(1) creates the events once. */
 int hstu_profile_enable(int on);

@@ -1,6 +1,6 @@
-// Plain bf16 GEMMs of the layer's two projections and their backward, through hipBLASLt (library GEMMs: the
-// contractions here are ordinary dense products with at most a residual added).  Row-major operands are handed to
-// the column-major library as their transposes: D^T = op(B)^T op(A)^T.
+// bf16 products of the layer that gemm_rows.hip does not take (gemm_rows_preferred: long reductions with much work; weight gradients
+// of widths that are no multiples of 128), through hipBLASLt: ordinary dense products with at most SiLU or a residual.  Row-major
+// operands are handed to the column-major library as their transposes: D^T = op(B)^T op(A)^T.
 // Host code only.  One hipBLASLt handle per device, created on first use; not thread-safe.
 //
 // Two caches.  The token count of a jagged batch differs from call to call, so what is expensive, choosing the kernel by

@@ -196,10 +196,8 @@ hipError_t launch_gated_norm_bwd(int64_t T, int D, int dtype, const void* dy, co
                                  const float* gamma, const float* beta, float eps, void* dattn, void* du, float* dgamma,
                                  float* dbeta, float* partial, hipStream_t stream);
 
-
-// pointwise.hip: SiLU of the [T, C] projection (bf16, contiguous, C a multiple of 8) and its backward
+// pointwise.hip: SiLU of the [T, C] projection (bf16, contiguous, C a multiple of 8)
 hipError_t launch_silu_fwd(int64_t T, int C, const void* pre, void* act, void* u_out, int u_cols, hipStream_t stream, int skip_cols = 0);
-hipError_t launch_silu_bwd(int64_t T, int C, const void* pre, void* dact, hipStream_t stream);
 
 // gemm.hip: row-major bf16 products with fp32 accumulation through hipBLASLt.
 //   kGemmNT: D[M,N] = A[M,K] B[N,K]^T    kGemmNN: D[M,N] = A[M,K] B[K,N]    kGemmTN: D[M,N] = A[K,M]^T B[K,N]

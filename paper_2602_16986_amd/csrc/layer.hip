@@ -313,7 +313,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
       if (st != HSTU_OK) return st;
     }
   }
-  {
+  {  // weight gradients: this library's slab-split products when the widths are multiples of 128, else the GEMM library
     ProfScope ps("gemm_dw1", stream);
     if (gemm_tn_supported((int)(4 * HD), (int)E)) {
       if (launch_gemm_tn(T, (int)(4 * HD), (int)E, dact, 4 * HD, xn, E, d_w1, (float*)(ws + l.tn_partial[0]), slabs[0], stream) != hipSuccess)
@@ -323,7 +323,7 @@ int hstu_layer_bwd(const hstu_layer_params* p, const void* z, const void* u_save
       if (st != HSTU_OK) return st;
     }
   }
-  {  // weight gradients: this library's slab-split kernel when the widths are multiples of 128, else the GEMM library
+  {
     ProfScope ps("gemm_dw2", stream);
     if (gemm_tn_supported((int)E, (int)HD)) {
       if (launch_gemm_tn(T, (int)E, (int)HD, dout, E, y, HD, d_w2, (float*)(ws + l.tn_partial[1]), slabs[1], stream) != hipSuccess) return HSTU_ERR_LAUNCH;

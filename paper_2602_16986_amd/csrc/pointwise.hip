@@ -1,5 +1,5 @@
-// SiLU of the U/V/Q/K projection (paper Eq. 2, phi_1) and its backward: HBM-bound elementwise kernels over
-// contiguous bf16 [T, C] buffers, 8 elements (16 bytes) per lane and step.
+// SiLU of the U/V/Q/K projection (paper Eq. 2, phi_1) where the product before it left it out: an HBM-bound elementwise kernel
+// over contiguous bf16 [T, C] buffers, 8 elements (16 bytes) per lane and step.  (Its derivative is taken where the gradients are stored.)
 #include "hstu_common.h"
 #include "hstu_kernels.h"
 
@@ -43,21 +43,6 @@ __global__ __launch_bounds__(kThreads) void silu_fwd_kernel(int64_t groups, int 
   }
 }
 
-// dpre = dact * d/dt [t sigmoid(t)] at t = pre, written over dact.
-__global__ __launch_bounds__(kThreads) void silu_bwd_kernel(int64_t groups, const u32x4* __restrict__ pre, u32x4* __restrict__ dact) {
-  for (int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x; g < groups; g += (int64_t)gridDim.x * kThreads) {
-    float t[8], d[8];
-    unpack8(pre[g], t);
-    unpack8(dact[g], d);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float sg = sigmoidf_fast(t[i]);
-      d[i] *= sg * (1.0f + t[i] * (1.0f - sg));
-    }
-    dact[g] = pack8(d);
-  }
-}
-
 int blocks_for(int64_t groups) {
   const int64_t b = (groups + kThreads - 1) / kThreads;
   return (int)(b < 1 ? 1 : (b > kMaxBlocks ? kMaxBlocks : b));
@@ -70,12 +55,6 @@ hipError_t launch_silu_fwd(int64_t T, int C, const void* pre, void* act, void* u
   if (groups <= 0) return hipSuccess;
   hipLaunchKernelGGL(silu_fwd_kernel, dim3(blocks_for(groups)), dim3(kThreads), 0, stream, groups, C / 8, skip_cols / 8, (const u32x4*)pre,
                      (u32x4*)act, (u32x4*)u_out, u_cols / 8);
-  return hipGetLastError();
-}
-
-hipError_t launch_silu_bwd(int64_t T, int C, const void* pre, void* dact, hipStream_t stream) {
-  const int64_t groups = T * (C / 8);
-  hipLaunchKernelGGL(silu_bwd_kernel, dim3(blocks_for(groups)), dim3(kThreads), 0, stream, groups, (const u32x4*)pre, (u32x4*)dact);
   return hipGetLastError();
 }
 
