@@ -206,10 +206,10 @@ hipError_t launch_one(int64_t M, int N, const void* A, const float* a_scale, con
 // gemm_rows.hip's tiles for K = 1024, where the resident rows of A take 128 registers a lane, and for K = 512 while the rows do not fill the chip several times
 // over with workgroups of this kernel.  us, here -> there: K = 1024 (two waves per 32 rows, half of K each, three barriers a chunk): 20,600 x 4096 with SiLU 155 -> 122, 60,000 x 1024 with a
 // residual 118 -> 93, 1,000 x 1024 8.1 -> 6.3;  K = 512: 6,000 x 2048 20.7 -> 14.4, 12,000 x 512 13.3 -> 8.6, 20,600 x 512 17.2 -> 16.4, but a
-// layer of 20,600 rows 160 -> 164-167; 100,000 x 2048 223, 221.  Few rows are one trip to memory here, and several k-tiles there, of
-// weights that a layer has to fetch from memory: the forward of a layer, widths of 512, 64 rows 26.1, there 28.4, 128 rows 28.5, 29.0; widths of 1024, 32 rows 28.8, there 30.9,
-// 64 rows 32.5, 35.0, 96 rows 34.6, 34.6, 128 rows 36.2, 34.8.
-bool rows_kernel(int64_t M, int K) { return K == 1024 ? M > 96 : K == 512 && M > 128 && M <= 16384; }
+// layer of 20,600 rows 160 -> 164-167; 100,000 x 2048 223, 221.  Few rows are one trip to memory here and a chain of k-tiles there: a
+// layer's forward, widths of 512, 1 row 21.3, there 23.0, 64 rows 26.1, 27.4, 80 rows 27.5, 27.6, 112 rows 28.2, 27.7; widths of 1024, 1 row 26.0, there 26.8, 32 rows 29.0,
+// 29.8, 48 rows 31.6, 31.5, 96 rows 34.7, 31.6.
+bool rows_kernel(int64_t M, int K) { return K == 1024 ? M > 40 : K == 512 && M > 80 && M <= 16384; }
 GemmRowsArgs rows_args(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale, void* D) {
   GemmRowsArgs g = {};
   g.M = M; g.N = N; g.K = K; g.A = A; g.lda = K; g.W = B; g.ldw = K; g.scale_a = a_scale; g.scale_w = b_scale; g.D = D; g.ldd = N;

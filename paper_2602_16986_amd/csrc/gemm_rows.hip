@@ -396,7 +396,8 @@ hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
   } else if constexpr (OP == kGemmFp8) {
     if constexpr (EPI != kEpiResidual)
       if (tile == kTile192) return launch_tile<2, 4, 3, 2, OP, EPI>(p, stream);
-    return tile == kTile64 ? launch_tile<2, 2, 1, 2, OP, EPI>(p, stream) : launch_tile<2, 4, 2, 2, OP, EPI>(p, stream);
+    return tile == kTile64Deep ? launch_tile<2, 2, 1, 5, OP, EPI>(p, stream)
+         : tile == kTile64 ? launch_tile<2, 2, 1, 2, OP, EPI>(p, stream) : launch_tile<2, 4, 2, 2, OP, EPI>(p, stream);
   } else {
     switch (tile) {
       case kTile64Deep: return launch_tile<2, 2, 1, 5, OP, EPI>(p, stream);

@@ -35,11 +35,13 @@ inline int gemm_rows_tile(int64_t M, int N, int64_t K, bool residual) {
 
 // E4M3: tiles of 64 x 128, 128 x 256 and 192 x 256 take 1 : 3.3 : 4.9, the small one 0.7 beside its rounds; with a residual, whose rows find no registers there, 192 rows
 // took 7.5, which never pays.  us for the three:  6,000 x 2048, K = 512, SiLU 16.9 17.1 14.4 *;  12,000 x 512, K = 512, residual 8.8 8.6 * 15.2;  20,600 x 4096, K = 1024, SiLU 177
-// 130 122 *;  20,600 x 1024, K = 1024, residual 39.3 34.7 * 44.6;  6,000 x 512, K = 1024, residual 7.9 * 10.5 17.0.
+// 130 122 *;  20,600 x 1024, K = 1024, residual 39.3 34.7 * 44.6;  6,000 x 512, K = 1024, residual 7.9 * 10.5 17.0.  One round of the small tile keeps more k-tiles in flight, as
+// above: a layer's forward, whose operands do not wait in the caches, widths of 1024, 128 rows 35.1 -> 32.3, 3,217 x 512 (K = 1024) 37.8 -> 36.3.
 inline int fp8_tile(int64_t M, int N, bool residual) {
   auto rounds = [&](int rows, int cols) { return (double)(((M + rows - 1) / rows * ((N + cols - 1) / cols) + 255) / 256); };
   const double t64 = rounds(64, 128) + 0.7, t128 = 3.3 * rounds(128, 256), t192 = 4.9 * rounds(192, 256);
-  return t64 <= t128 && (residual || t64 <= t192) ? kTile64 : residual || t128 <= t192 ? kTile128 : kTile192;
+  if (t64 <= t128 && (residual || t64 <= t192)) return rounds(64, 128) == 1 ? kTile64Deep : kTile64;
+  return residual || t128 <= t192 ? kTile128 : kTile192;
 }
 
 }  // namespace hstu

@@ -20,7 +20,7 @@ def test_fp8_product_rows_do_not_depend_on_the_row_count(N, K, residual):
         hb.hstu_norm_quant_fp8(torch.randn(q.shape, generator=gen, device="cuda").bfloat16(), None, None, None, 0.0, q, s)
     c = torch.randn(most, N, generator=gen, device="cuda").bfloat16() if residual else None
     got = []
-    for rows in (most, 16385, 16384, 5000, 300, 129, 128, 97, 96, 65, 64, 33, 1):
+    for rows in (most, 16385, 16384, 5000, 300, 129, 81, 80, 65, 41, 40, 1):
         d = torch.empty(rows, N, dtype=torch.bfloat16, device="cuda")
         hb.hstu_fp8_gemm_bias2d(a[:rows], sa[:rows], b, sb, c[:rows] if residual else None, d)
         got.append(d)
@@ -36,7 +36,7 @@ def test_fp8_layer_rows_do_not_depend_on_the_token_count(E):
     layer = lambda n: DeviceLayer(wl.build_layer("rows", [20] * n, 2, 128, E, seed=3, K1=16), fp8=True)
     whole = layer(1000)
     whole.fwd()
-    for n in (815, 100, 2, 1):
+    for n in (815, 100, 5, 4, 3, 2, 1):
         part = layer(n)
         for t in ("z", "w1_q", "w1_scale", "norm_w"):
             getattr(part, t).copy_(getattr(whole, t)[:getattr(part, t).shape[0]])
