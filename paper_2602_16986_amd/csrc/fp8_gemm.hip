@@ -25,10 +25,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBM = 128;            // rows of A per workgroup
 
-// K = 64 * KS (at 1024 the resident rows of A take 128 registers per lane and one workgroup runs per compute unit: for few rows only); kBN output features
-// per chunk (64: full 128-byte row segments of C and D).
-// SILU: the epilogue applies x sigmoid(x) before the rounding (the first projection of the layer, Eq. 2), and output
-// features [0, u_cols) go to u_out [M, u_cols] instead of D (the gate is kept apart from the rest of the projection).
+// K = 64 * KS (at 1024 the resident rows of A take 128 registers per lane and one workgroup runs per compute unit: for few rows
+// only); kBN output features per chunk (64: full 128-byte row segments of C and D).  SILU: the epilogue applies x sigmoid(x)
+// before the rounding (the first projection of the layer, Eq. 2), and output features [0, u_cols) go to u_out [M, u_cols] instead
+// of D (the gate is kept apart from the rest of the projection).
 template <int KS, int kBN, bool SILU>
 __global__ __launch_bounds__(256, KS >= 16 ? 1 : 2) void fp8_gemm_bias2d_kernel(int64_t M, int N, const unsigned char* __restrict__ A,
                                                                   const float* __restrict__ a_scale,
@@ -203,12 +203,13 @@ hipError_t launch_one(int64_t M, int N, const void* A, const float* a_scale, con
   return hipGetLastError();
 }
 
-// gemm_rows.hip's tiles for K = 1024, where the resident rows of A take 128 registers a lane, and for K = 512 while the rows do not fill the chip several times
-// over with workgroups of this kernel.  us, here -> there: K = 1024 (two waves per 32 rows, half of K each, three barriers a chunk): 20,600 x 4096 with SiLU 155 -> 122, 60,000 x 1024 with a
-// residual 118 -> 93, 1,000 x 1024 8.1 -> 6.3;  K = 512: 6,000 x 2048 20.7 -> 14.4, 12,000 x 512 13.3 -> 8.6, 20,600 x 512 17.2 -> 16.4, but a
-// layer of 20,600 rows 160 -> 164-167; 100,000 x 2048 223, 221.  Few rows are one trip to memory here and a chain of k-tiles there: a
-// layer's forward, widths of 512, 1 row 21.3, there 23.0, 64 rows 26.1, 27.4, 80 rows 27.5, 27.6, 112 rows 28.2, 27.7; widths of 1024, 1 row 26.0, there 26.8, 32 rows 29.0,
-// 29.8, 48 rows 31.6, 31.5, 96 rows 34.7, 31.6.
+// gemm_rows.hip's tiles for K = 1024, where the resident rows of A take 128 registers a lane, and for K = 512 while the rows do
+// not fill the chip several times over with workgroups of this kernel.  us, here -> there: K = 1024 (two waves per 32 rows, half
+// of K each, three barriers a chunk): 20,600 x 4096 with SiLU 155 -> 122, 60,000 x 1024 with a residual 118 -> 93, 1,000 x 1024
+// 8.1 -> 6.3;  K = 512: 6,000 x 2048 20.7 -> 14.4, 12,000 x 512 13.3 -> 8.6, 20,600 x 512 17.2 -> 16.4, but a layer of 20,600
+// rows 160 -> 164-167; 100,000 x 2048 223, 221.  Few rows are one trip to memory here and a chain of k-tiles there: a layer's
+// forward, widths of 512, 1 row 21.3, there 23.0, 64 rows 26.1, 27.4, 80 rows 27.5, 27.6, 112 rows 28.2, 27.7; widths of 1024, 1
+// row 26.0, there 26.8, 32 rows 29.0, 29.8, 48 rows 31.6, 31.5, 96 rows 34.7, 31.6.
 bool rows_kernel(int64_t M, int K) { return K == 1024 ? M > 40 : K == 512 && M > 80 && M <= 16384; }
 GemmRowsArgs rows_args(int64_t M, int N, int K, const void* A, const float* a_scale, const void* B, const float* b_scale, void* D) {
   GemmRowsArgs g = {};

@@ -14,7 +14,8 @@ constexpr int kRowsPerBlock = 4;        // forward: one wave per row, 4 waves pe
 constexpr int kBwdWaves = 8;            // backward: 8 waves per workgroup, each walking over rows
 constexpr int kMaxBwdBlocks = 512;      // two workgroups per CU; also the number of partial column-sum rows
 
-// op over the 64 lanes of a wave, in every lane: neighbours, pairs, quads (mirrored in 8), octets (mirrored in 16), then rows in pairs and halves
+// op over the 64 lanes of a wave, in every lane: neighbours, pairs, quads (mirrored in 8), octets (mirrored in 16), then rows in
+// pairs and halves
 template <typename Op> __device__ __forceinline__ float wave_all(float v, Op op) {
   v = op(v, dpp<0xB1>(v));                                 // quad_perm 1 0 3 2
   v = op(v, dpp<0x4E>(v));                                 // quad_perm 2 3 0 1
@@ -117,8 +118,9 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gated_norm_fwd_kernel(cons
   const E* urow = p.u ? (const E*)p.u + row * p.su : nullptr;       // no gate: plain layer norm
   E* yrow = (E*)p.y + row * p.sy;
   float a[NCH][8];
-  // Narrow bf16 rows: the gate's rows travel with the first loads, not after the reductions.  us, late -> early: 256 features, 300 rows 2.44 -> 2.36, 87,000 rows
-  // 29.5 -> 27.4, 512 features 43.6 -> 40.9; more registers of them cost occupancy: 2,048 features, 10,000 rows 19.7 -> 21.4, fp32, 3,000 rows 12.1 -> 13.6.
+  // Narrow bf16 rows: the gate's rows travel with the first loads, not after the reductions.  us, late -> early: 256 features,
+  // 300 rows 2.44 -> 2.36, 87,000 rows 29.5 -> 27.4, 512 features 43.6 -> 40.9; more registers of them cost occupancy: 2,048
+  // features, 10,000 rows 19.7 -> 21.4, fp32, 3,000 rows 12.1 -> 13.6.
   constexpr bool kEarly = NCH == 1 && sizeof(E) == 2;
   Raw8<E> ur;
 #pragma unroll
@@ -221,14 +223,13 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void norm_quant_fwd_kernel(cons
   }
 }
 
-// Backward.  Per row: ahat = (a - mu) rstd, dn = dy u, dU = dy (ahat gamma + beta), dahat = dn gamma,
-// dA = rstd (dahat - mean(dahat) - ahat mean(dahat ahat)).  Column sums dgamma = sum dn ahat and
-// dbeta = sum dn (if wanted) are kept per lane over the rows a wave visits, combined across the workgroup's
-// waves in a fixed order through LDS and written as one partial row per workgroup.
-// Few rows are a chain of latencies: the chunks of a row are fetched together, the reductions are DPP, and the waves' column sums meet in one step.
-// With the gradient's rows fetched behind the first reductions, lane permutations through LDS and the waves' sums added in turn, bf16, us with
-// the column-sum launch, before -> now: 384 features, 6,418 rows 16.7 -> 12.5, 20,000 rows 25.2 -> 19.1, 87,728 rows 80.9 -> 69.2; 512 features
-// 17.4 -> 12.6, 27.5 -> 21.2, 90.6 -> 89.9 (memory).
+// Backward.  Per row: ahat = (a - mu) rstd, dn = dy u, dU = dy (ahat gamma + beta), dahat = dn gamma, dA = rstd (dahat -
+// mean(dahat) - ahat mean(dahat ahat)).  Column sums dgamma = sum dn ahat and dbeta = sum dn (if wanted) are kept per lane over
+// the rows a wave visits, combined across the workgroup's waves in a fixed order through LDS and written as one partial row per
+// workgroup.  Few rows are a chain of latencies: the chunks of a row are fetched together, the reductions are DPP, and the waves'
+// column sums meet in one step.  With the gradient's rows fetched behind the first reductions, lane permutations through LDS and
+// the waves' sums added in turn, bf16, us with the column-sum launch, before -> now: 384 features, 6,418 rows 16.7 -> 12.5,
+// 20,000 rows 25.2 -> 19.1, 87,728 rows 80.9 -> 69.2; 512 features 17.4 -> 12.6, 27.5 -> 21.2, 90.6 -> 89.9 (memory).
 template <typename E> struct BwdRow { Raw8<E> a, dy, u; };          // what the reductions need
 template <typename E> struct BwdTail { Raw8<E> pre, res; };         // and what the results need
 template <typename E> constexpr bool kAhead = sizeof(E) == 2;      // a chunk of fp32 is 8 registers: fetched where it is used, nothing ahead
@@ -332,16 +333,19 @@ __global__ __launch_bounds__(64 * kBwdWaves, 4) void gated_norm_bwd_kernel(const
   }
 }
 
-// Backward for rows wider than 512 features: a workgroup of W waves shares one row, every thread owns one 16-byte chunk
-// of it (and the column sums of those 8 features over all the rows its workgroup visits, so the waves need no combination
-// at the end).  The row statistics cross the waves through LDS with two barriers per row: the sum of a first, then
-// sum (a - mu)^2, sum dahat and sum dahat (a - mu) together (mean(dahat ahat) = rstd times the last one / D).  The slots
-// alternate with the row parity, so a wave that runs ahead never overwrites what a slower one still reads.  One wave per
-// row needed 48 registers per 512 features (and spilled from 2048 features on).  What the reductions of the next row need is fetched a row ahead (bf16), 128 registers
-// keep 16 waves on a compute unit, and a wave sums eight and more slots a lane each (48 values in flight spilled at 16 waves).  bf16 without a bias, us with the
-// column-sum launch, before -> now: 1024 features, 6,418 rows 31.9 -> 22.8, 87,728 rows 214 -> 177; 2048 features, 6,418 rows 43.6 -> 32.8; 4096 features,
-// 20,000 rows 218 -> 165; 8192 features 2,029 -> 369; fp32 at 8192 features, 6,418 rows 283 -> 236.
-// The sum of W (up to 16) values in LDS, in every lane: eight and more a value per lane of a row of 16 (48 values in flight spill at W = 16).
+// Backward for rows wider than 512 features: a workgroup of W waves shares one row, every thread owns one 16-byte chunk of it
+// (and the column sums of those 8 features over all the rows its workgroup visits, so the waves need no combination at the end).
+// The row statistics cross the waves through LDS with two barriers per row: the sum of a first, then sum (a - mu)^2, sum dahat
+// and sum dahat (a - mu) together (mean(dahat ahat) = rstd times the last one / D).  The slots alternate with the row parity, so
+// a wave that runs ahead never overwrites what a slower one still reads.  One wave per row needed 48 registers per 512 features
+// (and spilled from 2048 features on).  What the reductions of the next row need is fetched a row ahead (bf16), 128 registers
+// keep 16 waves on a compute unit, and a wave sums eight and more slots a lane each (48 values in flight spilled at 16 waves).
+// bf16 without a bias, us with the column-sum launch, before -> now: 1024 features, 6,418 rows 31.9 -> 22.8, 87,728 rows 214 ->
+// 177; 2048 features, 6,418 rows 43.6 -> 32.8; 4096 features, 20,000 rows 218 -> 165; 8192 features 2,029 -> 369; fp32 at 8192
+// features, 6,418 rows 283 -> 236.
+//
+// The sum of W (up to 16) values in LDS, in every lane: eight and more a value per lane of a row of 16 (48 values in flight spill
+// at W = 16).
 template <int W> __device__ __forceinline__ float sum_slots(const float* slots, int lane) {
   if constexpr (W <= 4) {
     float v = slots[0];
@@ -365,9 +369,10 @@ __global__ __launch_bounds__(64 * W, W < 16 && (BETA || !kAhead<E>) ? 3 : 4) voi
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int D = p.D, e0 = threadIdx.x * 8;
   const bool on = e0 < D;
-  // Where registers are short, dahat is formed again instead of kept over the barrier, and at 16 waves of fp32 the bias read again.  us, kept -> again:
-  // bf16, 1,024 features, 30,000 rows 65 -> 61, 8,192 features, 3,000 rows 59.8 -> 52.4; fp32, 8,192 features with a bias, 1 row 18.7 -> 15.7 (before the
-  // rows were fetched ahead 16.4), without, 3,000 rows 121 -> 106; but fp32, 520 features, 30,000 rows 82 -> 89.
+  // Where registers are short, dahat is formed again instead of kept over the barrier, and at 16 waves of fp32 the bias read
+  // again.  us, kept -> again: bf16, 1,024 features, 30,000 rows 65 -> 61, 8,192 features, 3,000 rows 59.8 -> 52.4; fp32, 8,192
+  // features with a bias, 1 row 18.7 -> 15.7 (before the rows were fetched ahead 16.4), without, 3,000 rows 121 -> 106; but fp32,
+  // 520 features, 30,000 rows 82 -> 89.
   constexpr bool kHoldDah = !kAhead<E> && W < 16, kHoldBias = BETA && (kAhead<E> || W < 16);
   float gv[8], bv[8], gsum[8], bsum[8];
 #pragma unroll
@@ -466,9 +471,10 @@ __global__ __launch_bounds__(kThreads) void gated_norm_colsum_kernel(const Colsu
   column_sums<kThreads>(job, blockIdx.x, red);
 }
 
-// No more threads than there are rows to add need, and 256 where the columns alone fill the chip with workgroups.  The whole backward, us with
-// 1,024 threads everywhere -> this way (64 columns x 16 row groups before): 100 rows x 512 features 10.95 -> 10.5 (10.4); 1 row x 4,096 with
-// dbeta 10.8 -> 9.3 (9.2); 100 rows 13.1 -> 12.2 (12.0); 1,000 rows x 512 and more unchanged (11.4; 12.9 before), where 256 threads take 0.1-0.4 longer.
+// No more threads than there are rows to add need, and 256 where the columns alone fill the chip with workgroups.  The whole
+// backward, us with 1,024 threads everywhere -> this way (64 columns x 16 row groups before): 100 rows x 512 features 10.95 ->
+// 10.5 (10.4); 1 row x 4,096 with dbeta 10.8 -> 9.3 (9.2); 100 rows 13.1 -> 12.2 (12.0); 1,000 rows x 512 and more unchanged
+// (11.4; 12.9 before), where 256 threads take 0.1-0.4 longer.
 static hipError_t launch_colsum(int nblk, const NormBwdArgs& p, const float* partial, hipStream_t stream) {
   const ColsumJob job = {nblk, p.D, partial, p.dgamma, p.dbeta};
   const dim3 grid(job.blocks());

@@ -5,20 +5,24 @@
 // with the layer's pointwise work in the epilogue: SiLU with the gate's columns sent to a tensor of their own, the pre-activations
 // beside their SiLU, or the residual rows added.
 //
-// A workgroup owns tiles of WM 32 MI token rows x WN 64 columns, one of its WM WN multiplying waves 32 MI x 64 of it; the token rows sit on the
-// accumulators' lane axis, the columns on the register axis.  Both operands arrive in LDS by direct-to-LDS loads, 64 k at a time, one barrier per k-tile.
-// What bounds it, and what follows (87,728 rows, 2048 columns, K = 512, SiLU; the library's two products with it in their epilogue: 294 us):
-// 1. The L2's request rate.  Every load covers whole 128-byte lines: with 32 k at a time, 64-byte halves of lines whose other halves have left the
-//    first-level cache when they are wanted, 303 us.
-// 2. The stores of the output, which a burst of every compute unit at the end of its tile leaves to the memory (without them 185 us).  Memory operations of a wave
-//    complete in order, so a wave that stores cannot wait for a later load without waiting for the stores: four further waves only load, across
-//    tiles (the workgroups are persistent), and run on while the others store.  288 us without them.  Stores are non-temporal (282 without) and leave in whole lines:
-//    the accumulators go through LDS as fp32, 16 rows x 64 columns at a time and wave by wave (no barrier).  252 us with both.
+// A workgroup owns tiles of WM 32 MI token rows x WN 64 columns, one of its WM WN multiplying waves 32 MI x 64 of it; the token
+// rows sit on the accumulators' lane axis, the columns on the register axis.  Both operands arrive in LDS by direct-to-LDS loads,
+// 64 k at a time, one barrier per k-tile.
+// What bounds it, and what follows (87,728 rows, 2048 columns, K = 512, SiLU; the library's two products with it in their
+// epilogue: 294 us):
+// 1.  The L2's request rate.  Every load covers whole 128-byte lines: with 32 k at a time, 64-byte halves of lines whose other
+//    halves have left the first-level cache when they are wanted, 303 us.
+// 2.  The stores of the output, which a burst of every compute unit at the end of its tile leaves to the memory (without them
+//    185 us).  Memory operations of a wave complete in order, so a wave that stores cannot wait for a later load without waiting
+//    for the stores: four further waves only load, across tiles (the workgroups are persistent), and run on while the others
+//    store.  288 us without them.  Stores are non-temporal (282 without) and leave in whole lines: the accumulators go through
+//    LDS as fp32, 16 rows x 64 columns at a time and wave by wave (no barrier).  252 us with both.
 // 3. Power, then: products and LDS reads alone run at 1.1-1.2 PFLOP/s.
-// A wave's last products of a k-tile follow the barrier that publishes the next one, whose first operands are read in between: 250 us, and 346 instead of 362
-// for 40,000 x 1024 x K = 4096.
-// Rows of 128 bytes (operands with k contiguous) keep 16-byte chunk c of row r at c ^ (r / 2) % 8; rows of W [K, N], read through the LDS transpose loads, at
-// c ^ (4 (r % 4) + (r / 4) % 4): every read is free of bank conflicts, and the swizzle costs nothing because it is applied to the loads' source addresses.
+// A wave's last products of a k-tile follow the barrier that publishes the next one, whose first operands are read in between:
+// 250 us, and 346 instead of 362 for 40,000 x 1024 x K = 4096.
+// Rows of 128 bytes (operands with k contiguous) keep 16-byte chunk c of row r at c ^ (r / 2) % 8; rows of W [K, N], read through
+// the LDS transpose loads, at c ^ (4 (r % 4) + (r / 4) % 4): every read is free of bank conflicts, and the swizzle costs nothing
+// because it is applied to the loads' source addresses.
 #include <algorithm>
 #include <type_traits>
 
@@ -69,8 +73,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   const int hf = lane >> 5, l32 = lane & 31, i16 = lane & 15, grp16 = lane >> 4;
   constexpr bool kAT = OP == kGemmTN, kWT = OP == kGemmTN || OP == kGemmNN, kFp8 = OP == kGemmFp8;   // operands with k as their slow axis; E4M3 codes
   constexpr int kElem = kFp8 ? 1 : 2, kTileK = 128 / kElem;
-  // Workgroups go to the 8 dies round-robin; a die takes a contiguous range of tiles, columns first: the tiles of one range of token rows run
-  // beside each other and the rows come from memory once.
+  // Workgroups go to the 8 dies round-robin; a die takes a contiguous range of tiles, columns first: the tiles of one range of
+  // token rows run beside each other and the rows come from memory once.
   const int tiles_n = (p.N + S::kCols - 1) / S::kCols;
   const int tiles_slab = kAT ? (int)((p.M + S::kRows - 1) / S::kRows) * tiles_n : 1;               // (kGemmTN: of a slab of the reduction)
   // k of a tile: all, or the tile's slab
@@ -86,7 +90,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
   constexpr int kPitchW = S::kCols * 2, kPitchA = S::kRows * 2;                   // of operands with k as their slow axis
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void)smem;
   if (wave >= S::kWaves) {
-    // ---- global -> LDS.  Load c of a loader: rows 8 (lw + kLoaders c) .. + 7 of an operand with k contiguous.  Of W [K, N]: 1 KB of whole rows.
+    // ---- global -> LDS.  Load c of a loader: rows 8 (lw + kLoaders c) .. + 7 of an operand with k contiguous.  Of W [K, N]: 1
+    // KB of whole rows.
     const int lw = wave - S::kWaves;
     const uint32_t rowa = (uint32_t)(p.lda * kElem), roww = (uint32_t)(p.ldw * kElem);
     const uint32_t chunk = (uint32_t)((lane & 7) ^ ((4 * lw + (lane >> 4)) & 7));
@@ -94,7 +99,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     const int tail = kAT ? 0 : (int)(p.K % kTileK) * kElem;                     // bytes
     const bool in_tail = (int)(16 * chunk) < tail;                             // (of the last k-tile, where that is not whole)
     const uint32_t vw = (uint32_t)(8 * lw + (lane >> 3)) * roww + 16 * chunk;
-    // A descriptor holds the rows of the tile (rows past it read as zero); k advances in the scalar offset (for W [K, N] the descriptor advances).
+    // A descriptor holds the rows of the tile (rows past it read as zero); k advances in the scalar offset (for W [K, N] the
+    // descriptor advances).
     auto rsrc = [&](uint64_t addr, int left, int most, uint32_t row) -> i32x4 {
       return (i32x4){(int)(uint32_t)addr, (int)(uint32_t)(addr >> 32), (int)(left > 0 ? (uint32_t)min(left, most) * row : 0u), 0x00020000};
     };
@@ -102,8 +108,9 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
     };
     i32x4 ra, rw;
-    // An operand with k as its slow axis: load c brings 1 KB of whole rows of the tile's columns, a descriptor holds the 64 rows of a k-tile.  A row's swizzle depends
-    // on c through its parity at most.  (A loader's own instructions are what a k-tile of a small tile waits for: nothing is computed per load but a sum.)
+    // An operand with k as its slow axis: load c brings 1 KB of whole rows of the tile's columns, a descriptor holds the 64 rows
+    // of a k-tile.  A row's swizzle depends on c through its parity at most.  (A loader's own instructions are what a k-tile of a
+    // small tile waits for: nothing is computed per load but a sum.)
     struct Rows { uint64_t addr; uint32_t voff[2], stride; };
     auto aim_rows = [&](auto pitch, const void* base, int64_t k0, uint32_t row_bytes, int first_col, int cols, Rows& o) {
       constexpr int kPitch = decltype(pitch)::value, kPer = 1024 / kPitch, kChunks = kPitch / 16;
@@ -145,8 +152,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
       for (int c = 0; c < S::kLoadsW; ++c)
         dma16(dw, kWT ? ow.voff[c & 1] + (uint32_t)c * ow.stride : w0 + (uint32_t)(8 * kLoaders * c) * roww, kWT ? 0u : k_off, dst + (uint32_t)(S::kA + kLoaders * 1024 * c));
     };
-    // Loads run STAGES - 1 k-tiles ahead of the products, across tiles.  A loader waits for its loads alone: in a wave that stores as well, waiting for a
-    // load means waiting for every store in front of it.
+    // Loads run STAGES - 1 k-tiles ahead of the products, across tiles.  A loader waits for its loads alone: in a wave that
+    // stores as well, waiting for a load means waiting for every store in front of it.
     int t = tile, step = 0, s = 0, flying = 0;
     aim(t);
     auto next = [&]() {
@@ -185,7 +192,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_hi ^ columns) + (uint32_t)(4 * pitch)));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  // (E4M3: a lane's 32 codes of 64 k are two 16-byte chunks of its row, the same two for both operands, which is all that the product needs)
+  // (E4M3: a lane's 32 codes of 64 k are two 16-byte chunks of its row, the same two for both operands, which is all that the
+  // product needs)
   typedef typename std::conditional<kFp8, i32x8, bf16x8>::type Operand;
   auto contiguous = [&](uint32_t base, uint32_t at, int ks) -> Operand {
     if constexpr (kFp8) {
@@ -216,7 +224,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     for (int ni = 0; ni < 2; ++ni) wf[0][ni] = wfrag(off, 0, ni);
     af[0] = afrag(off, 0, 0);
   };
-  // this wave's reads of its k-tile are done and the loaders' loads of the next one have landed: the barrier frees the one and publishes the other
+  // this wave's reads of its k-tile are done and the loaders' loads of the next one have landed: the barrier frees the one and
+  // publishes the other
   auto turn = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
   turn();
   for (;;) {
@@ -279,11 +288,13 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
       for (int mi = 0; mi < MI; ++mi)
         if (32 * mi + l32 < rows) sa[mi] = p.scale_a[m0 + 32 * (MI * wm + mi) + l32];
     }
-    // Residual rows come kAhead parts early: memory operations complete in order, so waiting for a load waits for the stores before it, and 16 rows in flight per
-    // wave do not cover the latency.  Descriptors drop what lies outside (the row is in the lane's offset, which the range check covers): a branch would keep the
-    // compiler from counting the stores in between.  As many parts as the registers hold.  us, one part -> these: E4M3, K = 1024, 262,144 x 1024 444 -> 430,
-    // 100,000 x 1024 176 -> 171;  a bf16 layer's forward, widths 512, 6,400 rows 74.1 -> 72.8, 87,000 rows 643 -> 633.  Without a residual the rows' scales stay one
-    // part early: all of them at once 851 -> 876 (the forward of 100,000 rows, E = 1024, H D = 512: the stores come in one burst).
+    // Residual rows come kAhead parts early: memory operations complete in order, so waiting for a load waits for the stores
+    // before it, and 16 rows in flight per wave do not cover the latency.  Descriptors drop what lies outside (the row is in the
+    // lane's offset, which the range check covers): a branch would keep the compiler from counting the stores in between.  As
+    // many parts as the registers hold.  us, one part -> these: E4M3, K = 1024, 262,144 x 1024 444 -> 430, 100,000 x 1024 176 ->
+    // 171;  a bf16 layer's forward, widths 512, 6,400 rows 74.1 -> 72.8, 87,000 rows 643 -> 633.  Without a residual the rows'
+    // scales stay one part early: all of them at once 851 -> 876 (the forward of 100,000 rows, E = 1024, H D = 512: the stores
+    // come in one burst).
     constexpr int kAhead = !kRes ? 1 : MI == 1 || MI == 4 ? 2 : MI == 2 && S::kWavesPerSimd == 4 ? 3 : 4;
     u32x4 res[kAhead][2];
     __amdgpu_buffer_rsrc_t rc, rd;
@@ -341,7 +352,8 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
           for (int e = 0; e < 8; ++e) v[e] = (kRes ? v[e] : v[e] * sa[it]) * sb[e / 4][e % 4];
         }
         if (kRes) {
-          // (E4M3: the scaled product is rounded before the residual is added, as in fp8_gemm_bias2d_kernel: a row's results do not depend on how many rows are beside it)
+          // (E4M3: the scaled product is rounded before the residual is added, as in fp8_gemm_bias2d_kernel: a row's results do
+          // not depend on how many rows are beside it)
 #pragma clang fp contract(off)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -412,12 +424,15 @@ hipError_t launch_epi(const GemmRowsArgs& p, int tile, hipStream_t stream) {
 
 }  // namespace
 
-// With long rows and much work the library's kernels are the faster ones, once they have been chosen for the size.  They are chosen by timing on a class's
-// first call, which blocks, and then serve every count of the class, some of them badly.  So a class goes to the library as a whole, and only if its
-// smallest count is beyond the line: one call leaves nothing to choose for another of its class.  A layer's step with widths of 1024, us, library (chosen for
-// this count) -> here: 30,000 rows 1,939 -> 1,910, 60,000 rows 3,678 -> 3,602, 120,000 rows 7,232 -> 7,205 (forward 1,715 -> 1,746); 26,000 rows, chosen for
-// 24,000, the forward 482 -> 408.  Widths of 2048: 15,000 rows 2,854 -> 2,921, 50,000 rows 9,192 -> 9,689; 8,000 rows, chosen for 6,000, 1,739 -> 1,598, but
-// 7,500 rows, chosen for them, 1,489 -> 1,532.
+// With long rows and much work the library's kernels are the faster ones, once they have been chosen for the size.  They are
+// chosen by timing on a class's first call, which blocks, and then serve every count of the class, some of them badly.  So a
+// class goes to the library as a whole, and only if its smallest count is beyond the line: one call leaves nothing to choose for
+// another of its class.  A layer's step with widths of 1024, us, library (chosen for this count) -> here: 30,000 rows 1,939 ->
+// 1,910, 60,000 rows 3,678 -> 3,602, 120,000 rows 7,232 -> 7,205 (forward 1,715 -> 1,746); 26,000 rows, chosen for 24,000, the
+// forward 482 -> 408.  Widths of 2048: 15,000 rows 2,854 -> 2,921, 50,000 rows 9,192 -> 9,689; 8,000 rows, chosen for 6,000,
+// 1,739 -> 1,598, but 7,500 rows, chosen for them, 1,489 -> 1,532.  Below the line a forward is up to 11 % slower than with the
+// library's kernels chosen for the very count (16,000 rows, widths of 1024 231 -> 247, 5,000 rows, widths of 2048 227 -> 251), a
+// step as fast or faster, and neither waits for a choice.
 bool gemm_rows_preferred(int64_t M, int64_t N, int64_t K) { return K < 1024 || (double)(token_class(M) / 2) * (double)N * (double)K < 1e11; }
 
 hipError_t launch_gemm_rows(const GemmRowsArgs& p, int op, int epilogue, hipStream_t stream) {

@@ -1,8 +1,9 @@
 // Weight gradients of the layer's two projections (layer pseudocode of the paper's appendix: d_linear_w = X^T dY):
 //   C[n1, n2] = sum over token rows t of A[t, n1] * B[t, n2],   A [T, N1], B [T, N2] bf16 row-major, C fp32.
-// The reduction runs over the jagged token axis (10^5 rows) and the output is small (512 x 512 .. 2048 x 512), so the work is cut along t: gemm_rows.hip
-// multiplies 128 x 128 output tiles of slabs of token rows (both fragments through the LDS transpose loads), and launch_layer_sums adds the fp32 sums of
-// the slabs in a fixed order (deterministic, no atomics).  One slab writes C itself.
+// The reduction runs over the jagged token axis (10^5 rows) and the output is small (512 x 512 .. 2048 x 512), so the work is cut
+// along t: gemm_rows.hip multiplies 128 x 128 output tiles of slabs of token rows (both fragments through the LDS transpose
+// loads), and launch_layer_sums adds the fp32 sums of the slabs in a fixed order (deterministic, no atomics).  One slab writes C
+// itself.
 #include <algorithm>
 
 #include "hstu_common.h"
@@ -22,8 +23,9 @@ constexpr double kTileUs = 0.72, kSumsUs = 3.5;                    // 64 token r
 double slab_us(int N1, int N2) { return (double)N1 * N2 * 8 / 5e6; }
 int tiles_of(int N1, int N2) { return (N1 / kTile) * (N2 / kTile); }
 
-// No more slabs than k-tiles, nor than give every compute unit two workgroups; and slabs that take longer to write and read than the whole product never
-// pay.  None of the three falls as T grows: the room for the partial sums is sized by this, so that a workspace for T rows serves fewer rows too.
+// No more slabs than k-tiles, nor than give every compute unit two workgroups; and slabs that take longer to write and read than
+// the whole product never pay.  None of the three falls as T grows: the room for the partial sums is sized by this, so that a
+// workspace for T rows serves fewer rows too.
 int64_t most_slabs(int64_t T, int N1, int N2) {
   const int tiles = tiles_of(N1, N2);
   const int64_t k_tiles = (T + kBK - 1) / kBK;
@@ -33,9 +35,9 @@ int64_t most_slabs(int64_t T, int N1, int N2) {
 }
 }  // namespace
 
-// The number of slabs with the least time: a compute unit works through its tiles at 0.72 us per 64 token rows, and slabs cost a launch that adds them up and
-// a copy of the output each to write and read.  us of both launches, with a kernel of its own (64 x 64 per wave, tiles staged through registers, 512
-// workgroups) -> here:
+// The number of slabs with the least time: a compute unit works through its tiles at 0.72 us per 64 token rows, and slabs cost a
+// launch that adds them up and a copy of the output each to write and read.  us of both launches, with a kernel of its own (64 x
+// 64 per wave, tiles staged through registers, 512 workgroups) -> here:
 //   T          2048 x 512          512 x 512
 //   87,728     298  -> 260         73   -> 62
 //   20,000      70  ->  58
@@ -88,7 +90,8 @@ __global__ __launch_bounds__(kSumThreads) void layer_sums_kernel(const SumJobs j
 }
 }  // namespace
 
-// The partial sums of a layer's backward in one launch instead of four of 4-7 us: a training step of 6,418 rows 330 -> 324 us, of 14,000 rows (widths 256, 128) 248 -> 235.
+// The partial sums of a layer's backward in one launch instead of four of 4-7 us: a training step of 6,418 rows 330 -> 324 us, of
+// 14,000 rows (widths 256, 128) 248 -> 235.
 hipError_t launch_layer_sums(const SlabJob (&slabs)[2], const ColsumJob (&cols)[2], hipStream_t stream) {
   SumJobs j = {{slabs[0], slabs[1]}, {cols[0], cols[1]}, {}};
   int end = 0;

@@ -1,11 +1,13 @@
-// Sums of partial results in a fixed order: the column sums that the norms' backward leaves per workgroup, and the slabs of a weight gradient.
+// Sums of partial results in a fixed order: the column sums that the norms' backward leaves per workgroup, and the slabs of a
+// weight gradient.
 #pragma once
 #include "hstu_common.h"
 #include "hstu_kernels.h"
 
 namespace hstu {
 
-// A value from another lane of the same row of 16, by DPP (a lane permutation through LDS, which __shfl_xor is, takes some 100 cycles where this takes 8).
+// A value from another lane of the same row of 16, by DPP (a lane permutation through LDS, which __shfl_xor is, takes some 100
+// cycles where this takes 8).
 template <int kCtrl> __device__ __forceinline__ float dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xF, 0xF, true));
 }

@@ -12,19 +12,20 @@
 // and every entry of the sorted list is written once per head (heads adjacent): a single workgroup does all of this.
 // Semi-local attention costs O((K1+K2) L) only because of the skipping (paper Section 4.2.1).
 //
-// What bounds it: nothing but latency (a launch, a few dependent trips to memory, barriers), so the work is arranged to have
-// few of each: one workgroup per list, scans and reductions in DPP adds with one trip through LDS, a stable radix sort of 6
-// bits per pass (two passes for costs up to 4,095 tiles) instead of a comparison sort, and the expansion of the bias table
-// (and the clearing of the bias gradient's sums) in further workgroups of the same launch.  The instruction cache is cold on
-// every launch (the attention kernels fill it), so code that is walked once costs its fetches: loops stay rolled, what a
-// thread would keep in registers across them sits in LDS, and block and tile sizes are shifts.  Measured on the launch, with
-// the expansion in it: 10 blocks 4.9 us (11.3 with a comparison sort and 49 KB of unrolled code), 346 blocks of 512-2048-token
-// sequences 8.7 us (18.4 + 5.2 for the expansion's own launch), 690 blocks of 8k-16k tokens 9.4 us (27 + 5); of the last, 1.0 us
-// go to the offsets and their scan, 1.1 to pricing, 1.1 to each pass of the sort, 1.2 to writing the list.
-// Few blocks with many pieces (a query tail) spent their time on rounds of scans for the piece size and on one thread writing all pieces of its block, and
-// every call on the expansion's searches through the bucket bounds in global memory.  A forward, us, without -> with waves that share the pieces, staged
-// bounds and scans without barriers: tail of one 65,536-token history (1 head) 49.5 -> 37.4, of a 20,000-token one (4 heads) 34.7 -> 31.4, of eight 8k-16k
-// ones 81.5 -> 80.3;  short lists with few pieces: fp32, 426 tokens, 32.3 -> 31.9, 2,733 tokens (32 features) 30.6 -> 30.2.
+// What bounds it: nothing but latency (a launch, a few dependent trips to memory, barriers), so the work is arranged to have few
+// of each: one workgroup per list, scans and reductions in DPP adds with one trip through LDS, a stable radix sort of 6 bits per
+// pass (two passes for costs up to 4,095 tiles) instead of a comparison sort, and the expansion of the bias table (and the
+// clearing of the bias gradient's sums) in further workgroups of the same launch.  The instruction cache is cold on every launch
+// (the attention kernels fill it), so code that is walked once costs its fetches: loops stay rolled, what a thread would keep in
+// registers across them sits in LDS, and block and tile sizes are shifts.  Measured on the launch, with the expansion in it: 10
+// blocks 4.9 us (11.3 with a comparison sort and 49 KB of unrolled code), 346 blocks of 512-2048-token sequences 8.7 us (18.4 +
+// 5.2 for the expansion's own launch), 690 blocks of 8k-16k tokens 9.4 us (27 + 5); of the last, 1.0 us go to the offsets and
+// their scan, 1.1 to pricing, 1.1 to each pass of the sort, 1.2 to writing the list.  Few blocks with many pieces (a query tail)
+// spent their time on rounds of scans for the piece size and on one thread writing all pieces of its block, and every call on the
+// expansion's searches through the bucket bounds in global memory.  A forward, us, without -> with waves that share the pieces,
+// staged bounds and scans without barriers: tail of one 65,536-token history (1 head) 49.5 -> 37.4, of a 20,000-token one (4
+// heads) 34.7 -> 31.4, of eight 8k-16k ones 81.5 -> 80.3;  short lists with few pieces: fp32, 426 tokens, 32.3 -> 31.9, 2,733
+// tokens (32 features) 30.6 -> 30.2.
 #include <cmath>
 
 #include "hstu_common.h"
@@ -122,7 +123,7 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   if (tid == 0) { sh.bad = 0; sh.tiles = 0; sh.dense = 0; }
   __syncthreads();
 
-  // 1. Exclusive scan of blocks-per-sequence (per head).  The offsets live on the device and the host may never have seen
+  // 1.  Exclusive scan of blocks-per-sequence (per head).  The offsets live on the device and the host may never have seen
   // them: a batch whose offsets are not a non-decreasing walk from 0 to at most T in steps of at most max_seqlen, or whose
   // candidate counts leave [0, L], gets an empty list (every kernel that follows then returns at once) instead of rows
   // addressed outside the tensors.
@@ -236,12 +237,12 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
   const int max_cost = __builtin_amdgcn_readlane(row_max(sh.wave_total[2][col]), kSchedWaves - 1);
   const int64_t all_tiles = (int64_t)pair_tiles * H, all_dense = (int64_t)pair_dense * H;
 
-  // 3. Cut blocks that are much longer than the rest (CutRule; the few key blocks of a global prefix are seen by every query of
-  // their sequence).  Each piece
-  // becomes an entry of the list and accumulates into a partial-sum slot of its own (one per head).  The piece size
-  // doubles until the slots and the list fit, and grows by a quarter once the slots are
-  // short by a quarter (with a query tail) or a half: doubled there, most blocks are no longer than twice a piece and stay whole (16 sequences of 2,000-4,000
-  // tokens, 4 heads of 32 features, tail 500: 91 us, 69 this way; n tiles in pieces of n / (slots - blocks), which always fit, 86).
+  // 3.  Cut blocks that are much longer than the rest (CutRule; the few key blocks of a global prefix are seen by every query of
+  // their sequence).  Each piece becomes an entry of the list and accumulates into a partial-sum slot of its own (one per head).
+  // The piece size doubles until the slots and the list fit, and grows by a quarter once the slots are short by a quarter (with a
+  // query tail) or a half: doubled there, most blocks are no longer than twice a piece and stay whole (16 sequences of
+  // 2,000-4,000 tokens, 4 heads of 32 features, tail 500: 91 us, 69 this way; n tiles in pieces of n / (slots - blocks), which
+  // always fit, 86).
   int chunk = (int)fmin((double)0x3FFFFFFF, fmax((double)job.rule.min_chunk, ceil((double)all_tiles * (1.0 / job.rule.target_chunks))));
   // pieces of a block of `cost` tiles and their length: the fewest equal pieces of at most 2 x chunk tiles (every piece costs a
   // partial-sum slot and its traffic), or pieces of `chunk` tiles
@@ -314,8 +315,8 @@ __device__ void schedule_list(const SchedJob& job, SchedShared& sh, const int32_
     for (int idx = tid; idx < pairs; idx += kSchedThreads) sh.keys[0][idx] = key_of((int)costs[idx], idx);
   } else {
     int slot = slot0, rank = rank0, e = at - rank0 + slot0;
-    // A pair's pieces and heads are its thread's; with many pieces the waves share those of few pairs (all of them for a few pieces: 0.9 us, the
-    // instructions of 16 waves on 4 SIMDs)
+    // A pair's pieces and heads are its thread's; with many pieces the waves share those of few pairs (all of them for a few
+    // pieces: 0.9 us, the instructions of 16 waves on 4 SIMDs)
     const bool share = few && (max_cost >> 5) > chunk;
     const int first = share ? wave : 0, step = share ? kSchedWaves : 1;
 #pragma unroll 1

@@ -139,9 +139,9 @@ __device__ __forceinline__ int find_with_wave(const int32_t* __restrict__ off, i
   return lo;
 }
 
-// Rows of up to 512 bytes.  A step of a wave copies kUnroll groups of rows, a group as many consecutive rows as 16 bytes a lane of one instruction
-// cover.  The sequences around the step's first row sit in the lanes (a: the offsets that the rows are counted in, b: the others), so that finding a
-// group's sequence takes comparisons and no further trip to memory.
+// Rows of up to 512 bytes.  A step of a wave copies kUnroll groups of rows, a group as many consecutive rows as 16 bytes a lane
+// of one instruction cover.  The sequences around the step's first row sit in the lanes (a: the offsets that the rows are counted
+// in, b: the others), so that finding a group's sequence takes comparisons and no further trip to memory.
 constexpr int kUnroll = 8;
 struct Window { int32_t a, b; int first; bool covers; };
 struct Place { int32_t a0, a1, b0, b1; };    // a sequence in both offsets
@@ -182,9 +182,9 @@ __device__ __forceinline__ Place place(const Window& w, const int32_t* __restric
 }
 
 // GATHER as truncate_gather_kernel, rows counted in out_offsets; else as truncate_scatter_kernel, rows counted in offsets.
-// What bounds it: memory, once every lane has 16 bytes to move.  us, forward / backward, with the kernels above -> here: 439,000 rows of 256 bytes cut to
-// 120,000 28.9 / 77.5 -> 13.9 / 31.7 (4.4 TB/s), of 128 bytes 23 / 72 -> 12 / 20, 779,000 rows of 400 bytes 96 / 169 -> 62 / 96; rows of 1 KiB, which
-// stay with the kernels above, 134 -> 147 backward.
+// What bounds it: memory, once every lane has 16 bytes to move.  us, forward / backward, with the kernels above -> here: 439,000
+// rows of 256 bytes cut to 120,000 28.9 / 77.5 -> 13.9 / 31.7 (4.4 TB/s), of 128 bytes 23 / 72 -> 12 / 20, 779,000 rows of 400
+// bytes 96 / 169 -> 62 / 96; rows of 1 KiB, which stay with the kernels above, 134 -> 147 backward.
 template <bool GATHER>
 __global__ __launch_bounds__(kCopyThreads) void truncate_copy_kernel(int B, const int32_t* __restrict__ offsets, const int32_t* __restrict__ out_offsets,
                                                                      int lanes_per_row, const char* __restrict__ src,
@@ -231,10 +231,12 @@ int copy_grid(int64_t rows, int rows_per_step) {
   return (int)max((int64_t)1, min(wgs, (int64_t)256 * 32));
 }
 
-// Rows of up to 512 bytes, at least two to an instruction, where a step's chain of trips to memory is all there is to wait for (one step), or the steps fill the
-// chip.  In between a row an instruction spreads over more waves; and with few rows a sequence, which a step walks through, it takes more rows to pay.  us,
-// row an instruction -> steps: 64 sequences, 27,000 rows of 48 bytes 7.9 -> 5.8, 20,000 sequences, 200,000 rows 45 -> 10, one sequence, 51 rows of 16 bytes 4.7 ->
-// 2.5;  but one sequence, 2,400 rows of 128 bytes 5.1 -> 5.9, 512 sequences, 400 rows of 16 bytes 7.1 -> 10.4, 1,300 rows 6.9 -> 11.5, 5,000 sequences, 7,500 rows 8.0 -> 15.7.
+// Rows of up to 512 bytes, at least two to an instruction, where a step's chain of trips to memory is all there is to wait for
+// (one step), or the steps fill the chip.  In between a row an instruction spreads over more waves; and with few rows a sequence,
+// which a step walks through, it takes more rows to pay.  us, row an instruction -> steps: 64 sequences, 27,000 rows of 48 bytes
+// 7.9 -> 5.8, 20,000 sequences, 200,000 rows 45 -> 10, one sequence, 51 rows of 16 bytes 4.7 -> 2.5;  but one sequence, 2,400
+// rows of 128 bytes 5.1 -> 5.9, 512 sequences, 400 rows of 16 bytes 7.1 -> 10.4, 1,300 rows 6.9 -> 11.5, 5,000 sequences, 7,500
+// rows 8.0 -> 15.7.
 constexpr int64_t kNarrowRow = 512;
 bool in_steps(int B, int64_t rows, int64_t row_bytes) {
   if (row_bytes > kNarrowRow) return false;
