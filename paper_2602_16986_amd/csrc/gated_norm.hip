@@ -340,9 +340,9 @@ __global__ __launch_bounds__(64 * kBwdWaves, 4) void gated_norm_bwd_kernel(const
 // a wave that runs ahead never overwrites what a slower one still reads.  One wave per row needed 48 registers per 512 features
 // (and spilled from 2048 features on).  What the reductions of the next row need is fetched a row ahead (bf16), 128 registers
 // keep 16 waves on a compute unit, and a wave sums eight and more slots a lane each (48 values in flight spilled at 16 waves).
-// bf16 without a bias, us with the column-sum launch, before -> now: 1024 features, 6,418 rows 31.9 -> 22.8, 87,728 rows 214 ->
-// 177; 2048 features, 6,418 rows 43.6 -> 32.8; 4096 features, 20,000 rows 218 -> 165; 8192 features 2,029 -> 369; fp32 at 8192
-// features, 6,418 rows 283 -> 236.
+// bf16 without a bias, us with the column-sum launch, before -> now: 1024 features, 6,418 rows 31.8 -> 20.7, 87,728 rows 217 ->
+// 179; 2048 features, 6,418 rows 43.0 -> 29.7; 4096 features, 20,000 rows 227 -> 158; 8192 features 2,017 -> 324; fp32 at 8192
+// features, 6,418 rows 285 -> 208.
 //
 // The sum of W (up to 16) values in LDS, in every lane: eight and more a value per lane of a row of 16 (48 values in flight spill
 // at W = 16).
