@@ -180,7 +180,7 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
 
   // ---- LDS -> operands
   const int wm = wave / WN, wn = wave % WN;
-  const uint32_t row128 = (uint32_t)(l32 * 128 + 16 * (hf ^ ((l32 >> 1) & 7)));   // k-step ks of a tile: chunk ^ 2 ks
+  const uint32_t row128 = (uint32_t)(l32 * 128 + 16 * ((kFp8 ? 2 * hf : hf) ^ ((l32 >> 1) & 7)));   // k-step ks of a tile: chunk ^ 2 ks (E4M3: 4 ks)
   const uint32_t ta = smem_base + (uint32_t)(wm * 32 * MI * 128) + row128;
   const uint32_t tw = smem_base + S::kA + (uint32_t)(wn * 64 * 128) + row128;
   // Transposed: lanes of a half-wave take rows 8 hf + 0..3 (then + 4) of 16 k; lane l32 ends up with column l32's 8 values of k.
@@ -192,12 +192,12 @@ __global__ __launch_bounds__((Tile<WM, WN, MI, STAGES>::kThreads), (Tile<WM, WN,
     const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(at + (tr_hi ^ columns) + (uint32_t)(4 * pitch)));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  // (E4M3: a lane's 32 codes of 64 k are two 16-byte chunks of its row, the same two for both operands, which is all that the
-  // product needs)
+  // (E4M3: a lane's 32 codes of 64 k are two neighbouring 16-byte chunks of its row, as in fp8_gemm_bias2d_kernel: which codes
+  // meet in a lane changes the last bits of the matrix instruction's sums, and a row's results should not depend on the kernel)
   typedef typename std::conditional<kFp8, i32x8, bf16x8>::type Operand;
   auto contiguous = [&](uint32_t base, uint32_t at, int ks) -> Operand {
     if constexpr (kFp8) {
-      const i32x4 lo = *(lds_i4)(uintptr_t)((base ^ (uint32_t)(64 * ks)) + at), hi = *(lds_i4)(uintptr_t)((base ^ (uint32_t)(64 * ks + 32)) + at);
+      const i32x4 lo = *(lds_i4)(uintptr_t)((base ^ (uint32_t)(64 * ks)) + at), hi = *(lds_i4)(uintptr_t)((base ^ (uint32_t)(64 * ks + 16)) + at);
       return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     } else {
       return *(lds_b8)(uintptr_t)((base ^ (uint32_t)(32 * ks)) + at);

@@ -11,13 +11,16 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N,K", [(128, 512), (1024, 512), (192, 1024), (1024, 1024)])
 @pytest.mark.parametrize("residual", [False, True])
-def test_fp8_product_rows_do_not_depend_on_the_row_count(N, K, residual):
+@pytest.mark.parametrize("codes", ["quantised", "uniform"])
+def test_fp8_product_rows_do_not_depend_on_the_row_count(N, K, residual, codes):
     most = 20600
     gen = torch.Generator(device="cuda").manual_seed(N + K)
     quantised = lambda t: (torch.empty(t.shape, dtype=torch.uint8, device="cuda"), torch.empty(t.shape[0], device="cuda"))
     (a, sa), (b, sb) = (quantised(t) for t in (torch.empty(most, K), torch.empty(N, K)))
     for q, s in ((a, sa), (b, sb)):
         hb.hstu_norm_quant_fp8(torch.randn(q.shape, generator=gen, device="cuda").bfloat16(), None, None, None, 0.0, q, s)
+        if codes == "uniform":                               # every exponent as often as any other: sums of very unequal terms
+            q.copy_(torch.randint(0, 0x7F, q.shape, generator=gen, device="cuda") + 0x80 * torch.randint(0, 2, q.shape, generator=gen, device="cuda"))
     c = torch.randn(most, N, generator=gen, device="cuda").bfloat16() if residual else None
     got = []
     for rows in (most, 16385, 16384, 5000, 300, 129, 81, 80, 65, 41, 40, 1):
